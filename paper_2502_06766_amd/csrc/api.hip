@@ -512,7 +512,7 @@ static void fill_call(topk_attn_t* h, int layer, const void* q, int k, int n_que
     s->hist_cap = h->ws.hist_cap; s->tail_spw = 1; s->tail_wgs = 1;
     s->cand_cap = h->ws.cand_cap; s->bnd_cap = h->ws.bnd_cap; s->n_seg = 4; s->seg_cap = (h->ws.cand_cap / 4) & ~(kCandChunk - 1); s->samp_cap = kSampMax; s->n_chunk_cap = h->ws.n_chunk_cap;
     s->Ncap = c.max_tokens;
-    s->indexed = 0;
+    s->indexed = 0; s->attend = 0;
     s->paged = 0; s->no_rescan = 0;
     s->page_cap = (int)page_cap_of(&c); s->page_words = h->ws.page_words;
     s->force_redo = h->force_redo ? 1 : 0;
@@ -615,6 +615,22 @@ static int lengths_of(const topk_attn_t* h, int layer, int window, int64_t min_t
     return TOPK_ATTN_OK;
 }
 
+// Workgroups per head of the one-launch selection over the candidate list (attend.hip), 0 where the chip-wide tail takes
+// the call.  32 heads, k = 256 .. 2048, against the tail's two launches: 49 against 56 us at 48k tokens, 73 against 82 at 128k,
+// 213 against 222 at 512k.  Its limits: a list and the rows to fetch fit LDS; the keys a workgroup scores again
+// when a list turns out unusable are bounded; heads beyond the compute units get one workgroup each, which pays where the tail
+// would run at least four (chunks of queries: 16 queries at 128k tokens 172 against 185 us; batches of 16 sequences of 10k
+// tokens, one tail workgroup per head, 111 against 105 us).
+static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax) {
+    if (h->force_redo || s.k + s.window > kAttendRows) return 0;
+    if (make_plan(nmax, s.k < nmax ? s.k : (int)nmax, s.indexed).c_hi > kAttendList) return 0;
+    const int64_t heads = (int64_t)s.B * s.Hq;
+    if (heads > kAttendManyHeads && (s.tail_wgs < 4 || heads > 4 * kAttendManyHeads)) return 0;
+    int64_t shares = std::max<int64_t>(1, kAttendManyHeads / heads);
+    shares = std::min<int64_t>(std::min<int64_t>(shares, kAttendShares), s.n_chunk_cap);
+    return nmax <= kAttendShareKeys * shares ? (int)shares : 0;
+}
+
 static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, int causal, int k, int window,
                        float* out, int32_t* idx, float* vals, float* lse, void* hip_stream, bool use_static = false) {
     if (!h || !q || !out) return TOPK_ATTN_EINVAL;
@@ -652,8 +668,9 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
         const Plan longest = make_plan(nmax, k < nmax ? k : (int)nmax, s.indexed);
         int64_t total = 0;               // searched tokens of the whole call
         for (int i = 0; i < s.Bc; ++i) total += prefix_len(h->len[(size_t)layer * s.Bc + i], window);
-        fast = plan_is_fast(longest, nmax, s.cand_cap, h->path == TOPK_ATTN_PATH_FILTER,
-                            total >= kFilterBatchTokens ? kFilterMinNBatch : kFilterMinN);
+        const int64_t min_n = total >= kFilterBatchTokens ? kFilterMinNBatch
+                              : attend_list_shares(h, s, nmax) ? kAttendRowMax + 1 : kFilterMinN;
+        fast = plan_is_fast(longest, nmax, s.cand_cap, h->path == TOPK_ATTN_PATH_FILTER, min_n);
         int64_t c_hi = 0;
         for (int i = 0; i < s.Bc && fast; ++i) {
             const int64_t n = prefix_len(h->len[(size_t)layer * s.Bc + i], window);
@@ -677,6 +694,10 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
     // the selection that follows the filtered scan has limits of its own (count vectors, partial-sum slots); they hold
     // for every shape the scan takes with this workspace, and a shape beyond them takes the exact path like any other
     if (fast && !tail_supported(s)) { fast = false; s.indexed = 0; s.no_rescan = 0; }
+    // Selection and attention in one launch, where the work per head is small: over the candidate list, or over the
+    // score rows of the general path.
+    if (fast) s.attend = attend_list_shares(h, s, nmax);
+    else s.attend = s.k + s.window <= attend_row_rows((int64_t)s.B * s.Hq, nmax) ? 1 : 0;
     hipError_t e = hipSuccess;
     bool tail_done = false;
     if (use_static) {
@@ -714,15 +735,21 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
         if (e == hipSuccess) e = launch_tail(s, b, st);                // selection and gather (with a window: its partial sums too); redoes unusable heads itself
         tail_done = true;
     } else {
-        if (nmax > 0) {
+        if (nmax > 0 || s.attend) {
+            Shape all = s;
+            int64_t n_scored = nmax;
+            if (s.attend) {                  // the window's scores come from the scan too
+                all.window = 0;
+                for (int i = 0; i < s.Bc; ++i) n_scored = std::max(n_scored, h->len[(size_t)layer * s.Bc + i]);
+            }
             if (timed) e = hipEventRecord(h->ev[2 * h->ev_used], st);
-            if (e == hipSuccess) e = launch_scan_full(s, b, nmax, b.scores, st);
+            if (e == hipSuccess) e = launch_scan_full(all, b, n_scored, b.scores, st);
             if (e == hipSuccess && timed) e = hipEventRecord(h->ev[2 * h->ev_used + 1], st);
             if (e == hipSuccess && timed) h->ev_used++;
         }
         if (e == hipSuccess) e = launch_select_full(s, b, nmax, st);   // with nothing to search it only pads
     }
-    if (e == hipSuccess && !tail_done) e = launch_gather(s, b, st);
+    if (e == hipSuccess && !tail_done && !s.attend) e = launch_gather(s, b, st);
     h->last_fast = fast;
     h->last_paged = fast && s.paged;
     h->last_tail = tail_done;
@@ -881,7 +908,7 @@ int topk_attn_last_selection_records(topk_attn_t* h, uint32_t* records) {
     if (hipMemcpy(flags.data(), static_cast<char*>(c.workspace) + h->ws.flags, n * sizeof(uint32_t), hipMemcpyDeviceToHost) !=
         hipSuccess)
         return TOPK_ATTN_EDEVICE;
-    for (size_t i = 0; i < n; ++i) records[4 * i] |= flags[i] << 8;      // the head's flag word above the state
+    for (size_t i = 0; i < n; ++i) records[4 * i] |= (flags[i] % kArrivalUnit) << 8;      // the head's flag word above the state
     return TOPK_ATTN_OK;
 }
 

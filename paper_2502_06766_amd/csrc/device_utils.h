@@ -36,6 +36,63 @@ __device__ __forceinline__ T wave_xor(T v, int mask) {
     return __shfl_xor(v, mask, 64);
 }
 
+// Wave-wide scans and reductions in the vector unit (DPP row shifts and row broadcasts): six instructions, where the
+// shuffle form is a chain of six trips through LDS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t old, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)old, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_f32(float old, float v) {
+    return __uint_as_float(dpp_u32<CTRL, ROWS>(__float_as_uint(old), __float_as_uint(v)));
+}
+// inclusive prefix sum over the 16 lanes of a row
+__device__ __forceinline__ uint32_t row_scan_add(uint32_t v) {
+    v += dpp_u32<0x111, 0xF>(0u, v);      // row_shr:1
+    v += dpp_u32<0x112, 0xF>(0u, v);
+    v += dpp_u32<0x114, 0xF>(0u, v);
+    v += dpp_u32<0x118, 0xF>(0u, v);
+    return v;
+}
+// inclusive prefix sum over the wave
+__device__ __forceinline__ uint32_t wave_scan_add(uint32_t v) {
+    v = row_scan_add(v);
+    v += dpp_u32<0x142, 0xA>(0u, v);      // row_bcast:15 into rows 1 and 3
+    v += dpp_u32<0x143, 0xC>(0u, v);      // row_bcast:31 into rows 2 and 3
+    return v;
+}
+// largest value of the wave, in every lane
+__device__ __forceinline__ float wave_max(float v) {
+    v = fmaxf(v, dpp_f32<0x111, 0xF>(-INFINITY, v));
+    v = fmaxf(v, dpp_f32<0x112, 0xF>(-INFINITY, v));
+    v = fmaxf(v, dpp_f32<0x114, 0xF>(-INFINITY, v));
+    v = fmaxf(v, dpp_f32<0x118, 0xF>(-INFINITY, v));
+    v = fmaxf(v, dpp_f32<0x142, 0xA>(-INFINITY, v));
+    v = fmaxf(v, dpp_f32<0x143, 0xC>(-INFINITY, v));
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
+}
+__device__ __forceinline__ float wave_min(float v) { return -wave_max(-v); }
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+    uint32_t t;
+    t = dpp_u32<0x111, 0xF>(0u, v); v = t > v ? t : v;
+    t = dpp_u32<0x112, 0xF>(0u, v); v = t > v ? t : v;
+    t = dpp_u32<0x114, 0xF>(0u, v); v = t > v ? t : v;
+    t = dpp_u32<0x118, 0xF>(0u, v); v = t > v ? t : v;
+    t = dpp_u32<0x142, 0xA>(0u, v); v = t > v ? t : v;
+    t = dpp_u32<0x143, 0xC>(0u, v); v = t > v ? t : v;
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// v of this lane + v of lane ^ 16, and the same for lane ^ 32 (register swaps, no trip through LDS)
+__device__ __forceinline__ float add_lanes_16(float v) {
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_lanes_32(float v) {
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
 // widen the 16 bytes a lane loaded into fp32 values
 template <int DT> struct Elem;
 template <> struct Elem<0> {  // fp32

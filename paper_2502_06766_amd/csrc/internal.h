@@ -19,6 +19,8 @@ constexpr int kSampMin = 1024;
 // selecting over them is faster (measured crossovers: one sequence 16k tokens 46 against 56 us,
 // 30k tokens 72 against 65 us; in a batch the small kernels of the filtered path are shared by
 // more work and it wins from 8k tokens on once the call holds 128k tokens in all).
+// Where the one-launch selection over the candidate list applies (attend.hip) it wins as soon as a row no
+// longer fits its registers (20k tokens, 32 heads: 41 against 47 us).
 constexpr int kFilterMinN = 24576;
 constexpr int kFilterMinNBatch = 8192;
 constexpr int64_t kFilterBatchTokens = 131072;
@@ -37,6 +39,7 @@ struct Shape {
     int force_redo;   // measurement aid: treat every head as not filterable (exact redo of all heads)
     int paged;        // the scan skips the pages the coarse page index rules out
     int no_rescan;    // an unusable list is redone densely (the per-bin counts of a paged scan are not those of the plain tile order)
+    int attend;       // selection and attention of a head in one launch (attend.hip) by this many workgroups; 0: the other back ends
     int page_cap;     // pages per key stream the page index has room for (ceil(Ncap / 64))
     int page_words;   // 64-bit words of the page mask per key stream
     int k;            // requested k (k_eff = min(k, searched prefix of sequence b))
@@ -196,6 +199,22 @@ __host__ __device__ inline bool plan_is_fast(const Plan& p, int64_t N, int cand_
     return force || (N >= min_n && p.c_hi * 5 <= N * 4);
 }
 
+// Selection and attention of a head in one launch (attend.hip).
+constexpr int64_t kAttendRowMax = 16384;  // scores of the longest row
+constexpr int kAttendList = 10240;        // candidates of the longest list
+constexpr int kAttendRows = 4096;         // value rows (selected and window) whose positions and weights fit LDS beside a list
+constexpr int kAttendShares = 8;          // workgroups per head at most
+constexpr int64_t kAttendShareKeys = 131072;   // keys a workgroup may have to score again when a list is unusable
+constexpr uint32_t kArrivalUnit = 256;    // the flag word counts a head's workgroups above its flag bits
+// More heads than this fill the chip with one workgroup each: small workgroups, several to a compute unit, for short rows.
+constexpr int64_t kAttendManyHeads = 256;
+// Value rows a workgroup over score rows of up to Nmax scores holds: 0 where the rows are too long.
+inline int attend_row_rows(int64_t heads, int64_t Nmax) {
+    if (Nmax > kAttendRowMax || heads > 8 * kAttendManyHeads) return 0;     // (thousands of heads: the waves of the two kernels overlap as well)
+    if (heads <= kAttendManyHeads || Nmax > 8192) return 4096;
+    return Nmax <= 4096 ? 1024 : 2048;
+}
+
 // Position of sample s: one jittered position inside each stride-long stratum.
 __host__ __device__ inline int64_t sample_pos(int s, int stride) {
     uint32_t h = (uint32_t)s * 2654435761u;
@@ -211,6 +230,10 @@ bool scan_mfma_supported(const Shape& s);
 
 hipError_t launch_threshold(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st);
 hipError_t launch_select_full(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st);
+
+// selection and attention of a head in one launch (reached through launch_select_full and launch_tail, Shape::attend)
+hipError_t launch_attend_row(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st);
+hipError_t launch_attend_list(const Shape& s, const Bufs& b, hipStream_t st);
 
 hipError_t launch_gather(const Shape& s, const Bufs& b, hipStream_t st);
 

@@ -232,6 +232,26 @@ __device__ __forceinline__ Sel32 wg_select32(Keys keys, int64_t k, SelShared& sm
     return res;
 }
 
+// Rank of each of this thread's CI items among the composite keys in LDS (number of keys that
+// beat it), by comparing with every key: all lanes read the same key at a time (an LDS
+// broadcast), eight reads in flight.  `n8` is the list length rounded up to a multiple of eight,
+// the padding holds keys that beat nothing.
+template <int CI>
+__device__ __forceinline__ void rank_by_comparison(const uint64_t* keys, int n8, const uint64_t (&mine)[CI], uint32_t (&rank)[CI]) {
+#pragma unroll
+    for (int i = 0; i < CI; ++i) rank[i] = 0;
+    for (int base = 0; base < n8; base += 8) {
+        uint64_t o[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) o[u] = keys[base + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+#pragma unroll
+            for (int i = 0; i < CI; ++i) rank[i] += o[u] > mine[i] ? 1u : 0u;
+        }
+    }
+}
+
 // Slots the selection does not fill: position -1, score -inf.
 __device__ __forceinline__ void pad_outputs(int k_eff, int k, int32_t* idx, float* vals) {
     for (int j = k_eff + (int)threadIdx.x; j < k; j += (int)blockDim.x) {

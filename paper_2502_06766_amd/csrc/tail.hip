@@ -456,26 +456,6 @@ struct SrcListT {
 constexpr int kFinishInner = 2048;     // candidates the finishing workgroup ranks by direct comparison at most
 constexpr int kFinishSmall = 4096;     // boundary candidates the finishing workgroup holds in registers; more go through the radix select
 
-// Rank of each of this thread's CI items among the composite keys in LDS (number of keys that
-// beat it), by comparing with every key: all lanes read the same key at a time (an LDS
-// broadcast), eight reads in flight.  `n8` is the list length rounded up to a multiple of eight,
-// the padding holds keys that beat nothing.
-template <int CI>
-__device__ __forceinline__ void rank_by_comparison(const uint64_t* keys, int n8, const uint64_t (&mine)[CI], uint32_t (&rank)[CI]) {
-#pragma unroll
-    for (int i = 0; i < CI; ++i) rank[i] = 0;
-    for (int base = 0; base < n8; base += 8) {
-        uint64_t o[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) o[u] = keys[base + u];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-#pragma unroll
-            for (int i = 0; i < CI; ++i) rank[i] += o[u] > mine[i] ? 1u : 0u;
-        }
-    }
-}
-
 template <int DT, int NT>
 __global__ void __launch_bounds__(NT) tail_finish_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     constexpr int EPL = 8, NW = NT / kWave, CPT = 4, U = 8;       // U: value rows in flight per lane group
@@ -786,6 +766,7 @@ bool tail_supported(const Shape& s) {
 }
 
 hipError_t launch_tail(const Shape& s, const Bufs& b, hipStream_t st) {
+    if (s.attend) return launch_attend_list(s, b, st);
     const float scale = 1.0f / sqrtf((float)s.D);
     const float scale_log2e = scale * 1.4426950408889634f;
     const int n_win = (s.window + kGatherRows - 1) / kGatherRows;     // chunks of the recent-token window, if any
