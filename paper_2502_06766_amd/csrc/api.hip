@@ -631,6 +631,15 @@ static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax
     return nmax <= kAttendShareKeys * shares ? (int)shares : 0;
 }
 
+// Whether the general path takes one launch in all, a workgroup per key stream: it has to fill the chip, or be as short as a
+// launch.  us per call, scan and selection in two launches against one (32 query / 8 KV heads, ragged batches alike): 500
+// tokens, 1 sequence 16 / 14, 64 sequences 37 / 22; 1024 tokens, 8 sequences 18 / 20, 16 25 / 20, 192 134 / 94; 2000
+// tokens, 16 sequences 29 / 34, 32 49 / 39, 192 226 / 178; 4096 tokens, 16 sequences 51 / 63, 32 95 / 74, 192 437 / 345.
+static bool attend_short_applies(const Shape& s, int64_t nmax) {
+    if (!scan_mfma_supported(s) || scan_row_tiles(s) || s.window != 0 || s.k > attend_short_k(nmax)) return false;
+    return (int64_t)s.B * s.Hkv >= (nmax <= 512 ? 1 : nmax <= 1024 ? 128 : 256);
+}
+
 static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, int causal, int k, int window,
                        float* out, int32_t* idx, float* vals, float* lse, void* hip_stream, bool use_static = false) {
     if (!h || !q || !out) return TOPK_ATTN_EINVAL;
@@ -697,6 +706,7 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
     // Selection and attention in one launch, where the work per head is small: over the candidate list, or over the
     // score rows of the general path.
     if (fast) s.attend = attend_list_shares(h, s, nmax);
+    else if (attend_short_applies(s, nmax)) s.attend = kAttendShort;
     else s.attend = s.k + s.window <= attend_row_rows((int64_t)s.B * s.Hq, nmax) ? 1 : 0;
     hipError_t e = hipSuccess;
     bool tail_done = false;
@@ -743,11 +753,11 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
                 for (int i = 0; i < s.Bc; ++i) n_scored = std::max(n_scored, h->len[(size_t)layer * s.Bc + i]);
             }
             if (timed) e = hipEventRecord(h->ev[2 * h->ev_used], st);
-            if (e == hipSuccess) e = launch_scan_full(all, b, n_scored, b.scores, st);
+            if (e == hipSuccess) e = s.attend == kAttendShort ? launch_select_full(s, b, nmax, st) : launch_scan_full(all, b, n_scored, b.scores, st);
             if (e == hipSuccess && timed) e = hipEventRecord(h->ev[2 * h->ev_used + 1], st);
             if (e == hipSuccess && timed) h->ev_used++;
         }
-        if (e == hipSuccess) e = launch_select_full(s, b, nmax, st);   // with nothing to search it only pads
+        if (e == hipSuccess && s.attend != kAttendShort) e = launch_select_full(s, b, nmax, st);   // with nothing to search it only pads
     }
     if (e == hipSuccess && !tail_done && !s.attend) e = launch_gather(s, b, st);
     h->last_fast = fast;

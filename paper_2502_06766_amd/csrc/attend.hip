@@ -16,9 +16,12 @@
 // 13.9 us, at 128k tokens, k = 1800: 18.0 us (chip-wide tail: 11.6 + 11.6 and 14.8 + 9.6 us and a launch more).
 //
 //   SRC_ROW   the scores of a short cache, stored by the scan (general path)
+//   (attend_short_kernel: the scores too, for batches of short sequences)
 //   SRC_LIST  the candidate list the filtered scan left; a head whose list is unusable (a segment overflowed, too few
 //             or too many candidates) is scored again by the workgroups launched for it and selected from its full
 //             score row by the last of them to finish
+#include <type_traits>
+
 #include "device_utils.h"
 #include "internal.h"
 #include "scan_tiles.h"
@@ -36,42 +39,59 @@ struct AttendCfg {
 };
 using ListCfg = AttendCfg<1024, kAttendList / 1024, kAttendRows, 1024>;
 
-template <class Cfg, int SRC>
-struct AttendShared {
-    static constexpr int NW = Cfg::NW;
-    uint64_t cand[SRC == SRC_LIST ? Cfg::CPT * Cfg::NT : 1];           // candidates (score bits, position)
-    uint64_t rows[Cfg::ROWS];               // value rows to fetch (weight bits, position)
-    uint64_t keys[Cfg::NT + 8];             // segments of the candidate list (length, first entry); later composite keys of the bin that is ranked
-    uint32_t hist[Cfg::NB];
-    float acc[NW][256 + 1];
-    float red[2][2][NW];
-    uint32_t tot[2][NW];
+// The threads that select for one head: a whole workgroup, or one wave of it.
+template <int NT_>
+struct WorkgroupTeam {
+    static constexpr int NT = NT_, NW = NT_ / kWave;
+    static __device__ __forceinline__ int rank() { return (int)threadIdx.x; }
+    static __device__ __forceinline__ void sync() { __syncthreads(); }
+};
+struct WaveTeam {
+    static constexpr int NT = kWave, NW = 1;
+    static __device__ __forceinline__ int rank() { return lane_id(); }
+    static __device__ __forceinline__ void sync() { wave_sync(); }
+};
+
+// What a team shares while it selects; NB bins.
+template <class Team, int NB_>
+struct SelectShared {
+    static constexpr int NB = NB_;
+    uint64_t keys[Team::NT + 8];            // segments of the candidate list (length, first entry); later composite keys of the bin that is ranked
+    uint32_t hist[NB_];
+    float red[2][2][Team::NW];
+    uint32_t tot[2][Team::NW];
     uint32_t sel[3];
     uint32_t n_keys;
 };
 
-// Exclusive prefix sum of n over the threads; `total` for all.  One barrier; `slot` alternates between two places so that
+// Exclusive prefix sum of n over the team; `total` for all.  One barrier; `slot` alternates between two places so that
 // the next call need not wait for the readers of this one.
-template <class SM>
-__device__ __forceinline__ uint32_t wg_prefix(uint32_t n, uint32_t& total, SM& sm, int slot) {
-    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+template <class Team, class SM>
+__device__ __forceinline__ uint32_t team_prefix(uint32_t n, uint32_t& total, SM& sm, int slot) {
+    const int lane = lane_id();
     const uint32_t inc = wave_scan_add(n);
+    if (Team::NW == 1) {
+        total = (uint32_t)__builtin_amdgcn_readlane((int)inc, kWave - 1);
+        return inc - n;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (lane == kWave - 1) sm.tot[slot][wave] = inc;
-    __syncthreads();
-    const uint32_t t = row_scan_add((lane & 15) < SM::NW ? sm.tot[slot][lane & 15] : 0u);
-    total = (uint32_t)__builtin_amdgcn_readlane((int)t, SM::NW - 1);
+    Team::sync();
+    const uint32_t t = row_scan_add((lane & 15) < Team::NW ? sm.tot[slot][lane & 15] : 0u);
+    total = (uint32_t)__builtin_amdgcn_readlane((int)t, Team::NW - 1);
     const uint32_t before = wave ? (uint32_t)__builtin_amdgcn_readlane((int)t, wave - 1) : 0u;
     return before + inc - n;
 }
 
-// Smallest and largest of every thread's (lo, hi) over the workgroup, one barrier.
-template <class SM>
-__device__ __forceinline__ void wg_range(float& lo, float& hi, SM& sm, int slot) {
+// Smallest and largest of every thread's (lo, hi) over the team, one barrier.
+template <class Team, class SM>
+__device__ __forceinline__ void team_range(float& lo, float& hi, SM& sm, int slot) {
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     lo = wave_min(lo); hi = wave_max(hi);
+    if (Team::NW == 1) { Team::sync(); return; }
     if (lane == 0) { sm.red[slot][0][wave] = lo; sm.red[slot][1][wave] = hi; }
-    __syncthreads();
-    const int w = lane < SM::NW ? lane : 0;
+    Team::sync();
+    const int w = lane < Team::NW ? lane : 0;
     lo = wave_min(sm.red[slot][0][w]); hi = wave_max(sm.red[slot][1][w]);
 }
 
@@ -80,6 +100,122 @@ template <int NB>
 __device__ __forceinline__ int lin_bin(float x, float lo, float inv) {
     const float t = __fmul_rn(__fsub_rn(x, lo), inv);
     return (int)fminf(fmaxf(t, 0.f), (float)(NB - 1));
+}
+
+// Clears what team_select() counts in; a barrier has to follow (team_range()).
+template <class Team, class SM>
+__device__ __forceinline__ void select_clear(SM& sm) {
+#pragma unroll
+    for (int u = 0; u < SM::NB / Team::NT; ++u) sm.hist[Team::rank() + u * Team::NT] = 0;
+    if (Team::rank() == 0) sm.n_keys = 0;
+}
+
+struct Boundary { uint32_t in, need; };     // what the first step left to rank, and how many of it win
+
+// The k_eff best of the scores in question (1 <= k_eff <= their number), each handed to emit(place, score, position) once:
+// bins between the smallest and the largest score (lo, hi), narrowed until the bin the k_eff-th falls in
+// holds few.  Every step splits the scores in question: linearly by value, by their order-preserving keys where the
+// range is beyond fp32 arithmetic, by their positions where they are all equal (the lower position wins).
+// Slot j of a thread holds item j * NT + rank, its score is v(j); bit j of `act` says that there is one.  UNROLL: CPT where
+// the scores are registers, less where they are read from LDS.
+template <class Team, int CPT, int UNROLL, class Mask, class SM, class ScoreFn, class PosFn, class EmitFn>
+__device__ __forceinline__ Boundary team_select(ScoreFn v, Mask act, int n_items, int P, int k_eff, float lo, float hi,
+                                                SM& sm, PosFn pos, EmitFn emit) {
+    constexpr int NT = Team::NT, NB = SM::NB, BPT = NB / NT;
+    static_assert(NB % NT == 0 && CPT <= 8 * (int)sizeof(Mask), "whole bins per thread, a bit per score");
+    const int tid = Team::rank();
+    // bin b is counted at place(b): a thread's BPT bins lie NT apart (no bank conflicts in the prefix sum)
+    auto place = [](int b) { return (b % BPT) * NT + b / BPT; };
+    auto asked = [&](Mask m, int j) { return j * NT < n_items && ((m >> j) & 1u); };     // (the first part is uniform)
+    Boundary first{0u, 0u};
+    uint32_t need = (uint32_t)k_eff;
+    Mask win = 0;                                     // certain winners
+    float p_lo = -(float)P, p_hi = 0.f;               // range of the negated positions
+    enum { BY_VALUE, BY_KEY, BY_POSITION };
+    for (int it = 0; it < 64; ++it) {                 // (a few steps; scores that are not finite must not hang the team)
+        const int how = !(hi > lo) ? BY_POSITION : (hi - lo < INFINITY && (float)NB / (hi - lo) < INFINITY) ? BY_VALUE : BY_KEY;
+        const uint32_t k_lo = score_key(lo);
+        const float base = how == BY_VALUE ? lo : how == BY_KEY ? 0.f : p_lo;
+        const float inv = (float)NB / (how == BY_VALUE ? hi - lo : how == BY_KEY ? (float)(score_key(hi) - k_lo) : p_hi - p_lo);
+        auto value = [&](int j) {
+            float x = v(j);
+            if (how != BY_VALUE) x = how == BY_KEY ? (float)(score_key(x) - k_lo) : -(float)pos(j);
+            return x;
+        };
+#pragma unroll UNROLL
+        for (int j = 0; j < CPT; ++j)
+            if (asked(act, j)) atomicAdd(&sm.hist[place(lin_bin<NB>(value(j), base, inv))], 1u);
+        Team::sync();
+        {   // the bin in which the counts, summed from the top, reach `need`
+            uint32_t n[BPT], local = 0, total;
+#pragma unroll
+            for (int u = 0; u < BPT; ++u) { n[u] = sm.hist[place(NB - 1 - (tid * BPT + u))]; local += n[u]; }
+            uint32_t run = team_prefix<Team>(local, total, sm, 1);
+#pragma unroll
+            for (int u = 0; u < BPT; ++u) {
+                if (run < need && need <= run + n[u]) {          // exactly one thread
+                    sm.sel[0] = (uint32_t)(NB - 1 - (tid * BPT + u));
+                    sm.sel[1] = run;
+                    sm.sel[2] = n[u];
+                }
+                run += n[u];
+            }
+        }
+        Team::sync();
+        const int B = (int)sm.sel[0];
+        const uint32_t in = sm.sel[2];
+        need -= sm.sel[1];
+        if (it == 0) first = Boundary{in, need};
+        const bool last = in <= (uint32_t)NT || it == 63;
+        // few enough: the bin's scores are ranked by composite key (score key, then inverted position: larger beats
+        // smaller, equal scores go to the lower position, no two keys are equal), the need best win
+#pragma unroll UNROLL
+        for (int j = 0; j < CPT; ++j) {
+            if (asked(act, j)) {
+                const int bj = lin_bin<NB>(value(j), base, inv);
+                if (bj > B) win |= (Mask)1 << j;
+                if (bj != B) act &= ~((Mask)1 << j);
+                else if (last) {
+                    const uint32_t o = atomicAdd(&sm.n_keys, 1u);
+                    if (o < (uint32_t)NT) sm.keys[o] = ((uint64_t)score_key(v(j)) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)pos(j));
+                }
+            }
+        }
+        if (last) {
+            const int n_in = (int)(in < (uint32_t)NT ? in : (uint32_t)NT), n8 = (n_in + 7) & ~7;
+            if (tid < n8 - n_in) sm.keys[n_in + tid] = 0ull;             // beats nothing
+            // the certain winners come first, by thread, then slot: a fixed order
+            uint32_t n_win;
+            uint32_t at = team_prefix<Team>((uint32_t)__popcll((uint64_t)win), n_win, sm, 0);
+            if (Team::NW == 1) Team::sync();
+            if (tid < n_in) {
+                const uint64_t mine[1] = {sm.keys[tid]};
+                uint32_t rank[1];
+                rank_by_comparison<1>(sm.keys, n8, mine, rank);
+                if (rank[0] < need)
+                    emit((uint32_t)k_eff - need + rank[0], key_score((uint32_t)(mine[0] >> 32)), (int32_t)(0xFFFFFFFFu - (uint32_t)mine[0]));
+            }
+#pragma unroll UNROLL
+            for (int j = 0; j < CPT; ++j)
+                if (asked(win, j)) emit(at++, v(j), pos(j));
+            break;
+        }
+        float l2 = INFINITY, h2 = -INFINITY, pl = INFINITY, ph = -INFINITY;
+#pragma unroll UNROLL
+        for (int j = 0; j < CPT; ++j) {
+            if (asked(act, j)) {
+                const float p = -(float)pos(j), s = v(j);
+                l2 = fminf(l2, s); h2 = fmaxf(h2, s);
+                pl = fminf(pl, p); ph = fmaxf(ph, p);
+            }
+        }
+        if (Team::NW == 1) Team::sync();              // (every lane has read the selection)
+        select_clear<Team>(sm);
+        team_range<Team>(l2, h2, sm, 0);
+        team_range<Team>(pl, ph, sm, 1);
+        lo = l2; hi = h2; p_lo = pl; p_hi = ph;
+    }
+    return first;
 }
 
 // Exact scores of the head's keys into the score buffer, the tiles `first`, `first + step`, ... of 16 keys, one per wave
@@ -111,10 +247,14 @@ __device__ __forceinline__ void score_keys(const Shape& sh, const Bufs& bf, int 
 // to finish adds up the shares; so a head's rows are not bound by what one compute unit can fetch (about 64 GB/s).
 template <int DT, class Cfg, int SRC>
 __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4))) attend_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
-    constexpr int NT = Cfg::NT, NW = Cfg::NW, NB = Cfg::NB, CPT = Cfg::CPT, BPT = NB / NT;
+    constexpr int NT = Cfg::NT, NW = Cfg::NW, CPT = Cfg::CPT;
+    using Team = WorkgroupTeam<NT>;
     constexpr int EPL = Elem<DT>::kPerLoad;
     constexpr int U = 8;                                  // value rows in flight per lane group
-    __shared__ AttendShared<Cfg, SRC> sm;
+    __shared__ SelectShared<Team, Cfg::NB> sm;
+    __shared__ uint64_t cand_lds[SRC == SRC_LIST ? CPT * NT : 1];      // candidates (score bits, position)
+    __shared__ uint64_t rows_lds[Cfg::ROWS];              // value rows to fetch (weight bits, position)
+    __shared__ float acc_lds[NW][256 + 1];
     const int b = blockIdx.y, h = blockIdx.x;
     const int64_t bh = (int64_t)b * sh.Hq + h;
     const int tid = threadIdx.x, lane = lane_id();
@@ -147,7 +287,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     const int P = (int)prefix_len(N, sh.window), W = N - P;      // searched prefix, window
     const int k_eff = sh.k < P ? sh.k : P;
     const float* const row = bf.scores + bh * sh.Ncap;
-    auto pos = [&](int j) { return SRC == SRC_LIST ? (int32_t)(uint32_t)sm.cand[j * NT + tid] : j * NT + tid; };
+    auto pos = [&](int j) { return SRC == SRC_LIST ? (int32_t)(uint32_t)cand_lds[j * NT + tid] : j * NT + tid; };
     float lo = INFINITY, hi = -INFINITY;                  // range of the scores in question
     if (SRC == SRC_ROW) {
         n_items = P;
@@ -162,7 +302,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
         uint32_t total;
         const uint32_t longest_w = wave_max_u32(seg_len);
         if (lane == 0) sm.hist[wave] = longest_w;
-        const uint32_t at = wg_prefix(seg_len, total, sm, 0);
+        const uint32_t at = team_prefix<Team>(seg_len, total, sm, 0);
         uint2* const segs = reinterpret_cast<uint2*>(sm.keys);
         segs[tid] = make_uint2(seg_len, at);
         const uint32_t longest = wave_max_u32(lane < NW ? sm.hist[lane] : 0u);
@@ -176,7 +316,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
             auto place = [&](int i, uint64_t ent) {       // slot i of the list: entry e of segment g
                 const uint2 s = segs[cand_slot_segment(i, log2_n_seg)];
                 const uint32_t e = (uint32_t)cand_slot_entry(i, log2_n_seg);
-                if (e < s.x) sm.cand[s.y + e] = ent;
+                if (e < s.x) cand_lds[s.y + e] = ent;
             };
             __syncthreads();
 #pragma unroll
@@ -195,7 +335,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
             for (int j = 0; j < CPT; ++j) {
                 if (j * NT < n_items) {
                     const int i = j * NT + tid;
-                    v[j] = __uint_as_float((uint32_t)(sm.cand[i < n_items ? i : 0] >> 32));
+                    v[j] = __uint_as_float((uint32_t)(cand_lds[i < n_items ? i : 0] >> 32));
                     act |= i < n_items ? 1u << j : 0u;
                 }
             }
@@ -247,7 +387,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
                 for (int o = 1; o < lpr; o <<= 1) a += wave_xor(a, o);
                 if (i < W) {
                     w_top = fmaxf(w_top, a);
-                    if (c == 0) sm.rows[k_eff + i] = (uint64_t)__float_as_uint(a) << 32;
+                    if (c == 0) rows_lds[k_eff + i] = (uint64_t)__float_as_uint(a) << 32;
                 }
             }
         }
@@ -261,15 +401,13 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
             }
         }
     }
-#pragma unroll
-    for (int u = 0; u < BPT; ++u) sm.hist[tid + u * NT] = 0;
-    if (tid == 0) sm.n_keys = 0;
     if (SRC == SRC_LIST && !usable) __syncthreads();      // (n_keys was read above)
-    wg_range(lo, hi, sm, 0);
+    select_clear<Team>(sm);
+    team_range<Team>(lo, hi, sm, 0);
     float top = hi;                                       // largest selected score
     if (W > 0) {                                          // (uniform)
         float dummy = 0.f;
-        wg_range(dummy, w_top, sm, 1);
+        team_range<Team>(dummy, w_top, sm, 1);
     }
     float M = fmaxf(k_eff > 0 ? top : -INFINITY, w_top);  // the weights' reference score
     const bool writer = blockIdx.z == 0 || !usable;       // (uniform) the workgroup that writes the selection
@@ -280,101 +418,14 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
                 idx[o] = p;
                 vals[o] = s;
             }
-            sm.rows[o] = weight(s) | (uint64_t)(uint32_t)p;
+            rows_lds[o] = weight(s) | (uint64_t)(uint32_t)p;
         }
     };
 
-    // ---- the k_eff best: bins between the smallest and the largest score in question, narrowed until the bin the k_eff-th
-    // falls in holds few.  Every step splits the scores in question: linearly by value, by their order-preserving keys
-    // where the range is beyond fp32 arithmetic, by their positions where they are all equal (the lower position wins).
-    // Scores in higher bins are winners for certain (bits of `win`).
-    uint32_t first_in = 0, first_need = 0;                // what the first step left to rank (for the head's record)
+    // ---- the k_eff best
+    Boundary left{0u, 0u};
     if (usable && k_eff > 0) {
-        uint32_t need = (uint32_t)k_eff, win = 0;
-        float p_lo = -(float)P, p_hi = 0.f;               // range of the negated positions
-        enum { BY_VALUE, BY_KEY, BY_POSITION };
-        for (int it = 0; it < 64; ++it) {                 // (a few steps; scores that are not finite must not hang the workgroup)
-            const int how = !(hi > lo) ? BY_POSITION : (hi - lo < INFINITY && (float)NB / (hi - lo) < INFINITY) ? BY_VALUE : BY_KEY;
-            const uint32_t k_lo = score_key(lo);
-            const float base = how == BY_VALUE ? lo : how == BY_KEY ? 0.f : p_lo;
-            const float inv = (float)NB / (how == BY_VALUE ? hi - lo : how == BY_KEY ? (float)(score_key(hi) - k_lo) : p_hi - p_lo);
-            auto value = [&](int j) {
-                float x = v[j];
-                if (how != BY_VALUE) x = how == BY_KEY ? (float)(score_key(x) - k_lo) : -(float)pos(j);
-                return x;
-            };
-#pragma unroll
-            for (int j = 0; j < CPT; ++j)
-                if (j * NT < n_items && ((act >> j) & 1u)) atomicAdd(&sm.hist[lin_bin<NB>(value(j), base, inv)], 1u);
-            __syncthreads();
-            {   // the bin in which the counts, summed from the top, reach `need`
-                uint32_t n[BPT], local = 0, total;
-#pragma unroll
-                for (int u = 0; u < BPT; ++u) { n[u] = sm.hist[NB - 1 - (tid * BPT + u)]; local += n[u]; }
-                uint32_t run = wg_prefix(local, total, sm, 1);
-#pragma unroll
-                for (int u = 0; u < BPT; ++u) {
-                    if (run < need && need <= run + n[u]) {          // exactly one thread
-                        sm.sel[0] = (uint32_t)(NB - 1 - (tid * BPT + u));
-                        sm.sel[1] = run;
-                        sm.sel[2] = n[u];
-                    }
-                    run += n[u];
-                }
-            }
-            __syncthreads();
-            const int B = (int)sm.sel[0];
-            const uint32_t in = sm.sel[2];
-            need -= sm.sel[1];
-            if (it == 0) { first_in = in; first_need = need; }
-            const bool last = in <= (uint32_t)NT || it == 63;
-            // few enough: the bin's scores are ranked by composite key (score key, then inverted position: larger beats
-            // smaller, equal scores go to the lower position, no two keys are equal), the need best win
-#pragma unroll
-            for (int j = 0; j < CPT; ++j) {
-                if (j * NT < n_items && ((act >> j) & 1u)) {
-                    const int bj = lin_bin<NB>(value(j), base, inv);
-                    if (bj > B) win |= 1u << j;
-                    if (bj != B) act &= ~(1u << j);
-                    else if (last) {
-                        const uint32_t o = atomicAdd(&sm.n_keys, 1u);
-                        if (o < (uint32_t)NT) sm.keys[o] = ((uint64_t)score_key(v[j]) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)pos(j));
-                    }
-                }
-            }
-            if (last) {
-                const int n_in = (int)(in < (uint32_t)NT ? in : (uint32_t)NT), n8 = (n_in + 7) & ~7;
-                if (tid < n8 - n_in) sm.keys[n_in + tid] = 0ull;             // beats nothing
-                // the certain winners come first, by thread, then slot: a fixed order
-                uint32_t n_win;
-                uint32_t at = wg_prefix((uint32_t)__popc(win), n_win, sm, 0);
-                if (tid < n_in) {
-                    const uint64_t mine[1] = {sm.keys[tid]};
-                    uint32_t rank[1];
-                    rank_by_comparison<1>(sm.keys, n8, mine, rank);
-                    if (rank[0] < need)
-                        emit((uint32_t)k_eff - need + rank[0], key_score((uint32_t)(mine[0] >> 32)), (int32_t)(0xFFFFFFFFu - (uint32_t)mine[0]));
-                }
-#pragma unroll
-                for (int j = 0; j < CPT; ++j)
-                    if (j * NT < n_items && ((win >> j) & 1u)) emit(at++, v[j], pos(j));
-                break;
-            }
-            float l2 = INFINITY, h2 = -INFINITY, pl = INFINITY, ph = -INFINITY;
-#pragma unroll
-            for (int j = 0; j < CPT; ++j) {
-                if (j * NT < n_items && ((act >> j) & 1u)) {
-                    const float p = -(float)pos(j);
-                    l2 = fminf(l2, v[j]); h2 = fmaxf(h2, v[j]);
-                    pl = fminf(pl, p); ph = fmaxf(ph, p);
-                }
-            }
-#pragma unroll
-            for (int u = 0; u < BPT; ++u) sm.hist[tid + u * NT] = 0;
-            wg_range(l2, h2, sm, 0);
-            wg_range(pl, ph, sm, 1);
-            lo = l2; hi = h2; p_lo = pl; p_hi = ph;
-        }
+        left = team_select<Team, CPT, CPT>([&](int j) { return v[j]; }, act, n_items, P, k_eff, lo, hi, sm, pos, emit);
         if (writer) pad_outputs(k_eff, sh.k, idx, vals);
     } else if (k_eff == 0) {                              // nothing to search for this sequence
         if (writer) pad_outputs(0, sh.k, idx, vals);
@@ -383,18 +434,18 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
         top = key_score(wg_select_dense<NT, 0>(sh, bf, bh, P, k_eff, sel_sm));      // writes idx, vals and their padding
         M = fmaxf(top, w_top);
         __syncthreads();
-        for (int o = tid; o < k_eff; o += NT) sm.rows[o] = weight(vals[o]) | (uint64_t)(uint32_t)idx[o];
+        for (int o = tid; o < k_eff; o += NT) rows_lds[o] = weight(vals[o]) | (uint64_t)(uint32_t)idx[o];
     }
     if (SRC == SRC_LIST && tid == 0 && writer) {          // the head's record, as the chip-wide selection leaves it
         uint32_t* const rec = bf.tailrec + 4 * bh;
         const bool sel = usable && k_eff > 0;
         rec[0] = k_eff == 0 ? 2u : usable ? 0u : 1u;
-        rec[1] = sel ? (uint32_t)k_eff - first_need : 0u;
-        rec[2] = sel ? first_need : 0u;
-        rec[3] = sel ? first_in : 0u;
+        rec[1] = sel ? (uint32_t)k_eff - left.need : 0u;
+        rec[2] = sel ? left.need : 0u;
+        rec[3] = sel ? left.in : 0u;
     }
     for (int i = tid; i < W; i += NT)
-        sm.rows[k_eff + i] = weight(SRC == SRC_ROW ? row[P + i] : __uint_as_float((uint32_t)(sm.rows[k_eff + i] >> 32))) | (uint64_t)(uint32_t)(P + i);
+        rows_lds[k_eff + i] = weight(SRC == SRC_ROW ? row[P + i] : __uint_as_float((uint32_t)(rows_lds[k_eff + i] >> 32))) | (uint64_t)(uint32_t)(P + i);
     __syncthreads();
 
     // ---- the weighted value rows (of this workgroup's share)
@@ -413,7 +464,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int jj = j + u * step < row_end ? j + u * step : j;
-            const uint64_t e = sm.rows[jj];
+            const uint64_t e = rows_lds[jj];
             w[u] = j + u * step < row_end ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
             const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
             raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * Elem<DT>::kBytes);
@@ -444,14 +495,14 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     }
     if (rs == 0) {
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) sm.acc[wave][c * EPL + e] = acc[e];
-        if (c == 0) sm.acc[wave][256] = lsum;
+        for (int e = 0; e < EPL; ++e) acc_lds[wave][c * EPL + e] = acc[e];
+        if (c == 0) acc_lds[wave][256] = lsum;
     }
     __syncthreads();
     float a = 0.f, l = 0.f;                               // thread t < D: channel t (D <= NT)
     if (tid < D) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w) { a += sm.acc[w][tid]; l += sm.acc[w][256]; }
+        for (int w = 0; w < NW; ++w) { a += acc_lds[w][tid]; l += acc_lds[w][256]; }
     }
     if (SRC == SRC_LIST && shares > 1) {
         // Leave the share where the head's other workgroups see it (agent-scope stores go through to memory, and the wait
@@ -484,6 +535,150 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
         bf.out[bh * D + tid] = a / l;
         if (tid == 0 && bf.lse) bf.lse[bh] = M * scale + logf(l);
     }
+}
+
+// Batches of short sequences: scores, selection and attention of a KV head's query heads in one launch, a workgroup per key
+// stream.  The four waves score the stream's tiles with the scan's routines and leave the scores in LDS; then
+// each wave selects for one head of the group and fetches its rows, with no barrier between the waves.  The step is
+// bound by reading the keys; two or more workgroups per compute unit, each in a phase of its own, keep that going
+// while others select.  ROW: scores of the longest sequence.  192 sequences of 2048 .. 4096 tokens, k = 128 (1.2 GB of keys,
+// 0.2 GB of value rows): 281 us = 5.0 TB/s; scan with stored scores, radix select and gather before: 277 + 70 + 42 us.
+constexpr int kShortBins = 256;
+template <int DT, int D, int ROW>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
+attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
+    using v8 = typename Mfma<DT>::v8;
+    constexpr int CPT = ROW / kWave, ROWS = attend_short_k(ROW), EPL = 8, LPR = D / EPL, RPW = kWave / LPR, U = 8;
+    using Mask = typename std::conditional<(CPT > 32), uint64_t, uint32_t>::type;
+    __shared__ float scores_lds[4][ROW];
+    __shared__ uint64_t rows_all_lds[4][ROWS];            // rows to fetch (weight bits, position)
+    __shared__ SelectShared<WaveTeam, kShortBins> sms[4];
+    const int kvh = blockIdx.x, b = blockIdx.y, G = sh.G;
+    const int64_t head0 = (int64_t)b * sh.Hq + (int64_t)kvh * G;
+    const int lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int N = bf.len[b];                              // (no window on this path)
+    const char* const Kh = static_cast<const char*>(bf.K) + ((int64_t)b * sh.Hkv + kvh) * sh.Ncap * (D * 2);
+    {
+        v8 qa[D / 32];
+        load_query_a<DT, D>(bf.q, head0, G, qa);
+        struct TileB { v8 b[4][D / 32]; } ba, bb;
+        auto use = [&](TileB& t, int64_t ti) {
+            const f32x4 res = tile_mac<DT, D>(t.b, qa);
+            const int item = (int)ti * 64 + lane;
+            if (item < N) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (r < G) scores_lds[r][item] = res[r] + 0.0f;          // -0 counts as +0
+            }
+        };
+        const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
+        const int64_t rest = walk_tiles<ScanPipelined<D>::value>(wave, N / 64, 4, ba, bb,
+            [&](TileB& t, int64_t ti) { tile_load_full<DT, D>(Kh + ti * (64 * D * 2), lane_off, t.b); }, use);
+        if (rest * 64 < N) {                              // the tile the end of the sequence cuts short
+            tile_load<DT, D>(Kh, [&](int slot) { const int64_t p = rest * 64 + slot; return p < N ? p : (int64_t)(N - 1); }, ba.b);
+            use(ba, rest);
+        }
+    }
+    __syncthreads();
+    if (wave >= G) return;                                // (no barrier of the workgroup follows)
+
+    const int64_t bh = head0 + wave;
+    const int k_eff = sh.k < N ? sh.k : N;
+    int32_t* const idx = bf.sel_idx + bh * sh.k;
+    float* const vals = bf.sel_val + bh * sh.k;
+    SelectShared<WaveTeam, kShortBins>& sm = sms[wave];
+    // (64 scores of a lane in registers spilled: they stay in LDS, eight reads in flight)
+    const float* const row = scores_lds[wave] + lane;
+    Mask act = 0;
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll 8
+    for (int j = 0; j < CPT; ++j) {
+        if (j * kWave + lane < N) {
+            const float s = row[j * kWave];
+            act |= (Mask)1 << j;
+            lo = fminf(lo, s); hi = fmaxf(hi, s);
+        }
+    }
+    select_clear<WaveTeam>(sm);
+    team_range<WaveTeam>(lo, hi, sm, 0);
+    const float M = hi;                                   // the weights' reference score
+    uint64_t* const rows_lds = rows_all_lds[wave];
+    team_select<WaveTeam, CPT, 8>([&](int j) { return row[j * kWave]; }, act, N, N, k_eff, lo, hi, sm,
+                                  [&](int j) { return j * kWave + lane; }, [&](uint32_t o, float s, int32_t p) {
+        if (o < (uint32_t)k_eff) {                        // always true; guards the buffers
+            idx[o] = p;
+            vals[o] = s;
+            rows_lds[o] = ((uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32) | (uint64_t)(uint32_t)p;
+        }
+    });
+    for (int o = k_eff + lane; o < sh.k; o += kWave) { idx[o] = -1; vals[o] = -INFINITY; }
+    wave_sync();
+
+    const char* const Vh = static_cast<const char*>(bf.V) + ((int64_t)b * sh.Hkv + kvh) * sh.Ncap * (D * 2);
+    const int rs = lane / LPR, c = lane % LPR;
+    float acc[EPL], l = 0.f;
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+    for (int j = rs; j < k_eff; j += U * RPW) {
+        float w[U];
+        u32x4 raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint64_t e = rows_lds[j + u * RPW < k_eff ? j + u * RPW : j];
+            w[u] = j + u * RPW < k_eff ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
+            const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
+            raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * 2);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float vf[EPL];
+            Elem<DT>::widen(raw[u], vf);
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w[u], vf[e], acc[e]);
+            l += w[u];
+        }
+    }
+#pragma unroll
+    for (int o = LPR; o < kWave; o <<= 1) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] = o == 32 ? add_lanes_32(acc[e]) : o == 16 ? add_lanes_16(acc[e]) : acc[e] + wave_xor(acc[e], o);
+        l = o == 32 ? add_lanes_32(l) : o == 16 ? add_lanes_16(l) : l + wave_xor(l, o);
+    }
+    if (rs == 0) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) bf.out[bh * D + c * EPL + e] = acc[e] / l;
+    }
+    if (lane == 0) {
+        bf.hmax[bh] = M;
+        if (bf.lse) bf.lse[bh] = M * scale + logf(l);
+    }
+}
+
+hipError_t launch_attend_short(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
+    const float scale = 1.0f / sqrtf((float)s.D);
+    const float scale_log2e = scale * 1.4426950408889634f;
+    const dim3 grid((unsigned)s.Hkv, (unsigned)s.B);
+    if (s.M != 1 || s.G > 4 || s.window || s.k > attend_short_k(Nmax)) return hipErrorInvalidValue;
+#define TKA_AS(DT_, D_, ROW_) hipLaunchKernelGGL((attend_short_kernel<DT_, D_, ROW_>), grid, dim3(256), 0, st, s, b, scale, scale_log2e)
+#define TKA_AS_ROW(DT_, D_)                           \
+    do {                                              \
+        if (Nmax <= 1024) TKA_AS(DT_, D_, 1024);      \
+        else if (Nmax <= 2048) TKA_AS(DT_, D_, 2048); \
+        else TKA_AS(DT_, D_, 4096);                   \
+    } while (0)
+    if (s.dtype == DT_F16 && s.D == 128) TKA_AS_ROW(DT_F16, 128);
+    else if (s.dtype == DT_BF16 && s.D == 128) TKA_AS_ROW(DT_BF16, 128);
+    else if (s.dtype == DT_F16 && s.D == 64) TKA_AS_ROW(DT_F16, 64);
+    else if (s.dtype == DT_BF16 && s.D == 64) TKA_AS_ROW(DT_BF16, 64);
+    else if (s.dtype == DT_F16 && s.D == 256) TKA_AS_ROW(DT_F16, 256);
+    else if (s.dtype == DT_BF16 && s.D == 256) TKA_AS_ROW(DT_BF16, 256);
+    else if (s.dtype == DT_F16 && s.D == 32) TKA_AS_ROW(DT_F16, 32);
+    else if (s.dtype == DT_BF16 && s.D == 32) TKA_AS_ROW(DT_BF16, 32);
+    else return hipErrorInvalidValue;
+#undef TKA_AS_ROW
+#undef TKA_AS
+    return hipGetLastError();
 }
 
 hipError_t launch_attend_row(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {

@@ -39,7 +39,7 @@ struct Shape {
     int force_redo;   // measurement aid: treat every head as not filterable (exact redo of all heads)
     int paged;        // the scan skips the pages the coarse page index rules out
     int no_rescan;    // an unusable list is redone densely (the per-bin counts of a paged scan are not those of the plain tile order)
-    int attend;       // selection and attention of a head in one launch (attend.hip) by this many workgroups; 0: the other back ends
+    int attend;       // selection and attention of a head in one launch (attend.hip) by this many workgroups, kAttendShort: its scores too; 0: the other back ends
     int page_cap;     // pages per key stream the page index has room for (ceil(Ncap / 64))
     int page_words;   // 64-bit words of the page mask per key stream
     int k;            // requested k (k_eff = min(k, searched prefix of sequence b))
@@ -215,6 +215,11 @@ inline int attend_row_rows(int64_t heads, int64_t Nmax) {
     return Nmax <= 4096 ? 1024 : 2048;
 }
 
+// The same with the scores of a key stream in LDS (batches of short sequences): largest k for rows of up to Nmax scores, 0
+// where they are too long.  (Two workgroups of 4096 scores and 256 rows per head share a compute unit's LDS.)
+constexpr int attend_short_k(int64_t Nmax) { return Nmax <= 2048 ? 512 : Nmax <= 4096 ? 256 : 0; }
+constexpr int kAttendShort = -1;
+
 // Position of sample s: one jittered position inside each stride-long stratum.
 __host__ __device__ inline int64_t sample_pos(int s, int stride) {
     uint32_t h = (uint32_t)s * 2654435761u;
@@ -233,6 +238,7 @@ hipError_t launch_select_full(const Shape& s, const Bufs& b, int64_t Nmax, hipSt
 
 // selection and attention of a head in one launch (reached through launch_select_full and launch_tail, Shape::attend)
 hipError_t launch_attend_row(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st);
+hipError_t launch_attend_short(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st);
 hipError_t launch_attend_list(const Shape& s, const Bufs& b, hipStream_t st);
 
 hipError_t launch_gather(const Shape& s, const Bufs& b, hipStream_t st);

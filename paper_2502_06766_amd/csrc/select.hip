@@ -230,6 +230,7 @@ hipError_t launch_threshold(const Shape& s, const Bufs& b, int64_t Nmax, hipStre
     return hipGetLastError();
 }
 hipError_t launch_select_full(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
+    if (s.attend == kAttendShort) return launch_attend_short(s, b, Nmax, st);
     if (s.attend) return launch_attend_row(s, b, Nmax, st);
     const dim3 grid(s.Hq, s.B);
 #define TKA_SF(NT_, CPT_) hipLaunchKernelGGL((select_full_kernel<NT_, CPT_>), grid, dim3(NT_), 0, st, s, b)

@@ -71,6 +71,40 @@ def test_sizes_at_the_edges(dtype, B, Hq, Hkv, N, d, k, window):
         H.check_unmargined(tuple(r[b] for r in res), q[b], K[b], V[b], dtype, k, window, f"N={N} k={k} seq {b}")
 
 
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,N,d,k", [
+    (wl.F16, 2, 4, 1, 1, 64, 1),                     # one token
+    (wl.BF16, 1, 3, 3, 65, 32, 90),                  # k beyond the cache, a second tile of one key
+    (wl.F16, 3, 8, 2, 512, 128, 512),                # everything selected, as many rows as fit
+    (wl.F16, 3, 8, 2, 512, 128, 513),                # one too many: rows and scores in two launches
+    (wl.BF16, 32, 16, 4, 1024, 128, 100),            # 128 streams
+    (wl.F16, 32, 24, 8, 1025, 64, 512),              # 256 streams, groups of three
+    (wl.BF16, 32, 8, 8, 2048, 256, 33),              # groups of one
+    (wl.F16, 64, 8, 4, 2049, 32, 256),
+    (wl.BF16, 64, 16, 4, 4096, 64, 256),
+    (wl.BF16, 64, 8, 4, 4097, 64, 256),              # one token too many
+])
+def test_short_sequences_in_one_launch(dtype, B, Hq, Hkv, N, d, k):
+    q, K, V = _make(dtype, B, Hq, Hkv, N, d, seed=N + k + B)
+    res = _decode(q, K, V, dtype, k)
+    for b in sorted({0, B // 2, B - 1}):
+        H.check_unmargined(tuple(r[b] for r in res), q[b], K[b], V[b], dtype, k, 0, f"N={N} k={k} seq {b}")
+
+
+def test_short_sequences_with_ties():
+    """Hundreds of equal scores per head, more than a wave ranks at once: the bins go on over the positions."""
+    g = np.random.default_rng(17)
+    dtype, B, Hq, Hkv, N, d, k = wl.F16, 64, 16, 4, 3000, 64, 200
+    q = wl.quantize(g.integers(-1, 2, (B, Hq, d)).astype(np.float32), dtype)
+    q[1] = 0                                         # all scores of a sequence equal
+    K = [wl.quantize(g.integers(-1, 2, (Hkv, N, d)).astype(np.float32), dtype) for _ in range(B)]
+    V = [wl.quantize(g.standard_normal((Hkv, N, d)).astype(np.float32), dtype) for _ in range(B)]
+    res = _decode(q, K, V, dtype, k)
+    for b in (0, 1, 63):
+        ref = c_oracle.topk_attention(q[b], K[b], V[b], dtype, k)
+        H.check_against_oracle(*(r[b] for r in res), ref, np.full(Hq, 1e-30), k, H.out_tolerance(dtype),
+                               float(np.abs(wl.widen(V[b], dtype)).max()), f"seq {b}")
+
+
 @pytest.mark.parametrize("path,dtype,N,k", [(ta.PATH_FULL, wl.F16, 9000, 2500), (ta.PATH_FULL, wl.F32, 3000, 5),
                                             (ta.PATH_FILTER, wl.F16, 9000, 1300), (ta.PATH_FILTER, wl.BF16, 120000, 300)])
 @pytest.mark.parametrize("spread", [0, 1])
