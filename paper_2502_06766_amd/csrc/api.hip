@@ -168,6 +168,58 @@ __global__ void append_kernel(const char* __restrict__ ksrc, const char* __restr
     if (blockIdx.x == 0 && threadIdx.x == 0) *len_slot = new_len;
 }
 
+// The same with the int8 codes of the key rows (topk_attn.h: code = rint(x 127 / amax), scale = amax / 127): the rows are coded
+// from the registers that carry them, so a bulk import reads the keys once.  Blocks of rows in grid x, KV heads in
+// grid y; D / 8 lanes per row, kAppend8Rows rows in flight per lane group.  100001 tokens, 8 KV heads, d = 128
+// (0.93 GB moved): 220 us per import with the coding in a launch of its own, 172 us (5.4 TB/s) now.
+constexpr int kAppend8Rows = 4;
+template <int DT, int D>
+__global__ void __launch_bounds__(256)
+append8_kernel(const char* __restrict__ ksrc, const char* __restrict__ vsrc, char* __restrict__ kdst, char* __restrict__ vdst,
+               int64_t n_new, int64_t token_stride_b, int64_t head_stride_b, int64_t dst_head_stride_b, int8_t* __restrict__ codes,
+               float* __restrict__ scales, int64_t ncap, int32_t* len_slot, int32_t new_len) {
+    constexpr int LPR = D / 8, RPP = 256 / LPR, U = kAppend8Rows;      // lanes per row, rows per pass of the workgroup
+    const int h = blockIdx.y, c = threadIdx.x % LPR;
+    const int64_t t0 = (int64_t)blockIdx.x * (RPP * U) + threadIdx.x / LPR;
+    const char* const ks = ksrc + h * head_stride_b + c * 16;
+    const char* const vs = vsrc + h * head_stride_b + c * 16;
+    u32x4 k[U], v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t t = t0 + u * RPP, r = t < n_new ? t : n_new - 1;
+        k[u] = *reinterpret_cast<const u32x4*>(ks + r * token_stride_b);
+        v[u] = *reinterpret_cast<const u32x4*>(vs + r * token_stride_b);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t t = t0 + u * RPP;
+        float x[8];
+        Elem<DT>::widen(k[u], x);
+        float amax = 0.f;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(x[e]));
+        amax = group_reduce<MaxOp, LPR>(amax);
+        const bool live = amax >= kTinyRow;
+        const float inv = live ? 127.0f / amax : 0.f;
+        uint32_t w[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            uint32_t p = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) p |= ((uint32_t)(int)rintf(x[4 * i + e] * inv) & 0xFFu) << (8 * e);
+            w[i] = p;
+        }
+        if (t < n_new) {
+            const int64_t d_o = h * dst_head_stride_b + (t * LPR + c) * 16, row = h * ncap + t;
+            *reinterpret_cast<u32x4*>(kdst + d_o) = k[u];
+            *reinterpret_cast<u32x4*>(vdst + d_o) = v[u];
+            *reinterpret_cast<uint2*>(codes + row * D + c * 8) = make_uint2(w[0], w[1]);
+            if (c == 0) scales[row] = live ? amax / 127.0f : 0.f;
+        }
+    }
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *len_slot = new_len;
+}
+
 __global__ void set_len_kernel(int32_t* len_slot, int32_t v) { *len_slot = v; }
 
 // n_new tokens for every sequence of a layer: source [B][n_new][Hkv][row], destination row
@@ -402,6 +454,28 @@ int topk_attn_append_kv(topk_attn_t* h, int layer, int seq, const void* k_new, c
     char* vdst = static_cast<char*>(c.kv_storage) + h->kv_half + off;
     int32_t* len_dev = reinterpret_cast<int32_t*>(static_cast<char*>(c.workspace) + h->ws.len) + slot;
     const int chunks = (int)(row_b / 16);
+    if (c.index_kind == TOPK_ATTN_INDEX_INT8) {
+        char* base = static_cast<char*>(c.kv_storage) + 2 * h->kv_half;
+        const int64_t row0 = (int64_t)slot * c.n_kv_heads * c.max_tokens + cur;
+        int8_t* codes = reinterpret_cast<int8_t*>(base) + row0 * c.head_dim;
+        float* scales = reinterpret_cast<float*>(base + index_codes_bytes(&c)) + row0;
+        const int64_t rows_per_block = (int64_t)kAppend8Rows * (256 / (c.head_dim / 8));
+        const dim3 grid((unsigned)((n_new + rows_per_block - 1) / rows_per_block), (unsigned)c.n_kv_heads);
+#define TKA_A8(DT_, D_)                                                                                                     \
+    hipLaunchKernelGGL((append8_kernel<DT_, D_>), grid, dim3(256), 0, (hipStream_t)hip_stream, static_cast<const char*>(k_new), \
+                       static_cast<const char*>(v_new), kdst, vdst, n_new, token_stride * e, head_stride * e, head_b, codes,   \
+                       scales, c.max_tokens, len_dev, (int32_t)(cur + n_new))
+        if (c.dtype == TOPK_ATTN_F16 && c.head_dim == 128) TKA_A8(DT_F16, 128);
+        else if (c.dtype == TOPK_ATTN_BF16 && c.head_dim == 128) TKA_A8(DT_BF16, 128);
+        else if (c.dtype == TOPK_ATTN_F16 && c.head_dim == 64) TKA_A8(DT_F16, 64);
+        else if (c.dtype == TOPK_ATTN_BF16 && c.head_dim == 64) TKA_A8(DT_BF16, 64);
+        else if (c.dtype == TOPK_ATTN_F16 && c.head_dim == 256) TKA_A8(DT_F16, 256);
+        else TKA_A8(DT_BF16, 256);
+#undef TKA_A8
+        if (hipGetLastError() != hipSuccess) return TOPK_ATTN_EDEVICE;
+        h->len[slot] = cur + n_new;
+        return TOPK_ATTN_OK;
+    }
     const int64_t total = n_new * c.n_kv_heads * chunks;
     int64_t blocks = (total + 255) / 256;
     if (blocks > 65536) blocks = 65536;
@@ -410,15 +484,6 @@ int topk_attn_append_kv(topk_attn_t* h, int layer, int seq, const void* k_new, c
                        c.n_kv_heads, chunks, token_stride * e, head_stride * e, head_b, len_dev,
                        (int32_t)(cur + n_new));
     if (hipGetLastError() != hipSuccess) return TOPK_ATTN_EDEVICE;
-    if (c.index_kind == TOPK_ATTN_INDEX_INT8) {   // code the rows just written (stream order: after the copy)
-        char* base = static_cast<char*>(c.kv_storage) + 2 * h->kv_half;
-        const int64_t row0 = (int64_t)slot * c.n_kv_heads * c.max_tokens + cur;
-        int8_t* codes = reinterpret_cast<int8_t*>(base) + row0 * c.head_dim;
-        float* scales = reinterpret_cast<float*>(base + index_codes_bytes(&c)) + row0;
-        if (launch_quantize_rows(c.dtype, c.head_dim, kdst, n_new, head_b, c.n_kv_heads, codes, scales, c.max_tokens,
-                                 (hipStream_t)hip_stream) != hipSuccess)
-            return TOPK_ATTN_EDEVICE;
-    }
     if (c.index_kind == TOPK_ATTN_INDEX_PAGES) {   // balls of the pages just touched (stream order: after the copy)
         char* base = static_cast<char*>(c.kv_storage) + 2 * h->kv_half;
         const int64_t pcap = page_cap_of(&c);

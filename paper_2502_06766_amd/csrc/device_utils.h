@@ -93,6 +93,29 @@ __device__ __forceinline__ float add_lanes_32(float v) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// Sum or maximum over groups of LPR neighbouring lanes (4 .. 64, a power of two), in all lanes of the group: a butterfly over
+// lane ^ 1, ^ 2, ^ 4, ... in the vector unit.  (Where the lanes of a quad, or of half a row, already agree, the mirrored
+// lane holds what the exchanged lane does.)
+struct AddOp { static __device__ __forceinline__ float f(float a, float b) { return a + b; } };
+struct MaxOp { static __device__ __forceinline__ float f(float a, float b) { return fmaxf(a, b); } };
+template <class Op, int LPR>
+__device__ __forceinline__ float group_reduce(float v) {
+    static_assert(LPR >= 4 && LPR <= 64, "groups of 4 to 64 lanes");
+    v = Op::f(v, dpp_f32<0xB1, 0xF>(0.f, v));                  // quad_perm 1,0,3,2
+    v = Op::f(v, dpp_f32<0x4E, 0xF>(0.f, v));                  // quad_perm 2,3,0,1
+    if (LPR >= 8) v = Op::f(v, dpp_f32<0x141, 0xF>(0.f, v));   // row_half_mirror
+    if (LPR >= 16) v = Op::f(v, dpp_f32<0x140, 0xF>(0.f, v));  // row_mirror
+    if (LPR >= 32) {
+        const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = Op::f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    if (LPR >= 64) {
+        const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+        v = Op::f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    }
+    return v;
+}
+
 // widen the 16 bytes a lane loaded into fp32 values
 template <int DT> struct Elem;
 template <> struct Elem<0> {  // fp32

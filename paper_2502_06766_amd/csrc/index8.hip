@@ -20,8 +20,6 @@ namespace tka {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
-constexpr float kTinyRow = 7.888609052210118e-31f;   // 2^-100
-
 // ---------------------------------------------------------------------------------------
 // Row coding.  A row of D elements is spread over D / 8 lanes (16-bit storage, 16 bytes
 // per lane); row r is row r % rows_per_head of head r / rows_per_head.

@@ -227,6 +227,8 @@ __host__ __device__ inline int64_t sample_pos(int s, int stride) {
     return (int64_t)s * stride + (int64_t)(h % (uint32_t)stride);
 }
 
+constexpr float kTinyRow = 7.888609052210118e-31f;   // 2^-100: key rows whose largest element is below are coded as zeros (int8 index)
+
 // Launch wrappers (each returns the hipError_t of the launch).
 hipError_t launch_scan_sample(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st);
 hipError_t launch_scan_filter(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st);
