@@ -586,52 +586,54 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     }
 }
 
-// Plain FMA scoring for what the MFMA kernels do not take (fp32 caches): a row of D elements is spread over D*e/16 lanes, 16 bytes each.
-template <int DT>
+// Plain FMA scoring of fp32 caches: a row of D elements is spread over D / 4 lanes, 16 bytes each, U rows per lane group
+// with all loads under way before the query is staged.  Few rows are a chain of latencies (one head, 4096 rows: sixteen
+// workgroups that took their rows one after the other 11.4 us, a workgroup per 16 rows 3.0; 8 heads,
+// 16k tokens, d = 128 31.9 -> 5.3).
+template <int D, int U>
 __global__ void __launch_bounds__(256)
-scan_generic_kernel(Shape sh, Bufs bf, int rows_per_block, float* dst) {
-    constexpr int EPL = Elem<DT>::kPerLoad;
+scan_f32_kernel(Shape sh, Bufs bf, float* dst) {
+    constexpr int LPR = D / 4, RPP = 256 / LPR;            // lanes per row, rows per pass of the workgroup
     const int b = blockIdx.z, kvh = blockIdx.y;
-    const int G = sh.G, D = sh.D;
+    const int G = sh.G;
     const int64_t head0 = (int64_t)b * sh.Hq + (int64_t)kvh * G;
     const int64_t N = prefix_len(visible_len(sh, bf, b), sh.window);
-    const int64_t row_begin = (int64_t)blockIdx.x * rows_per_block;
-    if (row_begin >= N) return;
-
-    __shared__ float q_lds[16 * 256];
-    for (int i = threadIdx.x; i < G * D; i += blockDim.x) {
-        const char* qp = static_cast<const char*>(bf.q) + (head0 * D + i) * Elem<DT>::kBytes;
-        float v;
-        if (DT == DT_F32) v = *reinterpret_cast<const float*>(qp);
-        else if (DT == DT_F16) v = (float)*reinterpret_cast<const _Float16*>(qp);
-        else v = __uint_as_float((uint32_t)*reinterpret_cast<const uint16_t*>(qp) << 16);
-        q_lds[i] = v;
+    const int64_t row0 = (int64_t)blockIdx.x * (RPP * U) + threadIdx.x / LPR;
+    if ((int64_t)blockIdx.x * (RPP * U) >= N) return;
+    const int c = threadIdx.x % LPR;
+    const float* Kh = static_cast<const float*>(bf.K) + ((int64_t)cache_seq(sh, b) * sh.Hkv + kvh) * sh.Ncap * D + c * 4;
+    f32x4 k[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int64_t r = row0 + u * RPP;
+        k[u] = *reinterpret_cast<const f32x4*>(Kh + (r < N ? r : N - 1) * D);
     }
+    __shared__ __align__(16) float q_lds[16 * 256];
+    for (int i = threadIdx.x; i < G * D; i += 256) q_lds[i] = static_cast<const float*>(bf.q)[head0 * D + i];
     __syncthreads();
-
-    const int lpr = D / EPL;              // lanes per row (power of two, <= 64)
-    const int rows_per_pass = blockDim.x / lpr;
-    const int slot = threadIdx.x / lpr, chunk = threadIdx.x % lpr;
-    const char* Kh = static_cast<const char*>(bf.K) +
-                     ((int64_t)cache_seq(sh, b) * sh.Hkv + kvh) * sh.Ncap * D * Elem<DT>::kBytes;
-    int64_t row_end = row_begin + rows_per_block;
-    if (row_end > N) row_end = N;
-    for (int64_t base = row_begin; base < row_end; base += rows_per_pass) {
-        const int64_t row = base + slot;
-        const bool valid = row < row_end;
-        const int64_t lrow = valid ? row : row_end - 1;
-        const u32x4 raw = *reinterpret_cast<const u32x4*>(Kh + (lrow * D + chunk * EPL) * Elem<DT>::kBytes);
-        float kf[EPL];
-        Elem<DT>::widen(raw, kf);
-        for (int r = 0; r < G; ++r) {
-            const float* qr = q_lds + r * D + chunk * EPL;
+    for (int h = 0; h < G; ++h) {
+        const f32x4 q = *reinterpret_cast<const f32x4*>(q_lds + h * D + c * 4);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
             float acc = 0.f;
 #pragma unroll
-            for (int e = 0; e < EPL; ++e) acc = fmaf(kf[e], qr[e], acc);
-            for (int m = 1; m < lpr; m <<= 1) acc += wave_xor(acc, m);
-            if (valid && chunk == 0) dst[(head0 + r) * sh.Ncap + row] = acc;
+            for (int e = 0; e < 4; ++e) acc = fmaf(k[u][e], q[e], acc);
+            acc = group_reduce<AddOp, LPR>(acc);
+            const int64_t r = row0 + u * RPP;
+            if (r < N && c == 0) dst[(head0 + h) * sh.Ncap + r] = acc;
         }
     }
+}
+
+template <int D>
+static void launch_scan_f32(const Shape& s, const Bufs& b, int64_t Nmax, float* dst, hipStream_t st) {
+    // four rows per lane group once the chip is full of workgroups with one
+    constexpr int64_t kRowsPerPass = 256 / (D / 4);
+    const int64_t passes = (Nmax + kRowsPerPass - 1) / kRowsPerPass;
+    if (passes * s.Hkv * s.B <= 1024)
+        hipLaunchKernelGGL((scan_f32_kernel<D, 1>), dim3((unsigned)passes, (unsigned)s.Hkv, (unsigned)s.B), dim3(256), 0, st, s, b, dst);
+    else
+        hipLaunchKernelGGL((scan_f32_kernel<D, 4>), dim3((unsigned)((passes + 3) / 4), (unsigned)s.Hkv, (unsigned)s.B), dim3(256), 0, st, s, b, dst);
 }
 
 bool scan_mfma_supported(const Shape& s) {
@@ -724,17 +726,11 @@ hipError_t launch_scan_filter(const Shape& s, const Bufs& b, int64_t Nmax, hipSt
 
 hipError_t launch_scan_full(const Shape& s, const Bufs& b, int64_t Nmax, float* dst, hipStream_t st) {
     if (scan_mfma_supported(s)) return launch_mfma<MODE_FULL>(s, b, Nmax, dst, st);
-    const int epl = s.dtype == DT_F32 ? 4 : 8;
-    const int lpr = s.D / epl;
-    const int rows_per_pass = 256 / lpr;
-    int64_t rows_per_block = (int64_t)rows_per_pass * 16;
-    dim3 grid((unsigned)((Nmax + rows_per_block - 1) / rows_per_block), (unsigned)s.Hkv, (unsigned)s.B);
-    if (s.dtype == DT_F32)
-        hipLaunchKernelGGL((scan_generic_kernel<DT_F32>), grid, dim3(256), 0, st, s, b, (int)rows_per_block, dst);
-    else if (s.dtype == DT_F16)
-        hipLaunchKernelGGL((scan_generic_kernel<DT_F16>), grid, dim3(256), 0, st, s, b, (int)rows_per_block, dst);
-    else
-        hipLaunchKernelGGL((scan_generic_kernel<DT_BF16>), grid, dim3(256), 0, st, s, b, (int)rows_per_block, dst);
+    if (s.D == 64) launch_scan_f32<64>(s, b, Nmax, dst, st);
+    else if (s.D == 128) launch_scan_f32<128>(s, b, Nmax, dst, st);
+    else if (s.D == 256) launch_scan_f32<256>(s, b, Nmax, dst, st);
+    else if (s.D == 32) launch_scan_f32<32>(s, b, Nmax, dst, st);
+    else return hipErrorInvalidValue;
     return hipGetLastError();
 }
 
