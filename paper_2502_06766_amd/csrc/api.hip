@@ -25,7 +25,7 @@ inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 inline int elem_bytes(int dtype) { return dtype == TOPK_ATTN_F32 ? 4 : 2; }
 
 struct WsLayout {
-    size_t len, thr, bins, samp, seg_cnt, seg_max, seg_cnt2, flags, hmax, fallback, tailrec, qscale, q8, page_mask, page_cnt, page_list, hist, cand, bnd, scores, sel_idx, sel_val, part_acc, part_l, part_m, total;
+    size_t len, thr, bins, samp, seg_cnt, seg_max, seg_cnt2, flags, hmax, fallback, tailrec, page_mask, page_cnt, page_list, hist, cand, bnd, scores, sel_idx, sel_val, part_acc, part_l, part_m, total;
     int cand_cap, bnd_cap, n_chunk_cap, hist_cap, page_words;
 };
 
@@ -129,8 +129,6 @@ WsLayout ws_layout(const topk_attn_config* c) {
     w.hmax = take(BH * sizeof(float));
     w.fallback = take(sizeof(uint32_t));
     w.tailrec = take(BH * 4 * sizeof(uint32_t));
-    w.qscale = take(BH * sizeof(float));
-    w.q8 = take(BH * (size_t)c->head_dim);
     w.page_words = (int)((page_cap_of(c) + 63) / 64);
     const size_t page_streams = c->index_kind == TOPK_ATTN_INDEX_PAGES ? (size_t)c->n_seqs * c->n_kv_heads : 0;
     w.page_mask = take(page_streams * (size_t)w.page_words * sizeof(uint64_t));
@@ -605,8 +603,6 @@ static void fill_call(topk_attn_t* h, int layer, const void* q, int k, int n_que
     b->page_mask = reinterpret_cast<uint64_t*>(ws + h->ws.page_mask);
     b->page_cnt = reinterpret_cast<uint32_t*>(ws + h->ws.page_cnt);
     b->page_list = reinterpret_cast<int32_t*>(ws + h->ws.page_list);
-    b->q8 = reinterpret_cast<int8_t*>(ws + h->ws.q8);
-    b->qscale = reinterpret_cast<float*>(ws + h->ws.qscale);
     b->len = reinterpret_cast<int32_t*>(ws_len + h->ws.len) + (size_t)layer * c.n_seqs;
     b->thr = reinterpret_cast<float*>(ws + h->ws.thr);
     b->bins = reinterpret_cast<float*>(ws + h->ws.bins);
@@ -787,8 +783,7 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
     }
     const bool timed = h->timing && h->ev_used < kTimingSlots;
     if (fast && s.indexed) {
-        e = launch_quantize_rows(s.dtype, s.D, q, (int64_t)s.B * s.Hq, 0, 1, b.q8, b.qscale, 0, st);
-        if (e == hipSuccess) e = launch_scan8_sample(s, b, nmax, st);
+        e = launch_scan8_sample(s, b, nmax, st);
         if (e == hipSuccess) e = launch_threshold(s, b, nmax, st);
         if (e == hipSuccess && timed) e = hipEventRecord(h->ev[2 * h->ev_used], st);
         if (e == hipSuccess) e = launch_scan8_filter(s, b, st);
@@ -925,8 +920,7 @@ int topk_attn_scores(topk_attn_t* h, int layer, const void* q, float* scores, vo
     fill_call(h, layer, q, 1, 1, &s, &b);
     hipError_t e;
     if (h->path == TOPK_ATTN_PATH_INDEX && s.G <= 4) {   // approximate scores from the codes
-        e = launch_quantize_rows(s.dtype, s.D, q, (int64_t)s.B * s.Hq, 0, 1, b.q8, b.qscale, 0, (hipStream_t)hip_stream);
-        if (e == hipSuccess) e = launch_scan8_full(s, b, nmax, scores, (hipStream_t)hip_stream);
+        e = launch_scan8_full(s, b, nmax, scores, (hipStream_t)hip_stream);
     } else {
         e = launch_scan_full(s, b, nmax, scores, (hipStream_t)hip_stream);
     }
@@ -993,7 +987,7 @@ int topk_attn_debug_read_workspace(topk_attn_t* h, const char* name, void* dst, 
     const struct { const char* name; size_t at, end; } arrays[] = {
         {"thr", w.thr, w.bins}, {"bins", w.bins, w.samp}, {"samp", w.samp, w.seg_cnt}, {"seg_cnt", w.seg_cnt, w.seg_max},
         {"seg_max", w.seg_max, w.seg_cnt2}, {"seg_cnt2", w.seg_cnt2, w.flags}, {"flags", w.flags, w.hmax},
-        {"tailrec", w.tailrec, w.qscale}, {"page_mask", w.page_mask, w.page_cnt}, {"page_cnt", w.page_cnt, w.page_list},
+        {"tailrec", w.tailrec, w.page_mask}, {"page_mask", w.page_mask, w.page_cnt}, {"page_cnt", w.page_cnt, w.page_list},
         {"page_list", w.page_list, w.hist}, {"hist", w.hist, w.cand}, {"cand", w.cand, w.bnd}, {"bnd", w.bnd, w.scores}};
     for (const auto& a : arrays) {
         if (strcmp(a.name, name) != 0) continue;

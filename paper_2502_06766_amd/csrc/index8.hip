@@ -21,54 +21,8 @@ namespace tka {
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------------------
-// Row coding.  A row of D elements is spread over D / 8 lanes (16-bit storage, 16 bytes
-// per lane); row r is row r % rows_per_head of head r / rows_per_head.
+// Row coding.  A row of D elements is spread over D / 8 lanes (16-bit storage, 16 bytes per lane).
 // ---------------------------------------------------------------------------------------
-template <int DT>
-__global__ void __launch_bounds__(256)
-quantize_rows_kernel(const char* __restrict__ src, int64_t rows_per_head, int64_t src_head_stride_bytes,
-                     int64_t n_rows, int D, int8_t* __restrict__ dst, float* __restrict__ scale,
-                     int64_t dst_head_stride_rows) {
-    constexpr int EPL = Elem<DT>::kPerLoad;          // 8 for 16-bit storage
-    const int lpr = D / EPL;                         // lanes per row: 8, 16 or 32
-    const int rows_per_pass = 256 / lpr;
-    const int rs = threadIdx.x / lpr, c = threadIdx.x % lpr;
-    for (int64_t base = (int64_t)blockIdx.x * rows_per_pass; base < n_rows; base += (int64_t)gridDim.x * rows_per_pass) {
-        const int64_t r = base + rs;
-        const bool valid = r < n_rows;
-        const int64_t rr = valid ? r : n_rows - 1;
-        const int64_t head = rr / rows_per_head, t = rr - head * rows_per_head;
-        const u32x4 raw = *reinterpret_cast<const u32x4*>(src + head * src_head_stride_bytes +
-                                                          (t * D + c * EPL) * Elem<DT>::kBytes);
-        float x[EPL];
-        Elem<DT>::widen(raw, x);
-        float amax = 0.f;
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) amax = fmaxf(amax, fabsf(x[e]));
-        for (int o = 1; o < lpr; o <<= 1) amax = fmaxf(amax, wave_xor(amax, o));
-        const bool live = amax >= kTinyRow;
-        const float inv = live ? 127.0f / amax : 0.f;
-        uint32_t w[EPL / 4];
-#pragma unroll
-        for (int i = 0; i < EPL / 4; ++i) {
-            uint32_t p = 0;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int code = (int)rintf(x[4 * i + e] * inv);
-                p |= ((uint32_t)code & 0xFFu) << (8 * e);
-            }
-            w[i] = p;
-        }
-        if (valid) {
-            const int64_t drow = head * dst_head_stride_rows + t;
-            uint32_t* d = reinterpret_cast<uint32_t*>(dst + drow * D + c * EPL);
-#pragma unroll
-            for (int i = 0; i < EPL / 4; ++i) d[i] = w[i];
-            if (c == 0) scale[drow] = live ? amax / 127.0f : 0.f;
-        }
-    }
-}
-
 // Row coding of the tokens a batched append adds: source rows [B][n_new][Hkv] (contiguous),
 // row (b, t, h) is coded into row len[b] + t of (b, h) of the layer's index.
 template <int DT>
@@ -208,26 +162,6 @@ bool index8_supported(int dtype, int D, int G) {
     return (dtype == DT_F16 || dtype == DT_BF16) && (D == 64 || D == 128 || D == 256) && G >= 1 && G <= 4;
 }
 
-hipError_t launch_quantize_rows(int dtype, int D, const void* src, int64_t rows_per_head, int64_t src_head_stride_bytes,
-                                int n_heads, int8_t* dst, float* scale, int64_t dst_head_stride_rows, hipStream_t st) {
-    const int64_t n_rows = rows_per_head * n_heads;
-    if (n_rows <= 0) return hipSuccess;
-    const int rows_per_pass = 256 / (D / 8);
-    int64_t blocks = (n_rows + rows_per_pass - 1) / rows_per_pass;
-    if (blocks > 65536) blocks = 65536;
-    if (dtype == DT_F16)
-        hipLaunchKernelGGL((quantize_rows_kernel<DT_F16>), dim3((unsigned)blocks), dim3(256), 0, st,
-                           static_cast<const char*>(src), rows_per_head, src_head_stride_bytes, n_rows, D, dst, scale,
-                           dst_head_stride_rows);
-    else if (dtype == DT_BF16)
-        hipLaunchKernelGGL((quantize_rows_kernel<DT_BF16>), dim3((unsigned)blocks), dim3(256), 0, st,
-                           static_cast<const char*>(src), rows_per_head, src_head_stride_bytes, n_rows, D, dst, scale,
-                           dst_head_stride_rows);
-    else
-        return hipErrorInvalidValue;
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------------------
 // Scan over the codes (grouped layout: one query, up to four heads per KV head).
 // ---------------------------------------------------------------------------------------
@@ -247,6 +181,42 @@ __device__ __forceinline__ void tile_load8(const int8_t* Kh, const float* Sh, Ro
         for (int s = 0; s < KS; ++s) b[g][s] = p[4 * s];
     }
     ks = Sh[rowfn(lane)];
+}
+
+// Operand A of the scan, coded by every wave from the 16-bit query: lane (j, m) gets the code chunks 4 s + j of head m % 4
+// (zero for heads the group does not have); qs: the heads' scales.  (A launch of its own for the codes of a few rows
+// cost 4.8 us per step, the prologue of the scan kernels does not show it.)
+template <int DT, int D>
+__device__ __forceinline__ void load_query8(const void* q, int64_t head0, int G, i32x4 (&qa)[D / 64], float (&qs)[4]) {
+    const int lane = lane_id(), j = lane >> 4, r = lane & 3;
+    const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const char*>(q) + (head0 + (r < G ? r : 0)) * D * 2) + 2 * j;
+    float x[D / 64][16], amax = 0.f;
+#pragma unroll
+    for (int s = 0; s < D / 64; ++s) {
+        Elem<DT>::widen(p[8 * s], x[s]);
+        Elem<DT>::widen(p[8 * s + 1], x[s] + 8);
+    }
+#pragma unroll
+    for (int s = 0; s < D / 64; ++s) {
+#pragma unroll
+        for (int e = 0; e < 16; ++e) amax = fmaxf(amax, fabsf(x[s][e]));
+    }
+    amax = fmaxf(amax, wave_xor(amax, 16));
+    amax = fmaxf(amax, wave_xor(amax, 32));
+    const bool live = amax >= kTinyRow && r < G;
+    const float inv = live ? 127.0f / amax : 0.f, scale = live ? amax / 127.0f : 0.f;
+#pragma unroll
+    for (int s = 0; s < D / 64; ++s) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            uint32_t w = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w |= ((uint32_t)(int)rintf(x[s][4 * i + e] * inv) & 0xFFu) << (8 * e);
+            qa[s][i] = (int)w;
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) qs[i] = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(scale), i));
 }
 
 // Integer dot products of the tile: lane l gets res[r] = codes(q_{head0 + r}) . codes(K[row(l)]).
@@ -271,7 +241,7 @@ __device__ __forceinline__ i32x4 tile_mac8(const i32x4 (&b)[4][D / 64], const i3
     return res;
 }
 
-template <int D, int MODE>
+template <int DT, int D, int MODE>
 __global__ void __launch_bounds__(kScanWaves* kWave)
 scan8_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     constexpr int KS = D / 64;
@@ -305,20 +275,10 @@ scan8_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         if (tile_end > n_tiles_all) tile_end = n_tiles_all;
     }
 
-    // operand A: lane (j, m) holds the code chunk 4 s + j of head m % 4 (zero for missing heads)
     i32x4 qa[KS];
-    {
-        const int j = lane >> 4, r = lane & 3;
-        const i32x4* p = reinterpret_cast<const i32x4*>(bf.q8 + (head0 + (r < G ? r : 0)) * D) + j;
-#pragma unroll
-        for (int s = 0; s < KS; ++s) {
-            i32x4 v = p[4 * s];
-            if (r >= G) v = i32x4{0, 0, 0, 0};
-            qa[s] = v;
-        }
-    }
-    float qs0 = bf.qscale[head0], qs1 = 1 < G ? bf.qscale[head0 + 1] : 0.f, qs2 = 2 < G ? bf.qscale[head0 + 2] : 0.f,
-          qs3 = 3 < G ? bf.qscale[head0 + 3] : 0.f;
+    float qs[4];
+    load_query8<DT, D>(bf.q, head0, G, qa, qs);
+    const float qs0 = qs[0], qs1 = qs[1], qs2 = qs[2], qs3 = qs[3];
     const int64_t head_rows = ((int64_t)b * sh.Hkv + kvh) * sh.Ncap;
     const int8_t* Kh = bf.K8 + head_rows * D;
     const float* Sh = bf.Kscale + head_rows;
@@ -424,10 +384,15 @@ static hipError_t launch_scan8(const Shape& s, const Bufs& b, int64_t n_items, f
         const int64_t tiles = (n_items + 63) / 64, per_wg = (int64_t)tpw * kScanWaves;
         grid = dim3((unsigned)((tiles + per_wg - 1) / per_wg), (unsigned)s.Hkv, (unsigned)s.B);
     }
-    if (s.D == 128) hipLaunchKernelGGL((scan8_kernel<128, MODE>), grid, block, 0, st, s, b, tpw, dst);
-    else if (s.D == 64) hipLaunchKernelGGL((scan8_kernel<64, MODE>), grid, block, 0, st, s, b, tpw, dst);
-    else if (s.D == 256) hipLaunchKernelGGL((scan8_kernel<256, MODE>), grid, block, 0, st, s, b, tpw, dst);
+#define TKA_S8(DT_, D_) hipLaunchKernelGGL((scan8_kernel<DT_, D_, MODE>), grid, block, 0, st, s, b, tpw, dst)
+    if (s.dtype == DT_F16 && s.D == 128) TKA_S8(DT_F16, 128);
+    else if (s.dtype == DT_BF16 && s.D == 128) TKA_S8(DT_BF16, 128);
+    else if (s.dtype == DT_F16 && s.D == 64) TKA_S8(DT_F16, 64);
+    else if (s.dtype == DT_BF16 && s.D == 64) TKA_S8(DT_BF16, 64);
+    else if (s.dtype == DT_F16 && s.D == 256) TKA_S8(DT_F16, 256);
+    else if (s.dtype == DT_BF16 && s.D == 256) TKA_S8(DT_BF16, 256);
     else return hipErrorInvalidValue;
+#undef TKA_S8
     return hipGetLastError();
 }
 

@@ -64,8 +64,6 @@ struct Bufs {
     const void* q;          // [B][Hq][D]
     const int8_t* K8;       // this layer's int8 key codes [Bc][Hkv][Ncap][D] (compressed index), or null
     const float* Kscale;    // this layer's per-row code scales [Bc][Hkv][Ncap]
-    int8_t* q8;             // [B*Hq][D] query codes of this call
-    float* qscale;          // [B*Hq]
     const int32_t* len;     // [Bc] tokens cached per cache sequence (this layer)
     float* thr;             // [B*Hq] candidate threshold
     float* bins;            // [B*Hq][2] lower end and bins per unit of score of tail_bin()
@@ -258,8 +256,6 @@ hipError_t launch_scan_filter_paged(const Shape& s, const Bufs& b, hipStream_t s
 
 // int8 key index
 bool index8_supported(int dtype, int D, int G);
-hipError_t launch_quantize_rows(int dtype, int D, const void* src, int64_t rows_per_head, int64_t src_head_stride_bytes,
-                                int n_heads, int8_t* dst, float* scale, int64_t dst_head_stride_rows, hipStream_t st);
 hipError_t launch_append_step_small8(int dtype, int D, const void* ksrc, const void* vsrc, void* kdst, void* vdst,
                                      int64_t head_bytes, int B, int64_t n_new, int Hkv, int64_t Ncap, int32_t* len,
                                      int8_t* codes, float* scale, hipStream_t st);
