@@ -627,12 +627,14 @@ static void fill_call(topk_attn_t* h, int layer, const void* q, int k, int n_que
 }
 
 // Split of each head's candidate list into per-wave segments for the filtered scan:
-// about two 4-wave workgroups per compute unit over the whole grid, no more waves than
+// about two 4-wave workgroups per compute unit (as many as run at once: what does not fit starts a second round, with
+// its prologue in front of an idle memory system) over the whole grid, no more waves than
 // key tiles, and segments large enough for their share of the expected candidates plus
 // eight standard deviations.  False if no split fits (the caller takes the full path).
 static bool choose_segments(const topk_attn_t* h, const Shape& s, int64_t nmax, int64_t c_hi, int* n_seg,
                             int* seg_cap) {
-    const int64_t target_wgs = 2 * (int64_t)h->n_cu;
+    // (a scan with two row tiles runs one workgroup per compute unit: its stages take the LDS)
+    const int64_t target_wgs = (scan_row_tiles(s) && s.row_tiles == 2 ? 1 : 2) * (int64_t)h->n_cu;
     int64_t P = target_wgs / ((int64_t)scan_grid_z(s) * s.Hkv);
     const int64_t tiles = (nmax + 63) / 64;
     if (P * 4 > tiles) P = tiles / 4;
