@@ -79,10 +79,8 @@ __global__ void __launch_bounds__(NT) threshold_kernel(Shape sh, Bufs bf) {
         if (ok) mx = fmaxf(mx, sv[j]);
         if (ok && sv[j] > -INFINITY) mn = fminf(mn, sv[j]);
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        mx = fmaxf(mx, wave_xor(mx, o));
-        mn = fminf(mn, wave_xor(mn, o));
-    }
+    mx = wave_max(mx);
+    mn = wave_min(mn);
     if (lane == 0) { red_mx[wave] = mx; red_mn[wave] = mn; }
     __syncthreads();
     mx = red_mx[0]; mn = red_mn[0];
@@ -114,12 +112,7 @@ __global__ void __launch_bounds__(NT) threshold_kernel(Shape sh, Bufs bf) {
         }
 #pragma unroll
         for (int i = 0; i < BPL; ++i) local += c[i];
-        uint32_t incl = local;
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t v = __shfl_up(incl, o, kWave);
-            if (lane >= o) incl += v;
-        }
-        incl += above;
+        const uint32_t incl = wave_scan_add(local) + above;
         const uint32_t want[3] = {rank, rank_lo, rank_hi};
 #pragma unroll
         for (int q = 0; q < 3; ++q) {

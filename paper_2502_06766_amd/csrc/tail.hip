@@ -85,13 +85,10 @@ __device__ __forceinline__ void seg_summary(const Shape& sh, const Bufs& bf, int
         mxl = c > mxl ? c : mxl;
         km = m > km ? m : km;
     }
-    for (int o = 32; o > 0; o >>= 1) {
-        sum += __shfl_xor(sum, o, kWave);
-        const uint32_t t = __shfl_xor(mxl, o, kWave), u = __shfl_xor(km, o, kWave);
-        mxl = t > mxl ? t : mxl;
-        km = u > km ? u : km;
-    }
-    if (lane_id() == 0) {
+    sum = wave_scan_add(sum);               // (the total in the last lane)
+    mxl = wave_max_u32(mxl);
+    km = wave_max_u32(km);
+    if (lane_id() == kWave - 1) {
         const int w = threadIdx.x >> 6;
         sm.red[0][w] = sum; sm.red[1][w] = mxl; sm.red[2][w] = km;
     }
@@ -122,11 +119,7 @@ __device__ __forceinline__ HeadSel analyse_head(const Shape& sh, const Bufs& bf,
         uint32_t all = 0, before = 0;
 #pragma unroll
         for (int p = 0; p < kTailWaves; ++p) { all += sm.part[0][p][bin]; before += sm.part[1][p][bin]; }
-        uint32_t ia = all, ib = before;
-        for (int o = 1; o < kWave; o <<= 1) {
-            const uint32_t va = __shfl_up(ia, o, kWave), vb = __shfl_up(ib, o, kWave);
-            if (lane >= o) { ia += va; ib += vb; }
-        }
+        const uint32_t ia = wave_scan_add(all), ib = wave_scan_add(before);
         const uint32_t run = ia - all;
         if (run < (uint32_t)k_eff && (uint32_t)k_eff <= ia) {        // at most one lane
             sm.sel[0] = (uint32_t)bin;           // B: the bin the k-th score falls in
@@ -417,10 +410,11 @@ __global__ void __launch_bounds__(kTailThreads) tail_gather_kernel(Shape sh, Buf
     fetch_staged(RPW * U);
 
     // ---- this workgroup's partial sum (weights relative to the head's largest score)
+#pragma unroll
     for (int o = LPR; o < kWave; o <<= 1) {
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] += wave_xor(acc[e], o);
-        lsum += wave_xor(lsum, o);
+        for (int e = 0; e < EPL; ++e) acc[e] = o == 32 ? add_lanes_32(acc[e]) : o == 16 ? add_lanes_16(acc[e]) : acc[e] + wave_xor(acc[e], o);
+        lsum = o == 32 ? add_lanes_32(lsum) : o == 16 ? add_lanes_16(lsum) : lsum + wave_xor(lsum, o);
     }
     if (rs == 0) {
 #pragma unroll
@@ -595,7 +589,7 @@ __global__ void __launch_bounds__(NT) tail_finish_kernel(Shape sh, Bufs bf, floa
             const float sc = __uint_as_float((uint32_t)(ent[i] >> 32));
             if (i * NT + tid < have) { lo = fminf(lo, sc); hi = fmaxf(hi, sc); }
         }
-        for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, wave_xor(lo, o)); hi = fmaxf(hi, wave_xor(hi, o)); }
+        lo = wave_min(lo); hi = wave_max(hi);
         if (lane == 0) { s_red[wave] = lo; s_red[NW + wave] = hi; }
         for (int i = tid; i < kBins; i += NT) sm.hist[i] = 0;
         if (tid == 0) { sm.bin = 0u; sm.above = 0u; sm.cb = (uint32_t)have; }     // (overwritten below: 1 <= need <= have)
@@ -613,11 +607,7 @@ __global__ void __launch_bounds__(NT) tail_finish_kernel(Shape sh, Bufs bf, floa
         {   // the sub-bin in which the counts, summed from the top, reach `need`: thread t looks at the two bins 2t, 2t+1 from the top
             static_assert(kBins == 2 * NT, "two sub-bins per thread");
             const uint32_t c0 = sm.hist[kBins - 1 - 2 * tid], c1 = sm.hist[kBins - 2 - 2 * tid];
-            uint32_t inc = c0 + c1;
-            for (int o = 1; o < kWave; o <<= 1) {
-                const uint32_t v = __shfl_up(inc, o, kWave);
-                if (lane >= o) inc += v;
-            }
+            const uint32_t inc = wave_scan_add(c0 + c1);
             if (lane == kWave - 1) s_cnt[0][wave] = inc;
             __syncthreads();
             uint32_t before = inc - (c0 + c1);
@@ -733,10 +723,20 @@ __global__ void __launch_bounds__(NT) tail_finish_kernel(Shape sh, Bufs bf, floa
         gather_rows(0, need, [&](int j) { return (int64_t)s_pos[j]; }, [&](int j) { return s_w[j]; });
     }
 
-    for (int o = lpr; o < kWave; o <<= 1) {
+    for (int o = lpr; o < 16; o <<= 1) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) acc[e] += wave_xor(acc[e], o);
         lsum += wave_xor(lsum, o);
+    }
+    if (lpr <= 16) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_16(acc[e]);
+        lsum = add_lanes_16(lsum);
+    }
+    if (lpr <= 32) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_32(acc[e]);
+        lsum = add_lanes_32(lsum);
     }
     __syncthreads();                          // sm.wave_tot is reused below
     if (rs == 0) {
