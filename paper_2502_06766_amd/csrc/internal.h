@@ -218,6 +218,13 @@ inline int attend_row_rows(int64_t heads, int64_t Nmax) {
 constexpr int attend_short_k(int64_t Nmax) { return Nmax <= 2048 ? 512 : Nmax <= 4096 ? 256 : 0; }
 constexpr int kAttendShort = -1;
 
+// The filter scan works the thresholds out itself where a wave can: samples of at most kScanSampMax scores, the grouped
+// layout, 16-bit keys, and no page index (whose filter needs the thresholds before the scan).
+constexpr int kScanSampMax = 2048;
+inline bool threshold_in_scan(const Shape& s, int64_t Nmax) {
+    return s.M == 1 && s.G <= 4 && !s.indexed && !s.paged && make_plan(Nmax, s.k < Nmax ? s.k : (int)Nmax).n_samp <= kScanSampMax;
+}
+
 // Position of sample s: one jittered position inside each stride-long stratum.
 __host__ __device__ inline int64_t sample_pos(int s, int stride) {
     uint32_t h = (uint32_t)s * 2654435761u;

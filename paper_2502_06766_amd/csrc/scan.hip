@@ -24,12 +24,17 @@
 #include "internal.h"
 #include "scan_common.h"
 #include "scan_tiles.h"
+#include "threshold.h"
 
 namespace tka {
 
+// SAMPLED (filter mode only): the scan works out the thresholds of its heads itself (a wave per head, every workgroup of a
+// key stream the same ones), while the first key tiles are on their way; the first workgroup leaves them for the kernels
+// that follow.  For samples a wave can take at a glance this beats a launch of its own (8 KV heads: 48k
+// tokens 4.8 + 22.0 us and the gap between two launches against 24.7 us, 128k tokens 5.5 + 45.0 against 48.8).
 // PAGED (filter mode only): the wave skips the tiles whose bit in the page mask is clear (pages of 64 keys
 // that the coarse page index has ruled out for every head of the group).
-template <int DT, int D, int MODE, bool PAGED = false>
+template <int DT, int D, int MODE, bool PAGED = false, bool SAMPLED = false>
 __global__ void __launch_bounds__(kScanWaves* kWave)
 scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     using v8 = typename Mfma<DT>::v8;
@@ -85,14 +90,48 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     float top0 = -INFINITY, top1 = -INFINITY, top2 = -INFINITY, top3 = -INFINITY;   // largest score seen per head
     // candidates of this workgroup per score bin and head (the tail sorts them by bin)
     __shared__ uint32_t hist_lds[MODE == MODE_FILTER ? 4 * kTailBins : 1];
+    struct TileB { v8 b[4][D / 32]; } ba, bb;
+    const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
+    // filter: one tile per row of n_seg tiles; the rows made of whole tiles only
+    const int64_t rows_whole = MODE == MODE_FILTER ? N / 64 / tile_step : 0;
+    auto load_seg = [&](TileB& t, int64_t i) { tile_load_full<DT, D>(Kh + seg_tile(i, sid, (int)tile_step) * (64 * D * 2), lane_off, t.b); };
     if (MODE == MODE_FILTER) {
-        const float* bins = bf.bins + 2 * head0;
-        thr0 = bf.thr[head0]; lo0 = bins[0]; iw0 = bins[1];
-        if (1 < G) { thr1 = bf.thr[head0 + 1]; lo1 = bins[2]; iw1 = bins[3]; }
-        if (2 < G) { thr2 = bf.thr[head0 + 2]; lo2 = bins[4]; iw2 = bins[5]; }
-        if (3 < G) { thr3 = bf.thr[head0 + 3]; lo3 = bins[6]; iw3 = bins[7]; }
         for (int i = threadIdx.x; i < 4 * kTailBins; i += kScanWaves * kWave) hist_lds[i] = 0;
-        __syncthreads();
+        if constexpr (SAMPLED) {
+            constexpr int CPT = kScanSampMax / kWave;
+            __shared__ ThresholdShared<WaveTeam> thr_sm[kScanWaves];
+            __shared__ float thr_lds[4][3];
+            const bool mine = wave < G;                              // (uniform over the wave)
+            const int64_t bh = head0 + (mine ? wave : 0);
+            const Plan pl = make_plan(N > 0 ? N : 1, sh.k < N ? sh.k : (int)N);
+            float sv[CPT];
+#pragma unroll
+            for (int u = 0; u < CPT; ++u)
+                sv[u] = mine && u * kWave < pl.n_samp ? bf.samp[bh * sh.samp_cap + u * kWave + lane] : 0.f;
+            if (ScanPipelined<D>::value && rows_whole > 0) load_seg(ba, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (mine) {
+                for (int u = lane; u < kThrBins; u += kWave) thr_sm[wave].hist[u] = 0;
+                const Threshold t = N > 0 ? estimate_threshold<WaveTeam, CPT>(sv, pl, thr_sm[wave]) : Threshold{INFINITY, 0.f, 0.f};
+                if (lane == 0) {
+                    thr_lds[wave][0] = t.thr; thr_lds[wave][1] = t.bin_lo; thr_lds[wave][2] = t.bin_inv;
+                    if (blockIdx.x == 0) leave_threshold(bf, bh, t, N > 0 ? threshold_flags(sh, pl, N) : 0u);
+                }
+            }
+            __syncthreads();
+            auto uni = [](float x) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x))); };
+            thr0 = uni(thr_lds[0][0]); lo0 = uni(thr_lds[0][1]); iw0 = uni(thr_lds[0][2]);
+            if (1 < G) { thr1 = uni(thr_lds[1][0]); lo1 = uni(thr_lds[1][1]); iw1 = uni(thr_lds[1][2]); }
+            if (2 < G) { thr2 = uni(thr_lds[2][0]); lo2 = uni(thr_lds[2][1]); iw2 = uni(thr_lds[2][2]); }
+            if (3 < G) { thr3 = uni(thr_lds[3][0]); lo3 = uni(thr_lds[3][1]); iw3 = uni(thr_lds[3][2]); }
+        } else {
+            const float* bins = bf.bins + 2 * head0;
+            thr0 = bf.thr[head0]; lo0 = bins[0]; iw0 = bins[1];
+            if (1 < G) { thr1 = bf.thr[head0 + 1]; lo1 = bins[2]; iw1 = bins[3]; }
+            if (2 < G) { thr2 = bf.thr[head0 + 2]; lo2 = bins[4]; iw2 = bins[5]; }
+            if (3 < G) { thr3 = bf.thr[head0 + 3]; lo3 = bins[6]; iw3 = bins[7]; }
+            __syncthreads();
+        }
     }
 
     // row of tile slot `slot` for the tile starting at item `item0`
@@ -127,7 +166,6 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     };
 
-    struct TileB { v8 b[4][D / 32]; } ba, bb;
     auto load_rows = [&](TileB& t, int64_t ti) { tile_load<DT, D>(Kh, [&](int slot) { return row_of(ti * 64, slot); }, t.b); };
     auto use = [&](TileB& t, int64_t ti) { consume(tile_mac<DT, D>(t.b, qa), ti * 64); };
     if (MODE == MODE_SAMPLE) {
@@ -141,7 +179,6 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         const int32_t* plist = bf.page_list + stream * (int64_t)sh.page_words * 64;
         const int64_t n_kept = (int64_t)bf.page_cnt[stream];
         const int64_t n_whole = N / 64;
-        const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
         const int n_seg = (int)tile_step;
         const int64_t rows = (n_kept + n_seg - 1) / n_seg;      // rows of n_seg ranks; the last one may be short
         int64_t base = 0;                        // first row of the current group of 64
@@ -201,11 +238,8 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
             // one tile per row of n_seg tiles: the rows made of whole tiles only first, then the last one or two
             // (tiles beyond the cache are skipped, the one its end cuts short is loaded row by row)
             const int n_seg = (int)tile_step;
-            const int64_t n_whole = N / 64;
-            const int64_t rows_whole = n_whole / n_seg, rows = (n_tiles_all + n_seg - 1) / n_seg;
-            const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
-            walk_tiles<ScanPipelined<D>::value>(0, rows_whole, 1, ba, bb,
-                [&](TileB& t, int64_t i) { tile_load_full<DT, D>(Kh + seg_tile(i, sid, n_seg) * (64 * D * 2), lane_off, t.b); },
+            const int64_t rows = (n_tiles_all + n_seg - 1) / n_seg;
+            walk_tiles<ScanPipelined<D>::value, SAMPLED>(0, rows_whole, 1, ba, bb, load_seg,
                 [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid, n_seg)); });
             for (int64_t i = rows_whole; i < rows; ++i) {
                 const int64_t ti = seg_tile(i, sid, n_seg);
@@ -217,7 +251,6 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         } else {
             // whole tiles first, then the one tile (if any) that the end of the cache cuts short
             const int64_t n_whole = N / 64;
-            const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
             tile = walk_tiles<ScanPipelined<D>::value>(tile, tile_end < n_whole ? tile_end : n_whole, tile_step, ba, bb,
                               [&](TileB& t, int64_t ti) { tile_load_full<DT, D>(Kh + ti * (64 * D * 2), lane_off, t.b); }, use);
             for (; tile < tile_end; tile += tile_step) {
@@ -694,7 +727,7 @@ hipError_t launch_scan_filter_paged(const Shape& s, const Bufs& b, hipStream_t s
 }
 
 hipError_t launch_scan_filter(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
-    (void)Nmax;
+    const bool sampled = threshold_in_scan(s, Nmax);
     // one wave per candidate segment: n_seg / 4 workgroups per KV head
     const bool rows = scan_row_tiles(s);
     dim3 grid((unsigned)(s.n_seg / kScanWaves), (unsigned)s.Hkv, (unsigned)(scan_grid_z(s)));
@@ -707,6 +740,9 @@ hipError_t launch_scan_filter(const Shape& s, const Bufs& b, int64_t Nmax, hipSt
         else if (rows)                                                                                       \
             hipLaunchKernelGGL((scan_rows_kernel<DT_, D_, MODE_FILTER, 1>), grid, block, 0, st, s, b, 0,     \
                                (float*)nullptr);                                                             \
+        else if (sampled)                                                                                    \
+            hipLaunchKernelGGL((scan_mfma_kernel<DT_, D_, MODE_FILTER, false, true>), grid, block, 0, st, s, \
+                               b, 0, (float*)nullptr);                                                       \
         else                                                                                                 \
             hipLaunchKernelGGL((scan_mfma_kernel<DT_, D_, MODE_FILTER>), grid, block, 0, st, s, b, 0,        \
                                (float*)nullptr);                                                             \

@@ -85,12 +85,13 @@ __device__ __forceinline__ void tile_load_full(const char* tile_base, uint32_t l
 // prefetch is unconditional (past the end it re-reads a tile the wave already had, a cache
 // hit) so that the wait before the MFMAs only covers the tile they consume.  Returns the
 // first tile of the sequence at or past `end`.
-template <bool PIPELINED, class Buf, class Load, class Use>
+// FIRST_LOADED: the first tile is in `ba` or on its way (double-buffered walks only).
+template <bool PIPELINED, bool FIRST_LOADED = false, class Buf, class Load, class Use>
 __device__ __forceinline__ int64_t walk_tiles(int64_t tile, int64_t end, int64_t step, Buf& ba, Buf& bb, Load load,
                                               Use use) {
   if (PIPELINED) {
     if (tile < end) {
-        load(ba, tile);
+        if (!FIRST_LOADED) load(ba, tile);
         while (true) {
             const int64_t t1 = tile + step;
             load(bb, t1 < end ? t1 : tile);
