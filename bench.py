@@ -192,7 +192,7 @@ def main() -> int:
     if args.pages and M == 1:                                   # the pages kept, and one mask bit per page
         scan_bytes = pages_read * 64 * d * e + pages_total // 8
     scan_gbps = scan_bytes / (scan_ms * 1e-3) / 1e9
-    scan_kernel = "scan_generic_kernel<full>" if w.dtype == wl.F32 else "scan_rows_kernel<filter>" if M > 1 else \
+    scan_kernel = "scan_f32_kernel<full>" if w.dtype == wl.F32 else "scan_rows_kernel<filter>" if M > 1 else \
         "scan8_kernel<filter>" if args.index else "scan_mfma_kernel<filter,paged>" if args.pages else "scan_mfma_kernel<filter>"
 
     cpu = None
