@@ -3,7 +3,7 @@
 // result and the attention step of Algorithm 1 of arXiv 2502.06766.  One workgroup per (sequence, head).
 //
 // It takes over where a head has few scores to select from (a few thousand): a step is then a chain of latencies,
-// not a stream.  Every launch costs about 4 us with its ramp, and a radix select four passes of LDS
+// not a stream.  Every launch adds its ramp and a gap, and a radix select four passes of LDS
 // atomics over a handful of exponent bins.  Here the k-th score is found by linear bins between the smallest and
 // the largest score, over scores held in registers (the bin it falls in holds a few, which are ranked by
 // comparison), and the value rows are fetched by the same workgroup as soon as the winners' positions are in LDS.
