@@ -18,8 +18,8 @@ int topk_attn_scores(topk_attn_t* h, int layer, const void* q, float* scores, vo
 
 /* After the stream has been synchronised by the caller: number of (sequence, head)
  * pairs of the last decode whose filtered candidate list turned out unusable (a segment
- * overflowed, or fewer than k keys reached the sampled threshold) and were recomputed
- * exactly.  Heads of sequences that cannot be filtered at all (a few tokens only, or k too
+ * overflowed, fewer than k keys reached the sampled threshold, or more keys than the boundary
+ * list holds share the score bin of the k-th score) and were selected another way, exactly.  Heads of sequences that cannot be filtered at all (a few tokens only, or k too
  * dense) are recomputed the same way by design and are not counted.  Copies a few bytes
  * device->host (synchronous). */
 int topk_attn_last_fallbacks(topk_attn_t* h, int* n_heads);

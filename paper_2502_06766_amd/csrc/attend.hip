@@ -17,13 +17,13 @@
 //
 //   SRC_ROW   the scores of a short cache, stored by the scan (general path)
 //   (attend_short_kernel: the scores too, for batches of short sequences)
-//   SRC_LIST  the candidate list the filtered scan left; a head whose list is unusable (a segment overflowed, too few
-//             or too many candidates) is scored again by the workgroups launched for it and selected from its full
-//             score row by the last of them to finish
+//   SRC_LIST  the candidate list the filtered scan left (what becomes of one that is too long or unusable: below)
+#include <algorithm>
 #include <type_traits>
 
 #include "device_utils.h"
 #include "internal.h"
+#include "scan_common.h"
 #include "scan_tiles.h"
 #include "select_common.h"
 #include "team.h"
@@ -175,34 +175,141 @@ __device__ __forceinline__ Boundary team_select(ScoreFn v, Mask act, int n_items
     return first;
 }
 
-// Exact scores of the head's keys into the score buffer, the tiles `first`, `first + step`, ... of 16 keys, one per wave
-// and step (a head whose candidate list is unusable; the arithmetic of the scan).
+// A list longer than the registers hold, or unusable (a segment overflowed).  The scan's counts per score bin, which go on
+// where a segment is full, say which bin B the k-th score falls in and how many entries of the bins from B up every scan
+// workgroup left:
+//   LONG_CUT   they fit: every workgroup of the head takes those alone into its registers and goes on as with a short list
+//   LONG_TIED  they do not (most of them tie): one workgroup goes on alone, by radix select over the list
+//   RESCORE    a segment overflowed: the head's workgroups score the keys of its tiles again (arithmetic and dealing of the scan),
+//              put those from bin B up into the segments, and the last to finish goes on alone with that list
+//   SCORE_ROW  the same where the counts do not cover k keys or those from B up do not fit either: all scores go to
+//              the score buffer, and the last to finish goes on alone by radix select over the row
+// us per call, 32 heads, 8 KV heads, d = 128; chip-wide tail / before the list was cut by the counts (every such head scored
+// again, radix select over the row) / now.  A quarter of the keys identical and just below the k-th score (lists of 36k,
+// 135k at 512k tokens): 128k tokens, k = 2048 88 / 444 / 87; 512k tokens 287 / 1518 / 281; 16 queries at 128k tokens 292 / 2579 /
+// 237.  The same on top (tied): 279 / 548 / 244, at 16 queries 576 / 2789 / 509.  Overflow: one KV head, 4 query heads, 512k tokens, 92 %
+// identical 161 / - / 147; 8 KV heads, 512k tokens, 70 % on top (row) 3822 / 2957 / 2826.  Slower than the tail where one head of
+// a batch that fills the chip is scored by its one workgroup: 4 of 256 heads, 128k tokens, 97 % identical 1466 / - / 1951.
+enum { LIST_SHORT = 0, LONG_CUT, LONG_TIED, RESCORE, SCORE_ROW };
+
+// The head's segments first, first + step, ... (one per wave and step) for RESCORE and SCORE_ROW: exact scores of
+// their keys into the score buffer, and those of bin B and above (none: B = kTailBins) into the segment again.
 template <int DT, int D>
-__device__ __forceinline__ void score_keys(const Shape& sh, const Bufs& bf, int b, int h, int64_t N, int64_t first, int64_t step) {
+__device__ __forceinline__ void score_segments(const Shape& sh, const Bufs& bf, int b, int h, int64_t N, int first, int step,
+                                               int B, float bin_lo, float bin_inv, uint64_t* list) {
     using v8 = typename Mfma<DT>::v8;
+    constexpr int KS = D / 32, SUB = D <= 64 ? 4 : D <= 128 ? 2 : 1;       // runs of 16 keys in flight
     const int64_t bh = (int64_t)b * sh.Hq + h;
     const int lane = lane_id(), jj = lane >> 4, n = lane & 15;
     const char* Kh = static_cast<const char*>(bf.K) + ((int64_t)cache_seq(sh, b) * sh.Hkv + h / sh.G) * sh.Ncap * (D * 2);
     // operand A holds this head alone (rows 0, 4, 8, 12), so that accumulator element 0 is its score in every lane
-    v8 qa[D / 32];
+    v8 qa[KS];
     load_query_a<DT, D>(bf.q, bh, 1, qa);
-    for (int64_t t = first; t * 16 < N; t += step) {
-        const int64_t key = t * 16 + n;
-        const v8* p = reinterpret_cast<const v8*>(Kh + (key < N ? key : N - 1) * (D * 2)) + jj;
-        v8 kb[D / 32];
+    const int64_t n_tiles = (N + 63) / 64;
+    for (int sid = first; sid < sh.n_seg; sid += step) {
+        uint32_t cnt = 0;                                 // entries of bin B and above (uniform over the wave)
+        for (int64_t row = 0; row * sh.n_seg < n_tiles; ++row) {
+            const int64_t tile = seg_tile(row, sid, sh.n_seg);
+            if (tile >= n_tiles) continue;
+#pragma unroll 1
+            for (int sub0 = 0; sub0 < 4; sub0 += SUB) {
+                v8 kb[SUB][KS];
 #pragma unroll
-        for (int s = 0; s < D / 32; ++s) kb[s] = p[4 * s];
-        f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f};
+                for (int u = 0; u < SUB; ++u) {
+                    const int64_t key = tile * 64 + (sub0 + u) * 16 + n;
+                    const v8* p = reinterpret_cast<const v8*>(Kh + (key < N ? key : N - 1) * (D * 2)) + jj;
 #pragma unroll
-        for (int s = 0; s < D / 32; ++s) c = Mfma<DT>::mac(qa[s], kb[s], c);
-        if (jj == 0 && key < N) bf.scores[bh * sh.Ncap + key] = c[0] + 0.0f;
+                    for (int s = 0; s < KS; ++s) kb[u][s] = p[4 * s];
+                }
+#pragma unroll
+                for (int u = 0; u < SUB; ++u) {
+                    f32x4 c = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) c = Mfma<DT>::mac(qa[s], kb[u][s], c);
+                    const float sc = c[0] + 0.0f;
+                    const int64_t key = tile * 64 + (sub0 + u) * 16 + n;
+                    const bool mine = jj == 0 && key < N;               // every lane group holds the same scores: the first one writes
+                    if (mine) bf.scores[bh * sh.Ncap + key] = sc;
+                    const bool keep = mine && tail_bin(sc, bin_lo, bin_inv) >= B;
+                    const uint64_t m = __ballot(keep);
+                    const uint32_t e = cnt + (uint32_t)mask_rank(m);
+                    if (keep && e < (uint32_t)sh.seg_cap)
+                        list[cand_slot(e, sid, sh.n_seg)] = ((uint64_t)__float_as_uint(sc) << 32) | (uint64_t)(uint32_t)key;
+                    cnt += (uint32_t)__popcll(m);
+                }
+            }
+        }
+        if (lane == 0 && B < kTailBins) {
+            bf.seg_cnt2[bh * sh.n_seg + sid] = cnt < (uint32_t)sh.seg_cap ? cnt : (uint32_t)sh.seg_cap;
+            if (cnt > (uint32_t)sh.seg_cap) atomicOr(&bf.flags[bh], 2u);           // overflowed once more: the score buffer is used
+        }
     }
 }
 
-// Grid: heads x sequences x shares.  SRC_LIST: the gridDim.z workgroups of a head all select from its list (the same
+// LONG_CUT: the entries of bin B and above, `keep` of scan workgroup j (four segments) from place at(j) on.
+template <int NW>
+__device__ __forceinline__ void cut_list(const Shape& sh, int wave, int B, float bin_lo, float bin_inv, const uint2* segs,
+                                         const uint32_t* at, const uint64_t* list, uint64_t* kept, uint32_t n_kept) {
+    constexpr int U = 2;
+    const int lane = lane_id();
+    for (int j = wave; j < sh.n_seg / kScanWaves; j += NW) {
+        uint32_t o = at[j], len[kScanWaves], longest = 0;
+#pragma unroll
+        for (int s = 0; s < kScanWaves; ++s) {
+            len[s] = segs[j * kScanWaves + s].x;
+            longest = len[s] > longest ? len[s] : longest;
+        }
+        for (uint32_t e0 = 0; e0 < longest; e0 += U * kWave) {
+            uint64_t ent[kScanWaves][U];
+#pragma unroll
+            for (int s = 0; s < kScanWaves; ++s) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t e = e0 + u * kWave + lane;
+                    ent[s][u] = list[cand_slot(e < len[s] ? e : 0, j * kScanWaves + s, sh.n_seg)];
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < kScanWaves; ++s) {
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const bool keep = e0 + u * kWave + lane < len[s] &&
+                                      tail_bin(__uint_as_float((uint32_t)(ent[s][u] >> 32)), bin_lo, bin_inv) >= B;
+                    const uint64_t m = __ballot(keep);
+                    const uint32_t to = o + (uint32_t)mask_rank(m);
+                    if (keep && to < n_kept) kept[to] = ent[s][u];           // (below n_kept always; guards the buffer)
+                    o += (uint32_t)__popcll(m);
+                }
+            }
+        }
+    }
+}
+
+// LONG_TIED: the slots of the list as a source of the radix select; `segs`: lengths of its segments (LDS).
+template <int NT>
+struct SrcSegments {
+    static constexpr int kThreads = NT;
+    const uint64_t* list;
+    const uint2* segs;
+    int64_t n;
+    int log2_n_seg;
+    typedef uint64_t raw_t;
+    __device__ __forceinline__ int64_t slots() const { return n; }
+    __device__ __forceinline__ bool valid(int64_t i) const {
+        return i < n && (uint32_t)cand_slot_entry(i, log2_n_seg) < segs[cand_slot_segment(i, log2_n_seg)].x;
+    }
+    __device__ __forceinline__ const uint64_t* where(int64_t i) const { return list + i; }
+    __device__ __forceinline__ uint32_t key(uint64_t e) const { return score_key(__uint_as_float((uint32_t)(e >> 32))); }
+    __device__ __forceinline__ uint32_t ipos(uint64_t e, int64_t) const { return 0xFFFFFFFFu - (uint32_t)e; }
+    __device__ __forceinline__ void stash(int, uint64_t) const {}
+    __device__ __forceinline__ uint32_t cached_ipos(int) const { return 0u; }
+};
+
+// Grid: heads x sequences x workgroups per head.  SRC_LIST: Shape::attend workgroups of a head all select from its list (the same
 // winners, found side by side on compute units that would idle), each fetches its share of the value rows, and the last
 // to finish adds up the shares; so a head's rows are not bound by what one compute unit can fetch (about 64 GB/s).
-template <int DT, class Cfg, int SRC>
+// Further ones, where the heads are few, only lend a hand when keys have to be scored again.
+template <int DT, class Cfg, int SRC, int DIM = 0>     // DIM: the head dim of a list kernel
 __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4))) attend_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     constexpr int NT = Cfg::NT, NW = Cfg::NW, CPT = Cfg::CPT;
     using Team = WorkgroupTeam<NT>;
@@ -218,7 +325,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     int32_t* const idx = bf.sel_idx + bh * sh.k;
     float* const vals = bf.sel_val + bh * sh.k;
-    const int D = sh.D, lpr = D / EPL, rpw = kWave / lpr;          // lanes per key or value row, rows per wave and load
+    const int D = SRC == SRC_LIST ? DIM : sh.D, lpr = D / EPL, rpw = kWave / lpr;          // lanes per key or value row, rows per wave and load
     const int rs = lane / lpr, c = lane % lpr;
     const int64_t head_off = ((int64_t)cache_seq(sh, b) * sh.Hkv + h / sh.G) * sh.Ncap * D * Elem<DT>::kBytes;
 
@@ -226,18 +333,24 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     float v[CPT];
     int n_items = 0;
     uint32_t act = 0;                                     // bit j: v[j] is a score in question
-    bool usable = true;                                   // (uniform) there is a list
+    bool alone = false;                                   // (uniform) this workgroup goes on for the whole head
+    int how = LIST_SHORT;                                 // (uniform)
+    bool in_regs = true;                                  // (uniform) the scores to select from are in registers
+    uint32_t above = 0, in_b = 0;                         // not LIST_SHORT: keys above bin B, and in it
+    int n_slots = 0;                                      // slots of the list in use
     constexpr int PRE = 12;                               // list slots per thread asked for before the segments' lengths are known
     uint64_t pre[SRC == SRC_LIST ? PRE : 1];
-    const uint64_t* const list = bf.cand + bh * (int64_t)sh.cand_cap;
+    uint64_t* const list = bf.cand + bh * (int64_t)sh.cand_cap;
     uint32_t seg_len = 0, flags = 0;
+    const bool helper = SRC == SRC_LIST && (int)blockIdx.z >= sh.attend;     // (uniform)
     if (SRC == SRC_LIST) {
         if (tid < sh.n_seg) seg_len = bf.seg_cnt[bh * sh.n_seg + tid];
         flags = bf.flags[bh];
+        const int n_pre = helper ? 0 : sh.cand_cap;
 #pragma unroll
         for (int u = 0; u < PRE; ++u) {
             const int i = u * NT + tid;
-            pre[u] = list[i < sh.cand_cap ? i : 0];       // (any slot of the list may be read; what lies beyond its segment is ignored)
+            pre[u] = list[i < n_pre ? i : 0];             // (any slot of the list may be read; what lies beyond its segment is ignored)
         }
     }
     const int N = (int)visible_len(sh, bf, b);
@@ -255,37 +368,112 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
             act |= i < P ? 1u << j : 0u;
         }
     } else if (k_eff > 0) {
-        // lengths and places of the segments; the list is usable if it holds all that passed, at least k_eff and not more than fits
-        uint32_t total;
-        const uint32_t longest_w = wave_max_u32(seg_len);
-        if (lane == 0) sm.hist[wave] = longest_w;
-        const uint32_t at = team_prefix<Team>(seg_len, total, sm, 0);
+        // lengths and places of the segments
+        uint32_t total, longest;
         uint2* const segs = reinterpret_cast<uint2*>(sm.keys);
-        segs[tid] = make_uint2(seg_len, at);
-        const uint32_t longest = wave_max_u32(lane < NW ? sm.hist[lane] : 0u);
-        const bool over = longest > (uint32_t)sh.seg_cap || total < (uint32_t)k_eff;
+        const int log2_n_seg = 31 - __clz(sh.n_seg);
+        auto lay_out = [&]() {
+            const uint32_t longest_w = wave_max_u32(seg_len);
+            if (lane == 0) sm.hist[wave] = longest_w;
+            const uint32_t at = team_prefix<Team>(seg_len, total, sm, 0);
+            segs[tid] = make_uint2(seg_len, at);
+            longest = wave_max_u32(lane < NW ? sm.hist[lane] : 0u);
+            n_slots = (int)((longest + kCandChunk - 1) >> kCandChunkLog2) * sh.n_seg * kCandChunk;
+        };
+        lay_out();
         // (an index leaves the approximate scores of a head it marked as not filterable)
-        usable = !over && total <= (uint32_t)(CPT * NT) && !(flags & (sh.indexed ? 5u : 4u));
-        if (usable) {
-            n_items = (int)total;
-            const int log2_n_seg = 31 - __clz(sh.n_seg);
-            const int n_slots = (int)((longest + kCandChunk - 1) >> kCandChunkLog2) * sh.n_seg * kCandChunk;
-            auto place = [&](int i, uint64_t ent) {       // slot i of the list: entry e of segment g
-                const uint2 s = segs[cand_slot_segment(i, log2_n_seg)];
-                const uint32_t e = (uint32_t)cand_slot_entry(i, log2_n_seg);
-                if (e < s.x) cand_lds[s.y + e] = ent;
-            };
+        const bool over = longest > (uint32_t)sh.seg_cap || (flags & (sh.indexed ? 5u : 4u));
+        if (over || total < (uint32_t)k_eff || total > (uint32_t)(CPT * NT)) {
+            // the bin of the k-th score from the scan's counts: lane l of every wave looks at bin kTailBins - 1 - l
+            static_assert(kTailBins == kWave, "a bin per lane");
+            const int n_wg = sh.n_seg / kScanWaves;
+            const uint32_t* const hp = bf.hist + bh * (int64_t)sh.hist_cap * kTailBins;
+            const float bin_lo = bf.bins[2 * bh], bin_inv = bf.bins[2 * bh + 1];
+            uint32_t* const part = reinterpret_cast<uint32_t*>(cand_lds);
+            uint32_t n = 0;
+#pragma unroll 4
+            for (int j = wave; j < n_wg; j += NW) n += hp[j * kTailBins + lane];
+            part[wave * kTailBins + lane] = n;
             __syncthreads();
+            uint32_t all = 0;
 #pragma unroll
-            for (int u = 0; u < PRE; ++u)
-                if (u * NT < n_slots) place(u * NT + tid, pre[u]);           // (n_slots is a multiple of 64; a segment's slots lie below it)
-            for (int i0 = PRE * NT + tid; i0 < n_slots; i0 += 4 * NT) {
-                uint64_t ent[4];
+            for (int w = 0; w < NW; ++w) all += part[w * kTailBins + kTailBins - 1 - lane];
+            const uint32_t upto = wave_scan_add(all);
+            const uint64_t hit = __ballot(upto - all < (uint32_t)k_eff && (uint32_t)k_eff <= upto);      // (one lane, or the counts do not cover k_eff keys)
+            const int hit_lane = hit ? __builtin_ctzll(hit) : 0;
+            const int B = kTailBins - 1 - hit_lane;
+            in_b = (uint32_t)__builtin_amdgcn_readlane((int)all, hit_lane);
+            above = (uint32_t)__builtin_amdgcn_readlane((int)upto, hit_lane) - in_b;
+            const uint32_t n_cut = above + in_b;
+            if (!hit) how = SCORE_ROW;
+            else if (over) how = sh.no_rescan || n_cut > (uint32_t)(CPT * NT) ? SCORE_ROW : RESCORE;
+            else how = n_cut <= (uint32_t)(CPT * NT) ? LONG_CUT : LONG_TIED;
+            // a list that should have been usable (the measure of the chip-wide selection)
+            const bool fallback = (over || !hit || in_b > (uint32_t)sh.bnd_cap) && !(flags & 5u);
+            if (how == LONG_CUT) {
+#pragma unroll 4
+                for (int j = wave; j < n_wg; j += NW) {
+                    const uint32_t c = wave_scan_add(lane >= B ? hp[j * kTailBins + lane] : 0u);
+                    if (lane == kWave - 1) sm.hist[j] = c;
+                }
+                __syncthreads();
+                const uint32_t at = team_prefix<Team>(tid < n_wg ? sm.hist[tid] : 0u, total, sm, 1);     // (total: n_cut)
+                if (tid < n_wg) sm.hist[tid] = at;
+                __syncthreads();
+                cut_list<NW>(sh, wave, B, bin_lo, bin_inv, segs, sm.hist, list, cand_lds, (uint32_t)(CPT * NT));
+            } else if (how == LONG_TIED) {
+                if (blockIdx.z != 0) return;                                          // (uniform)
+                if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
+                alone = true;
+            } else {
+                if constexpr (SRC == SRC_LIST)
+                    score_segments<DT, DIM>(sh, bf, b, h, P, (int)blockIdx.z * NW + wave, (int)gridDim.z * NW,
+                                            how == SCORE_ROW ? kTailBins : B, bin_lo, bin_inv, list);
+                // every wave waits for its stores to arrive in the L2, one thread releases them all (a release writes back the whole
+                // L2 of the XCD; one per wave: 247 us per call instead of 147 at one KV head, 512k tokens, 92 % identical)
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+                __syncthreads();
+                if (tid == 0) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                    sm.n_keys = atomicAdd(&bf.flags[bh], kArrivalUnit);               // (the threshold estimate cleared the count)
+                }
+                __syncthreads();
+                const uint32_t arrived = sm.n_keys;
+                if (arrived / kArrivalUnit + 1u != gridDim.z) return;                 // (uniform)
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+                if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
+                alone = true;
+                if (how == RESCORE && (arrived & 2u)) how = SCORE_ROW;
+                if (how == RESCORE) {
+                    seg_len = tid < sh.n_seg ? bf.seg_cnt2[bh * sh.n_seg + tid] : 0u;
+                    lay_out();
+                }
+            }
+            in_regs = how == LONG_CUT || how == RESCORE;
+        }
+        if (helper && !alone) return;                     // (uniform)
+        if (in_regs) {
+            n_items = (int)total;
+            if (how != LONG_CUT) {
+                auto place = [&](int i, uint64_t ent) {   // slot i of the list: entry e of segment g
+                    const uint2 s = segs[cand_slot_segment(i, log2_n_seg)];
+                    const uint32_t e = (uint32_t)cand_slot_entry(i, log2_n_seg);
+                    if (e < s.x) cand_lds[s.y + e] = ent;
+                };
+                __syncthreads();
+                if (how == LIST_SHORT) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) ent[u] = list[i0 + u * NT < n_slots ? i0 + u * NT : 0];
+                    for (int u = 0; u < PRE; ++u)
+                        if (u * NT < n_slots) place(u * NT + tid, pre[u]);   // (n_slots is a multiple of 64; a segment's slots lie below it)
+                }
+                for (int i0 = (how == LIST_SHORT ? PRE * NT : 0) + tid; i0 < n_slots; i0 += 4 * NT) {
+                    uint64_t ent[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (i0 + u * NT < n_slots) place(i0 + u * NT, ent[u]);
+                    for (int u = 0; u < 4; ++u) ent[u] = list[i0 + u * NT < n_slots ? i0 + u * NT : 0];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (i0 + u * NT < n_slots) place(i0 + u * NT, ent[u]);
+                }
             }
             __syncthreads();
 #pragma unroll
@@ -296,23 +484,6 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
                     act |= i < n_items ? 1u << j : 0u;
                 }
             }
-        } else {
-            // all scores of the head to the score buffer, by all its workgroups; the last one to finish goes on
-            if constexpr (DT != DT_F32) {
-                const int64_t first = (int64_t)blockIdx.z * NW + wave, step = (int64_t)gridDim.z * NW;
-                if (D == 128) score_keys<DT, 128>(sh, bf, b, h, P, first, step);
-                else if (D == 64) score_keys<DT, 64>(sh, bf, b, h, P, first, step);
-                else if (D == 256) score_keys<DT, 256>(sh, bf, b, h, P, first, step);
-                else score_keys<DT, 32>(sh, bf, b, h, P, first, step);
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            __syncthreads();
-            if (tid == 0) sm.n_keys = atomicAdd(&bf.flags[bh], kArrivalUnit) / kArrivalUnit;     // (the threshold estimate cleared the count)
-            __syncthreads();
-            if (sm.n_keys + 1u != gridDim.z) return;      // (uniform)
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-            // a list that should have been usable (the measure of the chip-wide selection, whose lists are longer)
-            if (tid == 0 && (over || total > (uint32_t)sh.bnd_cap) && !(flags & 5u)) atomicAdd(bf.fallback_total, 1u);
         }
     }
 
@@ -349,7 +520,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
             }
         }
     }
-    if (usable) {
+    if (in_regs) {
 #pragma unroll
         for (int j = 0; j < CPT; ++j) {
             if (j * NT < n_items) {                       // (uniform)
@@ -358,7 +529,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
             }
         }
     }
-    if (SRC == SRC_LIST && !usable) __syncthreads();      // (n_keys was read above)
+    if (SRC == SRC_LIST && alone) __syncthreads();        // (what select_clear() writes was read above)
     select_clear<Team>(sm);
     team_range<Team>(lo, hi, sm, 0);
     float top = hi;                                       // largest selected score
@@ -367,7 +538,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
         team_range<Team>(dummy, w_top, sm, 1);
     }
     float M = fmaxf(k_eff > 0 ? top : -INFINITY, w_top);  // the weights' reference score
-    const bool writer = blockIdx.z == 0 || !usable;       // (uniform) the workgroup that writes the selection
+    const bool writer = blockIdx.z == 0 || alone;         // (uniform) the workgroup that writes the selection
     auto weight = [&](float s) { return (uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32; };
     auto emit = [&](uint32_t o, float s, int32_t p) {     // winner o of the head
         if (o < (uint32_t)k_eff) {                        // always true; guards the buffers
@@ -381,22 +552,30 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
 
     // ---- the k_eff best
     Boundary left{0u, 0u};
-    if (usable && k_eff > 0) {
+    if (in_regs && k_eff > 0) {
         left = team_select<Team, CPT, CPT>([&](int j) { return v[j]; }, act, n_items, P, k_eff, lo, hi, sm, pos, emit);
         if (writer) pad_outputs(k_eff, sh.k, idx, vals);
     } else if (k_eff == 0) {                              // nothing to search for this sequence
+        if (helper) return;
         if (writer) pad_outputs(0, sh.k, idx, vals);
-    } else if (SRC == SRC_LIST) {                         // radix select over the full score row
+    } else if (SRC == SRC_LIST) {                         // radix select over the list or the full score row
         __shared__ SelShared sel_sm;
-        top = key_score(wg_select_dense<NT, 0>(sh, bf, bh, P, k_eff, sel_sm));      // writes idx, vals and their padding
+        if (how == SCORE_ROW) {
+            top = key_score(wg_select_dense<NT, 0>(sh, bf, bh, P, k_eff, sel_sm));      // writes idx, vals and their padding
+        } else {
+            const SrcSegments<NT> src{list, reinterpret_cast<const uint2*>(sm.keys), n_slots, 31 - __clz(sh.n_seg)};
+            const Items<0, SrcSegments<NT>> items(src);
+            top = key_score(wg_topk_emit(items, k_eff, sh.k, idx, vals, sel_sm));
+        }
         M = fmaxf(top, w_top);
         __syncthreads();
         for (int o = tid; o < k_eff; o += NT) rows_lds[o] = weight(vals[o]) | (uint64_t)(uint32_t)idx[o];
     }
     if (SRC == SRC_LIST && tid == 0 && writer) {          // the head's record, as the chip-wide selection leaves it
         uint32_t* const rec = bf.tailrec + 4 * bh;
-        const bool sel = usable && k_eff > 0;
-        rec[0] = k_eff == 0 ? 2u : usable ? 0u : 1u;
+        const bool sel = how != SCORE_ROW && k_eff > 0;
+        if (how != LIST_SHORT) left = Boundary{in_b, (uint32_t)k_eff - above};
+        rec[0] = k_eff == 0 ? 2u : sel ? 0u : 1u;
         rec[1] = sel ? (uint32_t)k_eff - left.need : 0u;
         rec[2] = sel ? left.need : 0u;
         rec[3] = sel ? left.in : 0u;
@@ -412,7 +591,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
     float lsum = 0.f;
     const int step = NW * rpw;
-    const int shares = SRC == SRC_LIST && usable ? (int)gridDim.z : 1;
+    const int shares = SRC == SRC_LIST && !alone ? sh.attend : 1;
     const int share = shares > 1 ? (int)blockIdx.z : 0;
     const int row_end = (int)((int64_t)n_rows * (share + 1) / shares);
     for (int j = (int)((int64_t)n_rows * share / shares) + wave * rpw + rs; j < row_end; j += U * step) {
@@ -666,10 +845,20 @@ hipError_t launch_attend_row(const Shape& s, const Bufs& b, int64_t Nmax, hipStr
 hipError_t launch_attend_list(const Shape& s, const Bufs& b, hipStream_t st) {
     const float scale = 1.0f / sqrtf((float)s.D);
     const float scale_log2e = scale * 1.4426950408889634f;
-    const dim3 grid((unsigned)s.Hq, (unsigned)s.B, (unsigned)s.attend);
-    if (s.dtype == DT_F16) hipLaunchKernelGGL((attend_kernel<DT_F16, ListCfg, SRC_LIST>), grid, dim3(ListCfg::NT), 0, st, s, b, scale, scale_log2e);
-    else if (s.dtype == DT_BF16) hipLaunchKernelGGL((attend_kernel<DT_BF16, ListCfg, SRC_LIST>), grid, dim3(ListCfg::NT), 0, st, s, b, scale, scale_log2e);
+    // as many helpers as fit the compute units beside the shares, a wave of theirs per segment at most
+    const int64_t room = std::min<int64_t>(kAttendManyHeads / ((int64_t)s.Hq * s.B), s.n_seg / ListCfg::NW);
+    const dim3 grid((unsigned)s.Hq, (unsigned)s.B, (unsigned)std::max<int64_t>(s.attend, room));
+#define TKA_AL(DT_, D_) hipLaunchKernelGGL((attend_kernel<DT_, ListCfg, SRC_LIST, D_>), grid, dim3(ListCfg::NT), 0, st, s, b, scale, scale_log2e)
+    if (s.dtype == DT_F16 && s.D == 128) TKA_AL(DT_F16, 128);
+    else if (s.dtype == DT_BF16 && s.D == 128) TKA_AL(DT_BF16, 128);
+    else if (s.dtype == DT_F16 && s.D == 64) TKA_AL(DT_F16, 64);
+    else if (s.dtype == DT_BF16 && s.D == 64) TKA_AL(DT_BF16, 64);
+    else if (s.dtype == DT_F16 && s.D == 256) TKA_AL(DT_F16, 256);
+    else if (s.dtype == DT_BF16 && s.D == 256) TKA_AL(DT_BF16, 256);
+    else if (s.dtype == DT_F16 && s.D == 32) TKA_AL(DT_F16, 32);
+    else if (s.dtype == DT_BF16 && s.D == 32) TKA_AL(DT_BF16, 32);
     else return hipErrorInvalidValue;
+#undef TKA_AL
     return hipGetLastError();
 }
 

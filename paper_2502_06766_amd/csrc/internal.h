@@ -203,7 +203,7 @@ constexpr int64_t kAttendRowMax = 16384;  // scores of the longest row
 constexpr int kAttendList = 10240;        // candidates of the longest list
 constexpr int kAttendRows = 4096;         // value rows (selected and window) whose positions and weights fit LDS beside a list
 constexpr int kAttendShares = 8;          // workgroups per head at most
-constexpr int64_t kAttendShareKeys = 131072;   // keys a workgroup may have to score again when a list is unusable
+constexpr int64_t kAttendShareKeys = 131072;   // keys a workgroup may have to score again when a list is unusable (1.5 ms for one head alone)
 constexpr uint32_t kArrivalUnit = 256;    // the flag word counts a head's workgroups above its flag bits
 // More heads than this fill the chip with one workgroup each: small workgroups, several to a compute unit, for short rows.
 constexpr int64_t kAttendManyHeads = 256;

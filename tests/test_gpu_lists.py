@@ -1,0 +1,127 @@
+"""Candidate lists the one-launch selection (csrc/attend.hip) cannot take as they are: longer than a workgroup's registers, or with
+a segment that overflowed.  Groups of identical keys make them (a quarter of the cache that scores alike, just below the k-th
+score, is a list of tens of thousands).  All elements of q and K are small multiples of a power of two, so the
+scores are exact in fp32 and the selection has to equal the oracle's, ties to the lower position."""
+import numpy as np
+import pytest
+import torch
+
+import helpers as H
+from oracle import c_oracle
+from paper_2502_06766_amd import topk_attn as ta
+from paper_2502_06766_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0) if torch.cuda.is_available() else None
+IN_REGISTERS = 10240            # candidates a workgroup takes
+
+
+def make_tied(seed, M, Hq, Hkv, N, d, groups, hot=None):
+    """q [M, Hq, d], K, V [Hkv, N, d] (float32, exact in 16 bits).  groups: (share of the cache, score in standard deviations);
+    hot: positions of one more group, four standard deviations up.  The queries of a chunk differ in one channel, so that a
+    group scores alike for all of them."""
+    g = np.random.default_rng(seed)
+    q = np.repeat(g.integers(-3, 4, (1, Hq, d)).astype(np.float32) / 16, M, axis=0)
+    for m in range(1, M):
+        q[m, :, m % d] += 1 / 16
+    K = g.integers(-8, 9, (Hkv, N, d)).astype(np.float32)
+    V = g.standard_normal((Hkv, N, d)).astype(np.float32)
+    sigma = np.sqrt((17.0 ** 2 - 1) / 12)
+    for h in range(Hkv):
+        Q = q[0, h * (Hq // Hkv):(h + 1) * (Hq // Hkv)].astype(np.float64)
+        at = lambda z: np.rint(8 * np.linalg.lstsq(Q, z * sigma * np.linalg.norm(Q, axis=1), rcond=None)[0]) / 8
+        perm = g.permutation(N)
+        for share, z in groups:
+            n = int(share * N)
+            K[h, perm[:n]] = at(z)
+            perm = perm[n:]
+        if hot is not None:
+            K[h, hot] = at(4.0)
+    return q, K, V
+
+
+def check_exact(res, q, K, V, dtype, k, causal, window, label):
+    """res: (out, idx, vals, lse) of one sequence, numpy, [M, Hq, ...]."""
+    M, Hq, _ = q.shape
+    N = K.shape[1]
+    vmax = float(np.abs(wl.widen(V, dtype)).max())
+    for m in range(M):
+        n = N - (M - 1 - m) if causal else N
+        Km, Vm = (K, V) if n == N else (np.ascontiguousarray(K[:, :n]), np.ascontiguousarray(V[:, :n]))
+        ref = c_oracle.topk_attention_window(q[m], Km, Vm, dtype, k, window)
+        H.check_against_oracle(*(r[m] for r in res), ref, np.full(Hq, 1e-30), min(k, n - window), H.out_tolerance(dtype), vmax,
+                               f"{label} query {m}")
+
+
+def how_selected(cache, rows):
+    """Per row: what became of its list, from the records and the scan's counts."""
+    rec = ta.topk_attn_last_selection_records(cache.h, rows)
+    dims = ta.topk_attn_debug_read_workspace_dims(cache.h)
+    n_seg, seg_cap, bnd_cap = dims[4], dims[5], dims[1]
+    cnt = ta.topk_attn_debug_read_workspace(cache.h, "seg_cnt", np.uint32, n_seg * rows).reshape(rows, n_seg)
+    res, fallbacks = [], 0
+    for r, c in zip(rec, cnt):
+        over, cut = bool(c.max() > seg_cap), r[1] + r[3]
+        if r[0] & 0xFF == 1:
+            res.append("row")
+        elif not over and c.sum() <= IN_REGISTERS:
+            res.append("short")
+        else:
+            res.append(("rescored" if over else "long") + (", tied" if cut > IN_REGISTERS else ""))
+        fallbacks += over or r[0] & 0xFF == 1 or r[3] > bnd_cap
+    return res, fallbacks
+
+
+@pytest.mark.parametrize("expect,dtype,M,Hq,Hkv,N,d,k,window,groups", [
+    ("long", wl.F16, 1, 4, 2, 131072, 64, 2048, 0, [(0.25, 1.9)]),              # eight workgroups per head
+    ("long", wl.BF16, 9, 16, 2, 40000, 32, 300, 100, [(0.3, 1.8)]),             # one workgroup per head, causal chunk, window
+    ("long", wl.F16, 1, 1, 1, 100001, 256, 1000, 0, [(0.2, 2.0)]),
+    ("long", wl.BF16, 1, 8, 1, 150000, 128, 1000, 30, [(0.2, 2.1)]),            # the row-tile scan
+    ("long, tied", wl.BF16, 1, 8, 2, 131072, 256, 2048, 64, [(0.15, 3.0)]),
+    ("long, tied", wl.F16, 16, 16, 4, 50000, 64, 500, 0, [(0.5, 2.8)]),         # one workgroup per head
+    ("long, tied", wl.F16, 1, 8, 8, 100000, 64, 500, 0, [(0.7, 2.8)]),          # more ties than the boundary list holds: a fallback
+    ("rescored", wl.F16, 1, 2, 1, 524288, 64, 1500, 0, [(0.92, 1.5)]),
+    ("rescored", wl.BF16, 1, 1, 1, 524289, 256, 1500, 40, [(0.92, 1.5)]),
+    ("rescored", wl.BF16, 1, 3, 1, 524000, 32, 1500, 0, [(0.92, 1.5)]),
+    ("rescored", wl.F16, 3, 4, 1, 700000, 64, 1000, 50, [(0.8, 2.2)]),          # the row-tile scan, causal chunk
+    ("row", wl.F16, 1, 2, 1, 524288, 128, 1500, 0, [(0.92, 3.0)]),             # more ties than the segments hold
+])
+def test_lists_that_do_not_fit(expect, dtype, M, Hq, Hkv, N, d, k, window, groups):
+    q, K, V = (wl.quantize(a, dtype) for a in make_tied(N + k, M, Hq, Hkv, N, d, groups))
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, N, k, dtype, max_window=window, max_queries=M)
+    try:
+        cache.append(0, 0, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        qd = H.to_torch(q, dtype, DEV)[None].contiguous()
+        res = cache.decode_multi(0, qd, k, window=window)
+        fb = cache.last_fallbacks()
+        how, want_fb = how_selected(cache, M * Hq)
+        print(how[:8], "fallbacks", fb, flush=True)
+        assert set(how) == {expect}
+        assert fb == want_fb
+        again = cache.decode_multi(0, qd, k, window=window)
+        torch.cuda.synchronize()
+        for a, b in zip(res, again):
+            assert torch.equal(a, b)
+        check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, window, expect)
+    finally:
+        cache.close()
+
+
+def test_a_segment_that_overflows_again():
+    """512 of the best keys lie in the tiles of one wave segment, more than it holds, and still do when the bins
+    below the k-th score's are left out: the head is selected from its full score row."""
+    dtype, Hq, N, d, k, n_seg, sid = wl.F16, 2, 524288, 64, 1500, 1024, 517
+    tiles = [i * n_seg + ((sid + (((i * 0x9E3779B1) & 0xFFFFFFFF) >> 12)) & (n_seg - 1)) for i in range(N // 64 // n_seg)]
+    hot = np.concatenate([np.arange(t * 64, t * 64 + 64) for t in tiles])
+    q, K, V = (wl.quantize(a, dtype) for a in make_tied(11, 1, Hq, 1, N, d, [], hot))
+    cache = ta.TopkAttnCache(1, 1, Hq, 1, d, N, k, dtype)
+    try:
+        cache.append(0, 0, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        res = cache.decode_multi(0, H.to_torch(q, dtype, DEV)[None].contiguous(), k)
+        assert cache.last_fallbacks() == Hq
+        assert ta.topk_attn_debug_read_workspace_dims(cache.h)[4] == n_seg
+        rec = ta.topk_attn_last_selection_records(cache.h, Hq)
+        assert all(r[0] & 0xFF == 1 and r[0] >> 8 == 2 for r in rec), rec
+        check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, 0, "one hot segment")
+    finally:
+        cache.close()
