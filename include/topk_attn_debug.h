@@ -30,7 +30,7 @@ int topk_attn_last_fallbacks(topk_attn_t* h, int* n_heads);
 int topk_attn_last_pages_read(topk_attn_t* h, int64_t* pages_read, int64_t* pages_total);
 
 /* After the caller has synchronised the stream: what the selection of the last decode found for each
- * (sequence, query, head) row that took the filtered path with the chip-wide selection: records[4 i + 0] = 0 if
+ * (sequence, query, head) row that took the filtered path: records[4 i + 0] = 0 if
  * the head's candidate list was used or its keys were sorted again, 1 if it was selected from its full
  * score row, 2 if there was nothing to search, with the head's flag word in bits 8 and up (bit 8: its
  * sequence cannot be filtered, bit 9: the keys sorted again did not fit either, bit 10: forced redo); [4 i + 1] = keys
@@ -42,7 +42,8 @@ int topk_attn_last_selection_records(topk_attn_t* h, uint32_t* records);
 /* After the caller has synchronised the stream: copies the first `bytes` bytes of one of the per-call arrays of
  * the handle's workspace to the host array `dst` (for tests that look at what a decode left behind).  Names:
  * "thr", "bins", "samp", "seg_cnt", "seg_max", "seg_cnt2", "flags", "tailrec", "page_mask", "page_cnt",
- * "page_list", "hist", "cand", "bnd".  EINVAL for another name or more bytes than the array holds.  The second call
+ * "page_list", "hist", "cand", "bnd".  ("flags": the flag bits of the records below bit 8, above them how many workgroups of
+ * the one-launch selection have handed over their part of the head.)  EINVAL for another name or more bytes than the array holds.  The second call
  * reports dims[0..5] = entries per candidate list, entries per boundary list, scan workgroups the per-bin counts
  * have room for, most wave segments per head, and the wave segments and entries per segment of the last
  * filtered decode (0, 0 if the last decode was not filtered). */
@@ -51,8 +52,9 @@ int topk_attn_debug_read_workspace_dims(topk_attn_t* h, int32_t* dims);
 
 /* Measurement aid for the worst case of the filtered path: when enabled, every head of a decode
  * that takes the filtered path is treated like a head whose candidate list turned out unusable
- * (nothing passes its scan; all its keys are rescored exactly and selected from the full score
- * row).  Results are unchanged; such heads are not counted by topk_attn_last_fallbacks, which
+ * (all its keys are scored again exactly, and selected from those that can win or from the full score
+ * row), by the selection that the call takes anyway.  enable == 2: calls that would take the one-launch
+ * selection take the chip-wide one too.  Results are unchanged; such heads are not counted by topk_attn_last_fallbacks, which
  * counts lists that should have been usable. */
 int topk_attn_debug_force_redo(topk_attn_t* h, int enable);
 

@@ -325,7 +325,7 @@ struct topk_attn {
     int path;
     bool last_fast;
     bool last_static;           // the last decode used the built-in scratch
-    bool force_redo;            // measurement aid, see topk_attn_debug_force_redo
+    int force_redo;             // measurement aid, see topk_attn_debug_force_redo: 0, 1, or 2 (chip-wide selection)
     float page_beta;            // scale of the page radius in the page bound (1 = exact)
     bool last_paged;            // the last decode went through the page index
     bool last_tail;             // the last decode used the chip-wide selection (its per-head records are in the workspace)
@@ -378,7 +378,7 @@ int topk_attn_create(const topk_attn_config* cfg, topk_attn_t** out) {
     if (hipGetDeviceProperties(&prop, cfg->device) != hipSuccess) { delete h; return TOPK_ATTN_EDEVICE; }
     h->n_cu = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 256;
     h->last_static = false;
-    h->force_redo = false;
+    h->force_redo = 0;
     h->page_beta = 1.0f;
     h->last_paged = false;
     h->last_tail = false;
@@ -685,7 +685,7 @@ static int lengths_of(const topk_attn_t* h, int layer, int window, int64_t min_t
 // would run at least four (chunks of queries: 16 queries at 128k tokens 172 against 185 us; batches of 16 sequences of 10k
 // tokens, one tail workgroup per head, 111 against 105 us).
 static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax) {
-    if (h->force_redo || s.k + s.window > kAttendRows) return 0;
+    if (h->force_redo == 2 || s.k + s.window > kAttendRows) return 0;
     if (make_plan(nmax, s.k < nmax ? s.k : (int)nmax, s.indexed).c_hi > kAttendList) return 0;
     const int64_t heads = (int64_t)s.B * s.Hq;
     if (heads > kAttendManyHeads && (s.tail_wgs < 4 || heads > 4 * kAttendManyHeads)) return 0;
@@ -1009,7 +1009,7 @@ int topk_attn_debug_read_workspace_dims(topk_attn_t* h, int32_t* dims) {
 
 int topk_attn_debug_force_redo(topk_attn_t* h, int enable) {
     if (!h) return TOPK_ATTN_EINVAL;
-    h->force_redo = enable != 0;
+    h->force_redo = enable == 2 ? 2 : enable != 0;
     return TOPK_ATTN_OK;
 }
 

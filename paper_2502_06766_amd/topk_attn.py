@@ -272,8 +272,9 @@ def topk_attn_debug_read_workspace_dims(h):
     return tuple(d)
 
 
-def topk_attn_debug_force_redo(h, enable: bool):
-    _check(lib().topk_attn_debug_force_redo(h, 1 if enable else 0), "topk_attn_debug_force_redo")
+def topk_attn_debug_force_redo(h, enable):
+    """enable: False, True, or 2 (the same with the chip-wide selection for every call)."""
+    _check(lib().topk_attn_debug_force_redo(h, int(enable)), "topk_attn_debug_force_redo")
 
 
 def topk_attn_set_scan_timing(h, enable: bool):

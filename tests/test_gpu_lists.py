@@ -125,3 +125,45 @@ def test_a_segment_that_overflows_again():
         check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, 0, "one hot segment")
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("dtype,M,Hq,Hkv,N,d,k,window,index", [
+    (wl.F16, 1, 2, 1, 300000, 128, 1500, 0, ta.INDEX_NONE),
+    (wl.BF16, 1, 8, 2, 300000, 64, 800, 0, ta.INDEX_NONE),
+    (wl.BF16, 1, 3, 1, 200000, 32, 500, 0, ta.INDEX_NONE),
+    (wl.F16, 1, 4, 4, 150000, 256, 700, 100, ta.INDEX_NONE),
+    (wl.F16, 1, 8, 1, 300000, 128, 1500, 0, ta.INDEX_NONE),        # the row-tile scan
+    (wl.BF16, 1, 40, 2, 200000, 64, 600, 0, ta.INDEX_NONE),        # two row tiles
+    (wl.F16, 4, 8, 2, 100001, 128, 700, 0, ta.INDEX_NONE),
+    (wl.BF16, 16, 16, 4, 40000, 64, 400, 64, ta.INDEX_NONE),       # one workgroup per head
+    (wl.BF16, 1, 4, 1, 30000, 128, 4000, 90, ta.INDEX_NONE),       # as many rows as fit
+    (wl.F16, 1, 4, 1, 100000, 64, 700, 0, ta.INDEX_INT8),          # with an index: from the full score row
+    (wl.BF16, 1, 4, 2, 70001, 256, 300, 64, ta.INDEX_INT8),
+    (wl.F16, 1, 4, 2, 70000, 32, 500, 0, ta.INDEX_PAGES),
+    (wl.BF16, 1, 6, 2, 50001, 128, 300, 200, ta.INDEX_PAGES),
+])
+def test_forced_redo_by_both_selections(dtype, M, Hq, Hkv, N, d, k, window, index):
+    """Every head's list treated as unusable, by the one-launch selection (which these calls take) and by the chip-wide one: what the
+    second scoring keeps is what the scan counted, and the selection is the oracle's."""
+    q, K, V = (wl.quantize(a, dtype) for a in make_tied(N + k, M, Hq, Hkv, N, d, []))
+    rows = M * Hq
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, N, k, dtype, max_window=window, max_queries=M, index_kind=index)
+    try:
+        cache.set_path({ta.INDEX_NONE: ta.PATH_AUTO, ta.INDEX_INT8: ta.PATH_INDEX, ta.INDEX_PAGES: ta.PATH_PAGES}[index])
+        cache.append(0, 0, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        qd = H.to_torch(q, dtype, DEV)[None].contiguous()
+        for mode in (1, 2):
+            ta.topk_attn_debug_force_redo(cache.h, mode)
+            res = cache.decode_multi(0, qd, k, window=window)
+            assert cache.last_fallbacks() == 0          # forced, not counted
+            rec = ta.topk_attn_last_selection_records(cache.h, rows)
+            assert all(r[0] == (4 << 8 | (0 if index == ta.INDEX_NONE else 1)) for r in rec), rec
+            handed_over = ta.topk_attn_debug_read_workspace(cache.h, "flags", np.uint32, rows) >> 8
+            assert (handed_over > 0).all() if mode == 1 else (handed_over == 0).all()
+            if index == ta.INDEX_NONE:
+                dims = ta.topk_attn_debug_read_workspace_dims(cache.h)
+                kept = ta.topk_attn_debug_read_workspace(cache.h, "seg_cnt2", np.uint32, dims[4] * rows).reshape(rows, dims[4])
+                assert [int(c.sum()) for c in kept] == [r[1] + r[3] for r in rec]
+            check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, window, f"mode {mode}")
+    finally:
+        cache.close()
