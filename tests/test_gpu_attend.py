@@ -170,3 +170,19 @@ def test_replays_of_a_captured_call_equal_eager_calls(dtype, N, k, window):
                 assert torch.equal(got[0], eager[0]) and torch.equal(got[1], eager[1]), f"replay {rep}"
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("dtype,B,N,k,far", [(wl.F16, 1, 16384, 256, 3000.0), (wl.BF16, 1, 8000, 1000, 1000.0), (wl.F32, 1, 5000, 300, 30000.0),
+                                              (wl.F16, 64, 4000, 100, 3000.0), (wl.BF16, 40, 3000, 600, -3000.0)])
+def test_a_key_far_from_the_rest(dtype, B, N, k, far):
+    """One key scores hundreds of standard deviations away from all others (an attention sink): the linear bins over the range leave
+    most scores in one bin, which is split again."""
+    q, K, V = _make(dtype, B, 8, 2, N, 64, seed=N + k)
+    for b in range(B):
+        Kf = wl.widen(K[b], dtype).astype(np.float32).copy()
+        qf = wl.widen(q[b], dtype).astype(np.float32).reshape(2, 4, 64)
+        Kf[:, 5] = far / 64 * qf.mean(axis=1)
+        K[b] = wl.quantize(Kf, dtype)
+    res = _decode(q, K, V, dtype, k)
+    for b in sorted({0, B // 2, B - 1}):
+        H.check_unmargined(tuple(r[b] for r in res), q[b], K[b], V[b], dtype, k, 0, f"far {far} seq {b}")
