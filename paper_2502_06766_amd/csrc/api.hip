@@ -770,7 +770,7 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
     // score rows of the general path.
     if (fast) s.attend = attend_list_shares(h, s, nmax);
     else if (attend_short_applies(s, nmax)) s.attend = kAttendShort;
-    else s.attend = s.k + s.window <= attend_row_rows((int64_t)s.B * s.Hq, nmax) ? 1 : 0;
+    else s.attend = attend_row_applies((int64_t)s.B * s.Hq, nmax, s.k, s.window, s.D * elem_bytes(s.dtype)) ? 1 : 0;
     hipError_t e = hipSuccess;
     bool tail_done = false;
     if (use_static) {

@@ -826,7 +826,7 @@ hipError_t launch_attend_row(const Shape& s, const Bufs& b, int64_t Nmax, hipStr
     const float scale_log2e = scale * 1.4426950408889634f;
     const dim3 grid((unsigned)s.Hq, (unsigned)s.B);
     const bool many = (int64_t)s.Hq * s.B > kAttendManyHeads;
-    if (s.k + s.window > attend_row_rows((int64_t)s.Hq * s.B, Nmax)) return hipErrorInvalidValue;
+    if ((int64_t)s.k + s.window > attend_row_rows((int64_t)s.Hq * s.B, Nmax)) return hipErrorInvalidValue;
 #define TKA_AR(DT_, NT_, CPT_, NB_)                                                                                         \
     hipLaunchKernelGGL((attend_kernel<DT_, AttendCfg<NT_, CPT_, NT_ == 1024 ? 4096 : NT_ == 512 ? 2048 : 1024, NB_>, SRC_ROW>), \
                        grid, dim3(NT_), 0, st, s, b, scale, scale_log2e)

@@ -213,6 +213,18 @@ inline int attend_row_rows(int64_t heads, int64_t Nmax) {
     if (heads <= kAttendManyHeads || Nmax > 8192) return 4096;
     return Nmax <= 4096 ? 1024 : 2048;
 }
+// Whether one workgroup per head over score rows beats radix select and gather: not where it has more value rows to fetch than
+// it gains (it reaches about 64 GB/s, the gather has several per head), and where the heads fill the chip anyway not for
+// dense selections either.  One launch / radix select and gather, by value rows and their bytes, over 1 to 128 heads, 4k to 16k
+// tokens: 4096 rows of 256 bytes 0.83 - 1.00, 3000 of 512 0.82 - 0.97, 2048 of 1024 0.85 - 0.99; 4096 of 512 0.99 - 1.25, 3000 of
+// 1024 0.98 - 1.26, 4096 of 1024 1.12 - 1.79.  160 to 1024 heads: up to a quarter of the row 0.83 - 1.01, half to three
+// quarters of it, below 1 MB 0.6 - 1.02, from 1 MB 0.92 - 1.07; all of it, below 100 MB for all heads 0.70 - 1.01, beyond 1.0 - 1.35.
+inline bool attend_row_applies(int64_t heads, int64_t Nmax, int k, int window, int row_bytes) {
+    const int64_t n = (k < Nmax ? k : Nmax) + window, bytes = n * row_bytes, MB = 1 << 20;
+    if ((int64_t)k + window > attend_row_rows(heads, Nmax)) return false;
+    if (bytes > MB && (n > 3072 || bytes > 2 * MB)) return false;
+    return heads <= 128 || n * 4 <= Nmax || (n * 4 <= 3 * Nmax && bytes < MB) || heads * bytes <= 100 * MB;
+}
 
 // The same with the scores of a key stream in LDS (batches of short sequences): largest k for rows of up to Nmax scores, 0
 // where they are too long.  (Two workgroups of 4096 scores and 256 rows per head share a compute unit's LDS.)

@@ -186,3 +186,21 @@ def test_a_key_far_from_the_rest(dtype, B, N, k, far):
     res = _decode(q, K, V, dtype, k)
     for b in sorted({0, B // 2, B - 1}):
         H.check_unmargined(tuple(r[b] for r in res), q[b], K[b], V[b], dtype, k, 0, f"far {far} seq {b}")
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,N,d,k,window", [
+    (wl.F16, 1, 4, 2, 4096, 256, 3072, 0),           # 1.5 MB of value rows per head: one launch
+    (wl.F16, 1, 4, 2, 4096, 256, 3073, 0),           # radix select and gather
+    (wl.F32, 1, 4, 2, 5000, 256, 2048, 0),
+    (wl.F32, 1, 4, 2, 5000, 256, 1849, 200),
+    (wl.BF16, 5, 32, 8, 4000, 128, 1000, 0),         # 160 heads: a quarter of the row
+    (wl.F16, 5, 32, 8, 4000, 256, 3000, 0),
+    (wl.F32, 5, 32, 8, 2000, 128, 2000, 0),          # everything selected
+    (wl.F32, 5, 32, 8, 1000, 64, 1000, 7),
+])
+def test_selections_of_many_or_wide_value_rows(dtype, B, Hq, Hkv, N, d, k, window):
+    """Both sides of the rule that leaves large selections to radix select and gather."""
+    q, K, V = _make(dtype, B, Hq, Hkv, N, d, seed=N + k + d)
+    res = _decode(q, K, V, dtype, k, window)
+    for b in sorted({0, B - 1}):
+        H.check_unmargined(tuple(r[b] for r in res), q[b], K[b], V[b], dtype, k, window, f"N={N} k={k} seq {b}")
