@@ -680,12 +680,13 @@ static int lengths_of(const topk_attn_t* h, int layer, int window, int64_t min_t
 
 // Workgroups per head of the one-launch selection over the candidate list (attend.hip), 0 where the chip-wide tail takes
 // the call.  32 heads, k = 256 .. 2048, against the tail's two launches: 49 against 56 us at 48k tokens, 73 against 82 at 128k,
-// 213 against 222 at 512k.  Its limits: a list and the rows to fetch fit LDS; the keys a workgroup scores again
+// 213 against 222 at 512k.  Its limits: a list and the rows to fetch fit LDS; every workgroup scores the window; the keys a workgroup scores again
 // when a list turns out unusable are bounded; heads beyond the compute units get one workgroup each, which pays where the tail
 // would run at least four (chunks of queries: 16 queries at 128k tokens 172 against 185 us; batches of 16 sequences of 10k
 // tokens, one tail workgroup per head, 111 against 105 us).
 static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax) {
-    if (h->force_redo == 2 || s.k + s.window > kAttendRows) return 0;
+    if (h->force_redo == 2 || (int64_t)s.k + s.window > kAttendRows) return 0;
+    if ((int64_t)s.window * s.D * 2 > kAttendWindowBytes) return 0;
     if (make_plan(nmax, s.k < nmax ? s.k : (int)nmax, s.indexed).c_hi > kAttendList) return 0;
     const int64_t heads = (int64_t)s.B * s.Hq;
     if (heads > kAttendManyHeads && (s.tail_wgs < 4 || heads > 4 * kAttendManyHeads)) return 0;

@@ -204,6 +204,9 @@ constexpr int kAttendList = 10240;        // candidates of the longest list
 constexpr int kAttendRows = 4096;         // value rows (selected and window) whose positions and weights fit LDS beside a list
 constexpr int kAttendShares = 8;          // workgroups per head at most
 constexpr int64_t kAttendShareKeys = 131072;   // keys a workgroup may have to score again when a list is unusable (1.5 ms for one head alone)
+// Bytes of the window's keys, which every workgroup of a head scores (one launch / chip-wide tail, k = 256 .. 3000, 4 to 128
+// heads: up to 375 KB 0.68 - 1.04, 512 KB 0.79 - 1.04, 750 KB 0.82 - 1.03, 1000 KB 0.85 - 1.10, 1500 and 1900 KB 1.00 - 1.17).
+constexpr int64_t kAttendWindowBytes = 640 << 10;
 constexpr uint32_t kArrivalUnit = 256;    // the flag word counts a head's workgroups above its flag bits
 // More heads than this fill the chip with one workgroup each: small workgroups, several to a compute unit, for short rows.
 constexpr int64_t kAttendManyHeads = 256;

@@ -167,3 +167,21 @@ def test_forced_redo_by_both_selections(dtype, M, Hq, Hkv, N, d, k, window, inde
             check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, window, f"mode {mode}")
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("dtype,d,window,one_launch", [(wl.BF16, 256, 1280, True), (wl.BF16, 256, 1281, False), (wl.F16, 128, 2561, False),
+                                                       (wl.F16, 64, 3900, True)])
+def test_wide_windows_go_to_the_chip_wide_selection(dtype, d, window, one_launch):
+    """Every workgroup of the one-launch selection scores the whole window: both sides of the rule that bounds it."""
+    Hq, Hkv, N, k = 8, 2, 40000, 150
+    q, K, V = (wl.quantize(a, dtype) for a in make_tied(d + window, 1, Hq, Hkv, N, d, []))
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, N, k, dtype, max_window=window)
+    try:
+        cache.append(0, 0, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        res = cache.decode_multi(0, H.to_torch(q, dtype, DEV)[None].contiguous(), k, window=window)
+        torch.cuda.synchronize()
+        handed_over = ta.topk_attn_debug_read_workspace(cache.h, "flags", np.uint32, Hq) >> 8
+        assert (handed_over > 0).all() if one_launch else (handed_over == 0).all()
+        check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, window, f"window {window}")
+    finally:
+        cache.close()
