@@ -185,3 +185,20 @@ def test_wide_windows_go_to_the_chip_wide_selection(dtype, d, window, one_launch
         check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, window, f"window {window}")
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("N,filtered", [(16385, False), (24575, False), (24576, True)])
+def test_pages_of_a_short_cache_are_not_filtered(N, filtered):
+    """With a page index the filtered scan begins where it did without the one-launch selection."""
+    dtype, Hq, Hkv, d, k = wl.F16, 8, 2, 128, 100
+    q, K, V = (wl.quantize(a, dtype) for a in make_tied(N, 1, Hq, Hkv, N, d, []))
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, N, k, dtype, index_kind=ta.INDEX_PAGES)
+    try:
+        cache.set_path(ta.PATH_PAGES)
+        cache.append(0, 0, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        res = cache.decode_multi(0, H.to_torch(q, dtype, DEV)[None].contiguous(), k)
+        torch.cuda.synchronize()
+        assert (ta.topk_attn_debug_read_workspace_dims(cache.h)[4] > 0) == filtered
+        check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, 0, f"N={N}")
+    finally:
+        cache.close()
