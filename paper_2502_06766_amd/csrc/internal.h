@@ -235,10 +235,14 @@ constexpr int attend_short_k(int64_t Nmax) { return Nmax <= 2048 ? 512 : Nmax <=
 constexpr int kAttendShort = -1;
 
 // The filter scan works the thresholds out itself where a wave can: samples of at most kScanSampMax scores, the grouped
-// layout, 16-bit keys, and no page index (whose filter needs the thresholds before the scan).
+// layout, 16-bit keys, and no page index (whose filter needs the thresholds before the scan).  Whole call, in the scan / in a launch
+// of its own, 17k to 131k tokens, d = 64 and 128, k = 300 and 9000: 4 and more key streams 0.93 - 1.01; two 0.97 - 1.03 and
+// one 0.96 - 1.07 (mostly above 1); d = 256, whose scan has no tile on its way meanwhile, 0.99 - 1.03 (above 1 in 88 of 120).  Samples of up to 4096 in the
+// scan (64 scores per lane) cost 1.0 - 1.15 for every number of streams and every sample size, through its registers.
 constexpr int kScanSampMax = 2048;
+constexpr int kScanSampStreams = 4;
 inline bool threshold_in_scan(const Shape& s, int64_t Nmax) {
-    return s.M == 1 && s.G <= 4 && !s.indexed && !s.paged && make_plan(Nmax, s.k < Nmax ? s.k : (int)Nmax).n_samp <= kScanSampMax;
+    return s.M == 1 && s.G <= 4 && s.D < 256 && s.B * s.Hkv >= kScanSampStreams && !s.indexed && !s.paged && make_plan(Nmax, s.k < Nmax ? s.k : (int)Nmax).n_samp <= kScanSampMax;
 }
 
 // Position of sample s: one jittered position inside each stride-long stratum.

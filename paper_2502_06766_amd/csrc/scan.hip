@@ -741,7 +741,7 @@ hipError_t launch_scan_filter(const Shape& s, const Bufs& b, int64_t Nmax, hipSt
             hipLaunchKernelGGL((scan_rows_kernel<DT_, D_, MODE_FILTER, 1>), grid, block, 0, st, s, b, 0,     \
                                (float*)nullptr);                                                             \
         else if (sampled)                                                                                    \
-            hipLaunchKernelGGL((scan_mfma_kernel<DT_, D_, MODE_FILTER, false, true>), grid, block, 0, st, s, \
+            hipLaunchKernelGGL((scan_mfma_kernel<DT_, D_, MODE_FILTER, false, (D_ < 256)>), grid, block, 0, st, s, \
                                b, 0, (float*)nullptr);                                                       \
         else                                                                                                 \
             hipLaunchKernelGGL((scan_mfma_kernel<DT_, D_, MODE_FILTER>), grid, block, 0, st, s, b, 0,        \

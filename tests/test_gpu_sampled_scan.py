@@ -44,3 +44,17 @@ def test_thresholds_worked_out_by_the_scan(dtype, Hq, Hkv, d, lens, k, window):
             H.check_unmargined(tuple(t[b].cpu().numpy() for t in res), q[b], K[b], V[b], dtype, k, window, f"seq {b}")
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("dtype,Hq,Hkv,d,lens,k,window", [
+    (wl.F16, 16, 4, 64, [135167], 300, 0),                   # four key streams, the fewest that do without a launch; the largest sample
+    (wl.F16, 16, 4, 64, [135168], 300, 0),
+    (wl.F16, 12, 3, 64, [135167], 300, 0),                   # three
+    (wl.BF16, 4, 4, 128, [65536 + 63], 40, 0),               # groups of one
+    (wl.F16, 12, 4, 128, [30011], 500, 0),                   # groups of three
+    (wl.F16, 12, 4, 256, [30011], 500, 0),                   # one tile buffer per wave: a launch of its own
+    (wl.BF16, 8, 4, 32, [40000], 2000, 0),
+    (wl.BF16, 16, 4, 128, [60000], 9000, 0),                 # the chip-wide tail follows
+])
+def test_the_same_with_more_key_streams(dtype, Hq, Hkv, d, lens, k, window):
+    test_thresholds_worked_out_by_the_scan(dtype, Hq, Hkv, d, lens, k, window)
