@@ -695,13 +695,30 @@ static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax
     return nmax <= kAttendShareKeys * shares ? (int)shares : 0;
 }
 
-// Whether the general path takes one launch in all, a workgroup per key stream: it has to fill the chip, or be as short as a
-// launch.  us per call, scan and selection in two launches against one (32 query / 8 KV heads, ragged batches alike): 500
-// tokens, 1 sequence 16 / 14, 64 sequences 37 / 22; 1024 tokens, 8 sequences 18 / 20, 16 25 / 20, 192 134 / 94; 2000
-// tokens, 16 sequences 29 / 34, 32 49 / 39, 192 226 / 178; 4096 tokens, 16 sequences 51 / 63, 32 95 / 74, 192 437 / 345.
+// Whether the general path takes one launch in all, a workgroup per key stream.  A stream's keys and its heads' selections, a wave
+// per head, are one compute unit's work there, so the streams have to fill the chip, in rounds that are not half empty, and the
+// group has to have heads enough, or rows bytes enough, that the selecting waves do not set the time.  One launch / scan with
+// stored scores and the one-launch selection over them, 100 to 4096 tokens, k = 16 and 256, 1 to 2000 streams, range (median):
+//   up to 512 tokens                                       d < 256 0.40 - 1.02 (0.78), d = 256 0.61 - 1.32 (0.88; never slower than radix select)
+//   up to 1024 tokens, from 128 streams on                 d <= 64 0.52 - 1.03 (0.78); d >= 128, 128 streams 0.88 - 1.38 (1.09)
+//   groups of four, d = 64 and 128, from 256 streams on    0.56 - 1.00 (0.79)
+//   smaller groups of 64 and 128                           300 streams 0.93 - 1.26 (1.06); full rounds 0.64 - 1.13 (0.85), of them
+//                                                          groups of one at d = 64 0.79 - 1.24 (1.02)
+//   d = 256                                                256 streams 0.89 - 1.25 (1.03), groups of 3 and 4 0.77 - 1.01 (0.95); 512
+//                                                          and more 0.76 - 1.08 (0.91)
+//   d = 32 beyond 1024 tokens                              below 512 streams 0.85 - 1.71 (1.18); from there on groups of four
+//                                                          0.72 - 0.95 (0.86), smaller ones 0.83 - 1.71 (1.13)
 static bool attend_short_applies(const Shape& s, int64_t nmax) {
     if (!scan_mfma_supported(s) || scan_row_tiles(s) || s.window != 0 || s.k > attend_short_k(nmax)) return false;
-    return (int64_t)s.B * s.Hkv >= (nmax <= 512 ? 1 : nmax <= 1024 ? 128 : 256);
+    const int64_t streams = (int64_t)s.B * s.Hkv, round = kAttendManyHeads;      // (a workgroup per compute unit)
+    if (nmax <= 512) return true;
+    if (nmax <= 1024 && s.D <= 64) return streams >= 128;
+    if (streams < round) return false;
+    const bool middle = s.D == 64 || s.D == 128;
+    if (middle && s.G == 4) return true;
+    if (streams * 4 < 3 * round * ((streams + round - 1) / round)) return false;  // rounds of workgroups three quarters full on average
+    if (!middle && streams < 2 * round && !(s.D == 256 && s.G >= 3)) return false;
+    return nmax <= 1024 || s.G * s.D >= 128;
 }
 
 static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, int causal, int k, int window,

@@ -204,3 +204,19 @@ def test_selections_of_many_or_wide_value_rows(dtype, B, Hq, Hkv, N, d, k, windo
     res = _decode(q, K, V, dtype, k, window)
     for b in sorted({0, B - 1}):
         H.check_unmargined(tuple(r[b] for r in res), q[b], K[b], V[b], dtype, k, window, f"N={N} k={k} seq {b}")
+
+
+@pytest.mark.parametrize("dtype,B,Hq,Hkv,N,d,k", [
+    (wl.F16, 64, 8, 8, 1024, 32, 100),               # d = 32: up to 1024 tokens
+    (wl.F16, 64, 8, 8, 1025, 32, 100),
+    (wl.BF16, 64, 32, 8, 3000, 32, 100),             # groups of four, 512 streams
+    (wl.F16, 32, 16, 8, 3000, 64, 100),              # groups of two, one full round of streams
+    (wl.F16, 33, 16, 8, 3000, 64, 100),              # a second round nearly empty
+    (wl.BF16, 64, 16, 8, 1500, 256, 33),
+    (wl.BF16, 32, 16, 8, 1500, 256, 33),
+])
+def test_both_sides_of_the_rule_for_short_sequences(dtype, B, Hq, Hkv, N, d, k):
+    q, K, V = _make(dtype, B, Hq, Hkv, N, d, seed=N + k + B + d)
+    res = _decode(q, K, V, dtype, k)
+    for b in sorted({0, B - 1}):
+        H.check_unmargined(tuple(r[b] for r in res), q[b], K[b], V[b], dtype, k, 0, f"N={N} k={k} seq {b}")
