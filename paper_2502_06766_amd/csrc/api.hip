@@ -681,15 +681,20 @@ static int lengths_of(const topk_attn_t* h, int layer, int window, int64_t min_t
 // Workgroups per head of the one-launch selection over the candidate list (attend.hip), 0 where the chip-wide tail takes
 // the call.  32 heads, k = 256 .. 2048, against the tail's two launches: 49 against 56 us at 48k tokens, 73 against 82 at 128k,
 // 213 against 222 at 512k.  Its limits: a list and the rows to fetch fit LDS; every workgroup scores the window; the keys a workgroup scores again
-// when a list turns out unusable are bounded; heads beyond the compute units get one workgroup each, which pays where the tail
-// would run at least four (chunks of queries: 16 queries at 128k tokens 172 against 185 us; batches of 16 sequences of 10k
-// tokens, one tail workgroup per head, 111 against 105 us).
+// when a list turns out unusable are bounded; heads beyond the compute units get one workgroup each, in rounds of 256, which pays
+// for chunks of queries that fill their rounds (list / tail, 32 heads a query, 25k to 128k tokens, k = 300 .. 2000, mean: d = 64 9
+// queries 1.01, 12 to 16 0.98 - 0.91, 20 and 24 0.95 and 0.93, 32 1.01; d = 128 9 1.06, 12 to 14 1.02, 15 and 16 0.98, 17 1.02,
+// 24 0.98, 32 1.07; d = 256 9 1.04, 12 to 14 1.01, 15 and 16 0.98, 17 1.03, 32 1.05), not for batches (d = 64: 288 heads 1.00 - 1.16,
+// 512 0.99 - 1.09; d = 128 0.98 - 1.16), and where the tail would run at least four.
 static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax) {
     if (h->force_redo == 2 || (int64_t)s.k + s.window > kAttendRows) return 0;
     if ((int64_t)s.window * s.D * 2 > kAttendWindowBytes) return 0;
     if (make_plan(nmax, s.k < nmax ? s.k : (int)nmax, s.indexed).c_hi > kAttendList) return 0;
     const int64_t heads = (int64_t)s.B * s.Hq;
-    if (heads > kAttendManyHeads && (s.tail_wgs < 4 || heads > 4 * kAttendManyHeads)) return 0;
+    if (heads > kAttendManyHeads) {
+        const int64_t fewest = s.D <= 64 ? 384 : 480, most = s.D <= 64 ? 768 : 512;
+        if (s.M == 1 || s.tail_wgs < 4 || heads < fewest || heads > most) return 0;
+    }
     int64_t shares = std::max<int64_t>(1, kAttendManyHeads / heads);
     shares = std::min<int64_t>(std::min<int64_t>(shares, kAttendShares), s.n_chunk_cap);
     return nmax <= kAttendShareKeys * shares ? (int)shares : 0;

@@ -202,3 +202,35 @@ def test_pages_of_a_short_cache_are_not_filtered(N, filtered):
         check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, 0, f"N={N}")
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("B,M,Hq,Hkv,N,d,k,one_launch", [
+    (1, 15, 32, 8, 25000, 128, 500, True),           # a chunk of queries that fills its rounds of 256 workgroups
+    (1, 14, 32, 8, 25000, 128, 500, False),
+    (1, 12, 32, 8, 25000, 64, 500, True),
+    (1, 25, 32, 8, 25000, 64, 500, False),
+    (9, 1, 32, 8, 16000, 64, 500, False),            # a batch
+])
+def test_more_heads_than_compute_units(B, M, Hq, Hkv, N, d, k, one_launch):
+    """Where the one-launch selection takes over a call of more than 256 heads."""
+    dtype = wl.BF16
+    data = [tuple(wl.quantize(a, dtype) for a in make_tied(N + b, M, Hq, Hkv, N, d, [])) for b in range(B)]
+    cache = ta.TopkAttnCache(1, B, Hq, Hkv, d, N, k, dtype, max_queries=M)
+    try:
+        for b, (q, K, V) in enumerate(data):
+            cache.append(0, b, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        qd = torch.stack([H.to_torch(x[0], dtype, DEV) for x in data]).contiguous()
+        res = cache.decode_multi(0, qd, k)
+        torch.cuda.synchronize()
+        rec = ta.topk_attn_last_selection_records(cache.h, B * M * Hq)
+        # the chip-wide selection sorts by the scan's bins, whose counts the records then carry; the one-launch selection ranks finer bins
+        cnt = ta.topk_attn_debug_read_workspace_dims(cache.h)
+        hist = ta.topk_attn_debug_read_workspace(cache.h, "hist", np.uint32, cnt[2] * 64 * B * M * Hq).reshape(-1, cnt[2], 64)[:, :cnt[4] // 4].sum(axis=1)
+        top_down = np.cumsum(hist[:, ::-1], axis=1)
+        from_bins = [r[1] == c[c < k][-1] if (c < k).any() else r[1] == 0 for r, c in zip(rec, top_down)]
+        assert all(from_bins) != one_launch
+        for b in sorted({0, B - 1}):
+            q, K, V = data[b]
+            check_exact(tuple(t[b].cpu().numpy() for t in res), q, K, V, dtype, k, True, 0, f"seq {b}")
+    finally:
+        cache.close()
