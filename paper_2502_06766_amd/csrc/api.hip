@@ -634,7 +634,8 @@ static void fill_call(topk_attn_t* h, int layer, const void* q, int k, int n_que
 static bool choose_segments(const topk_attn_t* h, const Shape& s, int64_t nmax, int64_t c_hi, int* n_seg,
                             int* seg_cap) {
     // (a scan with two row tiles runs one workgroup per compute unit: its stages take the LDS)
-    const int64_t target_wgs = (scan_row_tiles(s) && s.row_tiles == 2 ? 1 : 2) * (int64_t)h->n_cu;
+    const bool one_per_cu = scan_row_tiles(s) && s.row_tiles == 2;
+    const int64_t target_wgs = (one_per_cu ? 1 : 2) * (int64_t)h->n_cu;
     int64_t P = target_wgs / ((int64_t)scan_grid_z(s) * s.Hkv);
     const int64_t tiles = (nmax + 63) / 64;
     if (P * 4 > tiles) P = tiles / 4;
@@ -642,7 +643,16 @@ static bool choose_segments(const topk_attn_t* h, const Shape& s, int64_t nmax, 
     if (P > s.hist_cap) P = s.hist_cap;     // every scan workgroup leaves its per-bin candidate counts
     if (P < 1) P = 1;
     while (P & (P - 1)) P &= P - 1;          // power of two: the selection indexes segments by mask
-    {   // rounding down may leave the chip a quarter empty: take the next power of two if it stays within 1.5 x
+    bool full = false;
+    if (one_per_cu) {
+        // the first power of two from there on whose rounds of workgroups are four fifths full, as long as a wave keeps a dozen tiles
+        // (17 queries over 8 KV heads, d = 256: 192 or 384 workgroups leave a quarter of the chip empty, 768 do not: 131k tokens, k = 600
+        // 338 -> 297 us; with 7 tiles a wave the split costs more than it fills: 24 queries at 60k, d = 128 153 -> 169)
+        const int64_t streams = (int64_t)scan_grid_z(s) * s.Hkv, cus = h->n_cu;
+        for (int64_t p = P; !full && p * 4 * 12 <= tiles && p * 4 <= kMaxSeg && p <= s.hist_cap; p *= 2)
+            if (streams * p * 5 >= 4 * cus * ((streams * p + cus - 1) / cus)) { P = p; full = true; }
+    }
+    if (!full) {   // rounding down may leave the chip a quarter empty: take the next power of two if it stays within 1.5 x
         const int64_t streams = (int64_t)scan_grid_z(s) * s.Hkv;
         if (streams * P * 8 < target_wgs * 7 && streams * P * 2 * 2 <= target_wgs * 3 && P * 2 * 4 <= tiles &&
             P * 2 * 4 <= kMaxSeg && P * 2 <= s.hist_cap)

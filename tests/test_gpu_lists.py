@@ -234,3 +234,20 @@ def test_more_heads_than_compute_units(B, M, Hq, Hkv, N, d, k, one_launch):
             check_exact(tuple(t[b].cpu().numpy() for t in res), q, K, V, dtype, k, True, 0, f"seq {b}")
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("N,n_seg", [(131072, 128), (98304, 128), (98000, 64)])
+def test_split_of_three_row_blocks(N, n_seg):
+    """17 queries, 8 KV heads: 24 streams of row blocks, split until their workgroups fill the chip while a wave keeps a dozen tiles."""
+    dtype, M, Hq, Hkv, d, k = wl.F16, 17, 32, 8, 32, 400
+    q, K, V = (wl.quantize(a, dtype) for a in make_tied(N, M, Hq, Hkv, N, d, []))
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, N, k, dtype, max_queries=M)
+    try:
+        cache.append(0, 0, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        res = cache.decode_multi(0, H.to_torch(q, dtype, DEV)[None].contiguous(), k)
+        torch.cuda.synchronize()
+        assert ta.topk_attn_debug_read_workspace_dims(cache.h)[4] == n_seg
+        assert cache.last_fallbacks() == 0
+        check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, 0, f"N={N}")
+    finally:
+        cache.close()
