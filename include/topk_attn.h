@@ -49,7 +49,7 @@ enum { TOPK_ATTN_F32 = 0, TOPK_ATTN_F16 = 1, TOPK_ATTN_BF16 = 2 }; /* element ty
 /* Which selection pipeline decode uses (see topk_attn_set_path). */
 enum {
     TOPK_ATTN_PATH_AUTO = 0,    /* filtered scan when the shape allows it, else full */
-    TOPK_ATTN_PATH_FULL = 1,    /* always materialise all N scores and select over them */
+    TOPK_ATTN_PATH_FULL = 1,    /* always score all N keys and select over all scores */
     TOPK_ATTN_PATH_FILTER = 2,  /* sampled-threshold scan whenever its candidate list fits the
                                    workspace, also for short caches (heads whose candidate list
                                    under- or overflows are still redone exactly) */

@@ -789,10 +789,7 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
 #pragma unroll
         for (int e = 0; e < EPL; ++e) bf.out[bh * D + c * EPL + e] = acc[e] / l;
     }
-    if (lane == 0) {
-        bf.hmax[bh] = M;
-        if (bf.lse) bf.lse[bh] = M * scale + logf(l);
-    }
+    if (lane == 0 && bf.lse) bf.lse[bh] = M * scale + logf(l);
 }
 
 hipError_t launch_attend_short(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {

@@ -62,15 +62,6 @@ __global__ void __launch_bounds__(NT) select_full_kernel(Shape sh, Bufs bf) {
     wg_select_dense<NT, CPT>(sh, bf, bh, N, k_eff, sm);
 }
 
-
-// The kernel is correct for any register-cache size (what does not fit is streamed); a
-// cache much larger than the data only costs loop trips over empty slots, which matters
-// when the whole step is a few tens of microseconds.
-// A call with many heads (a batch, 512 heads or more) whose rows are small takes 256-thread workgroups: several
-// fit a compute unit at once and every barrier of the select is cheaper; one head alone is
-// served faster by 1024 threads.
-static bool many_small_heads(const Shape& s) { return (int64_t)s.Hq * s.B >= 512; }
-
 hipError_t launch_threshold(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
     if (threshold_in_scan(s, Nmax)) return hipSuccess;
     const int n_samp = make_plan(Nmax, s.k < Nmax ? s.k : (int)Nmax, s.indexed).n_samp;
@@ -86,6 +77,9 @@ hipError_t launch_threshold(const Shape& s, const Bufs& b, int64_t Nmax, hipStre
 #undef TKA_TH
     return hipGetLastError();
 }
+// The kernel is correct for any register-cache size (what does not fit is streamed); a
+// cache much larger than the data only costs loop trips over empty slots, which matters
+// when the whole step is a few tens of microseconds.
 hipError_t launch_select_full(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
     if (s.attend == kAttendShort) return launch_attend_short(s, b, Nmax, st);
     if (s.attend) return launch_attend_row(s, b, Nmax, st);
