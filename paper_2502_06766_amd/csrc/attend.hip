@@ -8,12 +8,13 @@
 // the largest score, over scores held in registers (the bin it falls in holds a few, which are ranked by
 // comparison), and the value rows are fetched by the same workgroup as soon as the winners' positions are in LDS.
 //
-// What bounds it: instructions and barriers of one compute unit per head (a stamp per phase: loads 1.5-3 us, bins and
-// their prefix sum 1.6, ranking and emission 2, rows 1.5-2, sum and write 1.5), so scores stay in registers with
+// What bounds it: instructions and barriers of one compute unit per head (stamps of a first version: loads 1.5-3 us, bins and
+// their prefix sum 1.6, ranking and emission 2, rows 1.5-2, sum and write 1.5, which is 8 to 10 us of the 14 to 18 below; where the
+// rest goes, start and end of the launch included, was not measured), so scores stay in registers with
 // slots nobody uses skipped uniformly (the same phases as rolled loops over LDS: 23.6 us against 14.5 at 16k
 // tokens) and scans and reductions run in the vector unit instead of trips through LDS.  Measured, 32 heads, 8 KV heads:
-// a row of 16k scores, k = 256: 14.5 us (radix select + gather before: 18.7 + 7.9); a list at 48k tokens, k = 768:
-// 13.9 us, at 128k tokens, k = 1800: 18.0 us (chip-wide tail: 11.6 + 11.6 and 14.8 + 9.6 us and a launch more).
+// a row of 16k scores, k = 256: 14.6 us (radix select + gather before: 18.7 + 7.9); a list at 48k tokens, k = 768 on average:
+// 16.4 us, at 128k tokens, k = 2048: 18.9 us (chip-wide tail: 11.6 + 11.6 and 14.5 + 9.6 us and a launch more).
 //
 //   SRC_ROW   the scores of a short cache, stored by the scan (general path)
 //   (attend_short_kernel: the scores too, for batches of short sequences)
@@ -682,7 +683,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
 // each wave selects for one head of the group and fetches its rows, with no barrier between the waves.  The step is
 // bound by reading the keys; two or more workgroups per compute unit, each in a phase of its own, keep that going
 // while others select.  ROW: scores of the longest sequence.  192 sequences of 2048 .. 4096 tokens, k = 128 (1.2 GB of keys,
-// 0.2 GB of value rows): 281 us = 5.0 TB/s; scan with stored scores, radix select and gather before: 277 + 70 + 42 us.
+// 0.2 GB of value rows): 310 us = 4.6 TB/s; scan with stored scores, radix select and gather before: 277 + 70 + 42 us.
 constexpr int kShortBins = 256;
 template <int DT, int D, int ROW>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
@@ -822,6 +823,8 @@ hipError_t launch_attend_row(const Shape& s, const Bufs& b, int64_t Nmax, hipStr
     const float scale = 1.0f / sqrtf((float)s.D);
     const float scale_log2e = scale * 1.4426950408889634f;
     const dim3 grid((unsigned)s.Hq, (unsigned)s.B);
+    // (more heads than compute units, rows of up to 8192 scores: workgroups no larger than the row needs take 0.49 - 0.99 of the time
+    // of 1024 threads, median 0.81, over 320 to 1920 heads)
     const bool many = (int64_t)s.Hq * s.B > kAttendManyHeads;
     if ((int64_t)s.k + s.window > attend_row_rows((int64_t)s.Hq * s.B, Nmax)) return hipErrorInvalidValue;
 #define TKA_AR(DT_, NT_, CPT_, NB_)                                                                                         \

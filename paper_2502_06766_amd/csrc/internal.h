@@ -199,7 +199,7 @@ __host__ __device__ inline bool plan_is_fast(const Plan& p, int64_t N, int cand_
 }
 
 // Selection and attention of a head in one launch (attend.hip).
-constexpr int64_t kAttendRowMax = 16384;  // scores of the longest row
+constexpr int64_t kAttendRowMax = 16384;  // scores of the longest row (16 per thread; more per thread was not tried)
 constexpr int kAttendList = 10240;        // candidates of the longest list
 constexpr int kAttendRows = 4096;         // value rows (selected and window) whose positions and weights fit LDS beside a list
 constexpr int kAttendShares = 8;          // workgroups per head at most
