@@ -714,7 +714,7 @@ static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax
 // per head, are one compute unit's work there, so the streams have to fill the chip, in rounds that are not half empty, and the
 // group has to have heads enough, or rows bytes enough, that the selecting waves do not set the time.  One launch / scan with
 // stored scores and the one-launch selection over them, 100 to 4096 tokens, k = 16 and 256, 1 to 2000 streams, range (median):
-//   up to 512 tokens                                       d < 256 0.40 - 1.02 (0.78), d = 256 0.61 - 1.32 (0.88; never slower than radix select)
+//   up to 512 tokens                                       d < 256 0.40 - 1.02 (0.78), d = 256 0.61 - 1.32 (0.88; radix select at most 1.09: 1600 streams)
 //   up to 1024 tokens, from 128 streams on                 d <= 64 0.52 - 1.03 (0.78); d >= 128, 128 streams 0.88 - 1.38 (1.09)
 //   groups of four, d = 64 and 128, from 256 streams on    0.56 - 1.00 (0.79)
 //   smaller groups of 64 and 128                           300 streams 0.93 - 1.26 (1.06); full rounds 0.64 - 1.13 (0.85), of them
