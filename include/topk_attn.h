@@ -168,8 +168,8 @@ int topk_attn_decode(topk_attn_t* h, int layer, const void* q, int k, float* out
  * library: a device array of TOPK_ATTN_STATIC_SCRATCH_BYTES that every GPU the library runs on
  * holds until the process ends.  Only the cache lengths are still read from the handle's
  * workspace.  The call allocates and frees nothing and enqueues kernels only.
- * Limit: ESCRATCH (nothing enqueued) if topk_attn_workspace_bytes(cfg) minus the lengths' share
- * (n_layers * n_seqs * 4, rounded up to 256) exceeds TOPK_ATTN_STATIC_SCRATCH_BYTES -- one
+ * Limit: ESCRATCH (nothing enqueued) if topk_attn_workspace_bytes of the same configuration with
+ * n_layers = 1 minus the lengths' share (n_seqs * 4, rounded up to 256) exceeds TOPK_ATTN_STATIC_SCRATCH_BYTES -- one
  * Llama-8B-shaped layer of 128k tokens at k = 2048 fits, a million-token layer does not.
  * All calls on one GPU, from whatever handle, share the one array: the call clears the words
  * that must start at zero itself, and two such calls that overlap in time on one GPU race. */
@@ -217,8 +217,9 @@ int topk_attn_decode_multi(topk_attn_t* h, int layer, const void* q, int n_queri
 int topk_attn_k_schedule(int64_t total_k, int n_layers, double last_over_first, int32_t* k_out);
 
 /* Decode steps of n_layers consecutive layers [layer0, layer0 + n_layers) with a per-layer k
- * (e.g. from topk_attn_k_schedule), enqueued back to back on `hip_stream`: the same work as
- * n_layers calls of topk_attn_decode_window, one per layer, each with its own query block.
+ * (e.g. from topk_attn_k_schedule), enqueued on `hip_stream`: the same work and the same results as
+ * n_layers calls of topk_attn_decode_window, one per layer, each with its own query block (layers
+ * that take the same path share their launches; the workspace holds the buffers of several).
  * (In a transformer layer l+1's query depends on layer l's output; this entry point serves
  * callers that have all queries at hand, such as replaying recorded queries or measuring
  * a whole-model decode step.)

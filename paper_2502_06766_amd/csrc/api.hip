@@ -26,7 +26,7 @@ inline int elem_bytes(int dtype) { return dtype == TOPK_ATTN_F32 ? 4 : 2; }
 
 struct WsLayout {
     size_t len, thr, bins, samp, seg_cnt, seg_max, seg_cnt2, flags, hmax, fallback, tailrec, page_mask, page_cnt, page_list, hist, cand, bnd, scores, sel_idx, sel_val, part_acc, part_l, part_m, total;
-    int cand_cap, bnd_cap, n_chunk_cap, hist_cap, page_words;
+    int cand_cap, bnd_cap, n_chunk_cap, hist_cap, page_words, batch_layers;
 };
 
 bool config_ok(const topk_attn_config* c, int* why) {
@@ -86,9 +86,12 @@ size_t kv_total_bytes(const topk_attn_config* c) {
     return 2 * kv_half_bytes(c) + index_codes_bytes(c) + index_scales_bytes(c) + page_centres_bytes(c) + page_balls_bytes(c);
 }
 
-WsLayout ws_layout(const topk_attn_config* c) {
+// batch_layers: layers of a topk_attn_decode_layers call that share their launches, each with per-call buffers of its own (a
+// layer's heads and those of a further query of a chunk take the same room).
+WsLayout ws_layout(const topk_attn_config* c, int batch_layers) {
     WsLayout w;
-    const size_t BH = (size_t)c->n_seqs * (c->max_queries > 1 ? c->max_queries : 1) * c->n_q_heads;
+    const int per_seq = std::max(std::max(c->max_queries, 1), batch_layers);
+    const size_t BH = (size_t)c->n_seqs * per_seq * c->n_q_heads;
     const int64_t max_k = c->max_k < c->max_tokens ? c->max_k : c->max_tokens;
     // candidate list per head.  A call with few KV-head streams splits each stream into many wave
     // segments (up to about 1024 waves over the chip, doubled where the split is rounded up).
@@ -144,8 +147,20 @@ WsLayout ws_layout(const topk_attn_config* c) {
     w.part_l = take(BH * (size_t)w.n_chunk_cap * sizeof(float));
     w.part_m = take(BH * (size_t)w.n_chunk_cap * sizeof(float));
     w.total = o;
+    w.batch_layers = batch_layers;
     return w;
 }
+
+// Layers that share their launches: as many as kBatchScratchBytes of per-call buffers hold (8 KV heads, 32 query heads, 48k
+// tokens: 65 MB a layer).
+constexpr size_t kBatchScratchBytes = (size_t)1 << 30;
+int batch_layers_of(const topk_attn_config* c) {
+    const size_t one = ws_layout(c, 1).total;
+    int n = std::min(c->n_layers, kBatchLayers);
+    while (n > 1 && (ws_layout(c, n).total > std::max(one, kBatchScratchBytes) || (int64_t)c->n_seqs * n > 65535)) --n;
+    return n;
+}
+WsLayout ws_layout(const topk_attn_config* c) { return ws_layout(c, batch_layers_of(c)); }
 
 __global__ void append_kernel(const char* __restrict__ ksrc, const char* __restrict__ vsrc, char* __restrict__ kdst,
                               char* __restrict__ vdst, int64_t n_new, int Hkv, int chunks_per_row,
@@ -320,6 +335,7 @@ constexpr int kTimingSlots = 512;
 struct topk_attn {
     topk_attn_config cfg;
     WsLayout ws;
+    WsLayout ws_one;            // the layout without room for further layers (the built-in scratch)
     size_t kv_half;
     std::vector<int64_t> len;   // host mirror of the device lengths, [L][B]
     int path;
@@ -332,6 +348,7 @@ struct topk_attn {
     int last_queries;           // queries per sequence of the last decode
     int last_n_seg, last_seg_cap;   // the split of the last filtered decode's candidate lists (0: not filtered)
     int last_layer;
+    int last_slot;              // layers of the last call before its last one in the per-call buffers
     char* scratch_dev;          // this device's copy of the built-in scratch
     int n_cu;                   // compute units of the device
     // optional event pairs around the key scan of each decode (measurement only)
@@ -367,6 +384,7 @@ int topk_attn_create(const topk_attn_config* cfg, topk_attn_t** out) {
     if (!h) return TOPK_ATTN_ENOMEM;
     h->cfg = *cfg;
     h->ws = w;
+    h->ws_one = ws_layout(cfg, 1);
     h->kv_half = kv_half_bytes(cfg);
     h->len.assign((size_t)cfg->n_layers * cfg->n_seqs, 0);
     h->path = TOPK_ATTN_PATH_AUTO;
@@ -385,6 +403,7 @@ int topk_attn_create(const topk_attn_config* cfg, topk_attn_t** out) {
     h->last_queries = 1;
     h->last_n_seg = h->last_seg_cap = 0;
     h->last_layer = 0;
+    h->last_slot = 0;
     {   // cfg->device is current here
         void* p = nullptr;
         const int rc = scratch_address(cfg->device, &p);
@@ -575,13 +594,14 @@ static void fill_call(topk_attn_t* h, int layer, const void* q, int k, int n_que
     s->hist_cap = h->ws.hist_cap; s->tail_spw = 1; s->tail_wgs = 1;
     s->cand_cap = h->ws.cand_cap; s->bnd_cap = h->ws.bnd_cap; s->n_seg = 4; s->seg_cap = (h->ws.cand_cap / 4) & ~(kCandChunk - 1); s->samp_cap = kSampMax; s->n_chunk_cap = h->ws.n_chunk_cap;
     s->Ncap = c.max_tokens;
-    s->indexed = 0; s->attend = 0;
+    s->indexed = 0; s->attend = 0; s->share_wgs = 0; s->log2_layers = 0; s->layer_seqs = s->B; b->layer_k[0] = LayerK{k, 0};
     s->paged = 0; s->no_rescan = 0;
     s->page_cap = (int)page_cap_of(&c); s->page_words = h->ws.page_words;
     s->force_redo = h->force_redo ? 1 : 0;
     char* const ws_len = static_cast<char*>(c.workspace);
     // everything after the lengths is per-call scratch: the handle's workspace, or the library's own array
-    char* const ws = use_static ? reinterpret_cast<char*>(reinterpret_cast<uintptr_t>(h->scratch_dev) - h->ws.thr) : ws_len;
+    const WsLayout& w = use_static ? h->ws_one : h->ws;
+    char* const ws = use_static ? reinterpret_cast<char*>(reinterpret_cast<uintptr_t>(h->scratch_dev) - w.thr) : ws_len;
     const size_t layer_b = (size_t)c.n_seqs * c.n_kv_heads * (size_t)c.max_tokens * c.head_dim * e;
     b->K = static_cast<char*>(c.kv_storage) + (size_t)layer * layer_b;
     b->V = static_cast<char*>(c.kv_storage) + h->kv_half + (size_t)layer * layer_b;
@@ -600,30 +620,30 @@ static void fill_call(topk_attn_t* h, int layer, const void* q, int k, int n_que
         b->page_centres = base + layer_streams * (size_t)page_cap_of(&c) * c.head_dim * e;
         b->page_balls = reinterpret_cast<const float*>(base + page_centres_bytes(&c)) + layer_streams * (size_t)page_cap_of(&c) * 2;
     }
-    b->page_mask = reinterpret_cast<uint64_t*>(ws + h->ws.page_mask);
-    b->page_cnt = reinterpret_cast<uint32_t*>(ws + h->ws.page_cnt);
-    b->page_list = reinterpret_cast<int32_t*>(ws + h->ws.page_list);
+    b->page_mask = reinterpret_cast<uint64_t*>(ws + w.page_mask);
+    b->page_cnt = reinterpret_cast<uint32_t*>(ws + w.page_cnt);
+    b->page_list = reinterpret_cast<int32_t*>(ws + w.page_list);
     b->len = reinterpret_cast<int32_t*>(ws_len + h->ws.len) + (size_t)layer * c.n_seqs;
-    b->thr = reinterpret_cast<float*>(ws + h->ws.thr);
-    b->bins = reinterpret_cast<float*>(ws + h->ws.bins);
-    b->hist = reinterpret_cast<uint32_t*>(ws + h->ws.hist);
-    b->bnd = reinterpret_cast<uint64_t*>(ws + h->ws.bnd);
-    b->tailrec = reinterpret_cast<uint32_t*>(ws + h->ws.tailrec);
-    b->samp = reinterpret_cast<float*>(ws + h->ws.samp);
-    b->seg_cnt = reinterpret_cast<uint32_t*>(ws + h->ws.seg_cnt);
-    b->seg_max = reinterpret_cast<float*>(ws + h->ws.seg_max);
-    b->seg_cnt2 = reinterpret_cast<uint32_t*>(ws + h->ws.seg_cnt2);
-    b->flags = reinterpret_cast<uint32_t*>(ws + h->ws.flags);
-    b->hmax = reinterpret_cast<float*>(ws + h->ws.hmax);
-    b->cand = reinterpret_cast<uint64_t*>(ws + h->ws.cand);
-    b->scores = reinterpret_cast<float*>(ws + h->ws.scores);
-    b->sel_idx = reinterpret_cast<int32_t*>(ws + h->ws.sel_idx);
-    b->sel_val = reinterpret_cast<float*>(ws + h->ws.sel_val);
-    b->part_acc = reinterpret_cast<float*>(ws + h->ws.part_acc);
-    b->part_l = reinterpret_cast<float*>(ws + h->ws.part_l);
-    b->part_m = reinterpret_cast<float*>(ws + h->ws.part_m);
+    b->thr = reinterpret_cast<float*>(ws + w.thr);
+    b->bins = reinterpret_cast<float*>(ws + w.bins);
+    b->hist = reinterpret_cast<uint32_t*>(ws + w.hist);
+    b->bnd = reinterpret_cast<uint64_t*>(ws + w.bnd);
+    b->tailrec = reinterpret_cast<uint32_t*>(ws + w.tailrec);
+    b->samp = reinterpret_cast<float*>(ws + w.samp);
+    b->seg_cnt = reinterpret_cast<uint32_t*>(ws + w.seg_cnt);
+    b->seg_max = reinterpret_cast<float*>(ws + w.seg_max);
+    b->seg_cnt2 = reinterpret_cast<uint32_t*>(ws + w.seg_cnt2);
+    b->flags = reinterpret_cast<uint32_t*>(ws + w.flags);
+    b->hmax = reinterpret_cast<float*>(ws + w.hmax);
+    b->cand = reinterpret_cast<uint64_t*>(ws + w.cand);
+    b->scores = reinterpret_cast<float*>(ws + w.scores);
+    b->sel_idx = reinterpret_cast<int32_t*>(ws + w.sel_idx);
+    b->sel_val = reinterpret_cast<float*>(ws + w.sel_val);
+    b->part_acc = reinterpret_cast<float*>(ws + w.part_acc);
+    b->part_l = reinterpret_cast<float*>(ws + w.part_l);
+    b->part_m = reinterpret_cast<float*>(ws + w.part_m);
     b->out = nullptr; b->lse = nullptr;
-    b->fallback_total = reinterpret_cast<uint32_t*>(ws + h->ws.fallback);
+    b->fallback_total = reinterpret_cast<uint32_t*>(ws + w.fallback);
 }
 
 // Split of each head's candidate list into per-wave segments for the filtered scan:
@@ -736,10 +756,19 @@ static bool attend_short_applies(const Shape& s, int64_t nmax) {
     return nmax <= 1024 || s.G * s.D >= 128;
 }
 
-static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, int causal, int k, int window,
-                       float* out, int32_t* idx, float* vals, float* lse, void* hip_stream, bool use_static = false) {
+// A decode call: what is launched, and with what.
+struct Call {
+    Shape s;
+    Bufs b;
+    bool fast;             // filtered scan
+    int64_t nmax;          // longest searched prefix
+    int64_t n_scored;      // longest sequence (general path: keys whose scores are stored)
+};
+
+static int plan_call(topk_attn_t* h, int layer, const void* q, int n_queries, int causal, int k, int window,
+                     float* out, int32_t* idx, float* vals, float* lse, bool use_static, Call* call) {
     if (!h || !q || !out) return TOPK_ATTN_EINVAL;
-    if (use_static && h->ws.total - h->ws.thr > kStaticScratchBytes) return TOPK_ATTN_ESCRATCH;
+    if (use_static && h->ws_one.total - h->ws_one.thr > kStaticScratchBytes) return TOPK_ATTN_ESCRATCH;
     if (layer < 0 || layer >= h->cfg.n_layers) return TOPK_ATTN_EINVAL;
     if (k < 1 || k > h->cfg.max_k) return TOPK_ATTN_EINVAL;
     if (window < 0 || window > h->cfg.max_window) return TOPK_ATTN_EINVAL;
@@ -750,8 +779,8 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
     // query's); the earlier queries of a causal chunk search up to n_queries - 1 keys fewer
     int64_t nmin, nmax;
     if (lengths_of(h, layer, window, causal ? n_queries : 1, &nmin, &nmax) != TOPK_ATTN_OK) return TOPK_ATTN_EINVAL;
-    hipStream_t st = (hipStream_t)hip_stream;
-    Shape s; Bufs b;
+    Shape& s = call->s;
+    Bufs& b = call->b;
     fill_call(h, layer, q, k, n_queries, &s, &b, use_static);
     s.window = window;
     s.causal = causal ? 1 : 0;
@@ -805,6 +834,23 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
     if (fast) s.attend = attend_list_shares(h, s, nmax);
     else if (attend_short_applies(s, nmax)) s.attend = kAttendShort;
     else s.attend = attend_row_applies((int64_t)s.B * s.Hq, nmax, s.k, s.window, s.D * elem_bytes(s.dtype)) ? 1 : 0;
+    s.share_wgs = s.attend;
+    if (fast && !s.indexed) {
+        s.paged = want_pages ? 1 : 0;
+        s.no_rescan = s.paged;      // the paged scan deals its tiles to the waves by rank among the pages kept
+    }
+    call->fast = fast;
+    call->nmax = call->n_scored = nmax;
+    if (s.attend)                   // the window's scores come from the scan too
+        for (int i = 0; i < s.Bc; ++i) call->n_scored = std::max(call->n_scored, h->len[(size_t)layer * s.Bc + i]);
+    return TOPK_ATTN_OK;
+}
+
+static int enqueue_call(topk_attn_t* h, const Call& call, int layer, hipStream_t st, bool use_static) {
+    const Shape& s = call.s;
+    const Bufs& b = call.b;
+    const bool fast = call.fast;
+    const int64_t nmax = call.nmax;
     hipError_t e = hipSuccess;
     bool tail_done = false;
     if (use_static) {
@@ -829,8 +875,6 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
         if (e == hipSuccess) e = launch_tail(s, b, st);                // (with a window: its partial sums too)
         tail_done = true;
     } else if (fast) {
-        s.paged = want_pages ? 1 : 0;
-        s.no_rescan = s.paged;      // the paged scan deals its tiles to the waves by rank among the pages kept
         e = launch_scan_sample(s, b, nmax, st);
         if (e == hipSuccess) e = launch_threshold(s, b, nmax, st);
         if (e == hipSuccess && s.paged) e = launch_page_filter(s, b, h->page_beta, st);
@@ -843,13 +887,9 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
     } else {
         if (nmax > 0 || s.attend) {
             Shape all = s;
-            int64_t n_scored = nmax;
-            if (s.attend) {                  // the window's scores come from the scan too
-                all.window = 0;
-                for (int i = 0; i < s.Bc; ++i) n_scored = std::max(n_scored, h->len[(size_t)layer * s.Bc + i]);
-            }
+            if (s.attend) all.window = 0;    // the window's scores come from the scan too
             if (timed) e = hipEventRecord(h->ev[2 * h->ev_used], st);
-            if (e == hipSuccess) e = s.attend == kAttendShort ? launch_select_full(s, b, nmax, st) : launch_scan_full(all, b, n_scored, b.scores, st);
+            if (e == hipSuccess) e = s.attend == kAttendShort ? launch_select_full(s, b, nmax, st) : launch_scan_full(all, b, call.n_scored, b.scores, st);
             if (e == hipSuccess && timed) e = hipEventRecord(h->ev[2 * h->ev_used + 1], st);
             if (e == hipSuccess && timed) h->ev_used++;
         }
@@ -859,12 +899,52 @@ static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, 
     h->last_fast = fast;
     h->last_paged = fast && s.paged;
     h->last_tail = tail_done;
-    h->last_queries = n_queries;
+    h->last_queries = s.M;
     h->last_n_seg = fast ? s.n_seg : 0;
     h->last_seg_cap = fast ? s.seg_cap : 0;
-    h->last_layer = layer;
+    h->last_slot = (1 << s.log2_layers) - 1;
+    h->last_layer = layer + h->last_slot;
     h->last_static = use_static;
     return e == hipSuccess ? TOPK_ATTN_OK : TOPK_ATTN_EDEVICE;
+}
+
+static int decode_impl(topk_attn_t* h, int layer, const void* q, int n_queries, int causal, int k, int window,
+                       float* out, int32_t* idx, float* vals, float* lse, void* hip_stream, bool use_static = false) {
+    Call call;
+    const int rc = plan_call(h, layer, q, n_queries, causal, k, window, out, idx, vals, lse, use_static, &call);
+    return rc != TOPK_ATTN_OK ? rc : enqueue_call(h, call, layer, (hipStream_t)hip_stream, use_static);
+}
+
+// Whether layers share their launches with the layer of `all`, and how many at most.  A layer is taken through exactly the
+// launch shapes it has alone (the same segments, shares and workgroups), so its results are the same bits; only how many of them are
+// in flight differs.  (Not while the scans are timed one by one.)
+static bool joins(const topk_attn_t* h, const Call& all, const Call& one, int layers) {
+    const Shape &s = all.s, &o = one.s;
+    if (h->timing || layers > h->ws.batch_layers || s.paged || s.indexed || !s.attend || all.fast != one.fast || o.attend != s.attend) return false;
+    const int64_t nmax = std::max(all.nmax, one.nmax), layer_heads = (int64_t)s.layer_seqs * s.Hq, heads = layer_heads * layers;
+    // filtered: one round of workgroups, and no more keys for one of them to score again than alone
+    if (all.fast)
+        return s.n_seg == o.n_seg && s.seg_cap == o.seg_cap && heads <= kAttendManyHeads &&
+               nmax <= kAttendShareKeys * std::max<int64_t>(1, kAttendManyHeads / heads);
+    if (s.attend == kAttendShort) return std::max(s.k, o.k) <= attend_short_k(nmax);
+    return attend_row_class(layer_heads, all.nmax) == attend_row_class(layer_heads, one.nmax);
+}
+
+// Makes one call of the calls of n consecutive layers (a power of two, all of which join the first).
+static Call join_layers(const Call* calls, int n) {
+    Call all = calls[0];
+    Shape& s = all.s;
+    for (int i = 1; i < n; ++i) {
+        const Call& one = calls[i];
+        all.b.layer_k[i] = LayerK{one.s.k, all.b.layer_k[i - 1].before + all.b.layer_k[i - 1].k};
+        s.k = std::max(s.k, one.s.k);
+        all.nmax = std::max(all.nmax, one.nmax);
+        all.n_scored = std::max(all.n_scored, one.n_scored);
+    }
+    while ((1 << s.log2_layers) < n) ++s.log2_layers;
+    s.Bc = s.B = s.layer_seqs * n;
+    if (all.fast) s.share_wgs = (int)std::max<int64_t>(1, std::min<int64_t>(s.attend, kAttendManyHeads / ((int64_t)s.B * s.Hq)));
+    return all;
 }
 
 int topk_attn_decode(topk_attn_t* h, int layer, const void* q, int k, float* out, int32_t* idx, float* vals,
@@ -900,12 +980,27 @@ int topk_attn_decode_layers(topk_attn_t* h, int layer0, int n_layers, const void
     const size_t BH = (size_t)h->cfg.n_seqs * h->cfg.n_q_heads;
     const size_t q_step = BH * h->cfg.head_dim * elem_bytes(h->cfg.dtype);
     size_t sel_off = 0;
+    std::vector<Call> calls((size_t)n_layers);
     for (int l = 0; l < n_layers; ++l) {
-        const int rc = decode_impl(h, layer0 + l, static_cast<const char*>(q) + l * q_step, 1, 0, k[l], window,
-                                   out + l * BH * h->cfg.head_dim, idx ? idx + sel_off : nullptr,
-                                   vals ? vals + sel_off : nullptr, lse ? lse + l * BH : nullptr, hip_stream);
+        const int rc = plan_call(h, layer0 + l, static_cast<const char*>(q) + l * q_step, 1, 0, k[l], window,
+                                 out + l * BH * h->cfg.head_dim, idx ? idx + sel_off : nullptr,
+                                 vals ? vals + sel_off : nullptr, lse ? lse + l * BH : nullptr, false, &calls[l]);
         if (rc != TOPK_ATTN_OK) return rc;
         sel_off += BH * (size_t)k[l];
+    }
+    for (int l = 0, n; l < n_layers; l += n) {
+        Call all = calls[l];
+        for (n = 1; 2 * n <= n_layers - l; n *= 2) {        // twice as many layers, as long as all of them join
+            bool ok = true;
+            for (int i = n; ok && i < 2 * n; ++i) {
+                ok = joins(h, all, calls[l + i], 2 * n);
+                all.nmax = std::max(all.nmax, calls[l + i].nmax);
+                all.s.k = std::max(all.s.k, calls[l + i].s.k);
+            }
+            if (!ok) break;
+        }
+        const int rc = enqueue_call(h, n > 1 ? join_layers(&calls[l], n) : calls[l], layer0 + l, (hipStream_t)hip_stream, false);
+        if (rc != TOPK_ATTN_OK) return rc;
     }
     return TOPK_ATTN_OK;
 }
@@ -968,7 +1063,7 @@ int topk_attn_last_fallbacks(topk_attn_t* h, int* n_heads) {
     *n_heads = 0;
     if (!h->last_fast) return TOPK_ATTN_OK;
     uint32_t v = 0;
-    const char* where = h->last_static ? h->scratch_dev + (h->ws.fallback - h->ws.thr)
+    const char* where = h->last_static ? h->scratch_dev + (h->ws_one.fallback - h->ws_one.thr)
                                        : static_cast<char*>(h->cfg.workspace) + h->ws.fallback;
     if (hipMemcpy(&v, where, sizeof v, hipMemcpyDeviceToHost) !=
         hipSuccess)
@@ -1006,11 +1101,11 @@ int topk_attn_last_selection_records(topk_attn_t* h, uint32_t* records) {
     if (!h || !records || !h->last_tail || h->last_static) return TOPK_ATTN_EINVAL;
     const topk_attn_config& c = h->cfg;
     const size_t n = (size_t)c.n_seqs * h->last_queries * c.n_q_heads;
-    if (hipMemcpy(records, static_cast<char*>(c.workspace) + h->ws.tailrec, n * 4 * sizeof(uint32_t), hipMemcpyDeviceToHost) !=
+    if (hipMemcpy(records, static_cast<char*>(c.workspace) + h->ws.tailrec + h->last_slot * n * 4 * sizeof(uint32_t), n * 4 * sizeof(uint32_t), hipMemcpyDeviceToHost) !=
         hipSuccess)
         return TOPK_ATTN_EDEVICE;
     std::vector<uint32_t> flags(n);
-    if (hipMemcpy(flags.data(), static_cast<char*>(c.workspace) + h->ws.flags, n * sizeof(uint32_t), hipMemcpyDeviceToHost) !=
+    if (hipMemcpy(flags.data(), static_cast<char*>(c.workspace) + h->ws.flags + h->last_slot * n * sizeof(uint32_t), n * sizeof(uint32_t), hipMemcpyDeviceToHost) !=
         hipSuccess)
         return TOPK_ATTN_EDEVICE;
     for (size_t i = 0; i < n; ++i) records[4 * i] |= (flags[i] % kArrivalUnit) << 8;      // the head's flag word above the state
@@ -1020,15 +1115,17 @@ int topk_attn_last_selection_records(topk_attn_t* h, uint32_t* records) {
 int topk_attn_debug_read_workspace(topk_attn_t* h, const char* name, void* dst, size_t bytes) {
     if (!h || !name || !dst) return TOPK_ATTN_EINVAL;
     const WsLayout& w = h->ws;
-    const struct { const char* name; size_t at, end; } arrays[] = {
-        {"thr", w.thr, w.bins}, {"bins", w.bins, w.samp}, {"samp", w.samp, w.seg_cnt}, {"seg_cnt", w.seg_cnt, w.seg_max},
-        {"seg_max", w.seg_max, w.seg_cnt2}, {"seg_cnt2", w.seg_cnt2, w.flags}, {"flags", w.flags, w.hmax},
-        {"tailrec", w.tailrec, w.page_mask}, {"page_mask", w.page_mask, w.page_cnt}, {"page_cnt", w.page_cnt, w.page_list},
-        {"page_list", w.page_list, w.hist}, {"hist", w.hist, w.cand}, {"cand", w.cand, w.bnd}, {"bnd", w.bnd, w.scores}};
+    const struct { const char* name; size_t at, end, per_head; } arrays[] = {
+        {"thr", w.thr, w.bins, 4}, {"bins", w.bins, w.samp, 8}, {"samp", w.samp, w.seg_cnt, 4 * kSampMax}, {"seg_cnt", w.seg_cnt, w.seg_max, 4 * kMaxSeg},
+        {"seg_max", w.seg_max, w.seg_cnt2, 4 * kMaxSeg}, {"seg_cnt2", w.seg_cnt2, w.flags, 4 * kMaxSeg}, {"flags", w.flags, w.hmax, 4},
+        {"tailrec", w.tailrec, w.page_mask, 16}, {"page_mask", w.page_mask, w.page_cnt, 0}, {"page_cnt", w.page_cnt, w.page_list, 0},
+        {"page_list", w.page_list, w.hist, 0}, {"hist", w.hist, w.cand, (size_t)w.hist_cap * kTailBins * 4},
+        {"cand", w.cand, w.bnd, (size_t)w.cand_cap * 8}, {"bnd", w.bnd, w.scores, (size_t)w.bnd_cap * 8}};
     for (const auto& a : arrays) {
         if (strcmp(a.name, name) != 0) continue;
-        if (bytes > a.end - a.at) return TOPK_ATTN_EINVAL;
-        return hipMemcpy(dst, static_cast<char*>(h->cfg.workspace) + a.at, bytes, hipMemcpyDeviceToHost) == hipSuccess
+        const size_t at = a.at + (size_t)h->last_slot * h->cfg.n_seqs * h->cfg.n_q_heads * a.per_head;     // (the last layer of the call)
+        if (at > a.end || bytes > a.end - at) return TOPK_ATTN_EINVAL;
+        return hipMemcpy(dst, static_cast<char*>(h->cfg.workspace) + at, bytes, hipMemcpyDeviceToHost) == hipSuccess
                    ? TOPK_ATTN_OK : TOPK_ATTN_EDEVICE;
     }
     return TOPK_ATTN_EINVAL;

@@ -324,12 +324,18 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     __shared__ uint64_t cand_lds[SRC == SRC_LIST ? CPT * NT : 1];      // candidates (score bits, position)
     __shared__ uint64_t rows_lds[Cfg::ROWS];              // value rows to fetch (weight bits, position)
     __shared__ float acc_lds[NW][256 + 1];
-    const int b = blockIdx.y, h = blockIdx.x;
+    // SRC_LIST: grid z runs over the layers, then over the workgroups of a head
+    const int layer = SRC == SRC_LIST ? (int)blockIdx.z & ((1 << sh.log2_layers) - 1) : (int)blockIdx.z;
+    const int wg = SRC == SRC_LIST ? (int)blockIdx.z >> sh.log2_layers : 0, n_wgs = SRC == SRC_LIST ? (int)gridDim.z >> sh.log2_layers : 1;
+    const int b = (int)blockIdx.y + layer * sh.layer_seqs, h = blockIdx.x;
     const int64_t bh = (int64_t)b * sh.Hq + h;
     const int tid = threadIdx.x, lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    int32_t* const idx = bf.sel_idx + bh * sh.k;
-    float* const vals = bf.sel_val + bh * sh.k;
+    const LayerK lk = bf.layer_k[layer];
+    const int k = lk.k;
+    const int64_t sel0 = selection_at(sh, lk, blockIdx.y, h);
+    int32_t* const idx = bf.sel_idx + sel0;
+    float* const vals = bf.sel_val + sel0;
     const int D = SRC == SRC_LIST ? DIM : sh.D, lpr = D / EPL, rpw = kWave / lpr;          // lanes per key or value row, rows per wave and load
     const int rs = lane / lpr, c = lane % lpr;
     const int64_t head_off = ((int64_t)cache_seq(sh, b) * sh.Hkv + h / sh.G) * sh.Ncap * D * Elem<DT>::kBytes;
@@ -347,7 +353,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     uint64_t pre[SRC == SRC_LIST ? PRE : 1];
     uint64_t* const list = bf.cand + bh * (int64_t)sh.cand_cap;
     uint32_t seg_len = 0, flags = 0;
-    const bool helper = SRC == SRC_LIST && (int)blockIdx.z >= sh.attend;     // (uniform)
+    const bool helper = SRC == SRC_LIST && wg >= sh.share_wgs;     // (uniform)
     if (SRC == SRC_LIST) {
         if (tid < sh.n_seg) seg_len = bf.seg_cnt[bh * sh.n_seg + tid];
         flags = bf.flags[bh];
@@ -360,7 +366,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     }
     const int N = (int)visible_len(sh, bf, b);
     const int P = (int)prefix_len(N, sh.window), W = N - P;      // searched prefix, window
-    const int k_eff = sh.k < P ? sh.k : P;
+    const int k_eff = k < P ? k : P;
     const float* const row = bf.scores + bh * sh.Ncap;
     auto pos = [&](int j) { return SRC == SRC_LIST ? (int32_t)(uint32_t)cand_lds[j * NT + tid] : j * NT + tid; };
     float lo = INFINITY, hi = -INFINITY;                  // range of the scores in question
@@ -414,7 +420,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
             else if (over) how = sh.no_rescan || n_cut > (uint32_t)(CPT * NT) ? SCORE_ROW : RESCORE;
             else how = n_cut <= (uint32_t)(CPT * NT) ? LONG_CUT : LONG_TIED;
             // a list that should have been usable (the measure of the chip-wide selection)
-            const bool fallback = (over || !hit || in_b > (uint32_t)sh.bnd_cap) && !(flags & 5u);
+            const bool fallback = (over || !hit || in_b > (uint32_t)sh.bnd_cap) && !(flags & 5u) && counts_fallbacks(sh, b);
             if (how == LONG_CUT) {
 #pragma unroll 4
                 for (int j = wave; j < n_wg; j += NW) {
@@ -427,12 +433,12 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
                 __syncthreads();
                 cut_list<NW>(sh, wave, B, bin_lo, bin_inv, segs, sm.hist, list, cand_lds, (uint32_t)(CPT * NT));
             } else if (how == LONG_TIED) {
-                if (blockIdx.z != 0) return;                                          // (uniform)
+                if (wg != 0) return;                                               // (uniform)
                 if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
                 alone = true;
             } else {
                 if constexpr (SRC == SRC_LIST)
-                    score_segments<DT, DIM>(sh, bf, b, h, P, (int)blockIdx.z * NW + wave, (int)gridDim.z * NW,
+                    score_segments<DT, DIM>(sh, bf, b, h, P, wg * NW + wave, n_wgs * NW,
                                             how == SCORE_ROW ? kTailBins : B, bin_lo, bin_inv, list);
                 // every wave waits for its stores to arrive in the L2, one thread releases them all (a release writes back the whole
                 // L2 of the XCD; one per wave: 247 us per call instead of 147 at one KV head, 512k tokens, 92 % identical)
@@ -444,7 +450,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
                 }
                 __syncthreads();
                 const uint32_t arrived = sm.n_keys;
-                if (arrived / kArrivalUnit + 1u != gridDim.z) return;                 // (uniform)
+                if (arrived / kArrivalUnit + 1u != (uint32_t)n_wgs) return;                 // (uniform)
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
                 if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
                 alone = true;
@@ -543,7 +549,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
         team_range<Team>(dummy, w_top, sm, 1);
     }
     float M = fmaxf(k_eff > 0 ? top : -INFINITY, w_top);  // the weights' reference score
-    const bool writer = blockIdx.z == 0 || alone;         // (uniform) the workgroup that writes the selection
+    const bool writer = wg == 0 || alone;         // (uniform) the workgroup that writes the selection
     auto weight = [&](float s) { return (uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32; };
     auto emit = [&](uint32_t o, float s, int32_t p) {     // winner o of the head
         if (o < (uint32_t)k_eff) {                        // always true; guards the buffers
@@ -559,18 +565,18 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     Boundary left{0u, 0u};
     if (in_regs && k_eff > 0) {
         left = team_select<Team, CPT, CPT>([&](int j) { return v[j]; }, act, n_items, P, k_eff, lo, hi, sm, pos, emit);
-        if (writer) pad_outputs(k_eff, sh.k, idx, vals);
+        if (writer) pad_outputs(k_eff, k, idx, vals);
     } else if (k_eff == 0) {                              // nothing to search for this sequence
         if (helper) return;
-        if (writer) pad_outputs(0, sh.k, idx, vals);
+        if (writer) pad_outputs(0, k, idx, vals);
     } else if (SRC == SRC_LIST) {                         // radix select over the list or the full score row
         __shared__ SelShared sel_sm;
         if (how == SCORE_ROW) {
-            top = key_score(wg_select_dense<NT, 0>(sh, bf, bh, P, k_eff, sel_sm));      // writes idx, vals and their padding
+            top = key_score(wg_select_dense<NT, 0>(sh, bf, bh, P, k_eff, k, idx, vals, sel_sm));      // writes idx, vals and their padding
         } else {
             const SrcSegments<NT> src{list, reinterpret_cast<const uint2*>(sm.keys), n_slots, 31 - __clz(sh.n_seg)};
             const Items<0, SrcSegments<NT>> items(src);
-            top = key_score(wg_topk_emit(items, k_eff, sh.k, idx, vals, sel_sm));
+            top = key_score(wg_topk_emit(items, k_eff, k, idx, vals, sel_sm));
         }
         M = fmaxf(top, w_top);
         __syncthreads();
@@ -589,77 +595,85 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
         rows_lds[k_eff + i] = weight(SRC == SRC_ROW ? row[P + i] : __uint_as_float((uint32_t)(rows_lds[k_eff + i] >> 32))) | (uint64_t)(uint32_t)(P + i);
     __syncthreads();
 
-    // ---- the weighted value rows (of this workgroup's share)
+    // ---- the weighted value rows (of this workgroup's shares, one after the other)
     const char* const Vh = static_cast<const char*>(bf.V) + head_off;
-    float acc[EPL];
-#pragma unroll
-    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-    float lsum = 0.f;
     const int step = NW * rpw;
     const int shares = SRC == SRC_LIST && !alone ? sh.attend : 1;
-    const int share = shares > 1 ? (int)blockIdx.z : 0;
-    const int row_end = (int)((int64_t)n_rows * (share + 1) / shares);
-    for (int j = (int)((int64_t)n_rows * share / shares) + wave * rpw + rs; j < row_end; j += U * step) {
-        float w[U];
-        u32x4 raw[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int jj = j + u * step < row_end ? j + u * step : j;
-            const uint64_t e = rows_lds[jj];
-            w[u] = j + u * step < row_end ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
-            const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
-            raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * Elem<DT>::kBytes);
-        }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float vf[EPL];
-            Elem<DT>::widen(raw[u], vf);
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w[u], vf[e], acc[e]);
-            lsum += w[u];
-        }
-    }
-    for (int o = lpr; o < 16; o <<= 1) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] += wave_xor(acc[e], o);
-        lsum += wave_xor(lsum, o);
-    }
-    if (lpr <= 16) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_16(acc[e]);
-        lsum = add_lanes_16(lsum);
-    }
-    if (lpr <= 32) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_32(acc[e]);
-        lsum = add_lanes_32(lsum);
-    }
-    if (rs == 0) {
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc_lds[wave][c * EPL + e] = acc[e];
-        if (c == 0) acc_lds[wave][256] = lsum;
-    }
-    __syncthreads();
+    const int share_wgs = shares > 1 ? sh.share_wgs : 1;
+    float* const pa = bf.part_acc + bh * sh.n_chunk_cap * (int64_t)D;
+    float* const pl = bf.part_l + bh * sh.n_chunk_cap;
     float a = 0.f, l = 0.f;                               // thread t < D: channel t (D <= NT)
-    if (tid < D) {
+    for (int share = share_wgs > 1 ? wg : 0; share < shares; share += share_wgs) {       // (uniform)
+        float acc[EPL];
 #pragma unroll
-        for (int w = 0; w < NW; ++w) { a += acc_lds[w][tid]; l += acc_lds[w][256]; }
-    }
-    if (SRC == SRC_LIST && shares > 1) {
+        for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+        float lsum = 0.f;
+        const int row_end = (int)((uint32_t)(n_rows * (share + 1)) / (uint32_t)shares);      // (at most ROWS x 8)
+        for (int j = (int)((uint32_t)(n_rows * share) / (uint32_t)shares) + wave * rpw + rs; j < row_end; j += U * step) {
+            float w[U];
+            u32x4 raw[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int jj = j + u * step < row_end ? j + u * step : j;
+                const uint64_t e = rows_lds[jj];
+                w[u] = j + u * step < row_end ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
+                const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
+                raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * Elem<DT>::kBytes);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float vf[EPL];
+                Elem<DT>::widen(raw[u], vf);
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w[u], vf[e], acc[e]);
+                lsum += w[u];
+            }
+        }
+        for (int o = lpr; o < 16; o <<= 1) {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[e] += wave_xor(acc[e], o);
+            lsum += wave_xor(lsum, o);
+        }
+        if (lpr <= 16) {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_16(acc[e]);
+            lsum = add_lanes_16(lsum);
+        }
+        if (lpr <= 32) {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_32(acc[e]);
+            lsum = add_lanes_32(lsum);
+        }
+        if (rs == 0) {
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc_lds[wave][c * EPL + e] = acc[e];
+            if (c == 0) acc_lds[wave][256] = lsum;
+        }
+        __syncthreads();
+        float as = 0.f, ls = 0.f;
+        if (tid < D) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) { as += acc_lds[w][tid]; ls += acc_lds[w][256]; }
+        }
         // Leave the share where the head's other workgroups see it (agent-scope stores go through to memory, and the wait
         // below is for their arrival there), count it, and let the last workgroup add up all shares in their order.
         // No release or acquire fence: those write back and invalidate the whole L2 of the XCD, and nothing
-        // but these values passes between the workgroups.
-        float* const pa = bf.part_acc + bh * sh.n_chunk_cap * (int64_t)D;
-        float* const pl = bf.part_l + bh * sh.n_chunk_cap;
-        if (tid < D) __hip_atomic_store(pa + share * D + tid, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (tid == 0) __hip_atomic_store(pl + share, l, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // but these values passes between the workgroups.  (A workgroup that takes all shares adds them up as it goes.)
+        if (SRC == SRC_LIST && share_wgs > 1) {
+            if (tid < D) __hip_atomic_store(pa + share * D + tid, as, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (tid == 0) __hip_atomic_store(pl + share, ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            a += as; l += ls;
+        }
+        if (SRC == SRC_LIST && share + share_wgs < shares) __syncthreads();        // (acc_lds is written again)
+    }
+    if (SRC == SRC_LIST && share_wgs > 1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0)
             sm.n_keys = __hip_atomic_fetch_add(&bf.flags[bh], kArrivalUnit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) / kArrivalUnit;
         __syncthreads();
-        if (sm.n_keys + 1u != (uint32_t)shares) return;   // (uniform)
+        if (sm.n_keys + 1u != (uint32_t)share_wgs) return;   // (uniform)
         a = 0.f; l = 0.f;
         if (tid < D) {
             float ta[kAttendShares], tl[kAttendShares];
@@ -694,7 +708,7 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     __shared__ float scores_lds[4][ROW];
     __shared__ uint64_t rows_all_lds[4][ROWS];            // rows to fetch (weight bits, position)
     __shared__ SelectShared<WaveTeam, kShortBins> sms[4];
-    const int kvh = blockIdx.x, b = blockIdx.y, G = sh.G;
+    const int kvh = blockIdx.x, b = (int)blockIdx.y + (int)blockIdx.z * sh.layer_seqs, G = sh.G;
     const int64_t head0 = (int64_t)b * sh.Hq + (int64_t)kvh * G;
     const int lane = lane_id();
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -725,9 +739,11 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     if (wave >= G) return;                                // (no barrier of the workgroup follows)
 
     const int64_t bh = head0 + wave;
-    const int k_eff = sh.k < N ? sh.k : N;
-    int32_t* const idx = bf.sel_idx + bh * sh.k;
-    float* const vals = bf.sel_val + bh * sh.k;
+    const LayerK lk = bf.layer_k[blockIdx.z];
+    const int k = lk.k, k_eff = k < N ? k : N;
+    const int64_t sel0 = selection_at(sh, lk, blockIdx.y, kvh * G + wave);
+    int32_t* const idx = bf.sel_idx + sel0;
+    float* const vals = bf.sel_val + sel0;
     SelectShared<WaveTeam, kShortBins>& sm = sms[wave];
     // (64 scores of a lane in registers spilled: they stay in LDS, eight reads in flight)
     const float* const row = scores_lds[wave] + lane;
@@ -753,7 +769,7 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
             rows_lds[o] = ((uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32) | (uint64_t)(uint32_t)p;
         }
     });
-    for (int o = k_eff + lane; o < sh.k; o += kWave) { idx[o] = -1; vals[o] = -INFINITY; }
+    for (int o = k_eff + lane; o < k; o += kWave) { idx[o] = -1; vals[o] = -INFINITY; }
     wave_sync();
 
     const char* const Vh = static_cast<const char*>(bf.V) + ((int64_t)b * sh.Hkv + kvh) * sh.Ncap * (D * 2);
@@ -796,7 +812,7 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
 hipError_t launch_attend_short(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
     const float scale = 1.0f / sqrtf((float)s.D);
     const float scale_log2e = scale * 1.4426950408889634f;
-    const dim3 grid((unsigned)s.Hkv, (unsigned)s.B);
+    const dim3 grid((unsigned)s.Hkv, (unsigned)s.layer_seqs, 1u << s.log2_layers);
     if (s.M != 1 || s.G > 4 || s.window || s.k > attend_short_k(Nmax)) return hipErrorInvalidValue;
 #define TKA_AS(DT_, D_, ROW_) hipLaunchKernelGGL((attend_short_kernel<DT_, D_, ROW_>), grid, dim3(256), 0, st, s, b, scale, scale_log2e)
 #define TKA_AS_ROW(DT_, D_)                           \
@@ -822,21 +838,24 @@ hipError_t launch_attend_short(const Shape& s, const Bufs& b, int64_t Nmax, hipS
 hipError_t launch_attend_row(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
     const float scale = 1.0f / sqrtf((float)s.D);
     const float scale_log2e = scale * 1.4426950408889634f;
-    const dim3 grid((unsigned)s.Hq, (unsigned)s.B);
+    const dim3 grid((unsigned)s.Hq, (unsigned)s.layer_seqs, 1u << s.log2_layers);
     // (more heads than compute units, rows of up to 8192 scores: workgroups no larger than the row needs take 0.49 - 0.99 of the time
     // of 1024 threads, median 0.81, over 320 to 1920 heads)
-    const bool many = (int64_t)s.Hq * s.B > kAttendManyHeads;
-    if ((int64_t)s.k + s.window > attend_row_rows((int64_t)s.Hq * s.B, Nmax)) return hipErrorInvalidValue;
+    // (the heads of a layer: a call over several layers gives what a call per layer gives)
+    const int64_t heads = (int64_t)s.Hq * s.layer_seqs;
+    if ((int64_t)s.k + s.window > attend_row_rows(heads, Nmax)) return hipErrorInvalidValue;
 #define TKA_AR(DT_, NT_, CPT_, NB_)                                                                                         \
     hipLaunchKernelGGL((attend_kernel<DT_, AttendCfg<NT_, CPT_, NT_ == 1024 ? 4096 : NT_ == 512 ? 2048 : 1024, NB_>, SRC_ROW>), \
                        grid, dim3(NT_), 0, st, s, b, scale, scale_log2e)
 #define TKA_AR_SIZE(DT_)                                     \
     do {                                                     \
-        if (many && Nmax <= 2048) TKA_AR(DT_, 256, 8, 512);  \
-        else if (many && Nmax <= 4096) TKA_AR(DT_, 256, 16, 512);  \
-        else if (many && Nmax <= 8192) TKA_AR(DT_, 512, 16, 512);  \
-        else if (Nmax <= 4096) TKA_AR(DT_, 1024, 4, 1024);   \
-        else TKA_AR(DT_, 1024, 16, 1024);                    \
+        switch (attend_row_class(heads, Nmax)) {             \
+            case 0: TKA_AR(DT_, 256, 8, 512); break;         \
+            case 1: TKA_AR(DT_, 256, 16, 512); break;        \
+            case 2: TKA_AR(DT_, 512, 16, 512); break;        \
+            case 3: TKA_AR(DT_, 1024, 4, 1024); break;       \
+            default: TKA_AR(DT_, 1024, 16, 1024);            \
+        }                                                    \
     } while (0)
     if (s.dtype == DT_F32) TKA_AR_SIZE(DT_F32);
     else if (s.dtype == DT_F16) TKA_AR_SIZE(DT_F16);
@@ -851,7 +870,7 @@ hipError_t launch_attend_list(const Shape& s, const Bufs& b, hipStream_t st) {
     const float scale_log2e = scale * 1.4426950408889634f;
     // as many helpers as fit the compute units beside the shares, a wave of theirs per segment at most
     const int64_t room = std::min<int64_t>(kAttendManyHeads / ((int64_t)s.Hq * s.B), s.n_seg / ListCfg::NW);
-    const dim3 grid((unsigned)s.Hq, (unsigned)s.B, (unsigned)std::max<int64_t>(s.attend, room));
+    const dim3 grid((unsigned)s.Hq, (unsigned)s.layer_seqs, (unsigned)std::max<int64_t>(s.share_wgs, room) << s.log2_layers);
 #define TKA_AL(DT_, D_) hipLaunchKernelGGL((attend_kernel<DT_, ListCfg, SRC_LIST, D_>), grid, dim3(ListCfg::NT), 0, st, s, b, scale, scale_log2e)
     if (s.dtype == DT_F16 && s.D == 128) TKA_AL(DT_F16, 128);
     else if (s.dtype == DT_BF16 && s.D == 128) TKA_AL(DT_BF16, 128);

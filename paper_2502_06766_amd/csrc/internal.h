@@ -26,6 +26,7 @@ constexpr int kFilterMinN = 24576;
 constexpr int kFilterMinNBatch = 8192;
 constexpr int64_t kFilterBatchTokens = 131072;
 constexpr int kMaxSeg = 1024;       // most candidate segments per head
+constexpr int kBatchLayers = 16;    // most layers whose steps share their launches (a power of two)
 
 // Geometry of one decode call, passed by value to every kernel.
 struct Shape {
@@ -40,7 +41,10 @@ struct Shape {
     int force_redo;   // measurement aid: treat every head as not filterable (exact redo of all heads)
     int paged;        // the scan skips the pages the coarse page index rules out
     int no_rescan;    // an unusable list is redone densely (the per-bin counts of a paged scan are not those of the plain tile order)
-    int attend;       // selection and attention of a head in one launch (attend.hip) by this many workgroups, kAttendShort: its scores too; 0: the other back ends
+    int attend;       // selection and attention of a head in one launch (attend.hip), its value rows in this many shares; kAttendShort: its scores too; 0: the other back ends
+    int share_wgs;    // workgroups of a head that take the shares (as many, or fewer with several shares each)
+    int log2_layers;  // the call's sequences are those of 2^log2_layers consecutive layers, layer_seqs each
+    int layer_seqs;
     int page_cap;     // pages per key stream the page index has room for (ceil(Ncap / 64))
     int page_words;   // 64-bit words of the page mask per key stream
     int k;            // requested k (k_eff = min(k, searched prefix of sequence b))
@@ -57,6 +61,9 @@ struct Shape {
     int tail_wgs;     // tail: workgroups per head = ceil((n_seg / 4) / tail_spw)
     int64_t Ncap;     // row capacity per (layer, seq, kv head)
 };
+
+// k of a layer, and the sum over the layers of the call before it (where its block of idx / vals starts).
+struct LayerK { int k, before; };
 
 // Device pointers of one decode call.
 struct Bufs {
@@ -94,6 +101,7 @@ struct Bufs {
     float* out;             // [B*Hq][D]
     float* lse;             // [B*Hq] or null
     uint32_t* fallback_total; // [1]
+    LayerK layer_k[kBatchLayers];
 };
 
 // The MFMA scan has two kernels: one query and at most four heads per KV head go through
@@ -109,6 +117,15 @@ __device__ inline int64_t visible_len(const Shape& sh, const Bufs& bf, int b) {
     const int c = b / sh.M;
     return (int64_t)bf.len[c] - (sh.causal ? sh.M - 1 - (b - c * sh.M) : 0);
 }
+
+// Layer z of the call: its k, and where the selection of head h of its sequence y starts in idx / vals.  (The layer is a
+// coordinate of the grid and the table is read without a branch: a division, or a condition in front of the loads of the other
+// arguments, cost a call of one layer 0.6 to 2.4 us.)
+__device__ inline int64_t selection_at(const Shape& sh, const LayerK& lk, int y, int h) {
+    return ((int64_t)lk.before * sh.layer_seqs + (int64_t)y * lk.k) * sh.Hq + (int64_t)h * lk.k;
+}
+// Fallbacks are counted for the last layer of a call (what a call per layer would leave).
+__device__ inline bool counts_fallbacks(const Shape& sh, int b) { return b >= ((1 << sh.log2_layers) - 1) * sh.layer_seqs; }
 
 // Candidate list of one head: n_seg segments (one per scanning wave).  Runs of kCandChunk
 // consecutive entries of a segment are contiguous (a wave's flush writes whole 128-byte
@@ -216,6 +233,11 @@ inline int attend_row_rows(int64_t heads, int64_t Nmax) {
     if (heads <= kAttendManyHeads || Nmax > 8192) return 4096;
     return Nmax <= 4096 ? 1024 : 2048;
 }
+// Workgroup size and scores per thread of the one launch over score rows.
+inline int attend_row_class(int64_t heads, int64_t Nmax) {
+    if (heads > kAttendManyHeads && Nmax <= 8192) return Nmax <= 2048 ? 0 : Nmax <= 4096 ? 1 : 2;
+    return Nmax <= 4096 ? 3 : 4;
+}
 // Whether one workgroup per head over score rows beats radix select and gather: not where it has more value rows to fetch than
 // it gains (it reaches about 64 GB/s, the gather has several per head), and where the heads fill the chip anyway not for
 // dense selections either.  One launch / radix select and gather, by value rows and their bytes, over 1 to 128 heads, 4k to 16k
@@ -242,7 +264,7 @@ constexpr int kAttendShort = -1;
 constexpr int kScanSampMax = 2048;
 constexpr int kScanSampStreams = 4;
 inline bool threshold_in_scan(const Shape& s, int64_t Nmax) {
-    return s.M == 1 && s.G <= 4 && s.D < 256 && s.B * s.Hkv >= kScanSampStreams && !s.indexed && !s.paged && make_plan(Nmax, s.k < Nmax ? s.k : (int)Nmax).n_samp <= kScanSampMax;
+    return s.M == 1 && s.log2_layers == 0 && s.G <= 4 && s.D < 256 && s.B * s.Hkv >= kScanSampStreams && !s.indexed && !s.paged && make_plan(Nmax, s.k < Nmax ? s.k : (int)Nmax).n_samp <= kScanSampMax;
 }
 
 // Position of sample s: one jittered position inside each stride-long stratum.

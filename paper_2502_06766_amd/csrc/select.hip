@@ -22,9 +22,10 @@ template <int CPT, int NT>     // NT threads; the launcher makes sure n_samp <= 
 __global__ void __launch_bounds__(NT) threshold_kernel(Shape sh, Bufs bf) {
     using Team = WorkgroupTeam<NT>;
     __shared__ ThresholdShared<Team> sm;
-    const int b = blockIdx.y, h = blockIdx.x;
+    const int b = blockIdx.y + blockIdx.z * sh.layer_seqs, h = blockIdx.x;
     const int tid = threadIdx.x;
     const int64_t bh = (int64_t)b * sh.Hq + h;
+    const int k = bf.layer_k[blockIdx.z].k;
     // the sample scores are asked for before the sample size is known (it depends on the sequence
     // length, another trip to memory); what lies beyond the sample is ignored
     const float* samp = bf.samp + bh * sh.samp_cap;
@@ -38,7 +39,7 @@ __global__ void __launch_bounds__(NT) threshold_kernel(Shape sh, Bufs bf) {
     }
     // the sample was drawn by the plan of the cache sequence (shared by all its queries)
     const int64_t N = prefix_len(bf.len[cache_seq(sh, b)], sh.window);
-    const Plan pl = make_plan(N, sh.k < N ? sh.k : (int)N, sh.indexed);
+    const Plan pl = make_plan(N, k < N ? k : (int)N, sh.indexed);
     const Threshold t = estimate_threshold<Team, CPT>(sv, pl, sm);
     if (tid == 0) leave_threshold(bf, bh, t, threshold_flags(sh, pl, N));
 }
@@ -59,13 +60,13 @@ __global__ void __launch_bounds__(NT) select_full_kernel(Shape sh, Bufs bf) {
         if (threadIdx.x == 0) bf.hmax[bh] = -INFINITY;
         return;
     }
-    wg_select_dense<NT, CPT>(sh, bf, bh, N, k_eff, sm);
+    wg_select_dense<NT, CPT>(sh, bf, bh, N, k_eff, sh.k, bf.sel_idx + bh * sh.k, bf.sel_val + bh * sh.k, sm);
 }
 
 hipError_t launch_threshold(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
     if (threshold_in_scan(s, Nmax)) return hipSuccess;
     const int n_samp = make_plan(Nmax, s.k < Nmax ? s.k : (int)Nmax, s.indexed).n_samp;
-    const dim3 grid(s.Hq, s.B);
+    const dim3 grid(s.Hq, s.layer_seqs, 1u << s.log2_layers);
     static_assert(kSampMax <= 32 * 256, "the threshold kernel keeps every sample score in registers");
     // four waves per head whatever the sample size: the kernel is a chain of short phases between
     // barriers, which cost more with sixteen waves than the longer per-thread loops do with four

@@ -315,11 +315,11 @@ __device__ __forceinline__ uint32_t wg_topk_emit(const It& items, int k_eff, int
 
 // Exact selection of one head over its full score row (the general path's selection).
 template <int NT, int CPT>     // the first CPT * NT scores stay in registers, the rest is streamed
-__device__ __forceinline__ uint32_t wg_select_dense(const Shape& sh, const Bufs& bf, int64_t bh, int64_t N, int k_eff,
-                                                    SelShared& sm) {
+__device__ __forceinline__ uint32_t wg_select_dense(const Shape& sh, const Bufs& bf, int64_t bh, int64_t N, int k_eff, int k,
+                                                    int32_t* idx, float* vals, SelShared& sm) {
     const SrcDenseT<NT> src{bf.scores + bh * sh.Ncap, N};
     const Items<CPT, SrcDenseT<NT>> items(src);
-    const uint32_t kmax = wg_topk_emit(items, k_eff, sh.k, bf.sel_idx + bh * sh.k, bf.sel_val + bh * sh.k, sm);
+    const uint32_t kmax = wg_topk_emit(items, k_eff, k, idx, vals, sm);
     if (threadIdx.x == 0) bf.hmax[bh] = key_score(kmax);
     return kmax;              // key of the largest score (uniform)
 }

@@ -623,7 +623,7 @@ __global__ void __launch_bounds__(NT) tail_finish_kernel(Shape sh, Bufs bf, floa
     }
     if (how == BY_REDO) {
         // every score of the head is in the score buffer: exact selection over the full row
-        hmax = key_score(wg_select_dense<NT, 8>(sh, bf, bh, N, k_eff, sm));     // writes idx, vals, padding, hmax
+        hmax = key_score(wg_select_dense<NT, 8>(sh, bf, bh, N, k_eff, sh.k, idx, vals, sm));     // writes idx, vals, padding, hmax
         __syncthreads();                      // idx / vals written above are read below
         gather_rows(0, k_eff, [&](int j) { return (int64_t)idx[j]; },
                     [&](int j) { return exp2f((vals[j] - hmax) * scale_log2e); });

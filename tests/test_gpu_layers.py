@@ -1,0 +1,106 @@
+"""Layers of one topk_attn_decode_layers call share their launches: every output is bit for bit that of a call per layer
+(which the other tests judge against the oracle), whatever path the layers take and however many of them join."""
+import pytest
+import torch
+
+from paper_2502_06766_amd import topk_attn as ta
+from paper_2502_06766_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+TORCH = {wl.F32: torch.float32, wl.F16: torch.float16, wl.BF16: torch.bfloat16}
+
+# layers, sequences, (query, KV) heads, d, dtype, tokens per layer (cycled), k per layer (cycled), window, forced redo, key rows repeated
+CASES = {
+    "lists_8x48k_all_shares_in_one_workgroup": (8, 1, 32, 8, 128, wl.F16, (48001,), (512, 600, 700, 1000), 0, 0, 0),
+    "lists_7_layers_two_shares_a_workgroup": (7, 1, 16, 4, 64, wl.BF16, (33000, 32999), (300, 411), 0, 0, 0),
+    "lists_ragged_window": (4, 2, 8, 2, 128, wl.F16, (70000, 20001, 60000), (64, 700), 256, 0, 0),
+    "lists_row_tiles": (2, 1, 16, 2, 128, wl.BF16, (40003,), (500, 333), 100, 0, 0),
+    "lists_redo": (4, 1, 8, 2, 64, wl.F16, (40000,), (256,), 0, 1, 0),
+    "lists_tied": (4, 1, 8, 2, 64, wl.F16, (40000,), (256, 300), 0, 0, 40),
+    "lists_then_rows": (4, 1, 8, 2, 128, wl.BF16, (40000, 40000, 9000, 9000), (256, 300), 0, 0, 0),
+    "rows": (8, 1, 32, 8, 64, wl.BF16, (4096, 4001, 3000), (64, 65, 200), 0, 0, 0),
+    "rows_window_many_heads": (4, 10, 32, 8, 64, wl.F16, (2040, 2000), (64, 33), 64, 0, 0),
+    "rows_f32": (3, 1, 4, 1, 64, wl.F32, (5000, 7001), (100, 40), 0, 0, 0),
+    "short": (4, 6, 8, 4, 64, wl.F16, (500, 77), (30, 90), 0, 0, 0),
+    "few_tokens": (2, 1, 2, 1, 32, wl.F16, (1, 70), (5, 100), 0, 0, 0),
+    "tail_each_on_its_own": (2, 1, 8, 2, 64, wl.F16, (70000,), (5000,), 0, 0, 0),
+}
+
+
+@pytest.mark.parametrize("name", CASES)
+def test_layers_in_one_call_equal_a_call_per_layer(name):
+    L, B, Hq, Hkv, d, dtype, tokens, ks, window, redo, repeat = CASES[name]
+    ks = [ks[l % len(ks)] for l in range(L)]
+    cache = ta.TopkAttnCache(L, B, Hq, Hkv, d, max(tokens), max(ks), dtype, max_window=window)
+    try:
+        g = torch.Generator(device=DEV)
+        g.manual_seed(1)
+        for l in range(L):
+            for b in range(B):
+                n = max(1, tokens[l % len(tokens)] - 37 * b)
+                K, V = (torch.randn((Hkv, n, d), generator=g, device=DEV).to(TORCH[dtype]) for _ in range(2))
+                if repeat:                                     # most keys are copies of a few: long lists, ties
+                    K[:, :n * 9 // 10] = K[:, torch.arange(n * 9 // 10, device=DEV) % repeat]
+                cache.append(l, b, K, V, head_major=True)
+        q = torch.randn((L, B, Hq, d), generator=g, device=DEV).to(TORCH[dtype])
+        if redo:
+            ta.topk_attn_debug_force_redo(cache.h, redo)
+        single = [cache.decode(l, q[l], ks[l], window=window) for l in range(L)]
+        records = ta.topk_attn_last_selection_records(cache.h, B * Hq) if name.startswith("lists_8") else None
+        fallbacks = ta.topk_attn_last_fallbacks(cache.h)
+        st = torch.cuda.current_stream().cuda_stream
+        for want in (True, False):                             # with the selection, and without (kept in the workspace)
+            out = torch.full((L, B, Hq, d), 7.0, device=DEV)
+            lse = torch.full((L, B, Hq), 7.0, device=DEV)
+            idx = torch.full((B * Hq * sum(ks),), -7, dtype=torch.int32, device=DEV)
+            vals = torch.full((B * Hq * sum(ks),), 7.0, device=DEV)
+            ta.topk_attn_decode_layers(cache.h, 0, ks, q.data_ptr(), window, out.data_ptr(), idx.data_ptr() if want else 0,
+                                       vals.data_ptr() if want else 0, lse.data_ptr(), st)
+            torch.cuda.synchronize()
+            at = 0
+            for l in range(L):
+                n = B * Hq * ks[l]
+                assert torch.equal(out[l], single[l][0]) and torch.equal(lse[l], single[l][3]), f"layer {l}"
+                if want:
+                    assert torch.equal(idx[at:at + n], single[l][1].flatten()), f"layer {l}"
+                    assert torch.equal(vals[at:at + n], single[l][2].flatten()), f"layer {l}"
+                at += n
+            assert ta.topk_attn_last_fallbacks(cache.h) == fallbacks
+            if records is not None:
+                assert ta.topk_attn_last_selection_records(cache.h, B * Hq) == records
+    finally:
+        cache.close()
+
+
+def test_layers_in_one_call_under_graph_capture():
+    """Replays with changing queries, with eager work in between, equal the eager results."""
+    L, Hq, Hkv, d, N, ks = 4, 8, 2, 64, 30000, [200, 220, 240, 260]
+    cache = ta.TopkAttnCache(L, 1, Hq, Hkv, d, N, max(ks), wl.F16)
+    try:
+        g = torch.Generator(device=DEV)
+        g.manual_seed(2)
+        for l in range(L):
+            K, V = (torch.randn((Hkv, N, d), generator=g, device=DEV).half() for _ in range(2))
+            cache.append(l, 0, K, V, head_major=True)
+        q = torch.randn((L, 1, Hq, d), generator=g, device=DEV).half()
+        out = torch.empty((L, 1, Hq, d), device=DEV)
+
+        def call():
+            ta.topk_attn_decode_layers(cache.h, 0, ks, q.data_ptr(), 0, out.data_ptr(), stream=torch.cuda.current_stream().cuda_stream)
+
+        call()
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            call()
+        for i in range(4):
+            q.copy_(torch.randn((L, 1, Hq, d), generator=g, device=DEV).half())
+            graph.replay()
+            torch.cuda.synchronize()
+            got = out.clone()
+            want = torch.stack([cache.decode(l, q[l], ks[l])[0] for l in range(L)])
+            torch.cuda.synchronize()
+            assert torch.equal(got, want), i
+    finally:
+        cache.close()
