@@ -31,6 +31,19 @@ __device__ __forceinline__ int mask_rank(uint64_t m) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
+// Asks for every 64-byte line of the first BYTES bytes of kernel arguments at once.  A kernel reads its arguments where it needs
+// them, and each new line is a trip to memory of its own in a chain of dependent loads.
+template <int BYTES>
+__device__ __forceinline__ void fetch_args() {
+    typedef const __attribute__((address_space(4))) uint32_t* ArgPtr;
+    const ArgPtr p = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
+    uint32_t v[(BYTES + 63) / 64];
+#pragma unroll
+    for (int i = 0; i < (BYTES + 63) / 64; ++i) v[i] = p[16 * i];
+#pragma unroll
+    for (int i = 0; i < (BYTES + 63) / 64; ++i) asm volatile("" ::"s"(v[i]));
+}
+
 template <typename T>
 __device__ __forceinline__ T wave_xor(T v, int mask) {
     return __shfl_xor(v, mask, 64);

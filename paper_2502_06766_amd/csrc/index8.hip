@@ -244,6 +244,7 @@ __device__ __forceinline__ i32x4 tile_mac8(const i32x4 (&b)[4][D / 64], const i3
 template <int DT, int D, int MODE>
 __global__ void __launch_bounds__(kScanWaves* kWave)
 scan8_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
+    fetch_args<kArgBytes>();
     constexpr int KS = D / 64;
     const int b = blockIdx.z, kvh = blockIdx.y;
     const int G = sh.G;
@@ -418,6 +419,7 @@ constexpr int kRerankInFlight = 4;    // the best of 1, 2, 4, 8, 16 measured
 
 template <int DT>
 __global__ void __launch_bounds__(256) rerank_kernel(Shape sh, Bufs bf) {
+    fetch_args<kArgBytes>();
     constexpr int EPL = Elem<DT>::kPerLoad;
     constexpr int U = kRerankInFlight;
     __shared__ float qf[256];

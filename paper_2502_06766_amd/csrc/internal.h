@@ -1,6 +1,7 @@
 // Internal declarations shared by the translation units of libtopk_attn (gfx950 only).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace tka {
@@ -103,6 +104,9 @@ struct Bufs {
     uint32_t* fallback_total; // [1]
     LayerK layer_k[kBatchLayers];
 };
+
+// Bytes of (Shape, Bufs) as the first kernel arguments, without the layers after the first.
+constexpr int kArgBytes = sizeof(Shape) + offsetof(Bufs, layer_k) + sizeof(LayerK);
 
 // The MFMA scan has two kernels: one query and at most four heads per KV head go through
 // the grouped kernel (grid z = sequences), everything else through the row-tile kernel

@@ -116,6 +116,7 @@ page_ball_kernel(const char* __restrict__ K, int64_t Ncap, int64_t Pcap, int Hkv
 // the group?  A wave takes 64 pages: their centres are the "keys" of one MFMA tile.
 template <int DT, int D>
 __global__ void __launch_bounds__(256) page_filter_kernel(Shape sh, Bufs bf, float beta) {
+    fetch_args<kArgBytes>();
     using v8 = typename Mfma<DT>::v8;
     const int b = blockIdx.z, kvh = blockIdx.y;
     const int G = sh.G, lane = lane_id();
@@ -170,6 +171,7 @@ __global__ void __launch_bounds__(256) page_filter_kernel(Shape sh, Bufs bf, flo
 // One workgroup per key stream: compacts the mask into the ascending list of the pages kept.
 constexpr int kListThreads = 1024;
 __global__ void __launch_bounds__(kListThreads) page_list_kernel(Shape sh, Bufs bf) {
+    fetch_args<kArgBytes>();
     __shared__ uint32_t wave_tot[kListThreads / kWave];
     __shared__ uint32_t carry;
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;

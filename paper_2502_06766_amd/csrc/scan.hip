@@ -37,6 +37,7 @@ namespace tka {
 template <int DT, int D, int MODE, bool PAGED = false, bool SAMPLED = false>
 __global__ void __launch_bounds__(kScanWaves* kWave)
 scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
+    fetch_args<kArgBytes>();
     using v8 = typename Mfma<DT>::v8;
     const int b = blockIdx.z, kvh = blockIdx.y;
     const int G = sh.G;
@@ -637,6 +638,7 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
 template <int D, int U>
 __global__ void __launch_bounds__(256)
 scan_f32_kernel(Shape sh, Bufs bf, float* dst) {
+    fetch_args<kArgBytes>();
     constexpr int LPR = D / 4, RPP = 256 / LPR;            // lanes per row, rows per pass of the workgroup
     const int b = blockIdx.z, kvh = blockIdx.y;
     const int G = sh.G;

@@ -20,6 +20,7 @@ namespace tka {
 // Threshold of each head from its sample (threshold.h), a workgroup per head.
 template <int CPT, int NT>     // NT threads; the launcher makes sure n_samp <= CPT * NT <= samp_cap
 __global__ void __launch_bounds__(NT) threshold_kernel(Shape sh, Bufs bf) {
+    fetch_args<kArgBytes>();
     using Team = WorkgroupTeam<NT>;
     __shared__ ThresholdShared<Team> sm;
     const int b = blockIdx.y + blockIdx.z * sh.layer_seqs, h = blockIdx.x;
@@ -50,6 +51,7 @@ __global__ void __launch_bounds__(NT) threshold_kernel(Shape sh, Bufs bf) {
 // flight per compute unit and makes every barrier of the select cheaper.
 template <int NT, int CPT>
 __global__ void __launch_bounds__(NT) select_full_kernel(Shape sh, Bufs bf) {
+    fetch_args<kArgBytes>();
     __shared__ SelShared sm;
     const int b = blockIdx.y, h = blockIdx.x;
     const int64_t bh = (int64_t)b * sh.Hq + h;

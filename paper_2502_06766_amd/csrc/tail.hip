@@ -145,6 +145,7 @@ __device__ __forceinline__ HeadSel analyse_head(const Shape& sh, const Bufs& bf,
 
 template <int DT, int D, bool WIN>
 __global__ void __launch_bounds__(kTailThreads) tail_gather_kernel(Shape sh, Bufs bf, float scale_log2e) {
+    fetch_args<kArgBytes>();
     using v8 = typename Mfma<DT>::v8;
     if (WIN && (int)blockIdx.x >= sh.tail_wgs) {
         // the recent-token window rides in the same launch: the workgroups behind the head's tail_wgs leave the
@@ -452,6 +453,7 @@ constexpr int kFinishSmall = 4096;     // boundary candidates the finishing work
 
 template <int DT, int NT>
 __global__ void __launch_bounds__(NT) tail_finish_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
+    fetch_args<kArgBytes>();
     constexpr int EPL = 8, NW = NT / kWave, CPT = 4, U = 8;       // U: value rows in flight per lane group
     constexpr int CIMAX = kFinishSmall / NT;       // boundary candidates per thread on the small path
     __shared__ SelShared sm;
