@@ -8,17 +8,15 @@
 // the largest score, over scores held in registers (the bin it falls in holds a few, which are ranked by
 // comparison), and the value rows are fetched by the same workgroup as soon as the winners' positions are in LDS.
 //
-// What bounds it: instructions and barriers of one compute unit per head (stamps of a first version: loads 1.5-3 us, bins and
-// their prefix sum 1.6, ranking and emission 2, rows 1.5-2, sum and write 1.5, which is 8 to 10 us of the 14 to 18 below; where the
-// rest goes, start and end of the launch included, was not measured), so scores stay in registers with
-// slots nobody uses skipped uniformly (the same phases as rolled loops over LDS: 23.6 us against 14.5 at 16k
-// tokens) and scans and reductions run in the vector unit instead of trips through LDS.  Measured, 32 heads, 8 KV heads:
-// a row of 16k scores, k = 256: 14.6 us (radix select + gather before: 18.7 + 7.9); a list at 48k tokens, k = 768 on average:
-// 16.4 us, at 128k tokens, k = 2048: 18.9 us (chip-wide tail: 11.6 + 11.6 and 14.5 + 9.6 us and a launch more).
+// What bounds it: a chain of trips to memory and barriers of one compute unit per head, so everything a phase needs is asked for
+// ahead, scores stay in registers with slots nobody uses skipped uniformly (the same phases as rolled loops over LDS: 23.6 us
+// against 14.5 at 16k tokens) and scans and reductions run in the vector unit instead of trips through LDS.  Measured, 32
+// heads, 8 KV heads: a row of 16k scores, k = 256: 14.6 us (radix select + gather: 18.7 + 7.9); a list at 128k tokens, k = 2048:
+// 17.7 us (chip-wide tail: 14.5 + 9.6 us and a launch more); 512 heads (16 queries) at 128k tokens 54.8 us.
 //
-//   SRC_ROW   the scores of a short cache, stored by the scan (general path)
-//   (attend_short_kernel: the scores too, for batches of short sequences)
-//   SRC_LIST  the candidate list the filtered scan left (what becomes of one that is too long or unusable: below)
+//   attend_kernel        the scores of a short cache, stored by the scan (general path)
+//   attend_list_kernel   the candidate list the filtered scan left (what becomes of one that is unusable: below)
+//   attend_short_kernel  the scores too, for batches of short sequences
 #include <algorithm>
 #include <type_traits>
 
@@ -31,15 +29,12 @@
 
 namespace tka {
 
-enum { SRC_ROW = 0, SRC_LIST = 1 };
-
 // NT threads with CPT scores each in registers; ROWS: value rows whose positions and weights fit LDS; NB: bins.
 template <int NT_, int CPT_, int ROWS_, int NB_>
 struct AttendCfg {
     static constexpr int NT = NT_, CPT = CPT_, ROWS = ROWS_, NB = NB_, NW = NT_ / kWave;
     static_assert(NB % NT == 0 && NT % kWave == 0 && NW <= 16 && CPT <= 32, "whole bins per thread, a bit per score, a lane per wave");
 };
-using ListCfg = AttendCfg<1024, kAttendList / 1024, kAttendRows, 1024>;
 
 // What a team shares while it selects; NB bins.
 template <class Team, int NB_>
@@ -180,22 +175,18 @@ __device__ __forceinline__ Boundary team_select(ScoreFn v, Mask act, int n_items
     return first;
 }
 
-// A list longer than the registers hold, or unusable (a segment overflowed).  The scan's counts per score bin, which go on
-// where a segment is full, say which bin B the k-th score falls in and how many entries of the bins from B up every scan
-// workgroup left:
-//   LONG_CUT   they fit: every workgroup of the head takes those alone into its registers and goes on as with a short list
-//   LONG_TIED  they do not (most of them tie): one workgroup goes on alone, by radix select over the list
+// What becomes of a head's list (the scan's counts per score bin go on where a segment is full):
+//   LIST       the entries of the k-th score's bin B fit LDS: the usual case, however long the list is
+//   LIST_TIED  they do not (most of them tie): one workgroup goes on alone, by radix select over the list
 //   RESCORE    a segment overflowed: the head's workgroups score the keys of its tiles again (arithmetic and dealing of the scan),
 //              put those from bin B up into the segments, and the last to finish goes on alone with that list
-//   SCORE_ROW  the same where the counts do not cover k keys or those from B up do not fit either: all scores go to
+//   SCORE_ROW  the same where the counts do not cover k keys or the bin does not fit either: all scores go to
 //              the score buffer, and the last to finish goes on alone by radix select over the row
-// us per call, 32 heads, 8 KV heads, d = 128; chip-wide tail / before the list was cut by the counts (every such head scored
-// again, radix select over the row) / now.  A quarter of the keys identical and just below the k-th score (lists of 36k,
-// 135k at 512k tokens): 128k tokens, k = 2048 88 / 444 / 87; 512k tokens 287 / 1518 / 281; 16 queries at 128k tokens 292 / 2579 /
-// 237.  The same on top (tied): 279 / 548 / 244, at 16 queries 576 / 2789 / 509.  Overflow: one KV head, 4 query heads, 512k tokens, 92 %
-// identical 161 / - / 147; 8 KV heads, 512k tokens, 70 % on top (row) 3822 / 2957 / 2826.  Slower than the tail where one head of
-// a batch that fills the chip is scored by its one workgroup: 4 of 256 heads, 128k tokens, 97 % identical 1466 / - / 1951.
-enum { LIST_SHORT = 0, LONG_CUT, LONG_TIED, RESCORE, SCORE_ROW };
+// us per call, 32 heads, 8 KV heads, d = 128, chip-wide tail / here.  A quarter of the keys identical and just below the k-th score
+// (lists of 36k, 135k at 512k tokens): 128k tokens, k = 2048 88 / 87; 512k tokens 287 / 281; 16 queries at 128k tokens 292 / 237.
+// The same on top (tied): 279 / 244, at 16 queries 576 / 509.  Overflow: one KV head, 4 query heads, 512k tokens, 92 %
+// identical 161 / 147; 8 KV heads, 512k tokens, 70 % on top (row) 3822 / 2826.  Slower than the tail where one head of
+// a batch that fills the chip is scored by its one workgroup: 4 of 256 heads, 128k tokens, 97 % identical 1466 / 1951.
 
 // The head's segments first, first + step, ... (one per wave and step) for RESCORE and SCORE_ROW: exact scores of
 // their keys into the score buffer, and those of bin B and above (none: B = kTailBins) into the segment again.
@@ -251,57 +242,18 @@ __device__ __forceinline__ void score_segments(const Shape& sh, const Bufs& bf, 
     }
 }
 
-// LONG_CUT: the entries of bin B and above, `keep` of scan workgroup j (four segments) from place at(j) on.
-template <int NW>
-__device__ __forceinline__ void cut_list(const Shape& sh, int wave, int B, float bin_lo, float bin_inv, const uint2* segs,
-                                         const uint32_t* at, const uint64_t* list, uint64_t* kept, uint32_t n_kept) {
-    constexpr int U = 2;
-    const int lane = lane_id();
-    for (int j = wave; j < sh.n_seg / kScanWaves; j += NW) {
-        uint32_t o = at[j], len[kScanWaves], longest = 0;
-#pragma unroll
-        for (int s = 0; s < kScanWaves; ++s) {
-            len[s] = segs[j * kScanWaves + s].x;
-            longest = len[s] > longest ? len[s] : longest;
-        }
-        for (uint32_t e0 = 0; e0 < longest; e0 += U * kWave) {
-            uint64_t ent[kScanWaves][U];
-#pragma unroll
-            for (int s = 0; s < kScanWaves; ++s) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const uint32_t e = e0 + u * kWave + lane;
-                    ent[s][u] = list[cand_slot(e < len[s] ? e : 0, j * kScanWaves + s, sh.n_seg)];
-                }
-            }
-#pragma unroll
-            for (int s = 0; s < kScanWaves; ++s) {
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const bool keep = e0 + u * kWave + lane < len[s] &&
-                                      tail_bin(__uint_as_float((uint32_t)(ent[s][u] >> 32)), bin_lo, bin_inv) >= B;
-                    const uint64_t m = __ballot(keep);
-                    const uint32_t to = o + (uint32_t)mask_rank(m);
-                    if (keep && to < n_kept) kept[to] = ent[s][u];           // (below n_kept always; guards the buffer)
-                    o += (uint32_t)__popcll(m);
-                }
-            }
-        }
-    }
-}
-
-// LONG_TIED: the slots of the list as a source of the radix select; `segs`: lengths of its segments (LDS).
+// LIST_TIED: the slots of the list as a source of the radix select; `segs`: lengths of its segments (LDS).
 template <int NT>
 struct SrcSegments {
     static constexpr int kThreads = NT;
     const uint64_t* list;
-    const uint2* segs;
+    const uint32_t* segs;
     int64_t n;
     int log2_n_seg;
     typedef uint64_t raw_t;
     __device__ __forceinline__ int64_t slots() const { return n; }
     __device__ __forceinline__ bool valid(int64_t i) const {
-        return i < n && (uint32_t)cand_slot_entry(i, log2_n_seg) < segs[cand_slot_segment(i, log2_n_seg)].x;
+        return i < n && (uint32_t)cand_slot_entry(i, log2_n_seg) < segs[cand_slot_segment(i, log2_n_seg)];
     }
     __device__ __forceinline__ const uint64_t* where(int64_t i) const { return list + i; }
     __device__ __forceinline__ uint32_t key(uint64_t e) const { return score_key(__uint_as_float((uint32_t)(e >> 32))); }
@@ -310,53 +262,207 @@ struct SrcSegments {
     __device__ __forceinline__ uint32_t cached_ipos(int) const { return 0u; }
 };
 
-// Grid: heads x sequences x workgroups per head.  SRC_LIST: Shape::attend workgroups of a head all select from its list (the same
-// winners, found side by side on compute units that would idle), each fetches its share of the value rows, and the last
-// to finish adds up the shares; so a head's rows are not bound by what one compute unit can fetch (about 64 GB/s).
-// Further ones, where the heads are few, only lend a hand when keys have to be scored again.
-template <int DT, class Cfg, int SRC, int DIM = 0>     // DIM: the head dim of a list kernel
+// Sums over the lane groups of a wave (lpr lanes each).
+template <int EPL>
+__device__ __forceinline__ void lane_group_sums(int lpr, float (&acc)[EPL], float& lsum) {
+    for (int o = lpr; o < 16; o <<= 1) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] += wave_xor(acc[e], o);
+        lsum += wave_xor(lsum, o);
+    }
+    if (lpr <= 16) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_16(acc[e]);
+        lsum = add_lanes_16(lsum);
+    }
+    if (lpr <= 32) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_32(acc[e]);
+        lsum = add_lanes_32(lsum);
+    }
+}
+
+// The weighted value rows first, first + step, ... < end of the list in LDS (weight bits, position), summed over the workgroup:
+// thread t < D gets channel t, `l` the sum of the weights.
+template <int DT, int NT, int U>
+__device__ __forceinline__ void weighted_rows(const char* Vh, int D, int N, const uint64_t* rows, int first, int end, float (*acc_lds)[256 + 1],
+                                              float& a, float& l) {
+    constexpr int EPL = Elem<DT>::kPerLoad, NW = NT / kWave;
+    const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lpr = D / EPL, rpw = kWave / lpr;           // lanes per value row, rows per wave and load
+    const int rs = lane / lpr, c = lane % lpr, step = NW * rpw;
+    float acc[EPL];
+#pragma unroll
+    for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+    float lsum = 0.f;
+    for (int j = first + wave * rpw + rs; j < end; j += U * step) {
+        float w[U];
+        u32x4 raw[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int jj = j + u * step < end ? j + u * step : j;
+            const uint64_t e = rows[jj];
+            w[u] = j + u * step < end ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
+            const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
+            raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * Elem<DT>::kBytes);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float vf[EPL];
+            Elem<DT>::widen(raw[u], vf);
+#pragma unroll
+            for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w[u], vf[e], acc[e]);
+            lsum += w[u];
+        }
+    }
+    lane_group_sums(lpr, acc, lsum);
+    if (rs == 0) {
+#pragma unroll
+        for (int e = 0; e < EPL; ++e) acc_lds[wave][c * EPL + e] = acc[e];
+        if (c == 0) acc_lds[wave][256] = lsum;
+    }
+    __syncthreads();
+    a = 0.f; l = 0.f;
+    if (tid < D) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { a += acc_lds[w][tid]; l += acc_lds[w][256]; }
+    }
+}
+
+// Score rows.  Grid: heads x sequences x layers.
+template <int DT, class Cfg>
 __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4))) attend_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
+    fetch_args<kArgBytes>();
     constexpr int NT = Cfg::NT, NW = Cfg::NW, CPT = Cfg::CPT;
     using Team = WorkgroupTeam<NT>;
-    constexpr int EPL = Elem<DT>::kPerLoad;
-    constexpr int U = 8;                                  // value rows in flight per lane group
     __shared__ SelectShared<Team, Cfg::NB> sm;
-    __shared__ uint64_t cand_lds[SRC == SRC_LIST ? CPT * NT : 1];      // candidates (score bits, position)
     __shared__ uint64_t rows_lds[Cfg::ROWS];              // value rows to fetch (weight bits, position)
     __shared__ float acc_lds[NW][256 + 1];
-    // SRC_LIST: grid z runs over the layers, then over the workgroups of a head
-    const int layer = SRC == SRC_LIST ? (int)blockIdx.z & ((1 << sh.log2_layers) - 1) : (int)blockIdx.z;
-    const int wg = SRC == SRC_LIST ? (int)blockIdx.z >> sh.log2_layers : 0, n_wgs = SRC == SRC_LIST ? (int)gridDim.z >> sh.log2_layers : 1;
-    const int b = (int)blockIdx.y + layer * sh.layer_seqs, h = blockIdx.x;
+    const int b = (int)blockIdx.y + (int)blockIdx.z * sh.layer_seqs, h = blockIdx.x;
     const int64_t bh = (int64_t)b * sh.Hq + h;
-    const int tid = threadIdx.x, lane = lane_id();
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const LayerK lk = bf.layer_k[layer];
+    const int tid = threadIdx.x;
+    const LayerK lk = bf.layer_k[blockIdx.z];
     const int k = lk.k;
     const int64_t sel0 = selection_at(sh, lk, blockIdx.y, h);
     int32_t* const idx = bf.sel_idx + sel0;
     float* const vals = bf.sel_val + sel0;
-    const int D = SRC == SRC_LIST ? DIM : sh.D, lpr = D / EPL, rpw = kWave / lpr;          // lanes per key or value row, rows per wave and load
-    const int rs = lane / lpr, c = lane % lpr;
-    const int64_t head_off = ((int64_t)cache_seq(sh, b) * sh.Hkv + h / sh.G) * sh.Ncap * D * Elem<DT>::kBytes;
+    const int D = sh.D;
 
     // ---- the scores to select from, in registers: slot j of a thread holds item j * NT + tid
+    const int N = (int)visible_len(sh, bf, b);
+    const int P = (int)prefix_len(N, sh.window), W = N - P;      // searched prefix, window
+    const int k_eff = k < P ? k : P;
+    const float* const row = bf.scores + bh * sh.Ncap;
     float v[CPT];
-    int n_items = 0;
     uint32_t act = 0;                                     // bit j: v[j] is a score in question
-    bool alone = false;                                   // (uniform) this workgroup goes on for the whole head
-    int how = LIST_SHORT;                                 // (uniform)
-    bool in_regs = true;                                  // (uniform) the scores to select from are in registers
-    uint32_t above = 0, in_b = 0;                         // not LIST_SHORT: keys above bin B, and in it
-    int n_slots = 0;                                      // slots of the list in use
-    constexpr int PRE = 12;                               // list slots per thread asked for before the segments' lengths are known
-    uint64_t pre[SRC == SRC_LIST ? PRE : 1];
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+        const int i = j * NT + tid;
+        v[j] = row[i < P ? i : 0];                        // (P == 0: the window's scores are there)
+        act |= i < P ? 1u << j : 0u;
+    }
+    float lo = INFINITY, hi = -INFINITY;                  // range of the scores in question
+    float w_top = -INFINITY;                              // largest score of the window
+    for (int i = tid; i < W; i += NT) w_top = fmaxf(w_top, row[P + i]);
+#pragma unroll
+    for (int j = 0; j < CPT; ++j) {
+        if (j * NT < P) {                                 // (uniform)
+            v[j] += 0.0f;                                 // -0 counts as +0
+            if ((act >> j) & 1u) { lo = fminf(lo, v[j]); hi = fmaxf(hi, v[j]); }
+        }
+    }
+    select_clear<Team>(sm);
+    team_range<Team>(lo, hi, sm, 0);
+    if (W > 0) {                                          // (uniform)
+        float dummy = 0.f;
+        team_range<Team>(dummy, w_top, sm, 1);
+    }
+    const float M = fmaxf(k_eff > 0 ? hi : -INFINITY, w_top);    // the weights' reference score
+    auto weight = [&](float s) { return (uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32; };
+
+    // ---- the k_eff best
+    if (k_eff > 0)
+        team_select<Team, CPT, CPT>([&](int j) { return v[j]; }, act, P, P, k_eff, lo, hi, sm, [&](int j) { return j * NT + tid; },
+                                    [&](uint32_t o, float s, int32_t p) {           // winner o of the head
+            if (o < (uint32_t)k_eff) {                    // always true; guards the buffers
+                idx[o] = p;
+                vals[o] = s;
+                rows_lds[o] = weight(s) | (uint64_t)(uint32_t)p;
+            }
+        });
+    pad_outputs(k_eff, k, idx, vals);
+    for (int i = tid; i < W; i += NT) rows_lds[k_eff + i] = weight(row[P + i]) | (uint64_t)(uint32_t)(P + i);
+    __syncthreads();
+
+    // ---- the weighted value rows (at most ROWS: the launcher's rule)
+    const char* const Vh = static_cast<const char*>(bf.V) + ((int64_t)cache_seq(sh, b) * sh.Hkv + h / sh.G) * sh.Ncap * D * Elem<DT>::kBytes;
+    float a, l;
+    weighted_rows<DT, NT, 8>(Vh, D, N, rows_lds, 0, k_eff + W, acc_lds, a, l);
+    if (tid < D) {
+        bf.out[bh * D + tid] = a / l;
+        if (tid == 0 && bf.lse) bf.lse[bh] = M * scale + logf(l);
+    }
+}
+
+// Candidate lists.  Grid: heads x sequences x (workgroups per head x layers).  Shape::share_wgs workgroups of a head all select from
+// its list (the same winners, found side by side on compute units that would idle), each keeps and fetches its shares of the
+// value rows, and the last to finish adds up the shares; so a head's rows are not bound by what one compute unit can fetch
+// (about 64 GB/s).  Further ones, where the heads are few, only lend a hand when keys have to be scored again.
+//
+// The scan's counts per score bin say without a look at the list which bin B the k-th score falls in and how many entries lie
+// above it, and the largest score its waves saw is the weights' reference: an entry above B is a winner as soon as it is
+// read, and only those of B (a few hundred at most, as a rule) are ranked.  So a head costs four barriers: the segments'
+// lengths and the counts, the places of the winners, the ranking, the sum; stamps at 128k tokens: lengths and counts 3.8 us,
+// entries 2.4, places 1.3, emission and ranking 2.3, rows and sum 3.5, the shares' exchange 2.0.  The list stays in registers, not in
+// LDS, so that two workgroups of 512 threads share a compute unit where there are more than 256.  A first version put the list into
+// LDS, found its range, binned it again and split the k-th score's bin (nine barriers, one workgroup per compute unit): 32 heads
+// at 128k tokens 19.1 us and 17.7 now, 64 heads with a window 27.4 and 24.7, 512 heads 66.9 and 54.8.
+template <int DT, int NT, int D>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) attend_list_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
+    constexpr int NW = NT / kWave, EPL = 8, LPR = D / EPL, RPW = kWave / LPR;
+    constexpr int PRE = 8;                                // list slots per thread asked for before the segments' lengths are known
+    constexpr int EDGES = NT == 1024 ? kAttendList : 3584;              // entries of the k-th score's bin that fit LDS (two workgroups of 512 threads share a compute unit)
+    constexpr int FEW = 256;                              // more are split again before they are ranked
+    constexpr int SPT = kMaxSeg / NT;                     // segments per thread
+    using Team = WorkgroupTeam<NT>;
+    __shared__ SelectShared<Team, 1024> sm;
+    __shared__ uint64_t rows_lds[kAttendRows];            // value rows to fetch (weight bits, position)
+    __shared__ uint64_t edge_lds[EDGES];                  // composite keys of the entries of the k-th score's bin; later partial sums
+    __shared__ uint32_t segs[kMaxSeg];                    // lengths of the segments
+    __shared__ uint32_t bins_lds[NW][kTailBins];
+    __shared__ uint32_t red_lds[3][NW];
+    __shared__ uint32_t n_edge_lds;                       // entries of the k-th score's bin found
+    static_assert(sizeof(edge_lds) >= (NT == 1024 ? 2 : 1) * NW * 257 * sizeof(float) && kTailBins == kWave, "partial sums in place of the entries; a bin per lane");
+    float (*const acc_lds)[256 + 1] = reinterpret_cast<float (*)[256 + 1]>(edge_lds);
+    const int layer = (int)blockIdx.z & ((1 << sh.log2_layers) - 1);
+    const int wg = (int)blockIdx.z >> sh.log2_layers, n_wgs = (int)gridDim.z >> sh.log2_layers;
+    const int b = (int)blockIdx.y + layer * sh.layer_seqs, h = blockIdx.x;
+    const int64_t bh = (int64_t)b * sh.Hq + h;
+    const int tid = threadIdx.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int n_seg = sh.n_seg, log2_n_seg = 31 - __clz(n_seg), n_scan = n_seg / kScanWaves;
+    const bool helper = wg >= sh.share_wgs;               // (uniform)
+
+    // ---- everything the selection starts from is asked for at once
     uint64_t* const list = bf.cand + bh * (int64_t)sh.cand_cap;
-    uint32_t seg_len = 0, flags = 0;
-    const bool helper = SRC == SRC_LIST && wg >= sh.share_wgs;     // (uniform)
-    if (SRC == SRC_LIST) {
-        if (tid < sh.n_seg) seg_len = bf.seg_cnt[bh * sh.n_seg + tid];
-        flags = bf.flags[bh];
+    uint32_t seg_len[SPT];
+    float seg_top[SPT];
+#pragma unroll
+    for (int u = 0; u < SPT; ++u) {
+        const int g = u * NT + tid;
+        seg_len[u] = g < n_seg ? bf.seg_cnt[bh * n_seg + g] : 0u;
+        seg_top[u] = g < n_seg ? bf.seg_max[bh * n_seg + g] : -INFINITY;
+    }
+    const uint32_t flags = bf.flags[bh];
+    const float bin_lo = bf.bins[2 * bh], bin_inv = bf.bins[2 * bh + 1];
+    uint32_t n_bin = 0;                                   // this wave's share of the counts of bin `lane`
+    {
+        const uint32_t* const hp = bf.hist + bh * (int64_t)sh.hist_cap * kTailBins + lane;
+#pragma unroll 4
+        for (int j = wave; j < n_scan; j += NW) n_bin += hp[j * kTailBins];
+    }
+    uint64_t pre[PRE];
+    {
         const int n_pre = helper ? 0 : sh.cand_cap;
 #pragma unroll
         for (int u = 0; u < PRE; ++u) {
@@ -364,217 +470,257 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
             pre[u] = list[i < n_pre ? i : 0];             // (any slot of the list may be read; what lies beyond its segment is ignored)
         }
     }
+    const LayerK lk = bf.layer_k[layer];
+    const int k = lk.k;
+    const int64_t sel0 = selection_at(sh, lk, blockIdx.y, h);
+    int32_t* const idx = bf.sel_idx + sel0;
+    float* const vals = bf.sel_val + sel0;
     const int N = (int)visible_len(sh, bf, b);
     const int P = (int)prefix_len(N, sh.window), W = N - P;      // searched prefix, window
     const int k_eff = k < P ? k : P;
-    const float* const row = bf.scores + bh * sh.Ncap;
-    auto pos = [&](int j) { return SRC == SRC_LIST ? (int32_t)(uint32_t)cand_lds[j * NT + tid] : j * NT + tid; };
-    float lo = INFINITY, hi = -INFINITY;                  // range of the scores in question
-    if (SRC == SRC_ROW) {
-        n_items = P;
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) {
-            const int i = j * NT + tid;
-            v[j] = row[i < P ? i : 0];                    // (P == 0: the window's scores are there)
-            act |= i < P ? 1u << j : 0u;
-        }
-    } else if (k_eff > 0) {
-        // lengths and places of the segments
-        uint32_t total, longest;
-        uint2* const segs = reinterpret_cast<uint2*>(sm.keys);
-        const int log2_n_seg = 31 - __clz(sh.n_seg);
+    const int64_t head_off = ((int64_t)cache_seq(sh, b) * sh.Hkv + h / sh.G) * sh.Ncap * D * 2;
+
+    enum { LIST = 0, LIST_TIED, RESCORE, SCORE_ROW };
+    int how = LIST;                                       // (uniform)
+    bool alone = false;                                   // (uniform) this workgroup goes on for the whole head
+    uint32_t above = 0, in_b = 0, total = 0;              // keys above bin B, and in it; entries of the list
+    int B = kTailBins, n_slots = 0;                       // bin of the k-th score; slots of the list in use
+    float top = -INFINITY;                                // largest selected score
+    if (k_eff > 0) {
+        // lengths of the segments, and (with the first barrier) what all threads need to know of them
         auto lay_out = [&]() {
-            const uint32_t longest_w = wave_max_u32(seg_len);
-            if (lane == 0) sm.hist[wave] = longest_w;
-            const uint32_t at = team_prefix<Team>(seg_len, total, sm, 0);
-            segs[tid] = make_uint2(seg_len, at);
-            longest = wave_max_u32(lane < NW ? sm.hist[lane] : 0u);
-            n_slots = (int)((longest + kCandChunk - 1) >> kCandChunkLog2) * sh.n_seg * kCandChunk;
+            if (tid == 0) n_edge_lds = 0;
+            uint32_t sum = 0, longest = 0;
+            float mx = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < SPT; ++u) {
+                segs[u * NT + tid] = seg_len[u];
+                sum += seg_len[u];
+                longest = seg_len[u] > longest ? seg_len[u] : longest;
+                mx = fmaxf(mx, seg_top[u]);
+            }
+            sum = wave_scan_add(sum);
+            longest = wave_max_u32(longest);
+            mx = wave_max(mx);
+            if (lane == kWave - 1) { red_lds[0][wave] = sum; red_lds[1][wave] = longest; red_lds[2][wave] = __float_as_uint(mx); }
+            bins_lds[wave][lane] = n_bin;
+            __syncthreads();
+            const bool one = lane < NW;
+            const uint32_t t = wave_scan_add(one ? red_lds[0][lane] : 0u);
+            total = (uint32_t)__builtin_amdgcn_readlane((int)t, kWave - 1);
+            const uint32_t len = wave_max_u32(one ? red_lds[1][lane] : 0u);
+            top = wave_max(one ? __uint_as_float(red_lds[2][lane]) : -INFINITY) + 0.0f;
+            n_slots = (int)((len + kCandChunk - 1) >> kCandChunkLog2) * n_seg * kCandChunk;
+            return len;
         };
-        lay_out();
+        const uint32_t longest = lay_out();
+        uint32_t all = 0;                                 // lane l looks at bin kTailBins - 1 - l
+#pragma unroll
+        for (int w = 0; w < NW; ++w) all += bins_lds[w][kTailBins - 1 - lane];
+        const uint32_t upto = wave_scan_add(all);
+        const uint64_t hit = __ballot(upto - all < (uint32_t)k_eff && (uint32_t)k_eff <= upto);      // (one lane, or the counts do not cover k_eff keys)
+        const int hit_lane = hit ? __builtin_ctzll(hit) : 0;
+        B = kTailBins - 1 - hit_lane;
+        in_b = (uint32_t)__builtin_amdgcn_readlane((int)all, hit_lane);
+        above = (uint32_t)__builtin_amdgcn_readlane((int)upto, hit_lane) - in_b;
         // (an index leaves the approximate scores of a head it marked as not filterable)
         const bool over = longest > (uint32_t)sh.seg_cap || (flags & (sh.indexed ? 5u : 4u));
-        if (over || total < (uint32_t)k_eff || total > (uint32_t)(CPT * NT)) {
-            // the bin of the k-th score from the scan's counts: lane l of every wave looks at bin kTailBins - 1 - l
-            static_assert(kTailBins == kWave, "a bin per lane");
-            const int n_wg = sh.n_seg / kScanWaves;
-            const uint32_t* const hp = bf.hist + bh * (int64_t)sh.hist_cap * kTailBins;
-            const float bin_lo = bf.bins[2 * bh], bin_inv = bf.bins[2 * bh + 1];
-            uint32_t* const part = reinterpret_cast<uint32_t*>(cand_lds);
-            uint32_t n = 0;
-#pragma unroll 4
-            for (int j = wave; j < n_wg; j += NW) n += hp[j * kTailBins + lane];
-            part[wave * kTailBins + lane] = n;
+        if (!hit) how = SCORE_ROW;
+        else if (over) how = sh.no_rescan || in_b > (uint32_t)EDGES ? SCORE_ROW : RESCORE;
+        else if (in_b > (uint32_t)EDGES) how = LIST_TIED;
+        if (helper && how < RESCORE) return;              // (uniform)
+        // a list that should have been usable (the measure of the chip-wide selection)
+        const bool fallback = (over || !hit || in_b > (uint32_t)sh.bnd_cap) && !(flags & 5u) && counts_fallbacks(sh, b);
+        if (how == LIST_TIED) {
+            if (wg != 0) return;                          // (uniform)
+            if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
+            alone = true;
+        } else if (how != LIST) {
+            score_segments<DT, D>(sh, bf, b, h, P, wg * NW + wave, n_wgs * NW, how == SCORE_ROW ? kTailBins : B, bin_lo, bin_inv, list);
+            // every wave waits for its stores to arrive in the L2, one thread releases them all (a release writes back the whole
+            // L2 of the XCD; one per wave: 247 us per call instead of 147 at one KV head, 512k tokens, 92 % identical)
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
             __syncthreads();
-            uint32_t all = 0;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) all += part[w * kTailBins + kTailBins - 1 - lane];
-            const uint32_t upto = wave_scan_add(all);
-            const uint64_t hit = __ballot(upto - all < (uint32_t)k_eff && (uint32_t)k_eff <= upto);      // (one lane, or the counts do not cover k_eff keys)
-            const int hit_lane = hit ? __builtin_ctzll(hit) : 0;
-            const int B = kTailBins - 1 - hit_lane;
-            in_b = (uint32_t)__builtin_amdgcn_readlane((int)all, hit_lane);
-            above = (uint32_t)__builtin_amdgcn_readlane((int)upto, hit_lane) - in_b;
-            const uint32_t n_cut = above + in_b;
-            if (!hit) how = SCORE_ROW;
-            else if (over) how = sh.no_rescan || n_cut > (uint32_t)(CPT * NT) ? SCORE_ROW : RESCORE;
-            else how = n_cut <= (uint32_t)(CPT * NT) ? LONG_CUT : LONG_TIED;
-            // a list that should have been usable (the measure of the chip-wide selection)
-            const bool fallback = (over || !hit || in_b > (uint32_t)sh.bnd_cap) && !(flags & 5u) && counts_fallbacks(sh, b);
-            if (how == LONG_CUT) {
-#pragma unroll 4
-                for (int j = wave; j < n_wg; j += NW) {
-                    const uint32_t c = wave_scan_add(lane >= B ? hp[j * kTailBins + lane] : 0u);
-                    if (lane == kWave - 1) sm.hist[j] = c;
-                }
-                __syncthreads();
-                const uint32_t at = team_prefix<Team>(tid < n_wg ? sm.hist[tid] : 0u, total, sm, 1);     // (total: n_cut)
-                if (tid < n_wg) sm.hist[tid] = at;
-                __syncthreads();
-                cut_list<NW>(sh, wave, B, bin_lo, bin_inv, segs, sm.hist, list, cand_lds, (uint32_t)(CPT * NT));
-            } else if (how == LONG_TIED) {
-                if (wg != 0) return;                                               // (uniform)
-                if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
-                alone = true;
-            } else {
-                if constexpr (SRC == SRC_LIST)
-                    score_segments<DT, DIM>(sh, bf, b, h, P, wg * NW + wave, n_wgs * NW,
-                                            how == SCORE_ROW ? kTailBins : B, bin_lo, bin_inv, list);
-                // every wave waits for its stores to arrive in the L2, one thread releases them all (a release writes back the whole
-                // L2 of the XCD; one per wave: 247 us per call instead of 147 at one KV head, 512k tokens, 92 % identical)
-                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-                __syncthreads();
-                if (tid == 0) {
-                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-                    sm.n_keys = atomicAdd(&bf.flags[bh], kArrivalUnit);               // (the threshold estimate cleared the count)
-                }
-                __syncthreads();
-                const uint32_t arrived = sm.n_keys;
-                if (arrived / kArrivalUnit + 1u != (uint32_t)n_wgs) return;                 // (uniform)
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-                if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
-                alone = true;
-                if (how == RESCORE && (arrived & 2u)) how = SCORE_ROW;
-                if (how == RESCORE) {
-                    seg_len = tid < sh.n_seg ? bf.seg_cnt2[bh * sh.n_seg + tid] : 0u;
-                    lay_out();
-                }
-            }
-            in_regs = how == LONG_CUT || how == RESCORE;
-        }
-        if (helper && !alone) return;                     // (uniform)
-        if (in_regs) {
-            n_items = (int)total;
-            if (how != LONG_CUT) {
-                auto place = [&](int i, uint64_t ent) {   // slot i of the list: entry e of segment g
-                    const uint2 s = segs[cand_slot_segment(i, log2_n_seg)];
-                    const uint32_t e = (uint32_t)cand_slot_entry(i, log2_n_seg);
-                    if (e < s.x) cand_lds[s.y + e] = ent;
-                };
-                __syncthreads();
-                if (how == LIST_SHORT) {
-#pragma unroll
-                    for (int u = 0; u < PRE; ++u)
-                        if (u * NT < n_slots) place(u * NT + tid, pre[u]);   // (n_slots is a multiple of 64; a segment's slots lie below it)
-                }
-                for (int i0 = (how == LIST_SHORT ? PRE * NT : 0) + tid; i0 < n_slots; i0 += 4 * NT) {
-                    uint64_t ent[4];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) ent[u] = list[i0 + u * NT < n_slots ? i0 + u * NT : 0];
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (i0 + u * NT < n_slots) place(i0 + u * NT, ent[u]);
-                }
+            if (tid == 0) {
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+                sm.n_keys = atomicAdd(&bf.flags[bh], kArrivalUnit);               // (the threshold estimate cleared the count)
             }
             __syncthreads();
+            const uint32_t arrived = sm.n_keys;
+            if (arrived / kArrivalUnit + 1u != (uint32_t)n_wgs) return;           // (uniform)
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
+            alone = true;
+            if (how == RESCORE && (arrived & 2u)) how = SCORE_ROW;
+            if (how == RESCORE) {
 #pragma unroll
-            for (int j = 0; j < CPT; ++j) {
-                if (j * NT < n_items) {
-                    const int i = j * NT + tid;
-                    v[j] = __uint_as_float((uint32_t)(cand_lds[i < n_items ? i : 0] >> 32));
-                    act |= i < n_items ? 1u << j : 0u;
+                for (int u = 0; u < SPT; ++u) {
+                    const int g = u * NT + tid;
+                    seg_len[u] = g < n_seg ? bf.seg_cnt2[bh * n_seg + g] : 0u;
                 }
+                lay_out();                                // (its barrier comes after the readers of what it overwrites)
             }
         }
+    } else if (helper) {
+        return;                                           // nothing to search for this sequence
     }
 
-    // ---- the window's scores (a list has none: scored here with plain FMAs), into the places behind the winners'
+    // ---- the window's scores (plain FMAs), into the places behind the winners'
     float w_top = -INFINITY;                              // largest score of the window
-    const int n_rows = k_eff + W;                         // rows to fetch (at most ROWS: the launcher's rule)
-    if (SRC == SRC_ROW) {
-        for (int i = tid; i < W; i += NT) w_top = fmaxf(w_top, row[P + i]);
-    } else if (W > 0) {
+    const int n_rows = k_eff + W;                         // rows to fetch (at most kAttendRows: the launcher's rule)
+    if (W > 0) {                                          // (uniform)
+        const int rs = lane / LPR, c = lane % LPR;
         float qf[EPL];
-        Elem<DT>::widen(*reinterpret_cast<const u32x4*>(static_cast<const char*>(bf.q) + (bh * D + c * EPL) * Elem<DT>::kBytes), qf);
+        Elem<DT>::widen(*reinterpret_cast<const u32x4*>(static_cast<const char*>(bf.q) + (bh * D + c * EPL) * 2), qf);
         const char* const Kh = static_cast<const char*>(bf.K) + head_off;
-        constexpr int UW = 4;
-        const int step = NW * rpw;
-        for (int j = wave * rpw; j < W; j += UW * step) {            // (uniform over the wave)
+        constexpr int UW = 4, STEP = NW * RPW;
+        for (int j = wave * RPW; j < W; j += UW * STEP) {            // (uniform over the wave)
             u32x4 raw[UW];
 #pragma unroll
             for (int u = 0; u < UW; ++u) {
-                const int i = j + u * step + rs;
-                raw[u] = *reinterpret_cast<const u32x4*>(Kh + ((int64_t)(P + (i < W ? i : W - 1)) * D + c * EPL) * Elem<DT>::kBytes);
+                const int i = j + u * STEP + rs;
+                raw[u] = *reinterpret_cast<const u32x4*>(Kh + ((int64_t)(P + (i < W ? i : W - 1)) * D + c * EPL) * 2);
             }
 #pragma unroll
             for (int u = 0; u < UW; ++u) {
-                const int i = j + u * step + rs;
+                const int i = j + u * STEP + rs;
                 float kf[EPL], a = 0.f;
                 Elem<DT>::widen(raw[u], kf);
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) a = fmaf(kf[e], qf[e], a);
-                for (int o = 1; o < lpr; o <<= 1) a += wave_xor(a, o);
+                a = group_reduce<AddOp, LPR>(a);
                 if (i < W) {
                     w_top = fmaxf(w_top, a);
                     if (c == 0) rows_lds[k_eff + i] = (uint64_t)__float_as_uint(a) << 32;
                 }
             }
         }
-    }
-    if (in_regs) {
-#pragma unroll
-        for (int j = 0; j < CPT; ++j) {
-            if (j * NT < n_items) {                       // (uniform)
-                v[j] += 0.0f;                             // -0 counts as +0
-                if ((act >> j) & 1u) { lo = fminf(lo, v[j]); hi = fmaxf(hi, v[j]); }
-            }
-        }
-    }
-    if (SRC == SRC_LIST && alone) __syncthreads();        // (what select_clear() writes was read above)
-    select_clear<Team>(sm);
-    team_range<Team>(lo, hi, sm, 0);
-    float top = hi;                                       // largest selected score
-    if (W > 0) {                                          // (uniform)
         float dummy = 0.f;
         team_range<Team>(dummy, w_top, sm, 1);
     }
-    float M = fmaxf(k_eff > 0 ? top : -INFINITY, w_top);  // the weights' reference score
-    const bool writer = wg == 0 || alone;         // (uniform) the workgroup that writes the selection
+    float M = fmaxf(top, w_top);                          // the weights' reference score
+    const bool writer = wg == 0 || alone;                 // (uniform) the workgroup that writes the padding and the record
+    // this workgroup's shares, and the value rows they cover: only winners that fall there are emitted (all of them find the same)
+    const int shares = alone ? 1 : sh.attend, share_wgs = shares > 1 ? sh.share_wgs : 1;
+    const int share0 = share_wgs > 1 ? wg * shares / share_wgs : 0, share1 = share_wgs > 1 ? (wg + 1) * shares / share_wgs : shares;
+    auto share_row = [&](int share) { return (int)((uint32_t)(n_rows * share) / (uint32_t)shares); };
+    const uint32_t row0 = (uint32_t)share_row(share0), row1 = (uint32_t)share_row(share1);
     auto weight = [&](float s) { return (uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32; };
-    auto emit = [&](uint32_t o, float s, int32_t p) {     // winner o of the head
-        if (o < (uint32_t)k_eff) {                        // always true; guards the buffers
-            if (writer) {
-                idx[o] = p;
-                vals[o] = s;
-            }
-            rows_lds[o] = weight(s) | (uint64_t)(uint32_t)p;
+    auto emit = [&](uint32_t o, float s, uint32_t p) {    // winner o of the head
+        if (o - row0 < row1 - row0 && o < (uint32_t)k_eff) {         // (o < k_eff always; guards the buffers)
+            idx[o] = (int32_t)p;
+            vals[o] = s;
+            rows_lds[o] = weight(s) | (uint64_t)p;
         }
     };
+    auto score_of = [](uint64_t e) { return __uint_as_float((uint32_t)(e >> 32)); };
 
     // ---- the k_eff best
-    Boundary left{0u, 0u};
-    if (in_regs && k_eff > 0) {
-        left = team_select<Team, CPT, CPT>([&](int j) { return v[j]; }, act, n_items, P, k_eff, lo, hi, sm, pos, emit);
+    if (k_eff > 0 && (how == LIST || how == RESCORE)) {
+        const int n_pre = how == LIST ? PRE : 0;          // (uniform) slots per thread in registers
+        // bin of slot i's entry, -1 for a slot that holds none
+        auto bin_of = [&](int i, uint64_t ent) {
+            const bool in = (uint32_t)cand_slot_entry(i, log2_n_seg) < segs[cand_slot_segment(i, log2_n_seg)];
+            return in ? tail_bin(score_of(ent), bin_lo, bin_inv) : -1;
+        };
+        // (composite: score key, then inverted position: larger beats smaller, equal scores go to the lower position, no two are equal)
+        const bool few = in_b <= (uint32_t)FEW;           // (uniform) they are ranked, in whatever order they lie; more keep the list's
+        auto edge = [&](uint32_t o, uint64_t ent) {
+            if (o < (uint32_t)EDGES)                      // (always: in_b entries)
+                edge_lds[o] = ((uint64_t)score_key(score_of(ent)) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)ent);
+        };
+        uint32_t wins = 0, edges = 0, n_win = 0, n_edges = 0;
+#pragma unroll
+        for (int u = 0; u < PRE; ++u) {
+            if (u < n_pre && u * NT < n_slots) {          // (uniform; n_slots is a multiple of 64, a segment's slots lie below it)
+                const int bin = bin_of(u * NT + tid, pre[u]);
+                wins |= bin > B ? 1u << u : 0u;
+                edges |= bin == B ? 1u << u : 0u;
+                if (few && bin == B) edge(atomicAdd(&n_edge_lds, 1u), pre[u]);
+            }
+        }
+        n_win = (uint32_t)__popc(wins);
+        n_edges = (uint32_t)__popc(edges);
+        // a list longer than the registers hold is read twice
+        auto rest = [&](auto f) {
+            for (int i0 = n_pre * NT + tid; i0 < n_slots; i0 += 4 * NT) {
+                uint64_t ent[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) ent[u] = list[i0 + u * NT < n_slots ? i0 + u * NT : 0];
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (i0 + u * NT < n_slots) f(bin_of(i0 + u * NT, ent[u]), ent[u]);
+            }
+        };
+        rest([&](int bin, uint64_t ent) {
+            n_win += bin > B ? 1u : 0u;
+            n_edges += bin == B ? 1u : 0u;
+            if (few && bin == B) edge(atomicAdd(&n_edge_lds, 1u), ent);
+        });
+        uint32_t all_wins;                                // (`above` of them)
+        uint32_t at = team_prefix<Team>(n_win, all_wins, sm, 0);
+        if (__ballot(at < row1 && at + n_win > row0)) {   // (the places of a wave's winners follow one another)
+#pragma unroll
+            for (int u = 0; u < PRE; ++u)
+                if (u * NT < n_slots && ((wins >> u) & 1u)) emit(at++, score_of(pre[u]), (uint32_t)pre[u]);
+            rest([&](int bin, uint64_t ent) {
+                if (bin > B) emit(at++, score_of(ent), (uint32_t)ent);
+            });
+        }
+        // the best entries of the bin are the missing winners
+        const uint32_t need = (uint32_t)k_eff - above;
+        const int n_edge = (int)(in_b < (uint32_t)EDGES ? in_b : (uint32_t)EDGES);
+        auto edge_score = [&](uint64_t key) { return key_score((uint32_t)(key >> 32)); };
+        auto edge_pos = [&](uint64_t key) { return 0xFFFFFFFFu - (uint32_t)key; };
+        if (row1 <= above) {                              // (uniform) none of the missing winners is in this workgroup's shares
+        } else if (few) {                                 // each against all others, LP lanes per entry
+            constexpr int LP = NT / FEW;
+            static_assert(LP == 2 || LP == 4, "a pair or a quad of lanes");
+            const int j = tid / LP;
+            const uint64_t mine = edge_lds[j < n_edge ? j : 0];
+            uint32_t rank = 0;
+            if (j < n_edge) {
+#pragma unroll 8
+                for (int o = tid % LP; o < n_edge; o += LP) rank += edge_lds[o] > mine ? 1u : 0u;
+            }
+            rank += dpp_u32<0xB1, 0xF>(0u, rank);         // quad_perm 1,0,3,2
+            if (LP == 4) rank += dpp_u32<0x4E, 0xF>(0u, rank);       // quad_perm 2,3,0,1
+            if (j < n_edge && tid % LP == 0 && rank < need) emit(above + rank, edge_score(mine), edge_pos(mine));
+        } else {
+            constexpr int CPT = EDGES / NT;
+            uint32_t all_edges, to = team_prefix<Team>(n_edges, all_edges, sm, 1);
+#pragma unroll
+            for (int u = 0; u < PRE; ++u)
+                if (u * NT < n_slots && ((edges >> u) & 1u)) edge(to++, pre[u]);
+            rest([&](int bin, uint64_t ent) {
+                if (bin == B) edge(to++, ent);
+            });
+            __syncthreads();
+            uint32_t act = 0;
+            float lo = INFINITY, hi = -INFINITY;
+#pragma unroll 1
+            for (int j = 0; j < CPT; ++j) {
+                if (j * NT + tid < n_edge) {
+                    const float s = edge_score(edge_lds[j * NT + tid]);
+                    act |= 1u << j;
+                    lo = fminf(lo, s); hi = fmaxf(hi, s);
+                }
+            }
+            select_clear<Team>(sm);
+            team_range<Team>(lo, hi, sm, 0);
+            team_select<Team, CPT, 1>([&](int j) { return edge_score(edge_lds[j * NT + tid]); }, act, n_edge, P, (int)need, lo, hi, sm,
+                                      [&](int j) { return (int32_t)edge_pos(edge_lds[j * NT + tid]); },
+                                      [&](uint32_t o, float s, int32_t p) { emit(above + o, s, (uint32_t)p); });
+        }
         if (writer) pad_outputs(k_eff, k, idx, vals);
-    } else if (k_eff == 0) {                              // nothing to search for this sequence
-        if (helper) return;
+    } else if (k_eff == 0) {
         if (writer) pad_outputs(0, k, idx, vals);
-    } else if (SRC == SRC_LIST) {                         // radix select over the list or the full score row
+    } else {                                              // radix select over the list or the full score row
         __shared__ SelShared sel_sm;
         if (how == SCORE_ROW) {
             top = key_score(wg_select_dense<NT, 0>(sh, bf, bh, P, k_eff, k, idx, vals, sel_sm));      // writes idx, vals and their padding
         } else {
-            const SrcSegments<NT> src{list, reinterpret_cast<const uint2*>(sm.keys), n_slots, 31 - __clz(sh.n_seg)};
+            const SrcSegments<NT> src{list, segs, n_slots, log2_n_seg};
             const Items<0, SrcSegments<NT>> items(src);
             top = key_score(wg_topk_emit(items, k_eff, k, idx, vals, sel_sm));
         }
@@ -582,92 +728,95 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
         __syncthreads();
         for (int o = tid; o < k_eff; o += NT) rows_lds[o] = weight(vals[o]) | (uint64_t)(uint32_t)idx[o];
     }
-    if (SRC == SRC_LIST && tid == 0 && writer) {          // the head's record, as the chip-wide selection leaves it
+    if (tid == 0 && writer) {                             // the head's record (of a short list: all winners found, the size of bin B)
         uint32_t* const rec = bf.tailrec + 4 * bh;
-        const bool sel = how != SCORE_ROW && k_eff > 0;
-        if (how != LIST_SHORT) left = Boundary{in_b, (uint32_t)k_eff - above};
+        const bool sel = how != SCORE_ROW && k_eff > 0, found = how == LIST && total <= (uint32_t)kAttendList;
         rec[0] = k_eff == 0 ? 2u : sel ? 0u : 1u;
-        rec[1] = sel ? (uint32_t)k_eff - left.need : 0u;
-        rec[2] = sel ? left.need : 0u;
-        rec[3] = sel ? left.in : 0u;
+        rec[1] = sel ? (found ? (uint32_t)k_eff : above) : 0u;
+        rec[2] = sel && !found ? (uint32_t)k_eff - above : 0u;
+        rec[3] = sel ? in_b : 0u;
     }
     for (int i = tid; i < W; i += NT)
-        rows_lds[k_eff + i] = weight(SRC == SRC_ROW ? row[P + i] : __uint_as_float((uint32_t)(rows_lds[k_eff + i] >> 32))) | (uint64_t)(uint32_t)(P + i);
+        rows_lds[k_eff + i] = weight(__uint_as_float((uint32_t)(rows_lds[k_eff + i] >> 32))) | (uint64_t)(uint32_t)(P + i);
     __syncthreads();
 
     // ---- the weighted value rows (of this workgroup's shares, one after the other)
     const char* const Vh = static_cast<const char*>(bf.V) + head_off;
-    const int step = NW * rpw;
-    const int shares = SRC == SRC_LIST && !alone ? sh.attend : 1;
-    const int share_wgs = shares > 1 ? sh.share_wgs : 1;
     float* const pa = bf.part_acc + bh * sh.n_chunk_cap * (int64_t)D;
     float* const pl = bf.part_l + bh * sh.n_chunk_cap;
     float a = 0.f, l = 0.f;                               // thread t < D: channel t (D <= NT)
-    for (int share = share_wgs > 1 ? wg : 0; share < shares; share += share_wgs) {       // (uniform)
-        float acc[EPL];
-#pragma unroll
-        for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-        float lsum = 0.f;
-        const int row_end = (int)((uint32_t)(n_rows * (share + 1)) / (uint32_t)shares);      // (at most ROWS x 8)
-        for (int j = (int)((uint32_t)(n_rows * share) / (uint32_t)shares) + wave * rpw + rs; j < row_end; j += U * step) {
-            float w[U];
-            u32x4 raw[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int jj = j + u * step < row_end ? j + u * step : j;
-                const uint64_t e = rows_lds[jj];
-                w[u] = j + u * step < row_end ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
-                const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
-                raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * Elem<DT>::kBytes);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                float vf[EPL];
-                Elem<DT>::widen(raw[u], vf);
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w[u], vf[e], acc[e]);
-                lsum += w[u];
-            }
-        }
-        for (int o = lpr; o < 16; o <<= 1) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] += wave_xor(acc[e], o);
-            lsum += wave_xor(lsum, o);
-        }
-        if (lpr <= 16) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_16(acc[e]);
-            lsum = add_lanes_16(lsum);
-        }
-        if (lpr <= 32) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] = add_lanes_32(acc[e]);
-            lsum = add_lanes_32(lsum);
-        }
-        if (rs == 0) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc_lds[wave][c * EPL + e] = acc[e];
-            if (c == 0) acc_lds[wave][256] = lsum;
-        }
-        __syncthreads();
-        float as = 0.f, ls = 0.f;
-        if (tid < D) {
-#pragma unroll
-            for (int w = 0; w < NW; ++w) { as += acc_lds[w][tid]; ls += acc_lds[w][256]; }
-        }
-        // Leave the share where the head's other workgroups see it (agent-scope stores go through to memory, and the wait
-        // below is for their arrival there), count it, and let the last workgroup add up all shares in their order.
-        // No release or acquire fence: those write back and invalidate the whole L2 of the XCD, and nothing
-        // but these values passes between the workgroups.  (A workgroup that takes all shares adds them up as it goes.)
-        if (SRC == SRC_LIST && share_wgs > 1) {
+    // Leave a share where the head's other workgroups see it (agent-scope stores go through to memory, and the wait
+    // below is for their arrival there), count it, and let the last workgroup add up all shares in their order.
+    // No release or acquire fence: those write back and invalidate the whole L2 of the XCD, and nothing
+    // but these values passes between the workgroups.  (A workgroup that takes all shares adds them up as it goes.)
+    auto leave = [&](int share, float as, float ls) {
+        if (share_wgs > 1) {
             if (tid < D) __hip_atomic_store(pa + share * D + tid, as, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (tid == 0) __hip_atomic_store(pl + share, ls, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         } else {
             a += as; l += ls;
         }
-        if (SRC == SRC_LIST && share + share_wgs < shares) __syncthreads();        // (acc_lds is written again)
+    };
+    constexpr int STEP = NW * RPW, SU = 2;
+    if (share1 - share0 > 1 && NT == 1024 && n_rows <= SU * STEP * shares) {       // (uniform)
+        // several short shares: the rows of all of them are asked for before the first is added up (one after the other, each
+        // share was a trip to memory: 8 shares of 96 rows on each of 256 heads 38 us for the kernel, 29 like this)
+        const int rs = lane / LPR, c = lane % LPR;
+        u32x4 raw[kAttendShares][SU];
+        float w[kAttendShares][SU];
+#pragma unroll
+        for (int s = 0; s < kAttendShares; ++s) {
+            const int first = share_row(share0 + s), end = share0 + s < share1 ? share_row(share0 + s + 1) : first;
+#pragma unroll
+            for (int u = 0; u < SU; ++u) {
+                const int j = first + u * STEP + wave * RPW + rs;
+                const uint64_t e = rows_lds[j < end ? j : 0];
+                w[s][u] = j < end ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
+                const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N where j < end)
+                raw[s][u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * 2);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < kAttendShares; ++s) {
+            if (share0 + s < share1) {                    // (uniform)
+                // (two places in turn: a share is written while the one before it is read)
+                float (*const part)[256 + 1] = acc_lds + (s & 1) * NW;
+                float acc[EPL];
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
+                float lsum = 0.f;
+#pragma unroll
+                for (int u = 0; u < SU; ++u) {
+                    float vf[EPL];
+                    Elem<DT>::widen(raw[s][u], vf);
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w[s][u], vf[e], acc[e]);
+                    lsum += w[s][u];
+                }
+                lane_group_sums(LPR, acc, lsum);
+                if (rs == 0) {
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) part[wave][c * EPL + e] = acc[e];
+                    if (c == 0) part[wave][256] = lsum;
+                }
+                __syncthreads();
+                float as = 0.f, ls = 0.f;
+                if (tid < D) {
+#pragma unroll
+                    for (int v = 0; v < NW; ++v) { as += part[v][tid]; ls += part[v][256]; }
+                }
+                leave(share0 + s, as, ls);
+            }
+        }
+    } else {
+        for (int share = share0; share < share1; ++share) {   // (uniform)
+            float as, ls;
+            weighted_rows<DT, NT, 8>(Vh, D, N, rows_lds, share_row(share), share_row(share + 1), acc_lds, as, ls);
+            leave(share, as, ls);
+            if (share + 1 < share1) __syncthreads();      // (the partial sums are written again)
+        }
     }
-    if (SRC == SRC_LIST && share_wgs > 1) {
+    if (share_wgs > 1) {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
         if (tid == 0)
@@ -845,7 +994,7 @@ hipError_t launch_attend_row(const Shape& s, const Bufs& b, int64_t Nmax, hipStr
     const int64_t heads = (int64_t)s.Hq * s.layer_seqs;
     if ((int64_t)s.k + s.window > attend_row_rows(heads, Nmax)) return hipErrorInvalidValue;
 #define TKA_AR(DT_, NT_, CPT_, NB_)                                                                                         \
-    hipLaunchKernelGGL((attend_kernel<DT_, AttendCfg<NT_, CPT_, NT_ == 1024 ? 4096 : NT_ == 512 ? 2048 : 1024, NB_>, SRC_ROW>), \
+    hipLaunchKernelGGL((attend_kernel<DT_, AttendCfg<NT_, CPT_, NT_ == 1024 ? 4096 : NT_ == 512 ? 2048 : 1024, NB_>>), \
                        grid, dim3(NT_), 0, st, s, b, scale, scale_log2e)
 #define TKA_AR_SIZE(DT_)                                     \
     do {                                                     \
@@ -869,9 +1018,14 @@ hipError_t launch_attend_list(const Shape& s, const Bufs& b, hipStream_t st) {
     const float scale = 1.0f / sqrtf((float)s.D);
     const float scale_log2e = scale * 1.4426950408889634f;
     // as many helpers as fit the compute units beside the shares, a wave of theirs per segment at most
-    const int64_t room = std::min<int64_t>(kAttendManyHeads / ((int64_t)s.Hq * s.B), s.n_seg / ListCfg::NW);
+    const int64_t heads = (int64_t)s.Hq * s.B, room = std::min<int64_t>(kAttendManyHeads / heads, s.n_seg / (1024 / kWave));
     const dim3 grid((unsigned)s.Hq, (unsigned)s.layer_seqs, (unsigned)std::max<int64_t>(s.share_wgs, room) << s.log2_layers);
-#define TKA_AL(DT_, D_) hipLaunchKernelGGL((attend_kernel<DT_, ListCfg, SRC_LIST, D_>), grid, dim3(ListCfg::NT), 0, st, s, b, scale, scale_log2e)
+    const bool two_per_cu = heads * s.share_wgs > kAttendManyHeads;
+#define TKA_AL(DT_, D_)                                                                                                                 \
+    do {                                                                                                                                \
+        if (two_per_cu) hipLaunchKernelGGL((attend_list_kernel<DT_, 512, D_>), grid, dim3(512), 0, st, s, b, scale, scale_log2e);       \
+        else hipLaunchKernelGGL((attend_list_kernel<DT_, 1024, D_>), grid, dim3(1024), 0, st, s, b, scale, scale_log2e);                \
+    } while (0)
     if (s.dtype == DT_F16 && s.D == 128) TKA_AL(DT_F16, 128);
     else if (s.dtype == DT_BF16 && s.D == 128) TKA_AL(DT_BF16, 128);
     else if (s.dtype == DT_F16 && s.D == 64) TKA_AL(DT_F16, 64);
