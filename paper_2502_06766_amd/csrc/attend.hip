@@ -41,7 +41,7 @@ template <class Team, int NB_>
 struct SelectShared {
     static constexpr int NB = NB_;
     uint64_t keys[Team::NT + 8];            // segments of the candidate list (length, first entry); later composite keys of the bin that is ranked
-    uint32_t hist[NB_];
+    __attribute__((aligned(8))) uint32_t hist[NB_];
     float red[2][2][Team::NW];
     uint32_t tot[2][Team::NW];
     uint32_t sel[3];
@@ -842,21 +842,26 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
 }
 
 // Batches of short sequences: scores, selection and attention of a KV head's query heads in one launch, a workgroup per key
-// stream.  The four waves score the stream's tiles with the scan's routines and leave the scores in LDS; then
-// each wave selects for one head of the group and fetches its rows, with no barrier between the waves.  The step is
-// bound by reading the keys; two or more workgroups per compute unit, each in a phase of its own, keep that going
-// while others select.  ROW: scores of the longest sequence.  192 sequences of 2048 .. 4096 tokens, k = 128 (1.2 GB of keys,
-// 0.2 GB of value rows): 310 us = 4.6 TB/s; scan with stored scores, radix select and gather before: 277 + 70 + 42 us.
+// stream.  The four waves score the stream's tiles with the scan's routines and leave the scores in LDS (and their range);
+// then each wave selects for one head of the group and fetches its rows, with no barrier between the waves.  Two or more workgroups
+// per compute unit, each in a phase of its own, keep the keys coming while others select, if selecting is not what takes
+// longest: a wave that branches over each of its 64 scores a lane waits for LDS every time (about 50 us for 4096 scores, against 33
+// for the keys), so winners and ties are counted and placed without a branch, the weights follow for 64 winners at a time,
+// and twice the rows are in flight.  ROW: scores of the longest sequence.  192 sequences of 2048 .. 4096 tokens, k = 128 (1.2 GB of
+// keys, 0.2 GB of value rows): scan with stored scores, radix select and gather 277 + 70 + 42 us, first version of this kernel
+// 310, now 293.  (One workgroup per compute unit whose waves score one stream while others select for the one before: 371.)
 constexpr int kShortBins = 256;
 template <int DT, int D, int ROW>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
 attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     using v8 = typename Mfma<DT>::v8;
-    constexpr int CPT = ROW / kWave, ROWS = attend_short_k(ROW), EPL = 8, LPR = D / EPL, RPW = kWave / LPR, U = 8;
+    constexpr int CPT = ROW / kWave, ROWS = attend_short_k(ROW), EPL = 8, LPR = D / EPL, RPW = kWave / LPR;
+    constexpr int NB = kShortBins, BPT = NB / kWave;
     using Mask = typename std::conditional<(CPT > 32), uint64_t, uint32_t>::type;
-    __shared__ float scores_lds[4][ROW];
-    __shared__ uint64_t rows_all_lds[4][ROWS];            // rows to fetch (weight bits, position)
-    __shared__ SelectShared<WaveTeam, kShortBins> sms[4];
+    __shared__ __align__(16) float scores_lds[4][ROW];
+    __shared__ uint64_t rows_all_lds[4][ROWS];            // winners (score bits, position), then rows to fetch (weight bits, position)
+    __shared__ SelectShared<WaveTeam, NB> sms[4];
+    __shared__ float range_lds[2][4][4];                  // smallest and largest score of each head, per wave
     const int kvh = blockIdx.x, b = (int)blockIdx.y + (int)blockIdx.z * sh.layer_seqs, G = sh.G;
     const int64_t head0 = (int64_t)b * sh.Hq + (int64_t)kvh * G;
     const int lane = lane_id();
@@ -867,13 +872,19 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
         v8 qa[D / 32];
         load_query_a<DT, D>(bf.q, head0, G, qa);
         struct TileB { v8 b[4][D / 32]; } ba, bb;
+        float lo4[4], hi4[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { lo4[r] = INFINITY; hi4[r] = -INFINITY; }
         auto use = [&](TileB& t, int64_t ti) {
             const f32x4 res = tile_mac<DT, D>(t.b, qa);
             const int item = (int)ti * 64 + lane;
             if (item < N) {
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    if (r < G) scores_lds[r][item] = res[r] + 0.0f;          // -0 counts as +0
+                for (int r = 0; r < 4; ++r) {
+                    const float s = res[r] + 0.0f;        // -0 counts as +0
+                    lo4[r] = fminf(lo4[r], s); hi4[r] = fmaxf(hi4[r], s);
+                    if (r < G) scores_lds[r][item] = s;
+                }
             }
         };
         const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
@@ -883,7 +894,14 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
             tile_load<DT, D>(Kh, [&](int slot) { const int64_t p = rest * 64 + slot; return p < N ? p : (int64_t)(N - 1); }, ba.b);
             use(ba, rest);
         }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float lo = wave_min(lo4[r]), hi = wave_max(hi4[r]);
+            if (lane == 0) { range_lds[0][r][wave] = lo; range_lds[1][r][wave] = hi; }
+        }
     }
+    SelectShared<WaveTeam, NB>& sm = sms[wave];
+    select_clear<WaveTeam>(sm);
     __syncthreads();
     if (wave >= G) return;                                // (no barrier of the workgroup follows)
 
@@ -893,32 +911,100 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     const int64_t sel0 = selection_at(sh, lk, blockIdx.y, kvh * G + wave);
     int32_t* const idx = bf.sel_idx + sel0;
     float* const vals = bf.sel_val + sel0;
-    SelectShared<WaveTeam, kShortBins>& sm = sms[wave];
     // (64 scores of a lane in registers spilled: they stay in LDS, eight reads in flight)
     const float* const row = scores_lds[wave] + lane;
-    Mask act = 0;
-    float lo = INFINITY, hi = -INFINITY;
+    const float* const lo4 = range_lds[0][wave];
+    const float* const hi4 = range_lds[1][wave];
+    const float lo = fminf(fminf(lo4[0], lo4[1]), fminf(lo4[2], lo4[3])), hi = fmaxf(fmaxf(hi4[0], hi4[1]), fmaxf(hi4[2], hi4[3]));
+    const float M = hi;                                   // the weights' reference score
+    uint64_t* const rows = rows_all_lds[wave];
+    // ---- the k_eff best: linear bins between the smallest and the largest score, as team_select()'s first step
+    const float inv = (float)NB / (hi - lo);
+    bool done = hi > lo && hi - lo < INFINITY && inv < INFINITY;         // (uniform)
+    if (done) {
+        auto place = [](int bin) { return (bin % BPT) * kWave + bin / BPT; };
+        const int n_full = N / kWave;                     // slots that every lane has
 #pragma unroll 8
-    for (int j = 0; j < CPT; ++j) {
-        if (j * kWave + lane < N) {
-            const float s = row[j * kWave];
-            act |= (Mask)1 << j;
-            lo = fminf(lo, s); hi = fmaxf(hi, s);
+        for (int j = 0; j < n_full; ++j) atomicAdd(&sm.hist[place(lin_bin<NB>(row[j * kWave], lo, inv))], 1u);
+        if (n_full * kWave + lane < N) atomicAdd(&sm.hist[place(lin_bin<NB>(row[n_full * kWave], lo, inv))], 1u);
+        wave_sync();
+        uint32_t n[BPT], local = 0, total;
+#pragma unroll
+        for (int u = 0; u < BPT; ++u) { n[u] = sm.hist[place(NB - 1 - (lane * BPT + u))]; local += n[u]; }
+        uint32_t run = team_prefix<WaveTeam>(local, total, sm, 1);
+#pragma unroll
+        for (int u = 0; u < BPT; ++u) {
+            if (run < (uint32_t)k_eff && (uint32_t)k_eff <= run + n[u]) {        // exactly one lane
+                sm.sel[0] = (uint32_t)(NB - 1 - (lane * BPT + u));
+                sm.sel[1] = run;
+                sm.sel[2] = n[u];
+            }
+            run += n[u];
+        }
+        wave_sync();
+        const int B = (int)sm.sel[0], n_in = (int)sm.sel[2];
+        const uint32_t above = sm.sel[1];
+        done = n_in <= kWave;                             // more are split again (team_select() below)
+        if (done) {
+            // per lane: certain winners, and scores of bin B (upper half); then their places
+            uint32_t cnt = 0;
+            auto count = [&](int j) {
+                const int bin = lin_bin<NB>(row[j * kWave], lo, inv);
+                return (bin > B ? 1u : 0u) + (bin == B ? 0x10000u : 0u);
+            };
+#pragma unroll 8
+            for (int j = 0; j < n_full; ++j) cnt += count(j);
+            if (n_full * kWave + lane < N) cnt += count(n_full);
+            uint32_t at = team_prefix<WaveTeam>(cnt, total, sm, 0);      // (at most 4096 winners: the halves do not meet)
+            uint64_t* const keys = sm.keys;
+            uint64_t* const nowhere = reinterpret_cast<uint64_t*>(sm.hist) + lane;       // (the counts are not needed any more)
+            static_assert(NB * sizeof(uint32_t) >= kWave * sizeof(uint64_t), "a place per lane");
+            auto put = [&](int j) {
+                const float s = row[j * kWave];
+                const int bin = lin_bin<NB>(s, lo, inv);
+                const uint32_t p = (uint32_t)(j * kWave + lane);
+                const bool win = bin > B, edge = bin == B;
+                uint64_t* to = win ? rows + (at & 0xFFFFu) : edge ? keys + (at >> 16) : nowhere;
+                // a score of bin B: its composite key (larger beats smaller, equal scores go to the lower position)
+                *to = win ? ((uint64_t)__float_as_uint(s) << 32) | (uint64_t)p : ((uint64_t)score_key(s) << 32) | (uint64_t)(0xFFFFFFFFu - p);
+                at += (win ? 1u : 0u) + (edge ? 0x10000u : 0u);
+            };
+#pragma unroll 8
+            for (int j = 0; j < n_full; ++j) put(j);
+            if (n_full * kWave + lane < N) put(n_full);
+            const int n8 = (n_in + 7) & ~7;
+            if (lane < n8 - n_in) keys[n_in + lane] = 0ull;              // beats nothing
+            wave_sync();
+            if (lane < n_in) {
+                const uint64_t mine[1] = {keys[lane]};
+                uint32_t rank[1];
+                rank_by_comparison<1>(keys, n8, mine, rank);
+                if (above + rank[0] < (uint32_t)k_eff)
+                    rows[above + rank[0]] = ((uint64_t)__float_as_uint(key_score((uint32_t)(mine[0] >> 32))) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)mine[0]);
+            }
+        } else {
+            select_clear<WaveTeam>(sm);
+            wave_sync();
         }
     }
-    select_clear<WaveTeam>(sm);
-    team_range<WaveTeam>(lo, hi, sm, 0);
-    const float M = hi;                                   // the weights' reference score
-    uint64_t* const rows_lds = rows_all_lds[wave];
-    team_select<WaveTeam, CPT, 8>([&](int j) { return row[j * kWave]; }, act, N, N, k_eff, lo, hi, sm,
-                                  [&](int j) { return j * kWave + lane; }, [&](uint32_t o, float s, int32_t p) {
-        if (o < (uint32_t)k_eff) {                        // always true; guards the buffers
-            idx[o] = p;
-            vals[o] = s;
-            rows_lds[o] = ((uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32) | (uint64_t)(uint32_t)p;
-        }
-    });
-    for (int o = k_eff + lane; o < k; o += kWave) { idx[o] = -1; vals[o] = -INFINITY; }
+    if (!done) {                                          // (uniform) equal or crowded scores, or a range beyond fp32
+        Mask act = 0;
+        for (int j = 0; j < CPT; ++j) act |= j * kWave + lane < N ? (Mask)1 << j : (Mask)0;
+        team_select<WaveTeam, CPT, 1>([&](int j) { return row[j * kWave]; }, act, N, N, k_eff, lo, hi, sm,
+                                      [&](int j) { return j * kWave + lane; }, [&](uint32_t o, float s, int32_t p) {
+            if (o < (uint32_t)k_eff)                      // always true; guards the buffer
+                rows[o] = ((uint64_t)__float_as_uint(s) << 32) | (uint64_t)(uint32_t)p;
+        });
+    }
+    wave_sync();
+    for (int o = lane; o < k; o += kWave) {
+        const bool in = o < k_eff;
+        const uint64_t e = in ? rows[o] : 0ull;
+        const float s = __uint_as_float((uint32_t)(e >> 32));
+        idx[o] = in ? (int32_t)(uint32_t)e : -1;
+        vals[o] = in ? s : -INFINITY;
+        if (in) rows[o] = ((uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32) | (uint64_t)(uint32_t)e;
+    }
     wave_sync();
 
     const char* const Vh = static_cast<const char*>(bf.V) + ((int64_t)b * sh.Hkv + kvh) * sh.Ncap * (D * 2);
@@ -926,25 +1012,32 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     float acc[EPL], l = 0.f;
 #pragma unroll
     for (int e = 0; e < EPL; ++e) acc[e] = 0.f;
-    for (int j = rs; j < k_eff; j += U * RPW) {
-        float w[U];
-        u32x4 raw[U];
+    // as many rows in flight per lane group as there are, sixteen at most
+    auto fetch = [&](auto u_tag) __attribute__((always_inline)) {
+        constexpr int U = decltype(u_tag)::value;
+        for (int j = rs; j < k_eff; j += U * RPW) {
+            float w[U];
+            u32x4 raw[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const uint64_t e = rows_lds[j + u * RPW < k_eff ? j + u * RPW : j];
-            w[u] = j + u * RPW < k_eff ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
-            const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
-            raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * 2);
+            for (int u = 0; u < U; ++u) {
+                const uint64_t e = rows[j + u * RPW < k_eff ? j + u * RPW : j];
+                w[u] = j + u * RPW < k_eff ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
+                const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
+                raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * 2);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                float vf[EPL];
+                Elem<DT>::widen(raw[u], vf);
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w[u], vf[e], acc[e]);
+                l += w[u];
+            }
         }
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float vf[EPL];
-            Elem<DT>::widen(raw[u], vf);
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) acc[e] = fmaf(w[u], vf[e], acc[e]);
-            l += w[u];
-        }
-    }
+    };
+    if (k_eff <= 4 * RPW) fetch(std::integral_constant<int, 4>{});
+    else if (k_eff <= 8 * RPW) fetch(std::integral_constant<int, 8>{});
+    else fetch(std::integral_constant<int, 16>{});
 #pragma unroll
     for (int o = LPR; o < kWave; o <<= 1) {
 #pragma unroll
