@@ -282,11 +282,12 @@ __device__ __forceinline__ void lane_group_sums(int lpr, float (&acc)[EPL], floa
     }
 }
 
-// The weighted value rows first, first + step, ... < end of the list in LDS (weight bits, position), summed over the workgroup:
-// thread t < D gets channel t, `l` the sum of the weights.
+// The softmax-weighted value rows first .. end - 1 of the list in LDS (score bits, position), summed over the workgroup: thread t < D
+// gets channel t, `l` the sum of the weights, which are relative to score M.  (The weights are worked out by the lanes that
+// fetch the rows: a few each, where emitting a winner with its weight made every slot of a thread a branch with an exp2f behind it.)
 template <int DT, int NT, int U>
-__device__ __forceinline__ void weighted_rows(const char* Vh, int D, int N, const uint64_t* rows, int first, int end, float (*acc_lds)[256 + 1],
-                                              float& a, float& l) {
+__device__ __forceinline__ void weighted_rows(const char* Vh, int D, int N, const uint64_t* rows, int first, int end, float M, float scale_log2e,
+                                              float (*acc_lds)[256 + 1], float& a, float& l) {
     constexpr int EPL = Elem<DT>::kPerLoad, NW = NT / kWave;
     const int tid = threadIdx.x, lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lpr = D / EPL, rpw = kWave / lpr;           // lanes per value row, rows per wave and load
@@ -302,7 +303,7 @@ __device__ __forceinline__ void weighted_rows(const char* Vh, int D, int N, cons
         for (int u = 0; u < U; ++u) {
             const int jj = j + u * step < end ? j + u * step : j;
             const uint64_t e = rows[jj];
-            w[u] = j + u * step < end ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
+            w[u] = j + u * step < end ? exp2f((__uint_as_float((uint32_t)(e >> 32)) - M) * scale_log2e) : 0.f;
             const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
             raw[u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * Elem<DT>::kBytes);
         }
@@ -336,7 +337,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
     constexpr int NT = Cfg::NT, NW = Cfg::NW, CPT = Cfg::CPT;
     using Team = WorkgroupTeam<NT>;
     __shared__ SelectShared<Team, Cfg::NB> sm;
-    __shared__ uint64_t rows_lds[Cfg::ROWS];              // value rows to fetch (weight bits, position)
+    __shared__ uint64_t rows_lds[Cfg::ROWS];              // value rows to fetch (score bits, position)
     __shared__ float acc_lds[NW][256 + 1];
     const int b = (int)blockIdx.y + (int)blockIdx.z * sh.layer_seqs, h = blockIdx.x;
     const int64_t bh = (int64_t)b * sh.Hq + h;
@@ -378,26 +379,26 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
         team_range<Team>(dummy, w_top, sm, 1);
     }
     const float M = fmaxf(k_eff > 0 ? hi : -INFINITY, w_top);    // the weights' reference score
-    auto weight = [&](float s) { return (uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32; };
 
     // ---- the k_eff best
     if (k_eff > 0)
         team_select<Team, CPT, CPT>([&](int j) { return v[j]; }, act, P, P, k_eff, lo, hi, sm, [&](int j) { return j * NT + tid; },
                                     [&](uint32_t o, float s, int32_t p) {           // winner o of the head
-            if (o < (uint32_t)k_eff) {                    // always true; guards the buffers
-                idx[o] = p;
-                vals[o] = s;
-                rows_lds[o] = weight(s) | (uint64_t)(uint32_t)p;
-            }
+            if (o < (uint32_t)k_eff)                      // always true; guards the buffer
+                rows_lds[o] = ((uint64_t)__float_as_uint(s) << 32) | (uint64_t)(uint32_t)p;
         });
-    pad_outputs(k_eff, k, idx, vals);
-    for (int i = tid; i < W; i += NT) rows_lds[k_eff + i] = weight(row[P + i]) | (uint64_t)(uint32_t)(P + i);
+    for (int i = tid; i < W; i += NT) rows_lds[k_eff + i] = ((uint64_t)__float_as_uint(row[P + i]) << 32) | (uint64_t)(uint32_t)(P + i);
     __syncthreads();
+    for (int o = tid; o < k; o += NT) {
+        const uint64_t e = o < k_eff ? rows_lds[o] : ((uint64_t)0xFF800000u << 32) | 0xFFFFFFFFu;       // (padding: -inf, -1)
+        idx[o] = (int32_t)(uint32_t)e;
+        vals[o] = __uint_as_float((uint32_t)(e >> 32));
+    }
 
     // ---- the weighted value rows (at most ROWS: the launcher's rule)
     const char* const Vh = static_cast<const char*>(bf.V) + ((int64_t)cache_seq(sh, b) * sh.Hkv + h / sh.G) * sh.Ncap * D * Elem<DT>::kBytes;
     float a, l;
-    weighted_rows<DT, NT, 8>(Vh, D, N, rows_lds, 0, k_eff + W, acc_lds, a, l);
+    weighted_rows<DT, NT, 8>(Vh, D, N, rows_lds, 0, k_eff + W, M, scale_log2e, acc_lds, a, l);
     if (tid < D) {
         bf.out[bh * D + tid] = a / l;
         if (tid == 0 && bf.lse) bf.lse[bh] = M * scale + logf(l);
@@ -426,7 +427,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
     constexpr int SPT = kMaxSeg / NT;                     // segments per thread
     using Team = WorkgroupTeam<NT>;
     __shared__ SelectShared<Team, 1024> sm;
-    __shared__ uint64_t rows_lds[kAttendRows];            // value rows to fetch (weight bits, position)
+    __shared__ uint64_t rows_lds[kAttendRows];            // value rows to fetch (score bits, position)
     __shared__ uint64_t edge_lds[EDGES];                  // composite keys of the entries of the k-th score's bin; later partial sums
     __shared__ uint32_t segs[kMaxSeg];                    // lengths of the segments
     __shared__ uint32_t bins_lds[NW][kTailBins];
@@ -591,7 +592,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
                 a = group_reduce<AddOp, LPR>(a);
                 if (i < W) {
                     w_top = fmaxf(w_top, a);
-                    if (c == 0) rows_lds[k_eff + i] = (uint64_t)__float_as_uint(a) << 32;
+                    if (c == 0) rows_lds[k_eff + i] = ((uint64_t)__float_as_uint(a) << 32) | (uint64_t)(uint32_t)(P + i);
                 }
             }
         }
@@ -605,12 +606,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
     const int share0 = share_wgs > 1 ? wg * shares / share_wgs : 0, share1 = share_wgs > 1 ? (wg + 1) * shares / share_wgs : shares;
     auto share_row = [&](int share) { return (int)((uint32_t)(n_rows * share) / (uint32_t)shares); };
     const uint32_t row0 = (uint32_t)share_row(share0), row1 = (uint32_t)share_row(share1);
-    auto weight = [&](float s) { return (uint64_t)__float_as_uint(exp2f((s - M) * scale_log2e)) << 32; };
     auto emit = [&](uint32_t o, float s, uint32_t p) {    // winner o of the head
         if (o - row0 < row1 - row0 && o < (uint32_t)k_eff) {         // (o < k_eff always; guards the buffers)
-            idx[o] = (int32_t)p;
-            vals[o] = s;
-            rows_lds[o] = weight(s) | (uint64_t)p;
+            rows_lds[o] = ((uint64_t)__float_as_uint(s) << 32) | (uint64_t)p;
         }
     };
     auto score_of = [](uint64_t e) { return __uint_as_float((uint32_t)(e >> 32)); };
@@ -726,7 +724,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
         }
         M = fmaxf(top, w_top);
         __syncthreads();
-        for (int o = tid; o < k_eff; o += NT) rows_lds[o] = weight(vals[o]) | (uint64_t)(uint32_t)idx[o];
+        for (int o = tid; o < k_eff; o += NT) rows_lds[o] = ((uint64_t)__float_as_uint(vals[o]) << 32) | (uint64_t)(uint32_t)idx[o];
     }
     if (tid == 0 && writer) {                             // the head's record (of a short list: all winners found, the size of bin B)
         uint32_t* const rec = bf.tailrec + 4 * bh;
@@ -736,9 +734,14 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
         rec[2] = sel && !found ? (uint32_t)k_eff - above : 0u;
         rec[3] = sel ? in_b : 0u;
     }
-    for (int i = tid; i < W; i += NT)
-        rows_lds[k_eff + i] = weight(__uint_as_float((uint32_t)(rows_lds[k_eff + i] >> 32))) | (uint64_t)(uint32_t)(P + i);
     __syncthreads();
+    if (k_eff > 0 && (how == LIST || how == RESCORE)) {   // (the radix select has written its winners)
+        const uint32_t sel_end = row1 < (uint32_t)k_eff ? row1 : (uint32_t)k_eff;
+        for (uint32_t o = row0 + (uint32_t)tid; o < sel_end; o += NT) {
+            idx[o] = (int32_t)(uint32_t)rows_lds[o];
+            vals[o] = score_of(rows_lds[o]);
+        }
+    }
 
     // ---- the weighted value rows (of this workgroup's shares, one after the other)
     const char* const Vh = static_cast<const char*>(bf.V) + head_off;
@@ -771,7 +774,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
             for (int u = 0; u < SU; ++u) {
                 const int j = first + u * STEP + wave * RPW + rs;
                 const uint64_t e = rows_lds[j < end ? j : 0];
-                w[s][u] = j < end ? __uint_as_float((uint32_t)(e >> 32)) : 0.f;
+                w[s][u] = j < end ? exp2f((score_of(e) - M) * scale_log2e) : 0.f;
                 const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N where j < end)
                 raw[s][u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * 2);
             }
@@ -811,7 +814,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
     } else {
         for (int share = share0; share < share1; ++share) {   // (uniform)
             float as, ls;
-            weighted_rows<DT, NT, 8>(Vh, D, N, rows_lds, share_row(share), share_row(share + 1), acc_lds, as, ls);
+            weighted_rows<DT, NT, 8>(Vh, D, N, rows_lds, share_row(share), share_row(share + 1), M, scale_log2e, acc_lds, as, ls);
             leave(share, as, ls);
             if (share + 1 < share1) __syncthreads();      // (the partial sums are written again)
         }
