@@ -230,7 +230,8 @@ __host__ __device__ inline bool plan_is_fast(const Plan& p, int64_t N, int cand_
 
 // Selection and attention of a head in one launch (attend.hip).
 constexpr int64_t kAttendRowMax = 16384;  // scores of the longest row (16 per thread; more per thread was not tried)
-constexpr int kAttendList = 10240;        // candidates of the longest list
+constexpr int kAttendList = 10240;        // expected candidates beyond which the chip-wide tail is no slower (24576 in its place: 0.97 - 1.03 of the
+                                          // time over shapes between the two); also the entries of the k-th score's bin in LDS at 1024 threads
 constexpr int kAttendRows = 4096;         // value rows (selected and window) whose positions and weights fit LDS beside a list
 constexpr int kAttendShares = 8;          // workgroups per head at most
 constexpr int64_t kAttendShareKeys = 131072;   // keys a workgroup may have to score again when a list is unusable (1.5 ms for one head alone)
