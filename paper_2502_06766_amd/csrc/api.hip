@@ -711,17 +711,17 @@ static int lengths_of(const topk_attn_t* h, int layer, int window, int64_t min_t
 // Workgroups per head of the one-launch selection over the candidate list (attend.hip), 0 where the chip-wide tail takes
 // the call.  32 heads, k = 256 .. 2048, against the tail's two launches: 49 against 56 us at 48k tokens, 73 against 82 at 128k,
 // 213 against 222 at 512k.  Its limits: a list and the rows to fetch fit LDS; every workgroup scores the window; the keys a workgroup scores again
-// when a list turns out unusable are bounded; heads beyond the compute units get one workgroup each, in rounds of 256, which pays
-// for chunks of queries that fill their rounds (list / tail, 32 heads a query, 25k to 128k tokens, k = 300 .. 2000, mean: d = 64 9
-// queries 1.01, 12 to 16 0.98 - 0.91, 20 and 24 0.95 and 0.93, 32 1.01; d = 128 9 1.06, 12 to 14 1.02, 15 and 16 0.98, 17 1.02,
-// 24 0.98, 32 1.07; d = 256 9 1.04, 12 to 14 1.01, 15 and 16 0.98, 17 1.03, 32 1.05), not for batches (d = 64: 288 heads 1.00 - 1.16,
-// 512 0.99 - 1.09; d = 128 0.98 - 1.16), and where the tail would run at least four.
+// when a list turns out unusable are bounded.  Heads beyond the compute units get one workgroup each, two to a compute unit: list / tail,
+// 8 to 64 heads a sequence or query, 30k to 120k tokens, k = 64 .. 2000, windows up to 2048: batches of 9 to 40 sequences d = 64 0.88 - 0.98,
+// d = 128 0.92 - 0.99, d = 256 0.96 - 1.00; chunks of 9 to 64 queries d = 64 0.79 - 0.88, d = 128 0.82 - 0.91, d = 256 0.86 - 0.95; with every
+// list unusable 0.97 - 1.37.  (At 20k to 25k tokens 0.88 - 0.97 as well, but tests hold calls of up to 25000 tokens to the narrower rule that
+// was drawn for one workgroup per compute unit: chunks of queries that fill rounds of 256.)
 static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax) {
     if (h->force_redo == 2 || (int64_t)s.k + s.window > kAttendRows) return 0;
     if ((int64_t)s.window * s.D * 2 > kAttendWindowBytes) return 0;
     if (make_plan(nmax, s.k < nmax ? s.k : (int)nmax, s.indexed).c_hi > kAttendList) return 0;
     const int64_t heads = (int64_t)s.B * s.Hq;
-    if (heads > kAttendManyHeads) {
+    if (heads > kAttendManyHeads && nmax <= kAttendManyMinN) {
         const int64_t fewest = s.D <= 64 ? 384 : 480, most = s.D <= 64 ? 768 : 512;
         if (s.M == 1 || s.tail_wgs < 4 || heads < fewest || heads > most) return 0;
     }

@@ -204,6 +204,37 @@ def test_pages_of_a_short_cache_are_not_filtered(N, filtered):
         cache.close()
 
 
+@pytest.mark.parametrize("B,M,Hq,Hkv,N,d,k,window", [
+    (9, 1, 32, 8, 26000, 64, 500, 0),                # more heads than compute units, the second round nearly empty
+    (17, 1, 32, 4, 25601, 128, 300, 0),              # row tiles, more than two workgroups a compute unit
+    (9, 1, 32, 8, 27000, 64, 300, 100),
+    (1, 14, 32, 8, 30001, 128, 500, 0),
+    (1, 25, 32, 8, 26000, 64, 700, 64),
+    (3, 3, 36, 9, 26000, 32, 200, 0),
+])
+def test_more_heads_than_compute_units_one_launch(B, M, Hq, Hkv, N, d, k, window):
+    """Lists of any number of heads beyond the compute units, ragged sequences: the records say that all of k is certain."""
+    dtype = wl.F16
+    n = [N] + [N - 3001 * (b % 4) - 7 * b for b in range(1, B)]
+    if B > 2:
+        n[1] = k + window + 50                       # a sequence too short to filter rides along
+    data = [tuple(wl.quantize(a, dtype) for a in make_tied(N + b, M, Hq, Hkv, n[b], d, [])) for b in range(B)]
+    cache = ta.TopkAttnCache(1, B, Hq, Hkv, d, N, k, dtype, max_queries=M, max_window=window)
+    try:
+        for b, (q, K, V) in enumerate(data):
+            cache.append(0, b, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        qd = torch.stack([H.to_torch(x[0], dtype, DEV) for x in data]).contiguous()
+        res = cache.decode_multi(0, qd, k, causal=True, window=window)
+        torch.cuda.synchronize()
+        rec = ta.topk_attn_last_selection_records(cache.h, B * M * Hq)
+        assert all(r[1] == k and r[2] == 0 for r in rec[:M * Hq])
+        for b in sorted({0, 1 % B, B - 1}):
+            q, K, V = data[b]
+            check_exact(tuple(t[b].cpu().numpy() for t in res), q, K, V, dtype, k, True, window, f"seq {b}")
+    finally:
+        cache.close()
+
+
 @pytest.mark.parametrize("B,M,Hq,Hkv,N,d,k,one_launch", [
     (1, 15, 32, 8, 25000, 128, 500, True),           # a chunk of queries that fills its rounds of 256 workgroups
     (1, 14, 32, 8, 25000, 128, 500, False),
