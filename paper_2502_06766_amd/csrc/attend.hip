@@ -770,13 +770,20 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
 #pragma unroll
         for (int s = 0; s < kAttendShares; ++s) {
             const int first = share_row(share0 + s), end = share0 + s < share1 ? share_row(share0 + s + 1) : first;
+            if (first < end) {                            // (uniform)
 #pragma unroll
-            for (int u = 0; u < SU; ++u) {
-                const int j = first + u * STEP + wave * RPW + rs;
-                const uint64_t e = rows_lds[j < end ? j : 0];
-                w[s][u] = j < end ? exp2f((score_of(e) - M) * scale_log2e) : 0.f;
-                const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N where j < end)
-                raw[s][u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * 2);
+                for (int u = 0; u < SU; ++u) {
+                    const int j = first + u * STEP + wave * RPW + rs;
+                    // (a lane past the end takes the share's first row with weight 0: a selected row, so a value that is not finite
+                    // counts only where it would count anyway)
+                    const uint64_t e = rows_lds[j < end ? j : first];
+                    w[s][u] = j < end ? exp2f((score_of(e) - M) * scale_log2e) : 0.f;
+                    const uint32_t p = (uint32_t)e < (uint32_t)N ? (uint32_t)e : (uint32_t)(N - 1);     // (always below N)
+                    raw[s][u] = *reinterpret_cast<const u32x4*>(Vh + ((int64_t)p * D + c * EPL) * 2);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < SU; ++u) { w[s][u] = 0.f; raw[s][u] = u32x4{0u, 0u, 0u, 0u}; }
             }
         }
 #pragma unroll

@@ -73,6 +73,38 @@ def test_layers_in_one_call_equal_a_call_per_layer(name):
         cache.close()
 
 
+@pytest.mark.parametrize("L,Hq,Hkv,d,ks", [
+    (4, 32, 8, 128, (700, 701, 300, 1000)),          # workgroups that take two shares of eight, so some do not hold the first row
+    (2, 32, 8, 64, (256, 900)),
+    (8, 32, 8, 256, (3, 200)),                       # one workgroup a head; shares without a row
+])
+@pytest.mark.parametrize("bad", [float("inf"), float("nan")])
+def test_value_rows_that_were_not_selected_are_not_read(L, Hq, Hkv, d, ks, bad):
+    """Every value row that no head of its KV head selected is Inf or NaN: outputs stay finite and equal a call per layer."""
+    N, ks = 30001, [ks[l % len(ks)] for l in range(L)]
+    cache = ta.TopkAttnCache(L, 1, Hq, Hkv, d, N, max(ks), wl.F16)
+    try:
+        g = torch.Generator(device=DEV)
+        g.manual_seed(3)
+        K, V = (torch.randn((L, Hkv, N, d), generator=g, device=DEV).half() for _ in range(2))
+        q = torch.randn((L, 1, Hq, d), generator=g, device=DEV).half()
+        for l in range(L):
+            cache.append(l, 0, K[l], V[l], head_major=True)
+            sel = cache.decode(l, q[l], ks[l])[1].view(Hkv, -1).long()
+            keep = torch.zeros((Hkv, N), dtype=torch.bool, device=DEV).scatter_(1, sel, True)
+            cache.reset(l, 0)
+            cache.append(l, 0, K[l], torch.where(keep[..., None], V[l], torch.full_like(V[l], bad)), head_major=True)
+        single = torch.stack([cache.decode(l, q[l], ks[l])[0] for l in range(L)])
+        assert torch.isfinite(single).all()
+        for _ in range(3):
+            out = torch.empty((L, 1, Hq, d), device=DEV)
+            ta.topk_attn_decode_layers(cache.h, 0, ks, q.data_ptr(), 0, out.data_ptr(), stream=torch.cuda.current_stream().cuda_stream)
+            torch.cuda.synchronize()
+            assert torch.equal(out, single)
+    finally:
+        cache.close()
+
+
 def test_layers_in_one_call_under_graph_capture():
     """Replays with changing queries, with eager work in between, equal the eager results."""
     L, Hq, Hkv, d, N, ks = 4, 8, 2, 64, 30000, [200, 220, 240, 260]
