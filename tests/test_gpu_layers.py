@@ -15,6 +15,8 @@ CASES = {
     "lists_8x48k_all_shares_in_one_workgroup": (8, 1, 32, 8, 128, wl.F16, (48001,), (512, 600, 700, 1000), 0, 0, 0),
     "lists_7_layers_two_shares_a_workgroup": (7, 1, 16, 4, 64, wl.BF16, (33000, 32999), (300, 411), 0, 0, 0),
     "lists_ragged_window": (4, 2, 8, 2, 128, wl.F16, (70000, 20001, 60000), (64, 700), 256, 0, 0),
+    "lists_more_rows_than_are_asked_for_at_once": (8, 1, 32, 8, 128, wl.F16, (33001,), (2000, 1025, 1024, 2047), 0, 0, 0),
+    "lists_more_rows_than_shares": (8, 1, 32, 8, 64, wl.BF16, (33001,), (3, 5, 9, 1), 0, 0, 0),
     "lists_row_tiles": (2, 1, 16, 2, 128, wl.BF16, (40003,), (500, 333), 100, 0, 0),
     "lists_redo": (4, 1, 8, 2, 64, wl.F16, (40000,), (256,), 0, 1, 0),
     "lists_tied": (4, 1, 8, 2, 64, wl.F16, (40000,), (256, 300), 0, 0, 40),
