@@ -116,6 +116,15 @@ size_t topk_attn_kv_bytes(const topk_attn_config* cfg);
  * per-sequence lengths).  0 on invalid config. */
 size_t topk_attn_workspace_bytes(const topk_attn_config* cfg);
 
+/* The same with room for topk_attn_decode_layers to let up to n_layers layers share their launches (rounded
+ * down to a power of two; at most 16, and no more than the configuration has), each with per-call buffers of its
+ * own: n_layers times as much, but for the lengths.  n_layers = 0: as many layers as share their launches in steps of
+ * max_k over caches of max_tokens tokens, within 1 GiB -- 1 for configurations whose steps never do (through an index, max_k +
+ * max_window above 4096, caches of hundreds of thousands of tokens).  Optional: a workspace of topk_attn_workspace_bytes gives the
+ * same results, layer by layer; topk_attn_create takes what the size it is given has room for.  0 on invalid config or
+ * n_layers < 0. */
+size_t topk_attn_layers_workspace_bytes(const topk_attn_config* cfg, int n_layers);
+
 /* Build a handle over caller-owned storage (Algorithm 1's build_index for the exact
  * "list" index: the head-major key array itself is the index).  Zeroes the lengths
  * (synchronously).  The storage must stay valid until topk_attn_destroy. */
@@ -168,8 +177,8 @@ int topk_attn_decode(topk_attn_t* h, int layer, const void* q, int k, float* out
  * library: a device array of TOPK_ATTN_STATIC_SCRATCH_BYTES that every GPU the library runs on
  * holds until the process ends.  Only the cache lengths are still read from the handle's
  * workspace.  The call allocates and frees nothing and enqueues kernels only.
- * Limit: ESCRATCH (nothing enqueued) if topk_attn_workspace_bytes of the same configuration with
- * n_layers = 1 minus the lengths' share (n_seqs * 4, rounded up to 256) exceeds TOPK_ATTN_STATIC_SCRATCH_BYTES -- one
+ * Limit: ESCRATCH (nothing enqueued) if topk_attn_workspace_bytes(cfg) minus the lengths' share
+ * (n_layers * n_seqs * 4, rounded up to 256) exceeds TOPK_ATTN_STATIC_SCRATCH_BYTES -- one
  * Llama-8B-shaped layer of 128k tokens at k = 2048 fits, a million-token layer does not.
  * All calls on one GPU, from whatever handle, share the one array: the call clears the words
  * that must start at zero itself, and two such calls that overlap in time on one GPU race. */
@@ -219,7 +228,8 @@ int topk_attn_k_schedule(int64_t total_k, int n_layers, double last_over_first, 
 /* Decode steps of n_layers consecutive layers [layer0, layer0 + n_layers) with a per-layer k
  * (e.g. from topk_attn_k_schedule), enqueued on `hip_stream`: the same work and the same results as
  * n_layers calls of topk_attn_decode_window, one per layer, each with its own query block (layers
- * that take the same path share their launches; the workspace holds the buffers of several).
+ * that take the same path share their launches where the workspace has room for the buffers of several:
+ * topk_attn_layers_workspace_bytes).
  * (In a transformer layer l+1's query depends on layer l's output; this entry point serves
  * callers that have all queries at hand, such as replaying recorded queries or measuring
  * a whole-model decode step.)

@@ -151,16 +151,29 @@ WsLayout ws_layout(const topk_attn_config* c, int batch_layers) {
     return w;
 }
 
-// Layers that share their launches: as many as kBatchScratchBytes of per-call buffers hold (8 KV heads, 32 query heads, 48k
-// tokens: 65 MB a layer).
-constexpr size_t kBatchScratchBytes = (size_t)1 << 30;
-int batch_layers_of(const topk_attn_config* c) {
-    const size_t one = ws_layout(c, 1).total;
-    int n = std::min(c->n_layers, kBatchLayers);
-    while (n > 1 && (ws_layout(c, n).total > std::max(one, kBatchScratchBytes) || (int64_t)c->n_seqs * n > 65535)) --n;
+// Layers that may share their launches (a power of two): of the layers asked for, those the configuration has and a grid takes.
+int batch_layers_at_most(const topk_attn_config* c, int layers) {
+    int n = 1;
+    while (2 * n <= std::min(std::min(layers, c->n_layers), kBatchLayers) && (int64_t)c->n_seqs * 2 * n <= 65535) n *= 2;
     return n;
 }
-WsLayout ws_layout(const topk_attn_config* c) { return ws_layout(c, batch_layers_of(c)); }
+// The most layers for which the room is of use: whose steps over max_tokens tokens with max_k join (joins(); steps through an
+// index, of more than kAttendRows value rows or of lists that the chip-wide selection takes never do), within
+// kBatchScratchBytes (8 KV heads, 32 query heads, 48k tokens: 65 MB a layer).
+constexpr size_t kBatchScratchBytes = (size_t)1 << 30;
+int batch_layers_useful(const topk_attn_config* c) {
+    int n = batch_layers_at_most(c, kBatchLayers);
+    const int64_t heads = (int64_t)c->n_seqs * c->n_q_heads, k = std::min<int64_t>(c->max_k, c->max_tokens);
+    const int64_t window = std::min<int64_t>(c->max_window, c->max_tokens);
+    if (k + window > kAttendRows) return 1;
+    if (c->max_tokens > kAttendRowMax) {             // (shorter caches: over score rows)
+        if (c->dtype == TOPK_ATTN_F32 || c->index_kind != TOPK_ATTN_INDEX_NONE) return 1;
+        if (window * c->head_dim * 2 > kAttendWindowBytes || make_plan(c->max_tokens, (int)k).c_hi > kAttendList) return 1;
+        while (n > 1 && (heads * n > kAttendManyHeads || c->max_tokens > kAttendShareKeys * (kAttendManyHeads / (heads * n)))) n /= 2;
+    }
+    while (n > 1 && ws_layout(c, n).total > kBatchScratchBytes) n /= 2;
+    return n;
+}
 
 __global__ void append_kernel(const char* __restrict__ ksrc, const char* __restrict__ vsrc, char* __restrict__ kdst,
                               char* __restrict__ vdst, int64_t n_new, int Hkv, int chunks_per_row,
@@ -368,7 +381,13 @@ size_t topk_attn_kv_bytes(const topk_attn_config* cfg) {
 size_t topk_attn_workspace_bytes(const topk_attn_config* cfg) {
     int why;
     if (!config_ok(cfg, &why)) return 0;
-    return ws_layout(cfg).total;
+    return ws_layout(cfg, 1).total;
+}
+
+size_t topk_attn_layers_workspace_bytes(const topk_attn_config* cfg, int n_layers) {
+    int why;
+    if (n_layers < 0 || !config_ok(cfg, &why)) return 0;
+    return ws_layout(cfg, n_layers == 0 ? batch_layers_useful(cfg) : batch_layers_at_most(cfg, n_layers)).total;
 }
 
 int topk_attn_create(const topk_attn_config* cfg, topk_attn_t** out) {
@@ -378,13 +397,19 @@ int topk_attn_create(const topk_attn_config* cfg, topk_attn_t** out) {
     if (!config_ok(cfg, &why)) return why;
     if (!cfg->kv_storage || !cfg->workspace) return TOPK_ATTN_EINVAL;
     if (((uintptr_t)cfg->kv_storage | (uintptr_t)cfg->workspace) & (kAlign - 1)) return TOPK_ATTN_EINVAL;
-    WsLayout w = ws_layout(cfg);
-    if (cfg->kv_bytes < kv_total_bytes(cfg) || cfg->workspace_bytes < w.total) return TOPK_ATTN_ENOMEM;
+    const WsLayout one = ws_layout(cfg, 1);
+    if (cfg->kv_bytes < kv_total_bytes(cfg) || cfg->workspace_bytes < one.total) return TOPK_ATTN_ENOMEM;
+    WsLayout w = one;                        // as many layers share their launches as the workspace has room for
+    for (int n = batch_layers_at_most(cfg, kBatchLayers); n > 1; n /= 2) {
+        w = ws_layout(cfg, n);
+        if (w.total <= cfg->workspace_bytes) break;
+        w = one;
+    }
     topk_attn* h = new (std::nothrow) topk_attn;
     if (!h) return TOPK_ATTN_ENOMEM;
     h->cfg = *cfg;
     h->ws = w;
-    h->ws_one = ws_layout(cfg, 1);
+    h->ws_one = one;
     h->kv_half = kv_half_bytes(cfg);
     h->len.assign((size_t)cfg->n_layers * cfg->n_seqs, 0);
     h->path = TOPK_ATTN_PATH_AUTO;

@@ -20,7 +20,7 @@ PATH_AUTO, PATH_FULL, PATH_FILTER, PATH_INDEX, PATH_PAGES = 0, 1, 2, 3, 4
 INDEX_NONE, INDEX_INT8, INDEX_PAGES = 0, 1, 2
 
 EXPORTS = [
-    "topk_attn_kv_bytes", "topk_attn_workspace_bytes", "topk_attn_create", "topk_attn_append_kv", "topk_attn_append_step",
+    "topk_attn_kv_bytes", "topk_attn_workspace_bytes", "topk_attn_layers_workspace_bytes", "topk_attn_create", "topk_attn_append_kv", "topk_attn_append_step",
     "topk_attn_decode", "topk_attn_decode_static", "topk_attn_decode_window", "topk_attn_decode_multi", "topk_attn_decode_layers", "topk_attn_k_schedule", "topk_attn_scores", "topk_attn_length", "topk_attn_reset", "topk_attn_set_path",
     "topk_attn_last_fallbacks", "topk_attn_set_page_bound_scale", "topk_attn_last_pages_read", "topk_attn_last_selection_records", "topk_attn_debug_read_workspace", "topk_attn_debug_read_workspace_dims", "topk_attn_debug_force_redo", "topk_attn_set_scan_timing", "topk_attn_scan_time", "topk_attn_read_probe", "topk_attn_build_id", "topk_attn_strerror", "topk_attn_destroy",
 ]
@@ -70,6 +70,8 @@ def lib() -> ctypes.CDLL:
         L.topk_attn_kv_bytes.restype = sz
         L.topk_attn_workspace_bytes.argtypes = [cfgp]
         L.topk_attn_workspace_bytes.restype = sz
+        L.topk_attn_layers_workspace_bytes.argtypes = [cfgp, i32]
+        L.topk_attn_layers_workspace_bytes.restype = sz
         L.topk_attn_create.argtypes = [cfgp, ctypes.POINTER(vp)]
         L.topk_attn_create.restype = i32
         L.topk_attn_append_kv.argtypes = [vp, i32, i32, vp, vp, i64, i64, i64, vp]
@@ -159,6 +161,10 @@ def topk_attn_kv_bytes(cfg: Config) -> int:
 
 def topk_attn_workspace_bytes(cfg: Config) -> int:
     return int(lib().topk_attn_workspace_bytes(ctypes.byref(cfg)))
+
+
+def topk_attn_layers_workspace_bytes(cfg: Config, n_layers: int = 0) -> int:
+    return int(lib().topk_attn_layers_workspace_bytes(ctypes.byref(cfg), n_layers))
 
 
 def topk_attn_create(cfg: Config) -> int:
@@ -296,10 +302,13 @@ def topk_attn_read_probe(src_ptr, nbytes, sink_ptr, stream=0):
 # Convenience owner of the torch allocations a handle borrows (marshalling only).
 # --------------------------------------------------------------------------
 class TopkAttnCache:
-    """Allocates kv_storage/workspace as torch tensors and wraps the handle."""
+    """Allocates kv_storage/workspace as torch tensors and wraps the handle.
+
+    joined_layers: layers that topk_attn_decode_layers may let share their launches; the workspace grows in proportion.
+    0: as many as are of use, within 1 GiB.  1 for a program that decodes layer by layer."""
 
     def __init__(self, n_layers, n_seqs, n_q_heads, n_kv_heads, head_dim, max_tokens, max_k, dtype, device=0,
-                 max_window=0, max_queries=0, index_kind=0):
+                 max_window=0, max_queries=0, index_kind=0, joined_layers=0):
         import torch
         self.torch = torch
         self.shape = (n_layers, n_seqs, n_q_heads, n_kv_heads, head_dim, max_tokens, max_k, dtype)
@@ -307,7 +316,7 @@ class TopkAttnCache:
         self.device = torch.device("cuda", device)
         cfg = make_config(n_layers, n_seqs, n_q_heads, n_kv_heads, head_dim, max_tokens, max_k, dtype, device,
                           max_window=max_window, max_queries=max_queries, index_kind=index_kind)
-        kvb, wsb = topk_attn_kv_bytes(cfg), topk_attn_workspace_bytes(cfg)
+        kvb, wsb = topk_attn_kv_bytes(cfg), topk_attn_layers_workspace_bytes(cfg, joined_layers)
         if kvb == 0 or wsb == 0:
             h = ctypes.c_void_p()
             _check(lib().topk_attn_create(ctypes.byref(cfg), ctypes.byref(h)), "topk_attn_create")

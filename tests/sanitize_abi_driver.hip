@@ -71,12 +71,17 @@ int main() {
     CHECK(topk_attn_kv_bytes(&c) > kv);
     c.index_kind = 9;
     CHECK(topk_attn_kv_bytes(&c) == 0 && topk_attn_workspace_bytes(&c) == 0);
-    CHECK(topk_attn_kv_bytes(nullptr) == 0 && topk_attn_workspace_bytes(nullptr) == 0);
+    CHECK(topk_attn_kv_bytes(nullptr) == 0 && topk_attn_workspace_bytes(nullptr) == 0 && topk_attn_layers_workspace_bytes(nullptr, 2) == 0);
+    c = base_config();
+    CHECK(topk_attn_layers_workspace_bytes(&c, 1) == ws && topk_attn_layers_workspace_bytes(&c, -1) == 0);
+    CHECK(topk_attn_layers_workspace_bytes(&c, 2) > ws && topk_attn_layers_workspace_bytes(&c, 0) == topk_attn_layers_workspace_bytes(&c, 2));
+    CHECK(topk_attn_layers_workspace_bytes(&c, 0x7FFFFFFF) == topk_attn_layers_workspace_bytes(&c, 2));
     // the largest configurations the checks let through must not overflow the size arithmetic
     c = base_config();
     c.n_layers = 128; c.n_seqs = 64; c.max_tokens = 0x7FFFFF00ll; c.max_k = 1 << 28; c.max_window = 0x7FFFFFFF;
     c.max_queries = 1;
     CHECK(topk_attn_kv_bytes(&c) > 0 && topk_attn_workspace_bytes(&c) > 0);
+    CHECK(topk_attn_layers_workspace_bytes(&c, 0) >= topk_attn_workspace_bytes(&c) && topk_attn_layers_workspace_bytes(&c, 16) > 0);
     // every field out of range once
     topk_attn_t* h = reinterpret_cast<topk_attn_t*>(0x1);
     struct { int field; int64_t value; int want; } bad[] = {

@@ -82,6 +82,38 @@ def test_workspace_grows_with_max_queries():
     assert ta.topk_attn_workspace_bytes(cfg) == 0
 
 
+@pytest.mark.parametrize("layers,heads,tokens,k,kw,joined", [
+    (4, 32, 1048576, 16384, {}, 1),                              # the chip-wide selection takes its steps
+    (32, 32, 524288, 8192, {}, 1),
+    (8, 32, 524288, 2048, dict(index_kind=ta.INDEX_INT8), 1),    # nothing joins through an index
+    (8, 32, 100000, 1000, dict(index_kind=ta.INDEX_PAGES), 1),
+    (8, 32, 40000, 4000, dict(max_window=200), 1),               # more value rows than one launch takes
+    (8, 4, 40000, 100, dict(dtype=ta.F32), 1),
+    (8, 32, 48001, 1024, {}, 8),
+    (7, 32, 131072, 256, {}, 4),
+    (32, 32, 131072, 256, {}, 8),                                # 256 heads
+    (32, 32, 262145, 256, {}, 2),                                # keys a workgroup may have to score again
+    (32, 32, 8192, 256, {}, 16),
+    (8, 32, 16384, 64, dict(index_kind=ta.INDEX_INT8), 8),       # too short for the index
+    (1, 32, 8192, 256, {}, 1),
+])
+def test_room_for_layers_that_share_launches(layers, heads, tokens, k, kw, joined):
+    """The workspace holds one layer's buffers; room for further layers is asked for, and offered where layers can join."""
+    kw = {"dtype": ta.F16, **kw}
+    cfg = ta.make_config(layers, 1, heads, heads // 4, 128, tokens, k, **kw)
+    one = ta.topk_attn_workspace_bytes(cfg)
+    lengths = (layers * 4 + 255) // 256 * 256
+    alone = ta.make_config(1, 1, heads, heads // 4, 128, tokens, k, **kw)
+    assert one - lengths == ta.topk_attn_workspace_bytes(alone) - 256           # whatever the number of layers
+    assert ta.topk_attn_layers_workspace_bytes(cfg, 1) == one
+    assert ta.topk_attn_layers_workspace_bytes(cfg, 0) == ta.topk_attn_layers_workspace_bytes(cfg, joined)
+    most = min(16, 1 << (layers.bit_length() - 1))
+    for n in (2, 3, 4, 8, 16, 1000):
+        room, m = ta.topk_attn_layers_workspace_bytes(cfg, n), min(most, 1 << (min(n, 16).bit_length() - 1))
+        assert 0.98 * m * one < room <= m * one          # (the lengths, and the mask of a page index, are there once)
+    assert ta.topk_attn_layers_workspace_bytes(cfg, -1) == 0
+
+
 def test_int8_index_storage_and_supported_shapes():
     base = dict(n_layers=2, n_seqs=3, n_q_heads=8, n_kv_heads=2, head_dim=128, max_tokens=1000, max_k=64)
     plain = ta.topk_attn_kv_bytes(ta.make_config(dtype=ta.F16, **base))

@@ -75,6 +75,44 @@ def test_layers_in_one_call_equal_a_call_per_layer(name):
         cache.close()
 
 
+@pytest.mark.parametrize("tokens,k", [(30000, 300), (5000, 64)])
+def test_layers_over_a_smaller_workspace(tokens, k):
+    """A workspace with room for one layer, two, or all (and a few bytes short of that) gives the same bits."""
+    L, Hq, Hkv, d = 8, 8, 2, 64
+    cfg = ta.make_config(L, 1, Hq, Hkv, d, tokens, k, ta.F16)
+    sizes = [ta.topk_attn_layers_workspace_bytes(cfg, n) for n in (1, 2, 8)]
+    assert sizes[0] == ta.topk_attn_workspace_bytes(cfg) < sizes[1] < sizes[2] == ta.topk_attn_layers_workspace_bytes(cfg)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(4)
+    K, V = (torch.randn((L, Hkv, tokens, d), generator=g, device=DEV).half() for _ in range(2))
+    q = torch.randn((L, 1, Hq, d), generator=g, device=DEV).half()
+    kv = torch.empty(ta.topk_attn_kv_bytes(cfg), dtype=torch.uint8, device=DEV)
+    cfg.kv_storage, cfg.kv_bytes = kv.data_ptr(), kv.numel()
+    st = torch.cuda.current_stream().cuda_stream
+    results = []
+    for size in [*sizes, sizes[2] - 256]:
+        ws = torch.full((size + 256,), 0xEE, dtype=torch.uint8, device=DEV)
+        cfg.workspace, cfg.workspace_bytes = ws.data_ptr(), size
+        h = ta.topk_attn_create(cfg)
+        try:
+            for l in range(L):
+                ta.topk_attn_append_kv(h, l, 0, K[l].data_ptr(), V[l].data_ptr(), tokens, d, tokens * d, st)
+            out = torch.empty((L, 1, Hq, d), device=DEV)
+            idx = torch.empty((L, 1, Hq, k), dtype=torch.int32, device=DEV)
+            ta.topk_attn_decode_layers(h, 0, [k] * L, q.data_ptr(), 0, out.data_ptr(), idx.data_ptr(), stream=st)
+            torch.cuda.synchronize()
+            assert (ws[size:] == 0xEE).all()
+            results.append((out, idx))
+        finally:
+            ta.topk_attn_destroy(h)
+    for out, idx in results[1:]:
+        assert torch.equal(out, results[0][0]) and torch.equal(idx, results[0][1])
+    cfg.workspace_bytes = sizes[0] - 1
+    with pytest.raises(ta.TopkAttnError) as e:
+        ta.topk_attn_create(cfg)
+    assert e.value.code == ta.ENOMEM
+
+
 @pytest.mark.parametrize("L,Hq,Hkv,d,ks", [
     (4, 32, 8, 128, (700, 701, 300, 1000)),          # workgroups that take two shares of eight, so some do not hold the first row
     (2, 32, 8, 64, (256, 900)),
