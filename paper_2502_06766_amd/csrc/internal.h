@@ -201,13 +201,14 @@ __host__ __device__ inline Plan make_plan(int64_t N, int k_eff, int indexed = 0)
     // by exp(-t^2 / (2 (r0 + t / 3))).  The rank r = r0 + z^2 / 6 + z sqrt(z^2 / 36 + r0) makes that exp(-z^2 / 2), 1.5e-8 per head: the
     // threshold is then below the k-th score, and the candidate list holds about N r / n_samp entries.  (The rank that solves
     // r - z sqrt(r) = r0 is far beyond that: 216 against 202 for r0 = 128, 88 against 72 for 32, 65 against 47 for 16.  Whole call with
-    // it / now: 8 layers of 48k tokens 215 / 207 us, 16 queries at 128k tokens 153 / 146, page index at 1M tokens 194 / 184.)
+    // it / now: 8 layers of 48k tokens 215 / 207 us, 16 queries at 128k tokens 153 / 146.)  That wider margin is kept with the int8
+    // index, where coding noise comes on top of the sampling: recall depends on it (61 samples against 43 for r0 = 14).
     const double z = 6.0;
     const double r_true = (double)k_eff * (double)ns / (double)N;
     double r0 = r_true;
     if (indexed) r0 = 1.25 * r0 + 4.0;      // approximate scores: more candidates, so that coding noise loses none
     double sr = 0.5 * (z + sqrt(z * z + 4.0 * r0));
-    if (r0 >= kFewAbove) sr = sqrt(r0 + z * z / 6.0 + z * sqrt(z * z / 36.0 + r0));
+    if (r0 >= kFewAbove && !indexed) sr = sqrt(r0 + z * z / 6.0 + z * sqrt(z * z / 36.0 + r0));
     const double r = sr * sr;
     p.rank = (int)r + 2;
     p.rank_k = (int)r0 + 1;

@@ -306,3 +306,27 @@ def test_c4_batched_index_decode():
         np.testing.assert_allclose(approx[0].cpu().numpy(), exact[0].cpu().numpy(), rtol=0, atol=5e-3 * float(exact[0].abs().max()))
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("N,k", [(65536, 512), (131072, 900), (131072, 2048)])
+def test_samples_above_the_threshold_of_the_index(N, k):
+    """The candidate threshold lies below as many samples as the rank r with r - 6 sqrt(r) = r0 says, where r0 is 1.25 times the
+    samples expected above the k-th score and 4: coding noise comes on top of what the sampling may miss."""
+    Hq, Hkv, d, dtype = 4, 1, 128, wl.F16
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, N, k, dtype, index_kind=ta.INDEX_INT8)
+    try:
+        cache.set_path(ta.PATH_INDEX)
+        g = torch.Generator(device=DEV)
+        g.manual_seed(N + k)
+        K, V = (torch.randn((Hkv, N, d), generator=g, device=DEV).half() for _ in range(2))
+        cache.append(0, 0, K, V, head_major=True)
+        cache.decode(0, torch.randn((1, Hq, d), generator=g, device=DEV).half(), k)
+        assert cache.last_fallbacks() == 0
+        n_samp, r0 = N // 64, 1.25 * k / 64 + 4
+        rank = (0.5 * (6 + (36 + 4 * r0) ** 0.5)) ** 2
+        samp = ta.topk_attn_debug_read_workspace(cache.h, "samp", np.float32, 8192 * Hq).reshape(Hq, 8192)[:, :n_samp]
+        thr = ta.topk_attn_debug_read_workspace(cache.h, "thr", np.float32, Hq)
+        above = (samp >= thr[:, None]).sum(1)
+        assert (above >= int(rank)).all() and (above <= 1.5 * rank).all(), (above, rank)
+    finally:
+        cache.close()
