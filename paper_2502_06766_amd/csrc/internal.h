@@ -185,7 +185,8 @@ constexpr double kFewAbove = 8.0;
 
 // `indexed`: the sample scores are approximate (int8 index); a quarter more samples are
 // expected above the threshold so that coding noise at the k-th score stays inside the list.
-__host__ __device__ inline Plan make_plan(int64_t N, int k_eff, int indexed = 0) {
+// `wide`: with the wider margin (below), by which lists are sized.
+__host__ __device__ inline Plan make_plan(int64_t N, int k_eff, int indexed = 0, bool wide = false) {
     Plan p;
     int64_t ns = N / 64;
     if (ns > kSampMax) ns = kSampMax;
@@ -208,7 +209,7 @@ __host__ __device__ inline Plan make_plan(int64_t N, int k_eff, int indexed = 0)
     double r0 = r_true;
     if (indexed) r0 = 1.25 * r0 + 4.0;      // approximate scores: more candidates, so that coding noise loses none
     double sr = 0.5 * (z + sqrt(z * z + 4.0 * r0));
-    if (r0 >= kFewAbove && !indexed) sr = sqrt(r0 + z * z / 6.0 + z * sqrt(z * z / 36.0 + r0));
+    if (r0 >= kFewAbove && !indexed && !wide) sr = sqrt(r0 + z * z / 6.0 + z * sqrt(z * z / 36.0 + r0));
     const double r = sr * sr;
     p.rank = (int)r + 2;
     p.rank_k = (int)r0 + 1;

@@ -267,6 +267,27 @@ def test_more_heads_than_compute_units(B, M, Hq, Hkv, N, d, k, one_launch):
         cache.close()
 
 
+def test_many_tied_candidates_fit_the_list():
+    """16 sequences of 60000 tokens, k = 1000, 8 KV heads: a list holds 39000 keys that tie above the threshold (3072 entries in each
+    of its 16 segments)."""
+    B, Hq, Hkv, N, d, k = 16, 8, 8, 60000, 32, 1000
+    q, K, V = (wl.quantize(a, wl.F16) for a in make_tied(5, 1, Hq, Hkv, N, d, [(0.65, 1.5)]))
+    cache = ta.TopkAttnCache(1, B, Hq, Hkv, d, N, k, wl.F16)
+    try:
+        Kd, Vd = H.to_torch(K, wl.F16, DEV), H.to_torch(V, wl.F16, DEV)
+        for b in range(B):
+            cache.append(0, b, Kd if b == 3 else torch.randn_like(Kd), Vd, head_major=True)
+        qd = H.to_torch(q, wl.F16, DEV)[None].repeat(B, 1, 1, 1).contiguous()
+        res = cache.decode_multi(0, qd, k)
+        assert cache.last_fallbacks() == 0
+        dims = ta.topk_attn_debug_read_workspace_dims(cache.h)
+        cnt = ta.topk_attn_debug_read_workspace(cache.h, "seg_cnt", np.uint32, dims[4] * B * Hq).reshape(B, Hq, dims[4])
+        assert (cnt[3].sum(1) >= 39000).all() and cnt[3].max() <= dims[5]
+        check_exact(tuple(t[3].cpu().numpy() for t in res), q, K, V, wl.F16, k, True, 0, "tied")
+    finally:
+        cache.close()
+
+
 @pytest.mark.parametrize("N,n_seg", [(131072, 128), (98304, 128), (98000, 64)])
 def test_split_of_three_row_blocks(N, n_seg):
     """17 queries, 8 KV heads: 24 streams of row blocks, split until their workgroups fill the chip while a wave keeps a dozen tiles."""
