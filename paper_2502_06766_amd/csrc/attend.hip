@@ -412,7 +412,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
 //
 // The scan's counts per score bin say without a look at the list which bin B the k-th score falls in and how many entries lie
 // above it, and the largest score its waves saw is the weights' reference: an entry above B is a winner as soon as it is
-// read, and only those of B (a few hundred at most, as a rule) are ranked.  So a head costs four barriers: the segments'
+// read, and only those of B (a few hundred at most, as a rule) are ranked, or split once more.  So a head costs four barriers: the segments'
 // lengths and the counts, the places of the winners, the ranking, the sum; stamps at 128k tokens: lengths and counts 3.8 us,
 // entries 2.4, places 1.3, emission and ranking 2.3, rows and sum 3.5, the shares' exchange 2.0.  The list stays in registers, not in
 // LDS, so that two workgroups of 512 threads share a compute unit where there are more than 256.  A first version put the list into
@@ -421,12 +421,13 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
 template <int DT, int NT, int D>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) attend_list_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     constexpr int NW = NT / kWave, EPL = 8, LPR = D / EPL, RPW = kWave / LPR;
-    constexpr int PRE = 8;                                // list slots per thread asked for before the segments' lengths are known
     constexpr int EDGES = NT == 1024 ? kAttendList : 3584;              // entries of the k-th score's bin that fit LDS (two workgroups of 512 threads share a compute unit)
     constexpr int FEW = 256;                              // more are split again before they are ranked
     constexpr int SPT = kMaxSeg / NT;                     // segments per thread
     using Team = WorkgroupTeam<NT>;
-    __shared__ SelectShared<Team, 1024> sm;
+    constexpr int PRE = 8;                                // list slots of a thread in registers
+    constexpr int NB = 1024;
+    __shared__ SelectShared<Team, NB> sm;
     __shared__ uint64_t rows_lds[kAttendRows];            // value rows to fetch (score bits, position)
     __shared__ uint64_t edge_lds[EDGES];                  // composite keys of the entries of the k-th score's bin; later partial sums
     __shared__ uint32_t segs[kMaxSeg];                    // lengths of the segments
@@ -462,15 +463,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
 #pragma unroll 4
         for (int j = wave; j < n_scan; j += NW) n_bin += hp[j * kTailBins];
     }
+    // (slots before the segments' lengths are known: any slot of the list may be read, what lies beyond its segment is ignored)
+    static_assert(PRE * NT <= kMaxSeg * kCandChunk && PRE <= 32, "every list has room for as many; a bit per slot");
     uint64_t pre[PRE];
-    {
-        const int n_pre = helper ? 0 : sh.cand_cap;
 #pragma unroll
-        for (int u = 0; u < PRE; ++u) {
-            const int i = u * NT + tid;
-            pre[u] = list[i < n_pre ? i : 0];             // (any slot of the list may be read; what lies beyond its segment is ignored)
-        }
-    }
+    for (int u = 0; u < PRE; ++u) pre[u] = helper ? 0ull : (list + u * NT)[tid];
+#pragma unroll
+    for (int u = 0; u < NB / NT; ++u) sm.hist[u * NT + tid] = 0;         // (while the loads are under way)
     const LayerK lk = bf.layer_k[layer];
     const int k = lk.k;
     const int64_t sel0 = selection_at(sh, lk, blockIdx.y, h);
@@ -485,6 +484,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
     int how = LIST;                                       // (uniform)
     bool alone = false;                                   // (uniform) this workgroup goes on for the whole head
     uint32_t above = 0, in_b = 0, total = 0;              // keys above bin B, and in it; entries of the list
+    uint32_t before = 0;                                  // of them in the segments of the threads before this one
     int B = kTailBins, n_slots = 0;                       // bin of the k-th score; slots of the list in use
     float top = -INFINITY;                                // largest selected score
     if (k_eff > 0) {
@@ -500,7 +500,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
                 longest = seg_len[u] > longest ? seg_len[u] : longest;
                 mx = fmaxf(mx, seg_top[u]);
             }
+            before = sum;
             sum = wave_scan_add(sum);
+            before = sum - before;
             longest = wave_max_u32(longest);
             mx = wave_max(mx);
             if (lane == kWave - 1) { red_lds[0][wave] = sum; red_lds[1][wave] = longest; red_lds[2][wave] = __float_as_uint(mx); }
@@ -509,9 +511,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
             const bool one = lane < NW;
             const uint32_t t = wave_scan_add(one ? red_lds[0][lane] : 0u);
             total = (uint32_t)__builtin_amdgcn_readlane((int)t, kWave - 1);
+            before += wave ? (uint32_t)__builtin_amdgcn_readlane((int)t, wave - 1) : 0u;
             const uint32_t len = wave_max_u32(one ? red_lds[1][lane] : 0u);
             top = wave_max(one ? __uint_as_float(red_lds[2][lane]) : -INFINITY) + 0.0f;
-            n_slots = (int)((len + kCandChunk - 1) >> kCandChunkLog2) * n_seg * kCandChunk;
+            n_slots = __builtin_amdgcn_readfirstlane((int)((len + kCandChunk - 1) >> kCandChunkLog2) * n_seg * kCandChunk);
             return len;
         };
         const uint32_t longest = lay_out();
@@ -529,6 +532,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
         if (!hit) how = SCORE_ROW;
         else if (over) how = sh.no_rescan || in_b > (uint32_t)EDGES ? SCORE_ROW : RESCORE;
         else if (in_b > (uint32_t)EDGES) how = LIST_TIED;
+        how = __builtin_amdgcn_readfirstlane(how);        // (a branch for the compiler too: what one side holds in registers is free on the other)
         if (helper && how < RESCORE) return;              // (uniform)
         // a list that should have been usable (the measure of the chip-wide selection)
         const bool fallback = (over || !hit || in_b > (uint32_t)sh.bnd_cap) && !(flags & 5u) && counts_fallbacks(sh, b);
@@ -547,7 +551,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
                 sm.n_keys = atomicAdd(&bf.flags[bh], kArrivalUnit);               // (the threshold estimate cleared the count)
             }
             __syncthreads();
-            const uint32_t arrived = sm.n_keys;
+            const uint32_t arrived = (uint32_t)__builtin_amdgcn_readfirstlane((int)sm.n_keys);
             if (arrived / kArrivalUnit + 1u != (uint32_t)n_wgs) return;           // (uniform)
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
             if (tid == 0 && fallback) atomicAdd(bf.fallback_total, 1u);
@@ -561,6 +565,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
                 }
                 lay_out();                                // (its barrier comes after the readers of what it overwrites)
             }
+#pragma unroll
+            for (int u = 0; u < PRE; ++u) pre[u] = 0ull;  // (not kept in registers through the scoring)
         }
     } else if (helper) {
         return;                                           // nothing to search for this sequence
@@ -615,83 +621,170 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
 
     // ---- the k_eff best
     if (k_eff > 0 && (how == LIST || how == RESCORE)) {
-        const int n_pre = how == LIST ? PRE : 0;          // (uniform) slots per thread in registers
-        // bin of slot i's entry, -1 for a slot that holds none
-        auto bin_of = [&](int i, uint64_t ent) {
-            const bool in = (uint32_t)cand_slot_entry(i, log2_n_seg) < segs[cand_slot_segment(i, log2_n_seg)];
-            return in ? tail_bin(score_of(ent), bin_lo, bin_inv) : -1;
+        int n_pre = how == LIST ? PRE : 0;                // (uniform) slots per thread in registers
+        uint64_t* edges_lds = edge_lds;                   // entries to rank
+        auto bin_of = [&](uint64_t ent) { return tail_bin(score_of(ent), bin_lo, bin_inv); };
+        // whether slot i holds an entry (cand_slot(), in 32 bits)
+        auto filled = [&](int i) {
+            const int run = i >> kCandChunkLog2;
+            return (uint32_t)(((run >> log2_n_seg) << kCandChunkLog2) | (i & (kCandChunk - 1))) < segs[run & (n_seg - 1)];
         };
+        // f(slot, entry) for the entries that are not in registers.  (They are read for every purpose again, and most slots are empty
+        // there: the list is as deep as its longest segment.)
+        auto rest = [&](auto f) {
+            for (int i0 = n_pre * NT + tid; i0 < n_slots; i0 += 4 * NT) {       // (uniform over the wave)
+                bool in[4];
+                uint64_t ent[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int i = i0 + u * NT;
+                    in[u] = i < n_slots && filled(i);
+                }
+                if (!__any(in[0] || in[1] || in[2] || in[3])) continue;
+#pragma unroll
+                for (int u = 0; u < 4; ++u) ent[u] = in[u] ? list[i0 + u * NT] : 0ull;
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (in[u]) f(i0 + u * NT, ent[u]);
+            }
+        };
+        // Deeper lists that would fit the registers are put together in LDS first, each segment's entries behind those of the segments
+        // before.  (Sparse ones: one or two KV heads, whose 1024 segments hold a few entries each, or the page index, where whole pages of
+        // candidates fall into one segment.  Walked by slots for every purpose instead: one KV head, 16 query heads, 163k tokens
+        // 48.5 us per call and 44.5 now, page index at 170k tokens 72.0 and 61.3.)
+        const bool dense = n_slots > n_pre * NT && total <= (uint32_t)(PRE * NT) && total + in_b <= (uint32_t)EDGES;      // (uniform)
+        if (__builtin_expect(dense, 0)) {
+            uint32_t* const starts = reinterpret_cast<uint32_t*>(sm.keys);
+            static_assert(sizeof(sm.keys) >= kMaxSeg * sizeof(uint32_t), "a word per segment");
+            uint32_t start = before;
+#pragma unroll
+            for (int u = 0; u < SPT; ++u) { starts[u * NT + tid] = start; start += seg_len[u]; }
+            __syncthreads();
+            auto put = [&](int i, uint64_t ent) {
+                const int run = i >> kCandChunkLog2;
+                edge_lds[starts[run & (n_seg - 1)] + (uint32_t)(((run >> log2_n_seg) << kCandChunkLog2) | (i & (kCandChunk - 1)))] = ent;
+            };
+#pragma unroll
+            for (int u = 0; u < PRE; ++u)
+                if (u < n_pre && filled(u * NT + tid)) put(u * NT + tid, pre[u]);
+            rest(put);
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < PRE; ++u) pre[u] = edge_lds[u * NT + tid < (int)total ? u * NT + tid : 0];
+            n_pre = PRE;
+            n_slots = ((int)total + kWave - 1) & ~(kWave - 1);
+            edges_lds = edge_lds + total;
+        }
         // (composite: score key, then inverted position: larger beats smaller, equal scores go to the lower position, no two are equal)
-        const bool few = in_b <= (uint32_t)FEW;           // (uniform) they are ranked, in whatever order they lie; more keep the list's
         auto edge = [&](uint32_t o, uint64_t ent) {
-            if (o < (uint32_t)EDGES)                      // (always: in_b entries)
-                edge_lds[o] = ((uint64_t)score_key(score_of(ent)) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)ent);
+            if (o < in_b)                                 // (always)
+                edges_lds[o] = ((uint64_t)score_key(score_of(ent)) << 32) | (uint64_t)(0xFFFFFFFFu - (uint32_t)ent);
         };
-        uint32_t wins = 0, edges = 0, n_win = 0, n_edges = 0;
+        uint32_t wins = 0, edges = 0;                     // bit u: pre[u] is a certain winner, an entry of bin B
+        bool few = in_b <= (uint32_t)FEW;                 // (uniform) entries to rank, in whatever order they lie; more keep the list's
 #pragma unroll
         for (int u = 0; u < PRE; ++u) {
             if (u < n_pre && u * NT < n_slots) {          // (uniform; n_slots is a multiple of 64, a segment's slots lie below it)
-                const int bin = bin_of(u * NT + tid, pre[u]);
+                const int bin = (dense ? u * NT + tid < (int)total : filled(u * NT + tid)) ? bin_of(pre[u]) : -1;
                 wins |= bin > B ? 1u << u : 0u;
                 edges |= bin == B ? 1u << u : 0u;
                 if (few && bin == B) edge(atomicAdd(&n_edge_lds, 1u), pre[u]);
             }
         }
-        n_win = (uint32_t)__popc(wins);
-        n_edges = (uint32_t)__popc(edges);
-        // a list longer than the registers hold is read twice
-        auto rest = [&](auto f) {
-            for (int i0 = n_pre * NT + tid; i0 < n_slots; i0 += 4 * NT) {
-                uint64_t ent[4];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) ent[u] = list[i0 + u * NT < n_slots ? i0 + u * NT : 0];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (i0 + u * NT < n_slots) f(bin_of(i0 + u * NT, ent[u]), ent[u]);
-            }
+        // A crowded bin B is split into NB parts of its own range; S: the part the k-th score falls in, the parts above it win
+        // too.  (Not the bins that are open to one side.  Nearly every call has a head with a few hundred entries in B; splitting them as
+        // team_select() does costs 3 us more: d = 256, 29k tokens 52.8 us per call and 49.9 now, int8 index at 99k 50.0 and 47.1.)
+        int S = -1;
+        uint32_t sure = above, in_s = in_b;               // certain winners, entries that are left to rank
+        auto part_of = [&](uint64_t ent) {                // (monotone: tail_bin() before its rounding to whole bins)
+#pragma clang fp contract(off)
+            const float t = __fmul_rn(__fsub_rn(score_of(ent), bin_lo), bin_inv) - (float)(B - 1);
+            return (int)fminf(fmaxf(t * (float)NB, 0.f), (float)(NB - 1));
         };
-        rest([&](int bin, uint64_t ent) {
-            n_win += bin > B ? 1u : 0u;
-            n_edges += bin == B ? 1u : 0u;
-            if (few && bin == B) edge(atomicAdd(&n_edge_lds, 1u), ent);
+        if (__builtin_expect(!few && B > 0 && B < kTailBins - 1, 0)) {         // (uniform)
+            constexpr int BPT = NB / NT;
+            auto place = [](int part) { return (part % BPT) * NT + part / BPT; };
+#pragma unroll
+            for (int u = 0; u < PRE; ++u)
+                if (u * NT < n_slots && ((edges >> u) & 1u)) atomicAdd(&sm.hist[place(part_of(pre[u]))], 1u);
+            rest([&](int, uint64_t ent) {
+                if (bin_of(ent) == B) atomicAdd(&sm.hist[place(part_of(ent))], 1u);
+            });
+            __syncthreads();
+            uint32_t n[BPT], local = 0, all_parts;
+#pragma unroll
+            for (int u = 0; u < BPT; ++u) { n[u] = sm.hist[place(NB - 1 - (tid * BPT + u))]; local += n[u]; }
+            uint32_t run = above + team_prefix<Team>(local, all_parts, sm, 1);
+#pragma unroll
+            for (int u = 0; u < BPT; ++u) {
+                if (run < (uint32_t)k_eff && (uint32_t)k_eff <= run + n[u]) {        // exactly one thread
+                    sm.sel[0] = (uint32_t)(NB - 1 - (tid * BPT + u));
+                    sm.sel[1] = run;
+                    sm.sel[2] = n[u];
+                }
+                run += n[u];
+            }
+            __syncthreads();
+            S = __builtin_amdgcn_readfirstlane((int)sm.sel[0]);
+            sure = (uint32_t)__builtin_amdgcn_readfirstlane((int)sm.sel[1]);
+            in_s = (uint32_t)__builtin_amdgcn_readfirstlane((int)sm.sel[2]);
+            few = in_s <= (uint32_t)FEW;
+#pragma unroll
+            for (int u = 0; u < PRE; ++u) {
+                if (u * NT < n_slots && ((edges >> u) & 1u)) {
+                    const int part = part_of(pre[u]);
+                    if (part > S) wins |= 1u << u;
+                    if (part != S) edges &= ~(1u << u);
+                    else if (few) edge(atomicAdd(&n_edge_lds, 1u), pre[u]);
+                }
+            }
+        }
+        auto wins_for_certain = [&](uint64_t ent) { return bin_of(ent) > B || (S >= 0 && bin_of(ent) == B && part_of(ent) > S); };
+        auto is_edge = [&](uint64_t ent) { return bin_of(ent) == B && (S < 0 || part_of(ent) == S); };
+        uint32_t n_win = (uint32_t)__popc(wins), n_edges = (uint32_t)__popc(edges);
+        rest([&](int, uint64_t ent) {
+            const bool e = is_edge(ent);
+            n_win += wins_for_certain(ent) ? 1u : 0u;
+            n_edges += e ? 1u : 0u;
+            if (few && e) edge(atomicAdd(&n_edge_lds, 1u), ent);
         });
-        uint32_t all_wins;                                // (`above` of them)
+        uint32_t all_wins;                                // (`sure` of them)
         uint32_t at = team_prefix<Team>(n_win, all_wins, sm, 0);
         if (__ballot(at < row1 && at + n_win > row0)) {   // (the places of a wave's winners follow one another)
 #pragma unroll
             for (int u = 0; u < PRE; ++u)
                 if (u * NT < n_slots && ((wins >> u) & 1u)) emit(at++, score_of(pre[u]), (uint32_t)pre[u]);
-            rest([&](int bin, uint64_t ent) {
-                if (bin > B) emit(at++, score_of(ent), (uint32_t)ent);
+            rest([&](int, uint64_t ent) {
+                if (wins_for_certain(ent)) emit(at++, score_of(ent), (uint32_t)ent);
             });
         }
         // the best entries of the bin are the missing winners
-        const uint32_t need = (uint32_t)k_eff - above;
-        const int n_edge = (int)(in_b < (uint32_t)EDGES ? in_b : (uint32_t)EDGES);
+        const uint32_t need = (uint32_t)k_eff - sure;
+        const int n_edge = (int)(in_s < (uint32_t)EDGES ? in_s : (uint32_t)EDGES);
         auto edge_score = [&](uint64_t key) { return key_score((uint32_t)(key >> 32)); };
         auto edge_pos = [&](uint64_t key) { return 0xFFFFFFFFu - (uint32_t)key; };
-        if (row1 <= above) {                              // (uniform) none of the missing winners is in this workgroup's shares
+        if (row1 <= sure) {                               // (uniform) none of the missing winners is in this workgroup's shares
         } else if (few) {                                 // each against all others, LP lanes per entry
             constexpr int LP = NT / FEW;
             static_assert(LP == 2 || LP == 4, "a pair or a quad of lanes");
             const int j = tid / LP;
-            const uint64_t mine = edge_lds[j < n_edge ? j : 0];
+            const uint64_t mine = edges_lds[j < n_edge ? j : 0];
             uint32_t rank = 0;
             if (j < n_edge) {
 #pragma unroll 8
-                for (int o = tid % LP; o < n_edge; o += LP) rank += edge_lds[o] > mine ? 1u : 0u;
+                for (int o = tid % LP; o < n_edge; o += LP) rank += edges_lds[o] > mine ? 1u : 0u;
             }
             rank += dpp_u32<0xB1, 0xF>(0u, rank);         // quad_perm 1,0,3,2
             if (LP == 4) rank += dpp_u32<0x4E, 0xF>(0u, rank);       // quad_perm 2,3,0,1
-            if (j < n_edge && tid % LP == 0 && rank < need) emit(above + rank, edge_score(mine), edge_pos(mine));
+            if (j < n_edge && tid % LP == 0 && rank < need) emit(sure + rank, edge_score(mine), edge_pos(mine));
         } else {
             constexpr int CPT = EDGES / NT;
             uint32_t all_edges, to = team_prefix<Team>(n_edges, all_edges, sm, 1);
 #pragma unroll
             for (int u = 0; u < PRE; ++u)
                 if (u * NT < n_slots && ((edges >> u) & 1u)) edge(to++, pre[u]);
-            rest([&](int bin, uint64_t ent) {
-                if (bin == B) edge(to++, ent);
+            rest([&](int, uint64_t ent) {
+                if (is_edge(ent)) edge(to++, ent);
             });
             __syncthreads();
             uint32_t act = 0;
@@ -699,16 +792,16 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
 #pragma unroll 1
             for (int j = 0; j < CPT; ++j) {
                 if (j * NT + tid < n_edge) {
-                    const float s = edge_score(edge_lds[j * NT + tid]);
+                    const float s = edge_score(edges_lds[j * NT + tid]);
                     act |= 1u << j;
                     lo = fminf(lo, s); hi = fmaxf(hi, s);
                 }
             }
             select_clear<Team>(sm);
             team_range<Team>(lo, hi, sm, 0);
-            team_select<Team, CPT, 1>([&](int j) { return edge_score(edge_lds[j * NT + tid]); }, act, n_edge, P, (int)need, lo, hi, sm,
-                                      [&](int j) { return (int32_t)edge_pos(edge_lds[j * NT + tid]); },
-                                      [&](uint32_t o, float s, int32_t p) { emit(above + o, s, (uint32_t)p); });
+            team_select<Team, CPT, 1>([&](int j) { return edge_score(edges_lds[j * NT + tid]); }, act, n_edge, P, (int)need, lo, hi, sm,
+                                      [&](int j) { return (int32_t)edge_pos(edges_lds[j * NT + tid]); },
+                                      [&](uint32_t o, float s, int32_t p) { emit(sure + o, s, (uint32_t)p); });
         }
         if (writer) pad_outputs(k_eff, k, idx, vals);
     } else if (k_eff == 0) {

@@ -267,6 +267,54 @@ def test_more_heads_than_compute_units(B, M, Hq, Hkv, N, d, k, one_launch):
         cache.close()
 
 
+@pytest.mark.parametrize("dtype,M,Hq,Hkv,N,d,k,window,run,spread", [
+    (wl.F16, 1, 8, 2, 60000, 128, 900, 0, 1, 3),           # hundreds of distinct scores in the k-th score's bin, 1024 threads
+    (wl.BF16, 17, 16, 4, 50000, 64, 500, 40, 1, 3),        # 512 threads
+    (wl.F16, 1, 4, 1, 100000, 64, 700, 0, 1, 1),           # 1024 segments
+    (wl.F16, 1, 4, 1, 100000, 64, 700, 0, 64, 3),          # whole tiles of candidates: deep segments, few entries
+    (wl.BF16, 17, 16, 4, 50000, 32, 150, 0, 64, 3),
+    (wl.F16, 1, 8, 8, 80000, 256, 400, 100, 64, 2),
+    (wl.F16, 1, 8, 2, 60000, 128, 900, 0, 1, 0),           # all of them equal
+    (wl.BF16, 17, 16, 4, 50000, 64, 500, 0, 64, 0),
+])
+def test_crowded_bins_and_sparse_lists(dtype, M, Hq, Hkv, N, d, k, window, run, spread):
+    """1.4 k keys in runs of `run` score alike but for steps in `spread` channels, around the k-th score."""
+    q, K, V = make_tied(N + k + run, M, Hq, Hkv, N, d, [])
+    g = np.random.default_rng(k)
+    sigma = np.sqrt((17.0 ** 2 - 1) / 12)
+    for h in range(Hkv):
+        Q = q[0, h * (Hq // Hkv):(h + 1) * (Hq // Hkv)].astype(np.float64)
+        at = np.rint(8 * np.linalg.lstsq(Q, 3.0 * sigma * np.linalg.norm(Q, axis=1), rcond=None)[0]) / 8
+        starts = g.permutation((N - window) // run - 1)[:-(-7 * k // (5 * run))] * run
+        hot = (starts[:, None] + np.arange(run)).ravel()
+        K[h, hot] = at
+        for c in g.permutation(d)[:spread]:
+            K[h, hot, c] += g.integers(-8, 9, hot.size) / 8
+    q, K, V = (wl.quantize(a, dtype) for a in (q, K, V))
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, N, k, dtype, max_window=window, max_queries=M)
+    try:
+        cache.append(0, 0, H.to_torch(K, dtype, DEV), H.to_torch(V, dtype, DEV), head_major=True)
+        qd = H.to_torch(q, dtype, DEV)[None].contiguous()
+        res = cache.decode_multi(0, qd, k, window=window)
+        assert cache.last_fallbacks() == 0
+        rows = M * Hq
+        in_bin = max(r[3] for r in ta.topk_attn_last_selection_records(cache.h, rows))
+        n_seg = ta.topk_attn_debug_read_workspace_dims(cache.h)[4]
+        cnt = ta.topk_attn_debug_read_workspace(cache.h, "seg_cnt", np.uint32, n_seg * rows).reshape(rows, n_seg)
+        threads = 512 if rows > 256 else 1024
+        deep = (-(-cnt.max(1).astype(int) // 16) * 16 * n_seg > 8 * threads) & (cnt.sum(1) + in_bin <= min(8 * threads, 3584 if threads == 512 else 10240))
+        print("in the bin", in_bin, "segments", n_seg, "deep lists", deep.sum(), "of", rows, flush=True)
+        assert in_bin > 256 or run > 1
+        assert deep.any() or run == 1
+        again = cache.decode_multi(0, qd, k, window=window)
+        torch.cuda.synchronize()
+        for a, b in zip(res, again):
+            assert torch.equal(a, b)
+        check_exact(tuple(t[0].cpu().numpy() for t in res), q, K, V, dtype, k, True, window, "crowded")
+    finally:
+        cache.close()
+
+
 def test_many_tied_candidates_fit_the_list():
     """16 sequences of 60000 tokens, k = 1000, 8 KV heads: a list holds 39000 keys that tie above the threshold (3072 entries in each
     of its 16 segments)."""
