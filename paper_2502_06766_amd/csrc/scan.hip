@@ -80,7 +80,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     // filter: this wave's segment in each head's candidate list
     const int seg_cap = sh.seg_cap;
     const int n_seg = sh.n_seg;
-    int sid = (int)blockIdx.x * kScanWaves + wave;
+    const int sid = (int)blockIdx.x * kScanWaves + wave;
     uint64_t* const list0 = bf.cand + head0 * (int64_t)sh.cand_cap;
     __shared__ uint64_t stage_lds[MODE == MODE_FILTER ? kScanWaves * 4 * kStage : 1];
     uint64_t* const st0 = stage_lds + (MODE == MODE_FILTER ? wave * 4 * kStage : 0);
@@ -95,7 +95,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     struct TileB { v8 b[4][D / 32]; } ba, bb;
     const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
     // filter: one tile per row of n_seg tiles, the rows in which it is a whole one; the first is asked for ahead of the thresholds
-    int64_t rows_whole = MODE == MODE_FILTER ? seg_whole(N / 64, sid, n_seg) : 0;
+    const int64_t rows_whole = MODE == MODE_FILTER ? seg_whole(N / 64, sid, n_seg) : 0;
     auto load_seg = [&](TileB& t, int64_t i) { tile_load_full<DT, D>(Kh + seg_tile(i, sid, n_seg) * (64 * D * 2), lane_off, t.b); };
     constexpr bool kAhead = MODE == MODE_FILTER && !PAGED && ScanPipelined<D>::value;
     if (MODE == MODE_FILTER) {
@@ -249,53 +249,34 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     }
     if (MODE == MODE_FILTER) {
-        // The segments of part 0, 1, ... of the stream: one part per workgroup, or several one after the other (a part's
-        // first tile is asked for before the part in front of it is written out)
-        for (int part = blockIdx.x;;) {
-            if (!PAGED) {
-                walk_tiles<ScanPipelined<D>::value, kAhead>(0, rows_whole, 1, ba, bb, load_seg,
-                    [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid, n_seg)); });
-                if (N % 64 != 0 && seg_tile(N / 64 / n_seg, sid, n_seg) == N / 64) {      // the tile the end of the cache cuts short
-                    load_rows(ba, N / 64);
-                    use(ba, N / 64);
-                }
+        if (!PAGED) {
+            walk_tiles<ScanPipelined<D>::value, kAhead>(0, rows_whole, 1, ba, bb, load_seg,
+                [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid, n_seg)); });
+            if (N % 64 != 0 && seg_tile(N / 64 / n_seg, sid, n_seg) == N / 64) {      // the tile the end of the cache cuts short
+                load_rows(ba, N / 64);
+                use(ba, N / 64);
             }
-            const int done = part, sid_done = sid;
-            part += gridDim.x;
-            const bool more = !PAGED && part < n_seg / kScanWaves;       // (uniform)
-            if (more) {
-                sid = part * kScanWaves + wave;
-                rows_whole = seg_whole(N / 64, sid, n_seg);
-                if (kAhead && rows_whole > 0) load_seg(ba, 0);
-            }
-            stage_flush(cs0, seg_cap, n_seg, true);
-            if (1 < G) stage_flush(cs1, seg_cap, n_seg, true);
-            if (2 < G) stage_flush(cs2, seg_cap, n_seg, true);
-            if (3 < G) stage_flush(cs3, seg_cap, n_seg, true);
-            for (int o = 32; o > 0; o >>= 1) {
-                top0 = fmaxf(top0, wave_xor(top0, o)); top1 = fmaxf(top1, wave_xor(top1, o));
-                top2 = fmaxf(top2, wave_xor(top2, o)); top3 = fmaxf(top3, wave_xor(top3, o));
-            }
-            if (lane == 0) {
-                uint32_t* sc = bf.seg_cnt + head0 * (int64_t)n_seg + sid_done;
-                float* sx = bf.seg_max + head0 * (int64_t)n_seg + sid_done;
-                sc[0] = (uint32_t)cs0.n_glob;
-                sx[0] = top0;
-                if (1 < G) { sc[n_seg] = (uint32_t)cs1.n_glob; sx[n_seg] = top1; }
-                if (2 < G) { sc[2 * (int64_t)n_seg] = (uint32_t)cs2.n_glob; sx[2 * (int64_t)n_seg] = top2; }
-                if (3 < G) { sc[3 * (int64_t)n_seg] = (uint32_t)cs3.n_glob; sx[3 * (int64_t)n_seg] = top3; }
-            }
-            __syncthreads();
-            for (int i = threadIdx.x; i < G * kTailBins; i += kScanWaves * kWave)
-                bf.hist[((head0 + i / kTailBins) * sh.hist_cap + done) * kTailBins + i % kTailBins] = hist_lds[i];
-            if (!more) break;
-            __syncthreads();
-            for (int i = threadIdx.x; i < 4 * kTailBins; i += kScanWaves * kWave) hist_lds[i] = 0;
-            __syncthreads();
-            cs0.sid = cs1.sid = cs2.sid = cs3.sid = sid;
-            cs0.n_glob = cs1.n_glob = cs2.n_glob = cs3.n_glob = 0;
-            top0 = top1 = top2 = top3 = -INFINITY;
         }
+        stage_flush(cs0, seg_cap, n_seg, true);
+        if (1 < G) stage_flush(cs1, seg_cap, n_seg, true);
+        if (2 < G) stage_flush(cs2, seg_cap, n_seg, true);
+        if (3 < G) stage_flush(cs3, seg_cap, n_seg, true);
+        for (int o = 32; o > 0; o >>= 1) {
+            top0 = fmaxf(top0, wave_xor(top0, o)); top1 = fmaxf(top1, wave_xor(top1, o));
+            top2 = fmaxf(top2, wave_xor(top2, o)); top3 = fmaxf(top3, wave_xor(top3, o));
+        }
+        if (lane == 0) {
+            uint32_t* sc = bf.seg_cnt + head0 * (int64_t)n_seg + sid;
+            float* sx = bf.seg_max + head0 * (int64_t)n_seg + sid;
+            sc[0] = (uint32_t)cs0.n_glob;
+            sx[0] = top0;
+            if (1 < G) { sc[n_seg] = (uint32_t)cs1.n_glob; sx[n_seg] = top1; }
+            if (2 < G) { sc[2 * (int64_t)n_seg] = (uint32_t)cs2.n_glob; sx[2 * (int64_t)n_seg] = top2; }
+            if (3 < G) { sc[3 * (int64_t)n_seg] = (uint32_t)cs3.n_glob; sx[3 * (int64_t)n_seg] = top3; }
+        }
+        __syncthreads();
+        for (int i = threadIdx.x; i < G * kTailBins; i += kScanWaves * kWave)
+            bf.hist[((head0 + i / kTailBins) * sh.hist_cap + blockIdx.x) * kTailBins + i % kTailBins] = hist_lds[i];
     }
 }
 
@@ -687,8 +668,6 @@ bool scan_mfma_supported(const Shape& s) {
     return (s.dtype == DT_F16 || s.dtype == DT_BF16) && (s.D == 32 || s.D == 64 || s.D == 128 || s.D == 256) && s.G >= 1;
 }
 
-constexpr int64_t kScanResident = 512;     // workgroups of the grouped scan that run at once (two per compute unit, by registers)
-
 template <int MODE>
 static hipError_t launch_mfma(const Shape& s, const Bufs& b, int64_t n_items, float* dst, hipStream_t st) {
     const bool rows = scan_row_tiles(s);
@@ -744,13 +723,11 @@ hipError_t launch_scan_filter_paged(const Shape& s, const Bufs& b, hipStream_t s
 
 hipError_t launch_scan_filter(const Shape& s, const Bufs& b, int64_t Nmax, hipStream_t st) {
     const bool sampled = threshold_in_scan(s, Nmax);
-    // one wave per candidate segment: n_seg / 4 workgroups per KV head.  Where several layers share the launch they would be many
-    // rounds of workgroups with a few tiles each: as many as run at once take the segments one after the other
+    // one wave per candidate segment: n_seg / 4 workgroups per KV head.  (Also where several layers share the launch: with as many
+    // workgroups as run at once, which took the segments one after the other, 8 layers of 48k tokens 216 us per call, 209 like this; and the
+    // loop around the walk cost other calls too, 3 ragged sequences of 98k 137 and 128.)
     const bool rows = scan_row_tiles(s);
-    int64_t parts = s.n_seg / kScanWaves;
-    if (s.log2_layers > 0 && !rows)
-        while (parts > 1 && parts * s.Hkv * s.B > kScanResident) parts = (parts + 1) / 2;
-    dim3 grid((unsigned)parts, (unsigned)s.Hkv, (unsigned)(scan_grid_z(s)));
+    dim3 grid((unsigned)(s.n_seg / kScanWaves), (unsigned)s.Hkv, (unsigned)(scan_grid_z(s)));
     dim3 block(kScanWaves * kWave);
 #define TKA_LAUNCH(DT_, D_)                                                                                  \
     do {                                                                                                     \
