@@ -315,6 +315,29 @@ def test_crowded_bins_and_sparse_lists(dtype, M, Hq, Hkv, N, d, k, window, run, 
         cache.close()
 
 
+@pytest.mark.parametrize("M,Hq,Hkv,N,d,k,bound", [(16, 32, 8, 40000, 128, 2048, 1.5e-7), (20, 16, 4, 30000, 256, 2000, 1.7e-7)])
+def test_sums_of_workgroups_with_512_threads(M, Hq, Hkv, N, d, k, bound):
+    """Relative error (2-norm) of the weighted sum of the selected value rows against 64 bits, for more heads than compute units.  Bounds:
+    half way between the sums a lane makes of every fourth row (1.3e-7 and 1.4e-7 measured) and one sum of all its rows (1.75e-7 and
+    2.2e-7), whose rounding errors grow with the length of the chain (64 and 125 rows)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(M)
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, N, k, wl.F16, max_queries=M)
+    try:
+        K, V = (torch.randn((Hkv, N, d), generator=g, device=DEV).half() for _ in range(2))
+        cache.append(0, 0, K, V, head_major=True)
+        q = (torch.randn((1, M, Hq, d), generator=g, device=DEV) * 0.3).half()
+        out, idx, vals, _ = cache.decode_multi(0, q, k)
+        torch.cuda.synchronize()
+        w = torch.softmax(vals[0].double() / d ** 0.5, -1)
+        ref = torch.stack([(w[:, h, :, None] * V[h * Hkv // Hq].double()[idx[0, :, h].long()]).sum(1) for h in range(Hq)], 1)
+        err = ((out[0].double() - ref).norm() / ref.norm()).item()
+        print("error", err, flush=True)
+        assert err < bound
+    finally:
+        cache.close()
+
+
 def test_many_tied_candidates_fit_the_list():
     """16 sequences of 60000 tokens, k = 1000, 8 KV heads: a list holds 39000 keys that tie above the threshold (3072 entries in each
     of its 16 segments)."""
