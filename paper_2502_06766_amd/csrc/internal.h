@@ -178,11 +178,6 @@ struct Plan {
     int64_t c_hi;    // candidates expected at most (z-sigma above the mean)
 };
 
-// With fewer samples expected above the k-th score than this the older margin (r - z sqrt(r) = r0) is kept: six to twelve times k
-// candidates instead of four to eight, but of a k of a few hundred, and lists that short cost about the same either way (whole
-// call, older / Bernstein's: 40k tokens, k = 300 42.4 / 42.4 us, 128k 66.9 / 66.6, 1M tokens, k = 1000 371 / 368).
-constexpr double kFewAbove = 8.0;
-
 // `indexed`: the sample scores are approximate (int8 index); a quarter more samples are
 // expected above the threshold so that coding noise at the k-th score stays inside the list.
 // `wide`: with the wider margin (below), by which lists are sized.
@@ -209,7 +204,7 @@ __host__ __device__ inline Plan make_plan(int64_t N, int k_eff, int indexed = 0,
     double r0 = r_true;
     if (indexed) r0 = 1.25 * r0 + 4.0;      // approximate scores: more candidates, so that coding noise loses none
     double sr = 0.5 * (z + sqrt(z * z + 4.0 * r0));
-    if (r0 >= kFewAbove && !indexed && !wide) sr = sqrt(r0 + z * z / 6.0 + z * sqrt(z * z / 36.0 + r0));
+    if (!indexed && !wide) sr = sqrt(r0 + z * z / 6.0 + z * sqrt(z * z / 36.0 + r0));
     const double r = sr * sr;
     p.rank = (int)r + 2;
     p.rank_k = (int)r0 + 1;
