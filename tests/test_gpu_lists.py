@@ -74,7 +74,9 @@ def how_selected(cache, rows):
 
 @pytest.mark.parametrize("expect,dtype,M,Hq,Hkv,N,d,k,window,groups", [
     ("long", wl.F16, 1, 4, 2, 131072, 64, 2048, 0, [(0.25, 1.9)]),              # eight workgroups per head
-    ("long", wl.BF16, 9, 16, 2, 40000, 32, 300, 100, [(0.3, 1.8)]),             # one workgroup per head, causal chunk, window
+    # one workgroup per head, causal chunk, window.  (The threshold is the 33rd of 1024 samples.  1.3 % of the keys, 13 +- 3.6 of the samples,
+    # score above the group at 2.1 standard deviations, which therefore passes by five of theirs; at 1.8 they are 26 +- 5.)
+    ("long", wl.BF16, 9, 16, 2, 40000, 32, 300, 100, [(0.3, 2.1)]),
     ("long", wl.F16, 1, 1, 1, 100001, 256, 1000, 0, [(0.2, 2.0)]),
     ("long", wl.BF16, 1, 8, 1, 150000, 128, 1000, 30, [(0.2, 2.1)]),            # the row-tile scan
     ("long, tied", wl.BF16, 1, 8, 2, 131072, 256, 2048, 64, [(0.15, 3.0)]),
