@@ -741,17 +741,13 @@ static int lengths_of(const topk_attn_t* h, int layer, int window, int64_t min_t
 // when a list turns out unusable are bounded.  Heads beyond the compute units get one workgroup each, two to a compute unit: list / tail,
 // 8 to 64 heads a sequence or query, 30k to 120k tokens, k = 64 .. 2000, windows up to 2048: batches of 9 to 40 sequences d = 64 0.88 - 0.98,
 // d = 128 0.92 - 0.99, d = 256 0.96 - 1.00; chunks of 9 to 64 queries d = 64 0.79 - 0.88, d = 128 0.82 - 0.91, d = 256 0.86 - 0.95; with every
-// list unusable 0.97 - 1.37.  (At 20k to 25k tokens 0.88 - 0.97 as well, but tests hold calls of up to 25000 tokens to the narrower rule that
-// was drawn for one workgroup per compute unit: chunks of queries that fill rounds of 256.)
+// list unusable 0.97 - 1.37.  9k to 25k tokens: batches 0.81 - 1.01 (geometric mean 0.95), chunks of 25k 0.82 - 1.02 (0.90), and shorter chunks of more
+// than 16384 tokens, which are filtered where the lists are taken here, 0.40 - 0.74 of the general path's time.
 static int attend_list_shares(const topk_attn_t* h, const Shape& s, int64_t nmax) {
     if (h->force_redo == 2 || (int64_t)s.k + s.window > kAttendRows) return 0;
     if ((int64_t)s.window * s.D * 2 > kAttendWindowBytes) return 0;
     if (make_plan(nmax, s.k < nmax ? s.k : (int)nmax, s.indexed).c_hi > kAttendList) return 0;
     const int64_t heads = (int64_t)s.B * s.Hq;
-    if (heads > kAttendManyHeads && nmax <= kAttendManyMinN) {
-        const int64_t fewest = s.D <= 64 ? 384 : 480, most = s.D <= 64 ? 768 : 512;
-        if (s.M == 1 || s.tail_wgs < 4 || heads < fewest || heads > most) return 0;
-    }
     int64_t shares = std::max<int64_t>(1, kAttendManyHeads / heads);
     shares = std::min<int64_t>(std::min<int64_t>(shares, kAttendShares), s.n_chunk_cap);
     return nmax <= kAttendShareKeys * shares ? (int)shares : 0;

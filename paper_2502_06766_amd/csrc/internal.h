@@ -238,7 +238,6 @@ constexpr int64_t kAttendWindowBytes = 640 << 10;
 constexpr uint32_t kArrivalUnit = 256;    // the flag word counts a head's workgroups above its flag bits
 // More heads than this fill the chip with one workgroup each: small workgroups, several to a compute unit, for short rows.
 constexpr int64_t kAttendManyHeads = 256;
-constexpr int64_t kAttendManyMinN = 25600;       // tokens from which candidate lists of more heads than that take one launch whatever their number
 // Value rows a workgroup over score rows of up to Nmax scores holds: 0 where the rows are too long.
 inline int attend_row_rows(int64_t heads, int64_t Nmax) {
     if (Nmax > kAttendRowMax || heads > 8 * kAttendManyHeads) return 0;     // (thousands of heads: the waves of the two kernels overlap as well)
