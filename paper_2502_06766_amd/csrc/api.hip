@@ -1138,9 +1138,10 @@ int topk_attn_last_selection_records(topk_attn_t* h, uint32_t* records) {
 int topk_attn_debug_read_workspace(topk_attn_t* h, const char* name, void* dst, size_t bytes) {
     if (!h || !name || !dst) return TOPK_ATTN_EINVAL;
     const WsLayout& w = h->ws;
+    const size_t per_seg = 4 * (size_t)h->last_n_seg;        // (these arrays hold the segments the call used, head after head)
     const struct { const char* name; size_t at, end, per_head; } arrays[] = {
-        {"thr", w.thr, w.bins, 4}, {"bins", w.bins, w.samp, 8}, {"samp", w.samp, w.seg_cnt, 4 * kSampMax}, {"seg_cnt", w.seg_cnt, w.seg_max, 4 * kMaxSeg},
-        {"seg_max", w.seg_max, w.seg_cnt2, 4 * kMaxSeg}, {"seg_cnt2", w.seg_cnt2, w.flags, 4 * kMaxSeg}, {"flags", w.flags, w.hmax, 4},
+        {"thr", w.thr, w.bins, 4}, {"bins", w.bins, w.samp, 8}, {"samp", w.samp, w.seg_cnt, 4 * kSampMax}, {"seg_cnt", w.seg_cnt, w.seg_max, per_seg},
+        {"seg_max", w.seg_max, w.seg_cnt2, per_seg}, {"seg_cnt2", w.seg_cnt2, w.flags, per_seg}, {"flags", w.flags, w.hmax, 4},
         {"tailrec", w.tailrec, w.page_mask, 16}, {"page_mask", w.page_mask, w.page_cnt, 0}, {"page_cnt", w.page_cnt, w.page_list, 0},
         {"page_list", w.page_list, w.hist, 0}, {"hist", w.hist, w.cand, (size_t)w.hist_cap * kTailBins * 4},
         {"cand", w.cand, w.bnd, (size_t)w.cand_cap * 8}, {"bnd", w.bnd, w.scores, (size_t)w.bnd_cap * 8}};

@@ -1,5 +1,6 @@
 """Layers of one topk_attn_decode_layers call share their launches: every output is bit for bit that of a call per layer
 (which the other tests judge against the oracle), whatever path the layers take and however many of them join."""
+import numpy as np
 import pytest
 import torch
 
@@ -141,6 +142,38 @@ def test_value_rows_that_were_not_selected_are_not_read(L, Hq, Hkv, d, ks, bad):
             ta.topk_attn_decode_layers(cache.h, 0, ks, q.data_ptr(), 0, out.data_ptr(), stream=torch.cuda.current_stream().cuda_stream)
             torch.cuda.synchronize()
             assert torch.equal(out, single)
+    finally:
+        cache.close()
+
+
+def test_workspace_arrays_after_a_joined_call():
+    """What a joined call leaves for its last layer is what that layer leaves alone."""
+    L, Hq, Hkv, d, N, k = 4, 8, 2, 64, 30000, 300
+    cache = ta.TopkAttnCache(L, 1, Hq, Hkv, d, N, k, wl.F16)
+    try:
+        g = torch.Generator(device=DEV)
+        g.manual_seed(5)
+        for l in range(L):
+            K, V = (torch.randn((Hkv, N, d), generator=g, device=DEV).half() for _ in range(2))
+            cache.append(l, 0, K, V, head_major=True)
+        q = torch.randn((L, 1, Hq, d), generator=g, device=DEV).half()
+        out = torch.empty((L, 1, Hq, d), device=DEV)
+
+        def arrays():
+            torch.cuda.synchronize()
+            n_seg = ta.topk_attn_debug_read_workspace_dims(cache.h)[4]
+            assert 0 < n_seg < 1024
+            read = {n: ta.topk_attn_debug_read_workspace(cache.h, n, np.uint32, n_seg * Hq) for n in ("seg_cnt", "seg_max")}
+            read["thr"] = ta.topk_attn_debug_read_workspace(cache.h, "thr", np.uint32, Hq)
+            return read, ta.topk_attn_last_selection_records(cache.h, Hq)
+
+        cache.decode(L - 1, q[L - 1], k)
+        alone = arrays()
+        ta.topk_attn_decode_layers(cache.h, 0, [k] * L, q.data_ptr(), 0, out.data_ptr(), stream=torch.cuda.current_stream().cuda_stream)
+        joined = arrays()
+        assert joined[1] == alone[1]
+        for name in alone[0]:
+            assert (joined[0][name] == alone[0][name]).all(), name
     finally:
         cache.close()
 
