@@ -35,8 +35,9 @@ int topk_attn_last_pages_read(topk_attn_t* h, int64_t* pages_read, int64_t* page
  * score row, 2 if there was nothing to search, with the head's flag word in bits 8 and up (bit 8: its
  * sequence cannot be filtered, bit 9: the keys sorted again did not fit either, bit 10: forced redo); [4 i + 1] = keys
  * selected for certain (score bins above the one the k-th score falls in); [4 i + 2] = keys still to pick
- * from that bin; [4 i + 3] = candidates in that bin.  (Lists that the one-launch selection takes as they are read: all
- * of k are reported as certain, 0 as still to pick, and the candidates of the bin.)  `records` is a host array of 4 * n_seqs * n_q_heads
+ * from that bin; [4 i + 3] = candidates in that bin.  (Lists that the one-launch selection takes as they are, whatever
+ * their length: all of k are reported as certain, 0 as still to pick, and the candidates of the bin.  That tells them from lists of
+ * the chip-wide selection and from keys scored again.)  `records` is a host array of 4 * n_seqs * n_q_heads
  * words, times the queries per sequence of that decode.  TOPK_ATTN_EINVAL if the last decode took another path.  Copies device->host (synchronous). */
 int topk_attn_last_selection_records(topk_attn_t* h, uint32_t* records);
 

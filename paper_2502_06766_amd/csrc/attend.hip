@@ -837,9 +837,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
         __syncthreads();
         for (int o = tid; o < k_eff; o += NT) rows_lds[o] = ((uint64_t)__float_as_uint(vals[o]) << 32) | (uint64_t)(uint32_t)idx[o];
     }
-    if (tid == 0 && writer) {                             // the head's record (of a short list: all winners found, the size of bin B)
+    if (tid == 0 && writer) {                             // the head's record (of a list taken as it is: all winners found, the size of bin B)
         uint32_t* const rec = bf.tailrec + 4 * bh;
-        const bool sel = how != SCORE_ROW && k_eff > 0, found = how == LIST && total <= (uint32_t)kAttendList;
+        const bool sel = how != SCORE_ROW && k_eff > 0, found = how == LIST;
         rec[0] = k_eff == 0 ? 2u : sel ? 0u : 1u;
         rec[1] = sel ? (found ? (uint32_t)k_eff : above) : 0u;
         rec[2] = sel && !found ? (uint32_t)k_eff - above : 0u;

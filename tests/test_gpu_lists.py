@@ -353,6 +353,8 @@ def test_many_tied_candidates_fit_the_list():
         dims = ta.topk_attn_debug_read_workspace_dims(cache.h)
         cnt = ta.topk_attn_debug_read_workspace(cache.h, "seg_cnt", np.uint32, dims[4] * B * Hq).reshape(B, Hq, dims[4])
         assert (cnt[3].sum(1) >= 39000).all() and cnt[3].max() <= dims[5]
+        rec = ta.topk_attn_last_selection_records(cache.h, B * Hq)       # (lists of any length are reported alike)
+        assert all(r[0] == 0 and r[1] == k and r[2] == 0 for r in rec)
         check_exact(tuple(t[3].cpu().numpy() for t in res), q, K, V, wl.F16, k, True, 0, "tied")
     finally:
         cache.close()
