@@ -238,8 +238,8 @@ int topk_attn_k_schedule(int64_t total_k, int n_layers, double last_over_first, 
  *   idx / vals  device or NULL: ragged concatenation, layer l's [B, Hq, k[l]] block starts
  *         at element B * Hq * (k[0] + ... + k[l-1])
  *   lse   device [n_layers, B, Hq] or NULL
- * Errors as topk_attn_decode_window for any layer; nothing is enqueued unless all layers
- * pass the checks. */
+ * Errors as topk_attn_decode_window for any layer, ENOMEM (host memory for the layers' plans); nothing is enqueued
+ * unless all layers pass the checks. */
 int topk_attn_decode_layers(topk_attn_t* h, int layer0, int n_layers, const void* q, const int32_t* k,
                             int window, float* out, int32_t* idx, float* vals, float* lse,
                             void* hip_stream);

@@ -6,6 +6,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <utility>
@@ -1003,7 +1004,8 @@ int topk_attn_decode_layers(topk_attn_t* h, int layer0, int n_layers, const void
     const size_t BH = (size_t)h->cfg.n_seqs * h->cfg.n_q_heads;
     const size_t q_step = BH * h->cfg.head_dim * elem_bytes(h->cfg.dtype);
     size_t sel_off = 0;
-    std::vector<Call> calls((size_t)n_layers);
+    std::unique_ptr<Call[]> calls(new (std::nothrow) Call[(size_t)n_layers]);     // (no exception may leave a C entry)
+    if (!calls) return TOPK_ATTN_ENOMEM;
     for (int l = 0; l < n_layers; ++l) {
         const int rc = plan_call(h, layer0 + l, static_cast<const char*>(q) + l * q_step, 1, 0, k[l], window,
                                  out + l * BH * h->cfg.head_dim, idx ? idx + sel_off : nullptr,
