@@ -11,8 +11,8 @@
 // What bounds it: a chain of trips to memory and barriers of one compute unit per head, so everything a phase needs is asked for
 // ahead, scores stay in registers with slots nobody uses skipped uniformly (the same phases as rolled loops over LDS: 23.6 us
 // against 14.5 at 16k tokens) and scans and reductions run in the vector unit instead of trips through LDS.  Measured, 32
-// heads, 8 KV heads: a row of 16k scores, k = 256: 14.6 us (radix select + gather: 18.7 + 7.9); a list at 128k tokens, k = 2048:
-// 17.7 us (chip-wide tail: 14.5 + 9.6 us and a launch more); 512 heads (16 queries) at 128k tokens 54.8 us.
+// heads, 8 KV heads: a row of 16k scores, k = 256: 13.2 us (radix select + gather: 18.7 + 7.9); a list at 128k tokens, k = 2048:
+// 17.1 us (chip-wide tail: 14.5 + 9.6 us and a launch more); 512 heads (16 queries) at 128k tokens 51.0 us.
 //
 //   attend_kernel        the scores of a short cache, stored by the scan (general path)
 //   attend_list_kernel   the candidate list the filtered scan left (what becomes of one that is unusable: below)
@@ -435,7 +435,7 @@ __global__ void __launch_bounds__(Cfg::NT) __attribute__((amdgpu_waves_per_eu(4)
 // entries 2.4, places 1.3, emission and ranking 2.3, rows and sum 3.5, the shares' exchange 2.0.  The list stays in registers, not in
 // LDS, so that two workgroups of 512 threads share a compute unit where there are more than 256.  A first version put the list into
 // LDS, found its range, binned it again and split the k-th score's bin (nine barriers, one workgroup per compute unit): 32 heads
-// at 128k tokens 19.1 us and 17.7 now, 64 heads with a window 27.4 and 24.7, 512 heads 66.9 and 54.8.
+// at 128k tokens 19.1 us and 17.1 now, 64 heads with a window 27.4 and 24.7, 512 heads 66.9 and 51.0.
 template <int DT, int NT, int D>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) attend_list_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
     constexpr int NW = NT / kWave, EPL = 8, LPR = D / EPL, RPW = kWave / LPR;
@@ -874,7 +874,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
     constexpr int STEP = NW * RPW, SU = 2;
     if (share1 - share0 > 1 && NT == 1024 && n_rows <= SU * STEP * shares) {       // (uniform)
         // several short shares: the rows of all of them are asked for before the first is added up (one after the other, each
-        // share was a trip to memory: 8 shares of 96 rows on each of 256 heads 38 us for the kernel, 29 like this)
+        // share was a trip to memory: 8 shares of 96 rows on each of 256 heads 38 us for the kernel, 29 like this; two rows a lane and
+        // share are what the registers hold)
         const int rs = lane / LPR, c = lane % LPR;
         u32x4 raw[kAttendShares][SU];
         float w[kAttendShares][SU];
@@ -970,7 +971,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) at
 // for the keys), so winners and ties are counted and placed without a branch, the weights follow for 64 winners at a time,
 // and twice the rows are in flight.  ROW: scores of the longest sequence.  192 sequences of 2048 .. 4096 tokens, k = 128 (1.2 GB of
 // keys, 0.2 GB of value rows): scan with stored scores, radix select and gather 277 + 70 + 42 us, first version of this kernel
-// 310, now 293.  (One workgroup per compute unit whose waves score one stream while others select for the one before: 371.)
+// 310, now 295.  (One workgroup per compute unit whose waves score one stream while others select for the one before: 371.)
 constexpr int kShortBins = 256;
 template <int DT, int D, int ROW>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2)))
