@@ -1009,13 +1009,9 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
                 }
             }
         };
-        const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
-        const int64_t rest = walk_tiles<ScanPipelined<D>::value>(wave, N / 64, 4, ba, bb,
-            [&](TileB& t, int64_t ti) { tile_load_full<DT, D>(Kh + ti * (64 * D * 2), lane_off, t.b); }, use);
-        if (rest * 64 < N) {                              // the tile the end of the sequence cuts short
-            tile_load<DT, D>(Kh, [&](int slot) { const int64_t p = rest * 64 + slot; return p < N ? p : (int64_t)(N - 1); }, ba.b);
-            use(ba, rest);
-        }
+        const LaneOffsets lane_off = lane_offsets<D>();
+        walk_tiles<ScanPipelined<D>::value, true>(wave, (N + 63) / 64, 4, ba, bb,
+            [&](TileB& t, int64_t ti) { tile_load_at<DT, D>(Kh, ti, N, lane_off, t.b); }, use);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const float lo = wave_min(lo4[r]), hi = wave_max(hi4[r]);

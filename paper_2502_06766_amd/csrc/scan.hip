@@ -93,10 +93,11 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     // candidates of this workgroup per score bin and head (the tail sorts them by bin)
     __shared__ uint32_t hist_lds[MODE == MODE_FILTER ? 4 * kTailBins : 1];
     struct TileB { v8 b[4][D / 32]; } ba, bb;
-    const uint32_t lane_off = (uint32_t)(((lane & 15) * D + (lane >> 4) * 8) * 2);
-    // filter: one tile per row of n_seg tiles, the rows in which it is a whole one; the first is asked for ahead of the thresholds
-    const int64_t rows_whole = MODE == MODE_FILTER ? seg_whole(N / 64, sid, n_seg) : 0;
-    auto load_seg = [&](TileB& t, int64_t i) { tile_load_full<DT, D>(Kh + seg_tile(i, sid, n_seg) * (64 * D * 2), lane_off, t.b); };
+    const LaneOffsets lane_off = lane_offsets<D>();
+    // filter: one tile per row of n_seg tiles; the first is asked for ahead of the thresholds
+    const int64_t rows_mine = MODE == MODE_FILTER ? seg_rows((N + 63) / 64, sid, n_seg) : 0;
+    auto load_at = [&](TileB& t, int64_t ti) { tile_load_at<DT, D>(Kh, ti, N, lane_off, t.b); };
+    auto load_seg = [&](TileB& t, int64_t i) { load_at(t, seg_tile(i, sid, n_seg)); };
     constexpr bool kAhead = MODE == MODE_FILTER && !PAGED && ScanPipelined<D>::value;
     if (MODE == MODE_FILTER) {
         for (int i = threadIdx.x; i < 4 * kTailBins; i += kScanWaves * kWave) hist_lds[i] = 0;
@@ -111,7 +112,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
 #pragma unroll
             for (int u = 0; u < CPT; ++u)
                 sv[u] = mine && u * kWave < pl.n_samp ? bf.samp[bh * sh.samp_cap + u * kWave + lane] : 0.f;
-            if (kAhead && rows_whole > 0) load_seg(ba, 0);
+            if (kAhead && rows_mine > 0) load_seg(ba, 0);
             __builtin_amdgcn_sched_barrier(0);
             if (mine) {
                 for (int u = lane; u < kThrBins; u += kWave) thr_sm[wave].hist[u] = 0;
@@ -133,7 +134,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
             if (1 < G) { thr1 = bf.thr[head0 + 1]; lo1 = bins[2]; iw1 = bins[3]; }
             if (2 < G) { thr2 = bf.thr[head0 + 2]; lo2 = bins[4]; iw2 = bins[5]; }
             if (3 < G) { thr3 = bf.thr[head0 + 3]; lo3 = bins[6]; iw3 = bins[7]; }
-            if (kAhead && rows_whole > 0) load_seg(ba, 0);
+            if (kAhead && rows_mine > 0) load_seg(ba, 0);
             __syncthreads();
         }
     }
@@ -173,7 +174,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     auto load_rows = [&](TileB& t, int64_t ti) { tile_load<DT, D>(Kh, [&](int slot) { return row_of(ti * 64, slot); }, t.b); };
     auto use = [&](TileB& t, int64_t ti) { consume(tile_mac<DT, D>(t.b, qa), ti * 64); };
     if (MODE == MODE_SAMPLE) {
-        walk_tiles<ScanPipelined<D>::value>(tile, tile_end, tile_step, ba, bb, load_rows, use);
+        walk_tiles<ScanPipelined<D>::value, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
     } else if (MODE == MODE_FILTER && PAGED) {
         // The pages kept, ascending, are dealt to the wave segments by rank like the tiles of the plain scan
         // (seg_tile() over ranks; 64 rows looked up at a time, one per lane), so every wave reads as many
@@ -182,7 +183,6 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         const int64_t stream = (int64_t)b * sh.Hkv + kvh;
         const int32_t* plist = bf.page_list + stream * (int64_t)sh.page_words * 64;
         const int64_t n_kept = (int64_t)bf.page_cnt[stream];
-        const int64_t n_whole = N / 64;
         const int64_t rows = (n_kept + n_seg - 1) / n_seg;      // rows of n_seg ranks; the last one may be short
         int64_t base = 0;                        // first row of the current group of 64
         int32_t mine = 0;                        // lane i: page whose rank is this segment's in row base + i
@@ -205,23 +205,20 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
             m &= m - 1ull;
             return (int64_t)__builtin_amdgcn_readlane(mine, bit);
         };
-        auto load_any = [&](TileB& t, int64_t ti) {
-            if (ti < n_whole) tile_load_full<DT, D>(Kh + ti * (64 * D * 2), lane_off, t.b);
-            else load_rows(t, ti);
-        };
+        const int64_t past = (N + 63) / 64;      // (a tile of which nothing is read)
         if (rows > 0) {
             int64_t t0 = next();
             if (ScanPipelined<D>::value) {
                 if (t0 >= 0) {
-                    load_any(ba, t0);
+                    load_at(ba, t0);
                     while (true) {
                         const int64_t t1 = next();
-                        load_any(bb, t1 >= 0 ? t1 : t0);       // past the end: a tile the wave already had
+                        load_at(bb, t1 >= 0 ? t1 : past);
                         __builtin_amdgcn_sched_barrier(0);
                         use(ba, t0);
                         if (t1 < 0) break;
                         const int64_t t2 = next();
-                        load_any(ba, t2 >= 0 ? t2 : t1);
+                        load_at(ba, t2 >= 0 ? t2 : past);
                         __builtin_amdgcn_sched_barrier(0);
                         use(bb, t1);
                         if (t2 < 0) break;
@@ -230,7 +227,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
                 }
             } else {
                 for (; t0 >= 0; t0 = next()) {
-                    load_any(ba, t0);
+                    load_at(ba, t0);
                     __builtin_amdgcn_sched_barrier(0);
                     use(ba, t0);
                 }
@@ -238,24 +235,14 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     } else {
         if (MODE == MODE_FULL) {
-            // whole tiles first, then the one tile (if any) that the end of the cache cuts short
-            const int64_t n_whole = N / 64;
-            tile = walk_tiles<ScanPipelined<D>::value>(tile, tile_end < n_whole ? tile_end : n_whole, tile_step, ba, bb,
-                              [&](TileB& t, int64_t ti) { tile_load_full<DT, D>(Kh + ti * (64 * D * 2), lane_off, t.b); }, use);
-            for (; tile < tile_end; tile += tile_step) {
-                load_rows(ba, tile);
-                use(ba, tile);
-            }
+            walk_tiles<ScanPipelined<D>::value, true>(tile, tile_end, tile_step, ba, bb,
+                [&](TileB& t, int64_t ti) { tile_load_at<DT, D>(Kh, ti, ti < tile_end ? N : 0, lane_off, t.b); }, use);
         }
     }
     if (MODE == MODE_FILTER) {
         if (!PAGED) {
-            walk_tiles<ScanPipelined<D>::value, kAhead>(0, rows_whole, 1, ba, bb, load_seg,
+            walk_tiles<ScanPipelined<D>::value, true, kAhead>(0, rows_mine, 1, ba, bb, load_seg,
                 [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid, n_seg)); });
-            if (N % 64 != 0 && seg_tile(N / 64 / n_seg, sid, n_seg) == N / 64) {      // the tile the end of the cache cuts short
-                load_rows(ba, N / 64);
-                use(ba, N / 64);
-            }
         }
         stage_flush(cs0, seg_cap, n_seg, true);
         if (1 < G) stage_flush(cs1, seg_cap, n_seg, true);
@@ -571,30 +558,19 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         consume(c, ti * 64);
     };
     if (MODE == MODE_SAMPLE) {
-        walk_tiles<ScanPipelined<D>::value>(tile, tile_end, tile_step, ba, bb, load_rows, use);
+        walk_tiles<ScanPipelined<D>::value, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
     } else if (MODE == MODE_FILTER) {
-        // one tile per row of n_seg tiles (seg_tile()): the whole ones, then the one (if the wave has it) that the end of the
-        // cache cuts short
+        // one tile per row of n_seg tiles (seg_tile())
         const int n_seg = (int)tile_step;
         const int sid_w = (int)tile;                            // this wave's segment
-        const int64_t rows_whole = seg_whole(N / 64, sid_w, n_seg);
-        const uint32_t lane_off = (uint32_t)((n * D + j * 8) * 2);
-        walk_tiles<ScanPipelined<D>::value>(0, rows_whole, 1, ba, bb,
-            [&](TileB& t, int64_t i) { tile_load_full<DT, D>(Kh + seg_tile(i, sid_w, n_seg) * (64 * D * 2), lane_off, t.b); },
+        const LaneOffsets lane_off = lane_offsets<D>();
+        walk_tiles<ScanPipelined<D>::value, true>(0, seg_rows(tile_end, sid_w, n_seg), 1, ba, bb,
+            [&](TileB& t, int64_t i) { tile_load_at<DT, D>(Kh, seg_tile(i, sid_w, n_seg), N, lane_off, t.b); },
             [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid_w, n_seg)); });
-        if (N % 64 != 0 && seg_tile(N / 64 / n_seg, sid_w, n_seg) == N / 64) {
-            load_rows(ba, N / 64);
-            use(ba, N / 64);
-        }
     } else {
-        const int64_t n_whole = N / 64;
-        const uint32_t lane_off = (uint32_t)((n * D + j * 8) * 2);
-        tile = walk_tiles<ScanPipelined<D>::value>(tile, tile_end < n_whole ? tile_end : n_whole, tile_step, ba, bb,
-                          [&](TileB& t, int64_t ti) { tile_load_full<DT, D>(Kh + ti * (64 * D * 2), lane_off, t.b); }, use);
-        for (; tile < tile_end; tile += tile_step) {
-            load_rows(ba, tile);
-            use(ba, tile);
-        }
+        const LaneOffsets lane_off = lane_offsets<D>();
+        walk_tiles<ScanPipelined<D>::value, true>(tile, tile_end, tile_step, ba, bb,
+            [&](TileB& t, int64_t ti) { tile_load_at<DT, D>(Kh, ti, ti < tile_end ? N : 0, lane_off, t.b); }, use);
     }
     if (MODE == MODE_FILTER) {
 #pragma unroll

@@ -74,10 +74,10 @@ __host__ __device__ inline int64_t seg_tile(int64_t i, int sid, int n_seg) {
     return i * n_seg + (int64_t)(((uint32_t)sid + rot) & (uint32_t)(n_seg - 1));
 }
 
-// Whole tiles (of n_whole) that wave segment `sid` takes: its tiles in rows 0 .. seg_whole() - 1.
-__host__ __device__ inline int64_t seg_whole(int64_t n_whole, int sid, int n_seg) {
-    const int64_t rows = n_whole / n_seg;
-    return rows + (seg_tile(rows, sid, n_seg) < n_whole ? 1 : 0);
+// Tiles (of n_tiles) that wave segment `sid` takes: its tiles in rows 0 .. seg_rows() - 1.
+__host__ __device__ inline int64_t seg_rows(int64_t n_tiles, int sid, int n_seg) {
+    const int64_t rows = n_tiles / n_seg;
+    return rows + (seg_tile(rows, sid, n_seg) < n_tiles ? 1 : 0);
 }
 
 inline int tiles_per_wave_for(int64_t n_items, int B, int Hkv) {

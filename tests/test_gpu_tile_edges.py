@@ -1,0 +1,49 @@
+"""The tile that the end of a cache cuts short, in every scan over 16-bit keys: rows behind the end (NaN here) are neither read as keys
+nor missed.  Elements of q and K are small integers, so scores are exact in fp32 and the selection has to equal the oracle's."""
+import numpy as np
+import pytest
+import torch
+
+import helpers as H
+from oracle import c_oracle
+from paper_2502_06766_amd import topk_attn as ta
+from paper_2502_06766_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda", 0) if torch.cuda.is_available() else None
+PATHS = {"filter": ta.PATH_FILTER, "full": ta.PATH_FULL, "auto": ta.PATH_AUTO}
+
+
+@pytest.mark.parametrize("d", [32, 64, 128, 256])
+@pytest.mark.parametrize("path,Hq,Hkv,seqs", [
+    ("filter", 4, 1, 1), ("filter", 6, 2, 3), ("filter", 8, 1, 1), ("filter", 20, 1, 2), ("full", 4, 1, 1), ("full", 16, 2, 2), ("auto", 4, 2, 3),
+])
+def test_rows_behind_the_end_of_the_cache(d, path, Hq, Hkv, seqs):
+    g = np.random.default_rng(d + Hq)
+    for n0 in (300, 1983, 5000):                                      # (auto: the one launch over short sequences up to 512)
+        lens = [n0 // 64 * 64 + r for r in (1, 63, 16, 17, 0)]
+        if path == "auto":
+            lens = [n % 448 + 20 for n in lens]
+        for n in (lens if seqs == 1 else [lens]):
+            ns = [n] if seqs == 1 else n[:seqs]
+            k = 20
+            cache = ta.TopkAttnCache(1, seqs, Hq, Hkv, d, max(ns) + 130, k, wl.F16)
+            try:
+                cache.kv.fill_(0xFF)                                  # NaN
+                data = []
+                q = wl.quantize(g.integers(-3, 4, (seqs, Hq, d)).astype(np.float32), wl.F16)
+                for b, nb in enumerate(ns):
+                    K = wl.quantize(g.integers(-8, 9, (Hkv, nb, d)).astype(np.float32), wl.F16)
+                    K[:, -1] = 8 * np.sign(q[b].reshape(Hkv, -1, d)[:, 0])           # the last key is a winner of the group's first head
+                    V = wl.quantize(g.standard_normal((Hkv, nb, d)).astype(np.float32), wl.F16)
+                    cache.append(0, b, H.to_torch(K, wl.F16, DEV), H.to_torch(V, wl.F16, DEV), head_major=True)
+                    data.append((K, V))
+                cache.set_path(PATHS[path])
+                res = cache.decode(0, H.to_torch(q, wl.F16, DEV), k)
+                torch.cuda.synchronize()
+                for b, (K, V) in enumerate(data):
+                    ref = c_oracle.topk_attention(q[b], K, V, wl.F16, k)
+                    H.check_against_oracle(*(r[b].cpu().numpy() for r in res), ref, np.full(Hq, 1e-30), min(k, ns[b]), H.out_tolerance(wl.F16),
+                                           float(np.abs(wl.widen(V, wl.F16)).max()), f"d={d} {path} n={ns[b]}")
+            finally:
+                cache.close()
