@@ -66,6 +66,14 @@ __device__ __forceinline__ void tile_load(const char* Kh, RowFn rowfn, typename 
 // offset is in the lane's register and the instruction, which are what the range check looks at; a scalar offset need not be.)
 // Whole call, cut-short tile in a round of its own and a tile read again at the end / now: 16k tokens, where a wave has one tile,
 // 23.4 / 21.0 us, 8 layers of 48001 tokens (three tiles a wave) 207.7 / 197.3, 192 sequences of 2k to 4k tokens 308.9 / 300.3.
+// Rows of a tile, 0 .. 64, of the n_rows (wave-uniform) there are from its first one on.
+__device__ __forceinline__ uint32_t bounded_rows(int n_rows) {
+    // (two steps: a clamp to a range is a vector instruction, and a descriptor from there a loop over the lanes)
+    const int have = __builtin_amdgcn_readfirstlane(n_rows);
+    uint32_t rows = (uint32_t)(have < 0 ? 0 : have);
+    asm("" : "+s"(rows));
+    return rows > 64u ? 64u : rows;
+}
 struct LaneOffsets { uint32_t g[4]; };
 template <int D>
 __device__ __forceinline__ LaneOffsets lane_offsets() {
@@ -82,11 +90,7 @@ __device__ __forceinline__ void tile_load_rows(const char* tile_base, int n_rows
                                                typename Mfma<DT>::v8 (&b)[4][D / 32]) {
     using v8 = typename Mfma<DT>::v8;
     constexpr int KS = D / 32;
-    // (two steps: a clamp to a range is a vector instruction, and a descriptor from there a loop over the lanes)
-    const int have = __builtin_amdgcn_readfirstlane(n_rows);
-    uint32_t rows = (uint32_t)(have < 0 ? 0 : have);
-    asm("" : "+s"(rows));
-    rows = rows > 64u ? 64u : rows;
+    const uint32_t rows = bounded_rows(n_rows);
     // raw buffer (stride 0), rows * D * 2 bytes long, 32-bit data format
     const __amdgpu_buffer_rsrc_t rsrc =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(tile_base), 0, (int)rows * (D * 2), 0x00020000);

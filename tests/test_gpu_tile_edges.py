@@ -47,3 +47,32 @@ def test_rows_behind_the_end_of_the_cache(d, path, Hq, Hkv, seqs):
                                            float(np.abs(wl.widen(V, wl.F16)).max()), f"d={d} {path} n={ns[b]}")
             finally:
                 cache.close()
+
+
+@pytest.mark.parametrize("d,n", [(64, 20001), (128, 17023), (128, 16448), (256, 17040)])
+def test_codes_behind_the_end_of_the_cache(d, n):
+    """The same through the int8 index (codes of -1 and scales of NaN behind the end): the k keys far above all others, the last
+    one among them, are found."""
+    g = np.random.default_rng(d + n)
+    Hkv, k = 3, 20
+    q = g.integers(1, 4, (Hkv, d)).astype(np.float32) * g.choice([-1.0, 1.0], (Hkv, d)).astype(np.float32)
+    Kf = g.integers(-2, 3, (Hkv, n, d)).astype(np.float32)
+    for h in range(Hkv):
+        pos = np.append(g.permutation(n - 1)[:k - 1], n - 1)
+        for i, p in enumerate(pos):
+            Kf[h, p] = 8 * np.sign(q[h])
+            Kf[h, p, :i] = 0                                          # (scores that differ)
+    q, K = wl.quantize(q, wl.F16), wl.quantize(Kf, wl.F16)
+    V = wl.quantize(g.standard_normal((Hkv, n, d)).astype(np.float32), wl.F16)
+    cache = ta.TopkAttnCache(1, 1, Hkv, Hkv, d, n + 130, k, wl.F16, index_kind=ta.INDEX_INT8)
+    try:
+        cache.kv.fill_(0xFF)
+        cache.append(0, 0, H.to_torch(K, wl.F16, DEV), H.to_torch(V, wl.F16, DEV), head_major=True)
+        cache.set_path(ta.PATH_INDEX)
+        res = cache.decode(0, H.to_torch(q[None], wl.F16, DEV), k)
+        torch.cuda.synchronize()
+        H.check_against_oracle(*(r[0].cpu().numpy() for r in res), c_oracle.topk_attention(q, K, V, wl.F16, k), np.full(Hkv, 1e-30), k,
+                               H.out_tolerance(wl.F16), float(np.abs(wl.widen(V, wl.F16)).max()), f"int8 d={d} n={n}")
+        assert cache.last_fallbacks() == 0
+    finally:
+        cache.close()
