@@ -76,3 +76,28 @@ def test_codes_behind_the_end_of_the_cache(d, n):
         assert cache.last_fallbacks() == 0
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,n,k", [(64, 4, 1, 20001, 16), (64, 2, 2, 33000, 9000), (128, 4, 1, 17023, 1500), (128, 8, 8, 30000, 4000),
+                                          (256, 3, 1, 18000, 3000), (256, 8, 4, 25001, 300)])
+def test_exact_scores_of_coded_candidates(d, Hq, Hkv, n, k):
+    """Segments of a few candidates and of several hundred (rounds of 8 to 32 rows, batches of 64): every score that leaves the
+    index path is the exact product of its row, which integers make the same in any order of the sum."""
+    g = np.random.default_rng(d + n)
+    qi = g.integers(-3, 4, (Hq, d)).astype(np.float32)
+    Ki = g.integers(-8, 9, (Hkv, n, d)).astype(np.float32)
+    q, K = wl.quantize(qi, wl.BF16), wl.quantize(Ki, wl.BF16)
+    V = wl.quantize(g.standard_normal((Hkv, n, d)).astype(np.float32), wl.BF16)
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, n, k, wl.BF16, index_kind=ta.INDEX_INT8)
+    try:
+        cache.append(0, 0, H.to_torch(K, wl.BF16, DEV), H.to_torch(V, wl.BF16, DEV), head_major=True)
+        cache.set_path(ta.PATH_INDEX)
+        _, idx, vals, _ = cache.decode(0, H.to_torch(q[None], wl.BF16, DEV), k)
+        idx, vals = idx[0].cpu().numpy(), vals[0].cpu().numpy()
+        for h in range(Hq):
+            s = Ki[h // (Hq // Hkv)] @ qi[h]                          # (integers below 2^24: exact)
+            assert len(set(idx[h].tolist())) == k
+            assert np.array_equal(vals[h], s[idx[h]])
+            assert np.mean(vals[h] >= np.sort(s)[-k]) > 0.98          # coding noise: 0.4 % of a row's largest element per channel
+    finally:
+        cache.close()
