@@ -18,8 +18,6 @@
 //            a page index the wave reads only the tiles (pages) the index could not rule out
 //   full   : score every key and store the fp32 scores
 // fp32 caches go through a plain FMA kernel (full only).
-#include <type_traits>
-
 #include "device_utils.h"
 #include "internal.h"
 #include "scan_common.h"
@@ -279,12 +277,14 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
 // ---------------------------------------------------------------------------------------
 // LDS staging slots per (wave, row): the 64 entries one step can add on top of the remainder
 // (fewer than kCandChunk entries) an aligned flush leaves behind
-constexpr int kStageRow = 128;
-static_assert(kCandChunk <= 16 && kStageRow >= 64 + kCandChunk, "row stage too small for an aligned flush");
+constexpr int kStageRow = 96;
+static_assert(kCandChunk <= 16 && kStageRow >= 64 + kCandChunk - 1 && kStageRow <= 127, "row stage too small for an aligned flush");
 
 // NT row tiles (16 rows each) share every key tile: NT = 2 halves the passes over the keys for
-// 17..32 rows at the price of one wave per SIMD (512 registers) and 128 KiB of LDS stages,
-// which costs this kernel nothing measurable.
+// 17..32 rows at the price of one wave per SIMD (512 registers) and 96 KiB of LDS stages,
+// which costs this kernel nothing measurable.  (Four row tiles, with stages of 48 entries and two steps of two tiles, halve the
+// passes again but pay it back at one wave per SIMD: 10 to 16 queries, d = 128, 150k tokens and more 0.95 - 1.01 of the time, below and at
+// d = 64 1.0 - 1.13.)
 template <int DT, int D, int MODE, int NT>
 __global__ void __launch_bounds__(kScanWaves* kWave)
 __attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 2 : 1)))
@@ -324,15 +324,15 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     };
     // candidates per score bin (tail_bin()) of each row, counted as they leave the stage
     __shared__ uint32_t hist_lds[MODE == MODE_FILTER ? 16 * NT * kTailBins : 1];
-    if (MODE == MODE_FILTER) {
-        for (int i = threadIdx.x; i < 16 * NT * kTailBins; i += kScanWaves * kWave) hist_lds[i] = 0;
-        __syncthreads();
-    }
     auto prefix_of = [&](int rr) -> int {   // keys row rr searches (0 for rows the block does not have)
         if (rr >= R) return 0;
         const int m = (row0 + rr) / G;
         return (int)prefix_len(Nc - (sh.causal ? M - 1 - m : 0), sh.window);
     };
+    // filter: what a row's lanes need to know of it, worked out once (a division per row and lane was half the prologue)
+    struct Row { float thr, bin_lo, bin_inv; int prefix, head; };
+    __shared__ Row row_lds[MODE == MODE_FILTER ? 16 * NT : 1];
+    __shared__ uint32_t count_lds[MODE == MODE_FILTER ? kScanWaves * 16 * NT : 1];   // candidates appended so far, per wave and row
 
     int64_t n_items = N;
     int stride = 1;
@@ -345,9 +345,9 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     const int64_t n_tiles_all = (n_items + 63) / 64;
     int64_t tile, tile_end, tile_step;
     if (MODE == MODE_FILTER) {
-        tile = (int64_t)bx * kScanWaves + wave;
-        tile_step = (int64_t)gridDim.x * kScanWaves;
-        tile_end = n_tiles_all;
+        tile = 0;                           // (the filter's walk counts rows of n_seg tiles)
+        tile_step = 1;
+        tile_end = 0;
     } else {
         const int64_t tile0 = (int64_t)bx * tiles_per_wave * kScanWaves;
         if (tile0 >= n_tiles_all) return;
@@ -372,64 +372,89 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     }
     const char* Kh = static_cast<const char*>(bf.K) + ((int64_t)bc * sh.Hkv + kvh) * sh.Ncap * (D * 2);
 
-    // the rows this lane owns
-    auto row_at = [&](int x) { return 16 * (x >> 2) + 4 * j + (x & 3); };
-    int vh[X];              // head of each row (a 32-bit index: heads are few)
-    int P[X];
-    float thr[X], top[X];
-    int nl[X], ng[X];       // staged / already appended candidates (uniform over the 16 lanes of the row)
-#pragma unroll
-    for (int x = 0; x < X; ++x) {
-        int rr = row_at(x);
-        asm volatile("" : "+v"(rr));     // the row's bins are read here, not kept in registers across the tile loop
-        vh[x] = (int)head_of(rr < R ? rr : 0);
-        P[x] = prefix_of(rr);
-        thr[x] = (MODE == MODE_FILTER && rr < R) ? bf.thr[vh[x]] : INFINITY;
-        top[x] = -INFINITY;
-        nl[x] = 0;
-        ng[x] = 0;
-    }
+    // filter: one tile per row of n_seg tiles (seg_tile()); the first is asked for ahead of the rows' thresholds
     const int seg_cap = sh.seg_cap, n_seg = sh.n_seg;
     const int sid = bx * kScanWaves + wave;
-    // tail_bin() parameters of each row, a copy per wave (read when the wave's staged candidates are counted)
-    __shared__ float rows_all_lds[MODE == MODE_FILTER ? kScanWaves * 16 * NT * 2 : 1];
-    float* const rows_lds = rows_all_lds + (MODE == MODE_FILTER ? wave * 16 * NT * 2 : 0);
+    struct TileB { v8 b[4][KS]; } ba, bb;
+    const LaneOffsets lane_off = lane_offsets<D>();
+    constexpr bool kAhead = MODE == MODE_FILTER && ScanPipelined<D>::value;
+    const int64_t rows_mine = MODE == MODE_FILTER ? seg_rows(n_tiles_all, sid, n_seg) : 0;
+    auto load_seg = [&](TileB& t, int64_t i) { tile_load_at<DT, D>(Kh, seg_tile(i, sid, n_seg), N, lane_off, t.b); };
+    if (kAhead && rows_mine > 0) {
+        load_seg(ba, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     if (MODE == MODE_FILTER) {
+        for (int i = threadIdx.x; i < 16 * NT * kTailBins; i += kScanWaves * kWave) hist_lds[i] = 0;
+        for (int i = threadIdx.x; i < kScanWaves * 16 * NT; i += kScanWaves * kWave) count_lds[i] = 0;
+        const int rr = threadIdx.x;
+        if (rr < 16 * NT) {
+            const int64_t head = head_of(rr < R ? rr : 0);
+            row_lds[rr] = Row{rr < R ? bf.thr[head] : INFINITY, bf.bins[2 * head], bf.bins[2 * head + 1], prefix_of(rr), (int)head};
+        }
+        __syncthreads();
+    }
+
+    // the rows this lane owns
+    auto row_at = [&](int x) { return 16 * (x >> 2) + 4 * j + (x & 3); };
+    constexpr int XS = MODE == MODE_FILTER ? 1 : X;
+    int vh[XS], P[XS];      // sample, full: head (a 32-bit index: heads are few) and prefix of each row
+    float thr[X], top[X];   // filter
+    uint32_t staged[NT];    // staged candidates of the four rows of a row tile, a byte each (uniform over the 16 lanes of the rows)
 #pragma unroll
-        for (int x = 0; x < X; ++x) {
-            const float2 lw = *reinterpret_cast<const float2*>(bf.bins + 2 * vh[x]);
-            if (n == 0) *reinterpret_cast<float2*>(rows_lds + 2 * row_at(x)) = lw;
+    for (int t = 0; t < NT; ++t) staged[t] = 0;
+#pragma unroll
+    for (int x = 0; x < X; ++x) {
+        const int rr = row_at(x);
+        if constexpr (MODE == MODE_FILTER) {
+            thr[x] = row_lds[rr].thr;
+            top[x] = -INFINITY;
+        } else {
+            vh[x] = (int)head_of(rr < R ? rr : 0);
+            P[x] = prefix_of(rr);
         }
     }
     __shared__ uint64_t stage_lds[MODE == MODE_FILTER ? kScanWaves * 16 * NT * kStageRow : 1];
     uint64_t* const st0 = stage_lds + (MODE == MODE_FILTER ? wave * 16 * NT * kStageRow : 0);
 
+    uint32_t* const count = count_lds + (MODE == MODE_FILTER ? wave * 16 * NT : 0);
     // append the staged candidates of the rows at x (one per lane group) to their segments, up to
-    // the last whole run of kCandChunk entries unless `final` (see stage_flush)
-    auto flush = [&](int x, int& nl_i, int& ng_i, int64_t vh_i, bool final) {
+    // the last whole run of kCandChunk entries unless `final` (see stage_flush); returns how many stay
+    auto flush = [&](int x, int n_staged, bool final) -> int {
         wave_sync();
-        uint64_t* list = bf.cand + vh_i * (int64_t)sh.cand_cap;
-        uint64_t* src = st0 + row_at(x) * kStageRow;
-        const int total = ng_i + nl_i;
-        const int f = (final ? total : (total & ~(kCandChunk - 1))) - ng_i;
-        int rr = row_at(x);
-        asm volatile("" : "+v"(rr));     // the row's bins are read here, not kept in registers across the tile loop
-        const float bin_lo = rows_lds[2 * rr], bin_inv = rows_lds[2 * rr + 1];
+        const int rr = row_at(x);
+        uint64_t* list = bf.cand + row_lds[rr].head * (int64_t)sh.cand_cap;
+        uint64_t* src = st0 + rr * kStageRow;
+        const int n_glob = (int)count[rr];
+        const int total = n_glob + n_staged;
+        const int f = (final ? total : (total & ~(kCandChunk - 1))) - n_glob;
+        const float bin_lo = row_lds[rr].bin_lo, bin_inv = row_lds[rr].bin_inv;
         uint32_t* const hist = hist_lds + rr * kTailBins;
         for (int e = n; e < f; e += 16) {
-            const int slot = ng_i + e;
+            const int slot = n_glob + e;
             const uint64_t ent = src[e];
             if (slot < seg_cap) list[cand_slot(slot, sid, n_seg)] = ent;
             atomicAdd(&hist[tail_bin(__uint_as_float((uint32_t)(ent >> 32)), bin_lo, bin_inv)], 1u);   // also past a full segment
         }
-        const int r = f > 0 ? nl_i - f : nl_i;          // < kCandChunk <= 16 after a flush
+        const int r = f > 0 ? n_staged - f : n_staged;  // < kCandChunk <= 16 after a flush
         const bool mv = f > 0 && n < r;
         const uint64_t keep = mv ? src[f + n] : 0;
         wave_sync();
         if (mv) src[n] = keep;
+        if (f > 0) count[rr] = (uint32_t)(n_glob + f);  // (the same from all 16 lanes)
         wave_sync();
-        if (f > 0) ng_i += f;
-        nl_i = r;
+        return r;
+    };
+    // Rows of the row tile t: those whose stage cannot take `add` more entries (a byte each), or all at the end.  (A loop: the
+    // code of all rows in line, and their heads and counts, would take the registers of the tile loop.)
+    auto flush_rows = [&](int t, uint32_t& have, uint32_t add, bool final) __attribute__((always_inline)) {
+#pragma unroll 1
+        for (int i = 0; i < 4; ++i) {
+            const int n_staged = (int)((have >> (8 * i)) & 0xFFu);
+            const bool want = final || n_staged + (int)((add >> (8 * i)) & 0xFFu) > kStageRow;
+            if (!__ballot(want)) continue;
+            have -= (uint32_t)(n_staged - flush(4 * t + i, n_staged, final)) << (8 * i);
+        }
     };
 
     auto row_of = [&](int64_t item0, int slot) -> int64_t {
@@ -440,79 +465,91 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
         return p < N ? p : N - 1;
     };
-    // Filter step of a tile.  A lane counts its own passing keys of each row slot (at most 4,
-    // one per sub-tile), the counts of four row slots share a register (a byte each: a row has
-    // at most 64 passing keys per tile), and one inclusive scan over the 16 lanes of the row
-    // group (four DPP row shifts) ranks all of them at once: no per-row ballots, no scalar
-    // round trips.  Staged order within a row: by lane, then sub-tile (the selection does not
-    // depend on it).  A lane that has nothing to store for a (row slot, sub-tile) writes to a
-    // scratch slot of its own instead, so the stores need no branches.  WHOLE: the tile lies
-    // inside every row's searched prefix.
+    // Filter step of a tile.  A lane gathers which of its (row, sub-tile) scores pass in one
+    // mask (bit 16 t + 4 i + g), the counts of the four rows of a row tile share a register (a byte each: a row has at most 64
+    // passing keys per tile), and one inclusive scan over the 16 lanes of the rows (four DPP row shifts) ranks all of
+    // them at once.  The few that pass (one per lane for k = N / 64) are then taken bit by bit from a copy of the scores in LDS, which can be
+    // indexed by lane as registers cannot.  Staged order within a row: by lane, then sub-tile (the selection does not depend on it).
+    // What bounds it is instructions (one or two waves per SIMD hide little): a store per score, to a scratch slot for those that do not
+    // pass, took 18 per score, this 11.  Whole call, before / now: 17 queries of 241k tokens, d = 64 279 / 249 us, 32 queries of 27k 75.8 / 67.7,
+    // 5 queries of 95k 60.8 / 52.5, 64 heads over 111k tokens 70.0 / 66.0; 16 queries of 128k, d = 128, whose keys come at the rate of the
+    // L1, 146 / 146.
     const int Pmin = prefix_of(0);      // rows of a block search prefixes that grow with the row
-    __shared__ uint64_t dummy_lds[MODE == MODE_FILTER ? kScanWaves * kWave : 1];
-    uint64_t* const dummy = dummy_lds + (MODE == MODE_FILTER ? threadIdx.x : 0);
-    auto filter = [&](auto whole_tag, const f32x4 (&c)[NT][4], int64_t item0) {
-        constexpr bool WHOLE = decltype(whole_tag)::value;
+    __shared__ f32x4 score_lds[MODE == MODE_FILTER ? kScanWaves * NT * 4 * kWave : 1];
+    f32x4* const my_scores = score_lds + (MODE == MODE_FILTER ? wave * NT * 4 * kWave + lane : 0);
+    auto filter = [&](f32x4 (&c)[NT][4], int64_t item0) __attribute__((always_inline)) {
         const int item_n = (int)item0 + n;              // positions fit 31 bits
-        bool ps[X][4];
-        uint32_t pk[NT];
+        if (item0 + 64 > Pmin) {                        // (uniform) scores beyond a row's prefix become NaN, which no threshold lets through
 #pragma unroll
-        for (int t = 0; t < NT; ++t) pk[t] = 0;
+            for (int x = 0; x < X; ++x) {
+                const int Px = row_lds[row_at(x)].prefix;
 #pragma unroll
-        for (int x = 0; x < X; ++x) {
-            uint32_t cnt = 0;
-            float mx = top[x];
-            const int Px = WHOLE ? 0 : prefix_of(row_at(x));    // (worked out again for the few tiles at the end: a register less per row)
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                const float sc = c[x >> 2][g][x & 3];
-                const bool valid = WHOLE || item_n + 16 * g < Px;
-                if (valid) mx = fmaxf(mx, sc);
-                ps[x][g] = valid && sc >= thr[x];
-                cnt += ps[x][g] ? 1u : 0u;
+                for (int g = 0; g < 4; ++g)
+                    if (item_n + 16 * g >= Px) c[x >> 2][g][x & 3] = NAN;
             }
-            top[x] = mx;
-            pk[x >> 2] |= cnt << (8 * (x & 3));
         }
-        uint32_t anyp = pk[0];
+        uint32_t mask = 0;
 #pragma unroll
-        for (int t = 1; t < NT; ++t) anyp |= pk[t];
-        if (!__ballot(anyp != 0u)) return;              // (uniform) nothing passes anywhere in the tile
-        uint32_t incl[NT], tot[NT];
+        for (int x = X - 1; x >= 0; --x) {
+#pragma unroll
+            for (int g = 3; g >= 0; --g) mask = mask + mask + (c[x >> 2][g][x & 3] >= thr[x] ? 1u : 0u);
+#pragma unroll
+            for (int g = 0; g < 4; ++g) top[x] = fmaxf(top[x], c[x >> 2][g][x & 3]);
+        }
+        if (!__ballot(mask != 0u)) return;              // (uniform) nothing passes anywhere in the tile
 #pragma unroll
         for (int t = 0; t < NT; ++t) {
-            uint32_t v = pk[t];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) my_scores[(t * 4 + g) * kWave] = c[t][g];
+        }
+        uint32_t incl[NT], pk[NT], tot[NT];
+        uint32_t nib = mask - ((mask >> 1) & 0x55555555u);
+        nib = (nib & 0x33333333u) + ((nib >> 2) & 0x33333333u);       // passing scores per row, four bits each
+        bool over = false;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+            uint32_t v = (nib >> (16 * t)) & 0xFFFFu;
+            v = (v | (v << 8)) & 0x00FF00FFu;
+            v = (v | (v << 4)) & 0x0F0F0F0Fu;
+            pk[t] = v;
             v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);   // row_shr:1
             v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);   // row_shr:2
             v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);   // row_shr:4
             v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);   // row_shr:8
             incl[t] = v;
             tot[t] = (uint32_t)__builtin_amdgcn_ds_bpermute((lane | 15) << 2, (int)v);      // the group's last lane
+            // a byte beyond kStageRow sets its top bit (at most kStageRow + 64 + 127 - kStageRow = 191)
+            over |= ((staged[t] + tot[t] + 0x01010101u * (uint32_t)(127 - kStageRow)) & 0x80808080u) != 0u;
         }
-        bool full = false;
+        if (__builtin_expect(__ballot(over) != 0, 0)) {
 #pragma unroll
-        for (int x = 0; x < X; ++x) full |= nl[x] + (int)((tot[x >> 2] >> (8 * (x & 3))) & 0xFFu) > kStageRow;
-        if (__builtin_expect(__ballot(full) != 0, 0)) {
-#pragma unroll
-            for (int x = 0; x < X; ++x)
-                if (__ballot(nl[x] + (int)((tot[x >> 2] >> (8 * (x & 3))) & 0xFFu) > kStageRow))
-                    flush(x, nl[x], ng[x], vh[x], false);
+            for (int t = 0; t < NT; ++t) flush_rows(t, staged[t], tot[t], false);
         }
+        // where a lane's first passing score of each row goes (bytes of staged + incl are >= those of pk: no borrows)
+        uint64_t at = staged[0] + incl[0] - pk[0];
+        if (NT > 1) at |= (uint64_t)(staged[NT - 1] + incl[NT - 1] - pk[NT - 1]) << 32;
 #pragma unroll
-        for (int x = 0; x < X; ++x) {
-            // bytes of incl are >= those of pk: the packed subtraction has no borrows
-            int off = nl[x] + (int)(((incl[x >> 2] - pk[x >> 2]) >> (8 * (x & 3))) & 0xFFu);
-            uint64_t* row_st = st0 + row_at(x) * kStageRow;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                uint64_t* where = ps[x][g] ? row_st + off : dummy;
-                *where = ((uint64_t)__float_as_uint(c[x >> 2][g][x & 3] + 0.0f) << 32) | (uint64_t)(uint32_t)(item_n + 16 * g);
-                off += ps[x][g] ? 1 : 0;
-            }
-            nl[x] += (int)((tot[x >> 2] >> (8 * (x & 3))) & 0xFFu);
+        for (int t = 0; t < NT; ++t) staged[t] += tot[t];
+        // two at a time: their reads of the scores share a trip
+        while (mask) {
+            const int b0 = __builtin_ctz(mask);
+            mask &= mask - 1u;
+            const bool two = mask != 0u;
+            const int b1 = two ? __builtin_ctz(mask) : b0;
+            mask &= mask - 1u;                                        // (0 stays 0)
+            const float* const my = reinterpret_cast<const float*>(my_scores);
+            const float s0 = my[((b0 >> 2 & 4) + (b0 & 3)) * (kWave * 4) + (b0 >> 2 & 3)], s1 = my[((b1 >> 2 & 4) + (b1 & 3)) * (kWave * 4) + (b1 >> 2 & 3)];
+            auto put = [&](int b, float v) __attribute__((always_inline)) {
+                const int x = b >> 2;                                 // 4 t + i
+                const int o = (int)((uint32_t)(at >> (8 * x)) & 0xFFu);
+                at += 1ull << (8 * x);
+                st0[row_at(x) * kStageRow + o] = ((uint64_t)__float_as_uint(v + 0.0f) << 32) | (uint64_t)(uint32_t)(item_n + 16 * (b & 3));
+            };
+            put(b0, s0);
+            if (two) put(b1, s1);
         }
     };
-    auto consume = [&](const f32x4 (&c)[NT][4], int64_t item0) {
+    auto consume = [&](f32x4 (&c)[NT][4], int64_t item0) __attribute__((always_inline)) {
         if (MODE == MODE_SAMPLE) {
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
@@ -534,8 +571,7 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
                     if (item < P[x]) dst[(int64_t)vh[x] * sh.Ncap + item] = c[x >> 2][g][x & 3];
             }
         } else {
-            if (item0 + 64 <= Pmin) filter(std::true_type{}, c, item0);
-            else filter(std::false_type{}, c, item0);
+            filter(c, item0);
         }
     };
     auto mac = [&](const v8 (&b)[4][KS], f32x4 (&c)[NT][4]) {
@@ -550,9 +586,8 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     };
 
-    struct TileB { v8 b[4][KS]; } ba, bb;
     auto load_rows = [&](TileB& t, int64_t ti) { tile_load<DT, D>(Kh, [&](int slot) { return row_of(ti * 64, slot); }, t.b); };
-    auto use = [&](TileB& t, int64_t ti) {
+    auto use = [&](TileB& t, int64_t ti) __attribute__((always_inline)) {
         f32x4 c[NT][4];
         mac(t.b, c);
         consume(c, ti * 64);
@@ -560,31 +595,28 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     if (MODE == MODE_SAMPLE) {
         walk_tiles<ScanPipelined<D>::value, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
     } else if (MODE == MODE_FILTER) {
-        // one tile per row of n_seg tiles (seg_tile())
-        const int n_seg = (int)tile_step;
-        const int sid_w = (int)tile;                            // this wave's segment
-        const LaneOffsets lane_off = lane_offsets<D>();
-        walk_tiles<ScanPipelined<D>::value, true>(0, seg_rows(tile_end, sid_w, n_seg), 1, ba, bb,
-            [&](TileB& t, int64_t i) { tile_load_at<DT, D>(Kh, seg_tile(i, sid_w, n_seg), N, lane_off, t.b); },
-            [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid_w, n_seg)); });
+        walk_tiles<ScanPipelined<D>::value, true, kAhead>(0, rows_mine, 1, ba, bb, load_seg,
+            [&](TileB& t, int64_t i) __attribute__((always_inline)) { use(t, seg_tile(i, sid, n_seg)); });
     } else {
-        const LaneOffsets lane_off = lane_offsets<D>();
         walk_tiles<ScanPipelined<D>::value, true>(tile, tile_end, tile_step, ba, bb,
             [&](TileB& t, int64_t ti) { tile_load_at<DT, D>(Kh, ti, ti < tile_end ? N : 0, lane_off, t.b); }, use);
     }
     if (MODE == MODE_FILTER) {
 #pragma unroll
+        for (int t = 0; t < NT; ++t) flush_rows(t, staged[t], 0u, true);
+#pragma unroll
         for (int i = 0; i < X; ++i) {
-            flush(i, nl[i], ng[i], vh[i], true);
+            const int rr = row_at(i);
             for (int o = 8; o > 0; o >>= 1) top[i] = fmaxf(top[i], wave_xor(top[i], o));
-            if (n == 0 && row_at(i) < R) {
-                bf.seg_cnt[(int64_t)vh[i] * n_seg + sid] = (uint32_t)ng[i];
-                bf.seg_max[(int64_t)vh[i] * n_seg + sid] = top[i];
+            if (n == 0 && rr < R) {
+                const int64_t head = row_lds[rr].head;
+                bf.seg_cnt[head * n_seg + sid] = count[rr];
+                bf.seg_max[head * n_seg + sid] = top[i];
             }
         }
         __syncthreads();
         for (int i = threadIdx.x; i < R * kTailBins; i += kScanWaves * kWave)
-            bf.hist[(head_of(i / kTailBins) * sh.hist_cap + bx) * kTailBins + i % kTailBins] = hist_lds[i];
+            bf.hist[((int64_t)row_lds[i / kTailBins].head * sh.hist_cap + bx) * kTailBins + i % kTailBins] = hist_lds[i];
     }
 }
 

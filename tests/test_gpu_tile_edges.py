@@ -101,3 +101,47 @@ def test_exact_scores_of_coded_candidates(d, Hq, Hkv, n, k):
             assert np.mean(vals[h] >= np.sort(s)[-k]) > 0.98          # coding noise: 0.4 % of a row's largest element per channel
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("M,Hq,Hkv", [(1, 5, 1), (1, 16, 1), (1, 17, 1), (4, 8, 1), (11, 3, 1), (3, 16, 2)])
+@pytest.mark.parametrize("d,n,k,window,keys", [(64, 1991, 40, 0, "equal"), (64, 3000, 700, 9, "runs"), (128, 2049, 5, 0, "runs"), (128, 1983, 1500, 0, "random"),
+                                               (256, 1100, 64, 70, "runs")])
+def test_row_tiles_filter(d, n, k, window, keys, M, Hq, Hkv):
+    """What passes the row-tile filter: everything (tied keys, every lane's mask full and the stages flushed at each tile), runs of
+    64 and more high scores, few; with prefixes of a causal chunk that end within a tile.  Integers, so the selected scores are exact."""
+    g = np.random.default_rng(d + n + Hq)
+    qi = g.integers(1, 4, (M, Hq, d)).astype(np.float32)
+    Ki = g.integers(-8, 9, (Hkv, n, d)).astype(np.float32)
+    if keys == "equal":
+        Ki[:] = Ki[:, :1]
+    elif keys == "runs":
+        for lo in range(100, n - 150, 701):
+            Ki[:, lo:lo + 130] = np.abs(Ki[:, lo:lo + 130])           # (q is positive)
+    q, K = wl.quantize(qi, wl.BF16), wl.quantize(Ki, wl.BF16)
+    V = wl.quantize(g.standard_normal((Hkv, n, d)).astype(np.float32), wl.BF16)
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, n, k, wl.BF16, max_window=window, max_queries=M)
+    try:
+        cache.append(0, 0, H.to_torch(K, wl.BF16, DEV), H.to_torch(V, wl.BF16, DEV), head_major=True)
+        cache.set_path(ta.PATH_FILTER)
+        qd = H.to_torch(q, wl.BF16, DEV)[None].contiguous()
+        if M > 1:
+            out, idx, vals, _ = cache.decode_multi(0, qd, k, causal=True, window=window)
+        else:
+            out, idx, vals, _ = (r[:, None] for r in cache.decode(0, qd[:, 0].contiguous(), k, window=window))
+        out, idx, vals = (r[0].cpu().numpy() for r in (out, idx, vals))
+        Vf = wl.widen(V, wl.BF16).astype(np.float64)
+        for m in range(M):
+            p = n - (M - 1 - m)
+            for h in range(Hq):
+                s = Ki[h // (Hq // Hkv), :p].astype(np.float64) @ qi[m, h]
+                sel = idx[m, h]
+                assert len(set(sel.tolist())) == k and sel.min() >= 0 and sel.max() < p - window
+                assert np.array_equal(vals[m, h], s[sel])
+                assert np.array_equal(np.sort(vals[m, h]), np.sort(s[:p - window])[-k:])
+                pos = np.concatenate([sel, np.arange(p - window, p)])
+                w = np.exp((s[pos] - s[pos].max()) / np.sqrt(d))
+                ref = (w[:, None] * Vf[h // (Hq // Hkv), pos]).sum(0) / w.sum()
+                # sums of up to 1570 terms in 32 bits, weights by a base-2 exponential
+                assert np.abs(out[m, h] - ref).max() < 1e-5 * np.abs(Vf).max()
+    finally:
+        cache.close()
