@@ -385,7 +385,7 @@ scan8_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     else if (MODE == MODE_FULL)
         walk_tiles<true, true>(tile, tile_end, tile_step, ba, bb, [&](TileB& t, int64_t ti) { load_at(t, ti, ti < tile_end ? N : 0); }, use);
     else
-        walk_tiles<true, false>(tile, tile_end, tile_step, ba, bb,
+        walk_tiles<false, false>(tile, tile_end, tile_step, ba, bb,
             [&](TileB& t, int64_t ti) { tile_load8<D>(Kh, Sh, [&](int slot) { return row_of(ti * 64, slot); }, t.b, t.ks); }, use);
     if (MODE == MODE_FILTER) {
         stage_flush(cs0, seg_cap, sh.n_seg, true);

@@ -172,7 +172,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     auto load_rows = [&](TileB& t, int64_t ti) { tile_load<DT, D>(Kh, [&](int slot) { return row_of(ti * 64, slot); }, t.b); };
     auto use = [&](TileB& t, int64_t ti) { consume(tile_mac<DT, D>(t.b, qa), ti * 64); };
     if (MODE == MODE_SAMPLE) {
-        walk_tiles<ScanPipelined<D>::value, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
+        walk_tiles<false, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
     } else if (MODE == MODE_FILTER && PAGED) {
         // The pages kept, ascending, are dealt to the wave segments by rank like the tiles of the plain scan
         // (seg_tile() over ranks; 64 rows looked up at a time, one per lane), so every wave reads as many
@@ -287,7 +287,7 @@ static_assert(kCandChunk <= 16 && kStageRow >= 64 + kCandChunk - 1 && kStageRow 
 // d = 64 1.0 - 1.13.)
 template <int DT, int D, int MODE, int NT>
 __global__ void __launch_bounds__(kScanWaves* kWave)
-__attribute__((amdgpu_waves_per_eu(NT == 1 ? 2 : 1, NT == 1 ? 2 : 1)))
+__attribute__((amdgpu_waves_per_eu(NT == 1 || MODE == MODE_SAMPLE ? 2 : 1, MODE == MODE_SAMPLE ? 8 : NT == 1 ? 2 : 1)))
 scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     using v8 = typename Mfma<DT>::v8;
     constexpr int KS = D / 32;
@@ -593,7 +593,7 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         consume(c, ti * 64);
     };
     if (MODE == MODE_SAMPLE) {
-        walk_tiles<ScanPipelined<D>::value, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
+        walk_tiles<false, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
     } else if (MODE == MODE_FILTER) {
         walk_tiles<ScanPipelined<D>::value, true, kAhead>(0, rows_mine, 1, ba, bb, load_seg,
             [&](TileB& t, int64_t i) __attribute__((always_inline)) { use(t, seg_tile(i, sid, n_seg)); });
