@@ -178,9 +178,61 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         // (seg_tile() over ranks; 64 rows looked up at a time, one per lane), so every wave reads as many
         // tiles as any other.  They are walked like the plain sequence (next tile's loads in flight
         // while the current one is multiplied and filtered; one buffer at head_dim 256).
+        // Every workgroup finds its ranks in the mask itself, by the counts of 256 groups of mask words.  (A launch of one workgroup per
+        // key stream that wrote the list out for the scan took 6.3 us, this costs the scan 3: a million tokens 191.8 -> 185.5 us, calls of 140k to 400k tokens
+        // 1.08 - 1.16 times as fast.)
         const int64_t stream = (int64_t)b * sh.Hkv + kvh;
-        const int32_t* plist = bf.page_list + stream * (int64_t)sh.page_words * 64;
-        const int64_t n_kept = (int64_t)bf.page_cnt[stream];
+        const uint64_t* const words = bf.page_mask + stream * sh.page_words;
+        int32_t* const plist = bf.page_list + stream * (int64_t)sh.page_words * 64;
+        constexpr int kGroups = kScanWaves * kWave;
+        __shared__ uint32_t group_at[kGroups], wave_kept[kScanWaves];       // pages kept in the groups before; per wave
+        __shared__ uint64_t group_word[kGroups];                            // first word of the group
+        const int per_group = (sh.page_words + kGroups - 1) / kGroups;
+        {
+            const int w0 = (int)threadIdx.x * per_group;
+            uint64_t first = 0ull;
+            uint32_t cnt = 0;
+            for (int i = 0; i < per_group; ++i) {
+                const uint64_t word = w0 + i < sh.page_words ? words[w0 + i] : 0ull;
+                if (i == 0) first = word;
+                cnt += (uint32_t)__popcll(word);
+            }
+            const uint32_t inc = wave_scan_add(cnt);
+            if (lane == kWave - 1) wave_kept[wave] = inc;
+            __syncthreads();
+            uint32_t before = inc - cnt;
+            for (int w = 0; w < wave; ++w) before += wave_kept[w];
+            group_at[threadIdx.x] = before;
+            group_word[threadIdx.x] = first;
+            __syncthreads();
+        }
+        const int64_t n_kept = (int64_t)wave_kept[0] + wave_kept[1] + wave_kept[2] + wave_kept[3];
+        static_assert(kScanWaves == 4, "four waves' counts");
+        if (blockIdx.x == 0 && threadIdx.x == 0) bf.page_cnt[stream] = (uint32_t)n_kept;
+        auto page_of = [&](uint32_t rank) -> int32_t {          // rank < n_kept
+            int lo = 0;                                         // the last group that starts at or before the rank holds it
+#pragma unroll
+            for (int step = kGroups / 2; step > 0; step >>= 1)
+                if (group_at[lo + step] <= rank) lo += step;
+            uint32_t rest = rank - group_at[lo];
+            uint64_t word = group_word[lo];
+            int w = lo * per_group;
+            for (uint32_t c = (uint32_t)__popcll(word); rest >= c; c = (uint32_t)__popcll(word)) {
+                rest -= c;
+                word = words[++w];
+            }
+            // its rest-th set bit
+            int bit = 0;
+            uint32_t half = (uint32_t)word;
+            uint32_t c = (uint32_t)__popc(half);
+            if (rest >= c) { rest -= c; half = (uint32_t)(word >> 32); bit = 32; }
+#pragma unroll
+            for (int width = 16; width > 0; width >>= 1) {
+                c = (uint32_t)__popc(half & ((1u << width) - 1u));
+                if (rest >= c) { rest -= c; half >>= width; bit += width; }
+            }
+            return w * 64 + bit;
+        };
         const int64_t rows = (n_kept + n_seg - 1) / n_seg;      // rows of n_seg ranks; the last one may be short
         int64_t base = 0;                        // first row of the current group of 64
         int32_t mine = 0;                        // lane i: page whose rank is this segment's in row base + i
@@ -189,7 +241,11 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
             const int64_t i = base + lane;
             const int64_t r = seg_tile(i, sid, n_seg);
             const bool ok = i < rows && r < n_kept;
-            mine = ok ? plist[r] : 0;
+            mine = 0;
+            if (ok) {
+                mine = page_of((uint32_t)r);
+                plist[r] = mine;
+            }
             m = __ballot(ok);
         };
         if (rows > 0) look_up();

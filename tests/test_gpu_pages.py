@@ -352,3 +352,31 @@ def test_pages_edge_cases_tiny_caches_reset_and_static_scratch():
         assert torch.equal(out, res[0]) and torch.equal(idx, res[1]) and torch.equal(vals, res[2]) and torch.equal(lse, res[3])
     finally:
         cache.close()
+
+
+@pytest.mark.parametrize("N,seqs,Hkv,d,max_tokens", [(1_100_003, 1, 1, 32, 1_100_003), (70_000, 2, 2, 64, 2_200_000), (40_001, 3, 1, 128, 40_001)])
+def test_pages_dealt_by_rank_cover_the_selection(N, seqs, Hkv, d, max_tokens):
+    """Ranks looked up in the page mask: several mask words per group (room for more than a million tokens), words that are empty, one
+    and many rows of ranks.  The selection is that of the plain scan, in no more pages than the mask has."""
+    Hq, k = 2 * Hkv, 700
+    g = torch.Generator(device="cuda").manual_seed(N + d)
+    centres = torch.randn((Hkv, 64, d), generator=g, device="cuda")
+    topic = torch.randint(0, 64, (N // 640 + 1,), generator=g, device="cuda").repeat_interleave(640)[:N]
+    cache = ta.TopkAttnCache(1, seqs, Hq, Hkv, d, max_tokens, k, wl.F16, index_kind=ta.INDEX_PAGES)
+    try:
+        for b in range(seqs):
+            K = (centres[:, topic] + 0.02 * torch.randn((Hkv, N, d), generator=g, device="cuda")).half()
+            V = torch.randn((Hkv, N, d), generator=g, device="cuda").half()
+            cache.append(0, b, K, V, head_major=True)
+        q = (torch.randn((seqs, Hq, d), generator=g, device="cuda") + 0.5 * centres[:, :1].expand(Hkv, 2, d).reshape(1, Hq, d)).half()
+        cache.set_path(ta.PATH_FILTER)
+        plain = cache.decode(0, q, k)
+        cache.set_path(ta.PATH_PAGES)
+        res = cache.decode(0, q, k)
+        torch.cuda.synchronize()
+        read, total = ta.topk_attn_last_pages_read(cache.h)
+        assert 0 < read < total and cache.last_fallbacks() == 0
+        assert torch.equal(torch.sort(res[1], dim=2).values, torch.sort(plain[1], dim=2).values)
+        np.testing.assert_allclose(res[0].cpu().numpy(), plain[0].cpu().numpy(), rtol=2e-5, atol=1e-6)
+    finally:
+        cache.close()
