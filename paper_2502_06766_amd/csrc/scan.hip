@@ -187,13 +187,15 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         constexpr int kGroups = kScanWaves * kWave;
         __shared__ uint32_t group_at[kGroups], wave_kept[kScanWaves];       // pages kept in the groups before; per wave
         __shared__ uint64_t group_word[kGroups];                            // first word of the group
-        const int per_group = (sh.page_words + kGroups - 1) / kGroups;
+        const int n_words = (int)((N + 64 * 64 - 1) / (64 * 64));           // (of the sequence, not of the cache's room)
+        const int per_group = (n_words + kGroups - 1) / kGroups;
         {
             const int w0 = (int)threadIdx.x * per_group;
             uint64_t first = 0ull;
             uint32_t cnt = 0;
+#pragma unroll 4
             for (int i = 0; i < per_group; ++i) {
-                const uint64_t word = w0 + i < sh.page_words ? words[w0 + i] : 0ull;
+                const uint64_t word = w0 + i < n_words ? words[w0 + i] : 0ull;
                 if (i == 0) first = word;
                 cnt += (uint32_t)__popcll(word);
             }
