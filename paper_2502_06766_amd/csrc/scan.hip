@@ -110,7 +110,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
 #pragma unroll
             for (int u = 0; u < CPT; ++u)
                 sv[u] = mine && u * kWave < pl.n_samp ? bf.samp[bh * sh.samp_cap + u * kWave + lane] : 0.f;
-            if (kAhead && rows_mine > 0) load_seg(ba, 0);
+            if (kAhead) load_seg(ba, 0);                             // (without a tile for this wave it reads nothing)
             __builtin_amdgcn_sched_barrier(0);
             if (mine) {
                 for (int u = lane; u < kThrBins; u += kWave) thr_sm[wave].hist[u] = 0;
@@ -120,7 +120,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
                     if (blockIdx.x == 0) leave_threshold(bf, bh, t, N > 0 ? threshold_flags(sh, pl, N) : 0u);
                 }
             }
-            __syncthreads();
+            lds_barrier();
             auto uni = [](float x) { return __uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x))); };
             thr0 = uni(thr_lds[0][0]); lo0 = uni(thr_lds[0][1]); iw0 = uni(thr_lds[0][2]);
             if (1 < G) { thr1 = uni(thr_lds[1][0]); lo1 = uni(thr_lds[1][1]); iw1 = uni(thr_lds[1][2]); }
@@ -132,8 +132,8 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
             if (1 < G) { thr1 = bf.thr[head0 + 1]; lo1 = bins[2]; iw1 = bins[3]; }
             if (2 < G) { thr2 = bf.thr[head0 + 2]; lo2 = bins[4]; iw2 = bins[5]; }
             if (3 < G) { thr3 = bf.thr[head0 + 3]; lo3 = bins[6]; iw3 = bins[7]; }
-            if (kAhead && rows_mine > 0) load_seg(ba, 0);
-            __syncthreads();
+            if (kAhead) load_seg(ba, 0);
+            lds_barrier();
         }
     }
 
@@ -438,19 +438,35 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     constexpr bool kAhead = MODE == MODE_FILTER && ScanPipelined<D>::value;
     const int64_t rows_mine = MODE == MODE_FILTER ? seg_rows(n_tiles_all, sid, n_seg) : 0;
     auto load_seg = [&](TileB& t, int64_t i) { tile_load_at<DT, D>(Kh, seg_tile(i, sid, n_seg), N, lane_off, t.b); };
-    if (kAhead && rows_mine > 0) {
-        load_seg(ba, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    }
     if (MODE == MODE_FILTER) {
-        for (int i = threadIdx.x; i < 16 * NT * kTailBins; i += kScanWaves * kWave) hist_lds[i] = 0;
-        for (int i = threadIdx.x; i < kScanWaves * 16 * NT; i += kScanWaves * kWave) count_lds[i] = 0;
-        const int rr = threadIdx.x;
-        if (rr < 16 * NT) {
+        auto row_of_block = [&](int rr) -> Row {
             const int64_t head = head_of(rr < R ? rr : 0);
-            row_lds[rr] = Row{rr < R ? bf.thr[head] : INFINITY, bf.bins[2 * head], bf.bins[2 * head + 1], prefix_of(rr), (int)head};
+            return Row{rr < R ? bf.thr[head] : INFINITY, bf.bins[2 * head], bf.bins[2 * head + 1], prefix_of(rr), (int)head};
+        };
+        auto clear = [&]() {
+            for (int i = threadIdx.x; i < 16 * NT * kTailBins; i += kScanWaves * kWave) hist_lds[i] = 0;
+            for (int i = threadIdx.x; i < kScanWaves * 16 * NT; i += kScanWaves * kWave) count_lds[i] = 0;
+        };
+        // One row tile, two waves per SIMD: the tile first, the barrier waits for it (64 heads over 200k tokens 111.9 us per call, 112.5 the
+        // other way).  Two row tiles, one wave per SIMD: the rows' loads first, as loads return in order, and a barrier that does not wait for the
+        // tile (16 queries of 128k tokens 144.4, 145.9 the other way; 8 queries of 262k 175.9 and 177.5).
+        if constexpr (NT == 1) {
+            if (kAhead && rows_mine > 0) {
+                load_seg(ba, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            clear();
+            if (threadIdx.x < 16 * NT) row_lds[threadIdx.x] = row_of_block(threadIdx.x);
+            __syncthreads();
+        } else {
+            const Row row = row_of_block(threadIdx.x < 16 * NT ? threadIdx.x : 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (kAhead) load_seg(ba, 0);        // (without a tile for this wave it reads nothing)
+            __builtin_amdgcn_sched_barrier(0);
+            clear();
+            if (threadIdx.x < 16 * NT) row_lds[threadIdx.x] = row;
+            lds_barrier();
         }
-        __syncthreads();
     }
 
     // the rows this lane owns
