@@ -182,8 +182,7 @@ __global__ void __launch_bounds__(kTailThreads) tail_gather_kernel(Shape sh, Buf
     {
         const uint32_t* hp = bf.hist + bh * (int64_t)sh.hist_cap * kTailBins;
         const int bin = tid & (kTailBins - 1), part = tid >> 6;      // kTailBins == kWave: one wave per part
-        // (sixteen, all of them at 64 scan workgroups, in one trip to memory; eight at a time a million tokens took 417.9 us per call, now 415.8)
-#pragma unroll 16
+#pragma unroll 8
         for (int j = part; j < n_wg; j += kTailWaves) {
             const uint32_t c = hp[j * kTailBins + bin];
             h_all += c;
