@@ -44,7 +44,8 @@ int topk_attn_last_selection_records(topk_attn_t* h, uint32_t* records);
 /* After the caller has synchronised the stream: copies the first `bytes` bytes of one of the per-call arrays of
  * the handle's workspace to the host array `dst` (for tests that look at what a decode left behind).  Names:
  * "thr", "bins", "samp", "seg_cnt", "seg_max", "seg_cnt2", "flags", "tailrec", "page_mask", "page_cnt",
- * "page_list", "hist", "cand", "bnd".  ("flags": the flag bits of the records below bit 8, above them how many workgroups of
+ * "page_list", "hist", "cand", "bnd".  ("page_list", "page_cnt": the pages that the scan looked up in "page_mask" and their number, per key
+ * stream, 64 entries per mask word; no kernel reads them, they are there to be held against the mask.  "flags": the flag bits of the records below bit 8, above them how many workgroups of
  * the one-launch selection have handed over their part of the head.)  EINVAL for another name or more bytes than the array holds.  The second call
  * reports dims[0..5] = entries per candidate list, entries per boundary list, scan workgroups the per-bin counts
  * have room for, most wave segments per head, and the wave segments and entries per segment of the last

@@ -178,50 +178,83 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         // (seg_tile() over ranks; 64 rows looked up at a time, one per lane), so every wave reads as many
         // tiles as any other.  They are walked like the plain sequence (next tile's loads in flight
         // while the current one is multiplied and filtered; one buffer at head_dim 256).
-        // Every workgroup finds its ranks in the mask itself, by the counts of 256 groups of mask words.  (A launch of one workgroup per
+        // Every workgroup finds its ranks in the mask itself, by the counts of up to 1024 groups of mask words.  (A launch of one workgroup per
         // key stream that wrote the list out for the scan took 6.3 us, this costs the scan 3: a million tokens 191.8 -> 185.5 us, calls of 140k to 400k tokens
-        // 1.08 - 1.16 times as fast.)
+        // 1.08 - 1.16 times as fast.)  A group is one word up to 4.2 million tokens, and its word stays in LDS; the words of a longer group are
+        // asked for eight at a time when a rank is looked up in it, so that no load waits for another.  (256 groups, walked word after
+        // word: 4 million tokens of one KV head, d = 128 103.6 us per call, now 102.7; 33 million, d = 32 266.4 and 266.2; 2 KV heads of 8 million, d = 64
+        // 321 - 337 and 319 - 327.  With the list launch these took 112.8, 294.2 and 326 - 340.)
         const int64_t stream = (int64_t)b * sh.Hkv + kvh;
         const uint64_t* const words = bf.page_mask + stream * sh.page_words;
         int32_t* const plist = bf.page_list + stream * (int64_t)sh.page_words * 64;
-        constexpr int kGroups = kScanWaves * kWave;
-        __shared__ uint32_t group_at[kGroups], wave_kept[kScanWaves];       // pages kept in the groups before; per wave
+        constexpr int kThreads = kScanWaves * kWave, kGroups = 1024, kRounds = kGroups / kThreads, kParts = kGroups / kWave;
+        __shared__ uint32_t group_at[kGroups], part_kept[kParts];           // pages kept in the groups before; per 64 groups
         __shared__ uint64_t group_word[kGroups];                            // first word of the group
         const int n_words = (int)((N + 64 * 64 - 1) / (64 * 64));           // (of the sequence, not of the cache's room)
         const int per_group = (n_words + kGroups - 1) / kGroups;
+        const int n_groups = n_words > 0 ? (n_words + per_group - 1) / per_group : 0;
+        const int top_step = n_groups > 1 ? 1 << (31 - __builtin_clz(n_groups - 1)) : 0;      // groups 0 .. 2 top_step - 1 are looked at
+        const int n_rounds = top_step > kThreads / 2 ? 2 * top_step / kThreads : 1;
+        uint32_t n_kept;
         {
-            const int w0 = (int)threadIdx.x * per_group;
-            uint64_t first = 0ull;
-            uint32_t cnt = 0;
-#pragma unroll 4
-            for (int i = 0; i < per_group; ++i) {
-                const uint64_t word = w0 + i < n_words ? words[w0 + i] : 0ull;
-                if (i == 0) first = word;
-                cnt += (uint32_t)__popcll(word);
+            uint64_t first[kRounds];
+#pragma unroll
+            for (int u = 0; u < kRounds; ++u) {
+                const int w0 = (u * kThreads + (int)threadIdx.x) * per_group;
+                first[u] = w0 < n_words ? words[w0] : 0ull;
             }
-            const uint32_t inc = wave_scan_add(cnt);
-            if (lane == kWave - 1) wave_kept[wave] = inc;
+#pragma unroll
+            for (int u = 0; u < kRounds; ++u) {
+                if (u >= n_rounds) break;                                   // (uniform)
+                const int g = u * kThreads + (int)threadIdx.x;
+                uint32_t cnt = (uint32_t)__popcll(first[u]);
+                for (int i0 = 1; i0 < per_group; i0 += 8) {                 // (the last ones are asked for together too)
+#pragma unroll
+                    for (int i = i0; i < i0 + 8; ++i)
+                        cnt += i < per_group && g * per_group + i < n_words ? (uint32_t)__popcll(words[g * per_group + i]) : 0u;
+                }
+                const uint32_t inc = wave_scan_add(cnt);
+                if (lane == kWave - 1) part_kept[g / kWave] = inc;
+                group_at[g] = inc - cnt;
+                group_word[g] = first[u];
+            }
             __syncthreads();
-            uint32_t before = inc - cnt;
-            for (int w = 0; w < wave; ++w) before += wave_kept[w];
-            group_at[threadIdx.x] = before;
-            group_word[threadIdx.x] = first;
+            static_assert(kParts <= kWave, "a lane per part");
+            const uint32_t part = lane < n_rounds * kScanWaves ? part_kept[lane] : 0u;
+            const uint32_t parts = wave_scan_add(part);
+            n_kept = (uint32_t)__builtin_amdgcn_readlane((int)parts, kWave - 1);
+#pragma unroll
+            for (int u = 0; u < kRounds; ++u) {
+                if (u >= n_rounds) break;
+                group_at[u * kThreads + threadIdx.x] += (uint32_t)__builtin_amdgcn_readlane((int)(parts - part), u * kScanWaves + wave);
+            }
             __syncthreads();
         }
-        const int64_t n_kept = (int64_t)wave_kept[0] + wave_kept[1] + wave_kept[2] + wave_kept[3];
-        static_assert(kScanWaves == 4, "four waves' counts");
-        if (blockIdx.x == 0 && threadIdx.x == 0) bf.page_cnt[stream] = (uint32_t)n_kept;
+        if (blockIdx.x == 0 && threadIdx.x == 0) bf.page_cnt[stream] = n_kept;
         auto page_of = [&](uint32_t rank) -> int32_t {          // rank < n_kept
             int lo = 0;                                         // the last group that starts at or before the rank holds it
-#pragma unroll
-            for (int step = kGroups / 2; step > 0; step >>= 1)
+            for (int step = top_step; step > 0; step >>= 1)
                 if (group_at[lo + step] <= rank) lo += step;
             uint32_t rest = rank - group_at[lo];
             uint64_t word = group_word[lo];
             int w = lo * per_group;
-            for (uint32_t c = (uint32_t)__popcll(word); rest >= c; c = (uint32_t)__popcll(word)) {
-                rest -= c;
-                word = words[++w];
+            if (per_group > 1) {                                // (uniform)
+                const int end = w + per_group < n_words ? w + per_group : n_words;
+                bool found = false;
+                for (int w0 = w; w0 < end && !found; w0 += 8) {
+                    uint64_t v[8];
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = w0 + i < end ? words[w0 + i] : 0ull;
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) {
+                        const uint32_t c = (uint32_t)__popcll(v[i]);
+                        const bool here = !found && rest < c;
+                        word = here ? v[i] : word;
+                        w = here ? w0 + i : w;
+                        found |= here;
+                        rest -= found ? 0u : c;
+                    }
+                }
             }
             // its rest-th set bit
             int bit = 0;
@@ -235,7 +268,7 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
             }
             return w * 64 + bit;
         };
-        const int64_t rows = (n_kept + n_seg - 1) / n_seg;      // rows of n_seg ranks; the last one may be short
+        const int64_t rows = ((int64_t)n_kept + n_seg - 1) / n_seg;      // rows of n_seg ranks; the last one may be short
         int64_t base = 0;                        // first row of the current group of 64
         int32_t mine = 0;                        // lane i: page whose rank is this segment's in row base + i
         uint64_t m = 0ull;                       // rows of the group that hold a page for this segment, not yet taken

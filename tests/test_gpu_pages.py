@@ -354,10 +354,13 @@ def test_pages_edge_cases_tiny_caches_reset_and_static_scratch():
         cache.close()
 
 
-@pytest.mark.parametrize("N,seqs,Hkv,d,max_tokens", [(1_100_003, 1, 1, 32, 1_100_003), (70_000, 2, 2, 64, 2_200_000), (40_001, 3, 1, 128, 40_001)])
+@pytest.mark.parametrize("N,seqs,Hkv,d,max_tokens", [(1_100_003, 1, 1, 32, 1_100_003), (70_000, 2, 2, 64, 2_200_000), (40_001, 3, 1, 128, 40_001),
+                                                     (2_300_017, 1, 2, 32, 2_300_017), (4_194_305, 1, 1, 32, 4_300_000), (9_000_001, 1, 1, 32, 9_000_001),
+                                                     (38_000_003, 1, 1, 32, 38_000_003)])
 def test_pages_dealt_by_rank_cover_the_selection(N, seqs, Hkv, d, max_tokens):
-    """Ranks looked up in the page mask: several mask words per group (room for more than a million tokens), words that are empty, one
-    and many rows of ranks.  The selection is that of the plain scan, in no more pages than the mask has."""
+    """Ranks looked up in the page mask: one mask word per group, in one, two and four rounds of groups, several words per group (from
+    4,194,305 tokens on; more than the eight that are asked for together at 38 million), words that are empty, one and many rows of
+    ranks.  The selection is that of the plain scan, and the pages that the scan looked up are those of the mask, each once and in order."""
     Hq, k = 2 * Hkv, 700
     g = torch.Generator(device="cuda").manual_seed(N + d)
     centres = torch.randn((Hkv, 64, d), generator=g, device="cuda")
@@ -378,5 +381,13 @@ def test_pages_dealt_by_rank_cover_the_selection(N, seqs, Hkv, d, max_tokens):
         assert 0 < read < total and cache.last_fallbacks() == 0
         assert torch.equal(torch.sort(res[1], dim=2).values, torch.sort(plain[1], dim=2).values)
         np.testing.assert_allclose(res[0].cpu().numpy(), plain[0].cpu().numpy(), rtol=2e-5, atol=1e-6)
+        words, streams = (max_tokens + 4095) // 4096, seqs * Hkv
+        mask = ta.topk_attn_debug_read_workspace(cache.h, "page_mask", np.uint64, streams * words).reshape(streams, words)
+        cnt = ta.topk_attn_debug_read_workspace(cache.h, "page_cnt", np.uint32, streams)
+        looked_up = ta.topk_attn_debug_read_workspace(cache.h, "page_list", np.int32, streams * words * 64).reshape(streams, words * 64)
+        for st in range(streams):
+            kept = np.flatnonzero(np.unpackbits(mask[st].view(np.uint8), bitorder="little"))
+            assert cnt[st] == kept.size
+            assert np.array_equal(looked_up[st, :kept.size], kept)
     finally:
         cache.close()
