@@ -368,8 +368,13 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
 // ---------------------------------------------------------------------------------------
 // LDS staging slots per (wave, row): the 64 entries one step can add on top of the remainder
 // (fewer than kCandChunk entries) an aligned flush leaves behind
-constexpr int kStageRow = 96;
-static_assert(kCandChunk <= 16 && kStageRow >= 64 + kCandChunk - 1 && kStageRow <= 127, "row stage too small for an aligned flush");
+template <int NT>
+struct RowStage {
+    // as many as LDS holds for two workgroups of one row tile per compute unit, or one of two.  (One row tile with 96 empties its stages
+    // a sixth more often: 4 queries over a million tokens, k = 16384 530.8 us per call, with 112 525.2)
+    static constexpr int value = NT == 1 ? 112 : 96;
+    static_assert(kCandChunk <= 16 && value >= 64 + kCandChunk - 1 && value <= 127, "row stage too small for an aligned flush");
+};
 
 // NT row tiles (16 rows each) share every key tile: NT = 2 halves the passes over the keys for
 // 17..32 rows at the price of one wave per SIMD (512 registers) and 96 KiB of LDS stages,
@@ -381,7 +386,7 @@ __global__ void __launch_bounds__(kScanWaves* kWave)
 __attribute__((amdgpu_waves_per_eu(NT == 1 || MODE == MODE_SAMPLE ? 2 : 1, MODE == MODE_SAMPLE ? 8 : NT == 1 ? 2 : 1)))
 scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     using v8 = typename Mfma<DT>::v8;
-    constexpr int KS = D / 32;
+    constexpr int KS = D / 32, kStageRow = RowStage<NT>::value;
     constexpr int X = 4 * NT;          // rows a lane owns: row 16 t + 4 j + i at x = 4 t + i
     const int G = sh.G, M = sh.M;
     // Workgroup -> (key stream bx of kv head kvh of cache sequence bc, row block blk).  With several
