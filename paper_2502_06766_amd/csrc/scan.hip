@@ -366,27 +366,28 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
 // lanes that own the row.  A row's candidates are counted per score bin when they leave
 // the row's LDS stage for its segment (the same counts the grouped kernel leaves).
 // ---------------------------------------------------------------------------------------
-// LDS staging slots per (wave, row): the 64 entries one step can add on top of the remainder
-// (fewer than kCandChunk entries) an aligned flush leaves behind
-template <int NT>
+// LDS staging slots per (wave, row): the 64 entries one step can add on top of the remainder (fewer than kCandChunk entries) an
+// aligned flush leaves behind, and as many more as fit: one row tile and the scores' copy (FEW) leave room for 112 where two workgroups share a
+// compute unit (4 queries over a million tokens, k = 16384: scan 372 us with 96, 363 with 112).  Two row tiles and the copy take as long with 96, 112
+// and 118; 120 and 127 without the copy as long as 112.
+template <int NT, bool FEW>
 struct RowStage {
-    // as many as LDS holds for two workgroups of one row tile per compute unit, or one of two.  (One row tile with 96 empties its stages
-    // a sixth more often: 4 queries over a million tokens, k = 16384 530.8 us per call, with 112 525.2)
-    static constexpr int value = NT == 1 ? 112 : 96;
+    static constexpr int value = FEW && NT == 2 ? 96 : 112;
     static_assert(kCandChunk <= 16 && value >= 64 + kCandChunk - 1 && value <= 127, "row stage too small for an aligned flush");
 };
 
 // NT row tiles (16 rows each) share every key tile: NT = 2 halves the passes over the keys for
-// 17..32 rows at the price of one wave per SIMD (512 registers) and 96 KiB of LDS stages,
+// 17..32 rows at the price of one wave per SIMD (308 registers at d = 128) and 96 or 112 KiB of LDS stages,
 // which costs this kernel nothing measurable.  (Four row tiles, with stages of 48 entries and two steps of two tiles, halve the
 // passes again but pay it back at one wave per SIMD: 10 to 16 queries, d = 128, 150k tokens and more 0.95 - 1.01 of the time, below and at
 // d = 64 1.0 - 1.13.)
-template <int DT, int D, int MODE, int NT>
+// FEW (filter): few scores pass, they are staged one by one; otherwise every score has a store of its own (launch_scan_filter has the rule).
+template <int DT, int D, int MODE, int NT, bool FEW = false>
 __global__ void __launch_bounds__(kScanWaves* kWave)
 __attribute__((amdgpu_waves_per_eu(NT == 1 || MODE == MODE_SAMPLE ? 2 : 1, MODE == MODE_SAMPLE ? 8 : NT == 1 ? 2 : 1)))
 scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     using v8 = typename Mfma<DT>::v8;
-    constexpr int KS = D / 32, kStageRow = RowStage<NT>::value;
+    constexpr int KS = D / 32, kStageRow = RowStage<NT, FEW>::value;
     constexpr int X = 4 * NT;          // rows a lane owns: row 16 t + 4 j + i at x = 4 t + i
     const int G = sh.G, M = sh.M;
     // Workgroup -> (key stream bx of kv head kvh of cache sequence bc, row block blk).  With several
@@ -485,8 +486,9 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
             for (int i = threadIdx.x; i < 16 * NT * kTailBins; i += kScanWaves * kWave) hist_lds[i] = 0;
             for (int i = threadIdx.x; i < kScanWaves * 16 * NT; i += kScanWaves * kWave) count_lds[i] = 0;
         };
-        // One row tile, two waves per SIMD: the tile first, the barrier waits for it (64 heads over 200k tokens 111.9 us per call, 112.5 the
-        // other way).  Two row tiles, one wave per SIMD: the rows' loads first, as loads return in order, and a barrier that does not wait for the
+        // One row tile, two waves per SIMD: the tile first, the barrier waits for it.  (The other way 15 shapes, 2 to 4 queries or 5 to 16 heads per
+        // KV head, 27k to a million tokens, take 0.994 - 1.019 times as long, 1.006 in the geometric mean: 4 queries over a million tokens 523 us per call
+        // and 526, over 524k 290 and 294, 64 heads over 33k 40.6 and 41.4.)  Two row tiles, one wave per SIMD: the rows' loads first, as loads return in order, and a barrier that does not wait for the
         // tile (16 queries of 128k tokens 144.4, 145.9 the other way; 8 queries of 262k 175.9 and 177.5).
         if constexpr (NT == 1) {
             if (kAhead && rows_mine > 0) {
@@ -580,15 +582,17 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
     // Filter step of a tile.  A lane gathers which of its (row, sub-tile) scores pass in one
     // mask (bit 16 t + 4 i + g), the counts of the four rows of a row tile share a register (a byte each: a row has at most 64
     // passing keys per tile), and one inclusive scan over the 16 lanes of the rows (four DPP row shifts) ranks all of
-    // them at once.  The few that pass (one per lane for k = N / 64) are then taken bit by bit from a copy of the scores in LDS, which can be
-    // indexed by lane as registers cannot.  Staged order within a row: by lane, then sub-tile (the selection does not depend on it).
+    // them at once.  Staged order within a row: by lane, then sub-tile (the selection does not depend on it).
+    // FEW: those that pass (one per lane for k = N / 64) are taken bit by bit from a copy of the scores in LDS, which can be
+    // indexed by lane as registers cannot.  Otherwise a store per score, from its register and under its bit.
     // What bounds it is instructions (one or two waves per SIMD hide little): a store per score, to a scratch slot for those that do not
-    // pass, took 18 per score, this 11.  Whole call, before / now: 17 queries of 241k tokens, d = 64 279 / 249 us, 32 queries of 27k 75.8 / 67.7,
-    // 5 queries of 95k 60.8 / 52.5, 64 heads over 111k tokens 70.0 / 66.0; 16 queries of 128k, d = 128, whose keys come at the rate of the
-    // L1, 146 / 146.
+    // pass, took 18 per score.  Whole call, that way / now, few: 17 queries of 241k tokens, d = 64 275 / 240 us, 32 queries of 27k 84.5 / 80.2,
+    // 4 queries of 60k 53.5 / 49.2, 64 heads over 111k tokens 68.9 / 65.0; 16 queries of 128k, d = 128, whose keys come at the rate of the
+    // L1, 148 / 146.  A third of the keys selected, that way / taken from the mask / now: 8 queries of 200k, d = 64 430 / 456 / 425; 16 queries of 30k,
+    // d = 128 191.5 / 199.3 / 190.8.
     const int Pmin = prefix_of(0);      // rows of a block search prefixes that grow with the row
-    __shared__ f32x4 score_lds[MODE == MODE_FILTER ? kScanWaves * NT * 4 * kWave : 1];
-    f32x4* const my_scores = score_lds + (MODE == MODE_FILTER ? wave * NT * 4 * kWave + lane : 0);
+    __shared__ f32x4 score_lds[MODE == MODE_FILTER && FEW ? kScanWaves * NT * 4 * kWave : 1];
+    f32x4* const my_scores = score_lds + (MODE == MODE_FILTER && FEW ? wave * NT * 4 * kWave + lane : 0);
     auto filter = [&](f32x4 (&c)[NT][4], int64_t item0) __attribute__((always_inline)) {
         const int item_n = (int)item0 + n;              // positions fit 31 bits
         if (item0 + 64 > Pmin) {                        // (uniform) scores beyond a row's prefix become NaN, which no threshold lets through
@@ -609,10 +613,12 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
             for (int g = 0; g < 4; ++g) top[x] = fmaxf(top[x], c[x >> 2][g][x & 3]);
         }
         if (!__ballot(mask != 0u)) return;              // (uniform) nothing passes anywhere in the tile
+        if constexpr (FEW) {
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
+            for (int t = 0; t < NT; ++t) {
 #pragma unroll
-            for (int g = 0; g < 4; ++g) my_scores[(t * 4 + g) * kWave] = c[t][g];
+                for (int g = 0; g < 4; ++g) my_scores[(t * 4 + g) * kWave] = c[t][g];
+            }
         }
         uint32_t incl[NT], pk[NT], tot[NT];
         uint32_t nib = mask - ((mask >> 1) & 0x55555555u);
@@ -642,6 +648,23 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         if (NT > 1) at |= (uint64_t)(staged[NT - 1] + incl[NT - 1] - pk[NT - 1]) << 32;
 #pragma unroll
         for (int t = 0; t < NT; ++t) staged[t] += tot[t];
+        if constexpr (!FEW) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                const uint32_t to = (uint32_t)(at >> (32 * t));
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint64_t* where = st0 + row_at(4 * t + i) * kStageRow + ((to >> (8 * i)) & 0xFFu);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const bool pass = (mask >> (16 * t + 4 * i + g)) & 1u;
+                        if (pass) *where = ((uint64_t)__float_as_uint(c[t][g][i] + 0.0f) << 32) | (uint64_t)(uint32_t)(item_n + 16 * g);
+                        where += pass ? 1 : 0;
+                    }
+                }
+            }
+            return;
+        }
         // two at a time: their reads of the scores share a trip
         while (mask) {
             const int b0 = __builtin_ctz(mask);
@@ -847,11 +870,21 @@ hipError_t launch_scan_filter(const Shape& s, const Bufs& b, int64_t Nmax, hipSt
     // workgroups as run at once, which took the segments one after the other, 8 layers of 48k tokens 216 us per call, 209 like this; and the
     // loop around the walk cost other calls too, 3 ragged sequences of 98k 137 and 128.)
     const bool rows = scan_row_tiles(s);
+    // how the row-tile scan stages what passes (scan_rows_kernel, FEW).  Whole call, a store per score / scores taken from the mask, by keys per selected key:
+    // 128 0.99 - 1.03 (median 1.00), 64 0.98 - 1.02 (1.00), 32 0.96 - 1.01 (0.98), 10 0.91 - 1.00 (0.97), 4 0.89 - 1.00 (0.95); most with two row
+    // tiles and small head_dim.  (2 to 16 queries over 30k to 400k tokens, d = 32 to 256.)
+    const bool few = (int64_t)s.k * 48 < Nmax;
     dim3 grid((unsigned)(s.n_seg / kScanWaves), (unsigned)s.Hkv, (unsigned)(scan_grid_z(s)));
     dim3 block(kScanWaves * kWave);
 #define TKA_LAUNCH(DT_, D_)                                                                                  \
     do {                                                                                                     \
-        if (rows && s.row_tiles == 2)                                                                        \
+        if (rows && few && s.row_tiles == 2)                                                                 \
+            hipLaunchKernelGGL((scan_rows_kernel<DT_, D_, MODE_FILTER, 2, true>), grid, block, 0, st, s, b, 0, \
+                               (float*)nullptr);                                                             \
+        else if (rows && few)                                                                                \
+            hipLaunchKernelGGL((scan_rows_kernel<DT_, D_, MODE_FILTER, 1, true>), grid, block, 0, st, s, b, 0, \
+                               (float*)nullptr);                                                             \
+        else if (rows && s.row_tiles == 2)                                                                   \
             hipLaunchKernelGGL((scan_rows_kernel<DT_, D_, MODE_FILTER, 2>), grid, block, 0, st, s, b, 0,     \
                                (float*)nullptr);                                                             \
         else if (rows)                                                                                       \

@@ -105,10 +105,11 @@ def test_exact_scores_of_coded_candidates(d, Hq, Hkv, n, k):
 
 @pytest.mark.parametrize("M,Hq,Hkv", [(1, 5, 1), (1, 16, 1), (1, 17, 1), (4, 8, 1), (11, 3, 1), (3, 16, 2)])
 @pytest.mark.parametrize("d,n,k,window,keys", [(64, 1991, 40, 0, "equal"), (64, 3000, 700, 9, "runs"), (128, 2049, 5, 0, "runs"), (128, 1983, 1500, 0, "random"),
-                                               (256, 1100, 64, 70, "runs")])
+                                               (256, 1100, 64, 70, "runs"), (64, 2400, 49, 0, "runs"), (64, 2400, 50, 0, "runs"), (32, 2401, 50, 5, "equal"), (32, 2400, 600, 5, "equal")])
 def test_row_tiles_filter(d, n, k, window, keys, M, Hq, Hkv):
     """What passes the row-tile filter: everything (tied keys, every lane's mask full and the stages flushed at each tile), runs of
-    64 and more high scores, few; with prefixes of a causal chunk that end within a tile.  Integers, so the selected scores are exact."""
+    64 and more high scores, few; k on both sides of where what passes is staged another way (48 k = n); with prefixes of a causal chunk that
+    end within a tile.  Integers, so the selected scores are exact."""
     g = np.random.default_rng(d + n + Hq)
     qi = g.integers(1, 4, (M, Hq, d)).astype(np.float32)
     Ki = g.integers(-8, 9, (Hkv, n, d)).astype(np.float32)
