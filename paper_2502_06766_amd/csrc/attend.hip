@@ -1010,7 +1010,7 @@ attend_short_kernel(Shape sh, Bufs bf, float scale, float scale_log2e) {
             }
         };
         const LaneOffsets lane_off = lane_offsets<D>();
-        walk_tiles<ScanPipelined<D>::value, true>(wave, (N + 63) / 64, 4, ba, bb,
+        walk_tiles<ScanPipelined<D>::value>(wave, (N + 63) / 64, 4, ba, bb,
             [&](TileB& t, int64_t ti) { tile_load_at<DT, D>(Kh, ti, N, lane_off, t.b); }, use);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {

@@ -349,12 +349,8 @@ scan8_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         if (3 < G) thr3 = bf.thr[head0 + 3];
     }
 
-    auto row_of = [&](int64_t item0, int slot) -> int64_t {
-        int64_t p = item0 + slot;
-        if (MODE == MODE_SAMPLE) {
-            if (p > n_items - 1) p = n_items - 1;
-            p = sample_pos((int)p, stride);
-        }
+    auto sample_row = [&](int64_t item) -> int64_t {        // key row of a sample (beyond the last one: the last one's)
+        const int64_t p = sample_pos((int)(item < n_items ? item : n_items - 1), stride);
         return p < N ? p : N - 1;
     };
     auto consume = [&](const i32x4& res, float ks, int64_t item0) {
@@ -381,12 +377,12 @@ scan8_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
 
     auto use = [&](TileB& t, int64_t ti) { consume(tile_mac8<D>(t.b, qa), t.ks, ti * 64); };
     if (MODE == MODE_FILTER)
-        walk_tiles<true, true, true>(0, rows_mine, 1, ba, bb, load_seg, [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid, sh.n_seg)); });
+        walk_tiles<true, true>(0, rows_mine, 1, ba, bb, load_seg, [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid, sh.n_seg)); });
     else if (MODE == MODE_FULL)
-        walk_tiles<true, true>(tile, tile_end, tile_step, ba, bb, [&](TileB& t, int64_t ti) { load_at(t, ti, ti < tile_end ? N : 0); }, use);
+        walk_tiles<true>(tile, tile_end, tile_step, ba, bb, [&](TileB& t, int64_t ti) { load_at(t, ti, ti < tile_end ? N : 0); }, use);
     else
-        walk_tiles<false, false>(tile, tile_end, tile_step, ba, bb,
-            [&](TileB& t, int64_t ti) { tile_load8<D>(Kh, Sh, [&](int slot) { return row_of(ti * 64, slot); }, t.b, t.ks); }, use);
+        walk_tiles<false>(tile, tile_end, tile_step, ba, bb,
+            [&](TileB& t, int64_t ti) { tile_load8<D>(Kh, Sh, [&](int slot) { return sample_row(ti * 64 + slot); }, t.b, t.ks); }, use);
     if (MODE == MODE_FILTER) {
         stage_flush(cs0, seg_cap, sh.n_seg, true);
         if (1 < G) stage_flush(cs1, seg_cap, sh.n_seg, true);

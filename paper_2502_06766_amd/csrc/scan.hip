@@ -137,13 +137,8 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     }
 
-    // row of tile slot `slot` for the tile starting at item `item0`
-    auto row_of = [&](int64_t item0, int slot) -> int64_t {
-        int64_t p = item0 + slot;
-        if (MODE == MODE_SAMPLE) {
-            if (p > n_items - 1) p = n_items - 1;
-            p = sample_pos((int)p, stride);
-        }
+    auto sample_row = [&](int64_t item) -> int64_t {        // key row of a sample (beyond the last one: the last one's)
+        const int64_t p = sample_pos((int)(item < n_items ? item : n_items - 1), stride);
         return p < N ? p : N - 1;
     };
     auto consume = [&](const f32x4& res, int64_t item0) {
@@ -169,10 +164,10 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     };
 
-    auto load_rows = [&](TileB& t, int64_t ti) { tile_load<DT, D>(Kh, [&](int slot) { return row_of(ti * 64, slot); }, t.b); };
+    auto load_sample = [&](TileB& t, int64_t ti) { tile_load<DT, D>(Kh, [&](int slot) { return sample_row(ti * 64 + slot); }, t.b); };
     auto use = [&](TileB& t, int64_t ti) { consume(tile_mac<DT, D>(t.b, qa), ti * 64); };
     if (MODE == MODE_SAMPLE) {
-        walk_tiles<false, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
+        walk_tiles<false>(tile, tile_end, tile_step, ba, bb, load_sample, use);
     } else if (MODE == MODE_FILTER && PAGED) {
         // The pages kept, ascending, are dealt to the wave segments by rank like the tiles of the plain scan
         // (seg_tile() over ranks; 64 rows looked up at a time, one per lane), so every wave reads as many
@@ -324,13 +319,13 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     } else {
         if (MODE == MODE_FULL) {
-            walk_tiles<ScanPipelined<D>::value, true>(tile, tile_end, tile_step, ba, bb,
+            walk_tiles<ScanPipelined<D>::value>(tile, tile_end, tile_step, ba, bb,
                 [&](TileB& t, int64_t ti) { tile_load_at<DT, D>(Kh, ti, ti < tile_end ? N : 0, lane_off, t.b); }, use);
         }
     }
     if (MODE == MODE_FILTER) {
         if (!PAGED) {
-            walk_tiles<ScanPipelined<D>::value, true, kAhead>(0, rows_mine, 1, ba, bb, load_seg,
+            walk_tiles<ScanPipelined<D>::value, kAhead>(0, rows_mine, 1, ba, bb, load_seg,
                 [&](TileB& t, int64_t i) { use(t, seg_tile(i, sid, n_seg)); });
         }
         stage_flush(cs0, seg_cap, n_seg, true);
@@ -571,12 +566,8 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     };
 
-    auto row_of = [&](int64_t item0, int slot) -> int64_t {
-        int64_t p = item0 + slot;
-        if (MODE == MODE_SAMPLE) {
-            if (p > n_items - 1) p = n_items - 1;
-            p = sample_pos((int)p, stride);
-        }
+    auto sample_row = [&](int64_t item) -> int64_t {        // key row of a sample (beyond the last one: the last one's)
+        const int64_t p = sample_pos((int)(item < n_items ? item : n_items - 1), stride);
         return p < N ? p : N - 1;
     };
     // Filter step of a tile.  A lane gathers which of its (row, sub-tile) scores pass in one
@@ -721,19 +712,19 @@ scan_rows_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         }
     };
 
-    auto load_rows = [&](TileB& t, int64_t ti) { tile_load<DT, D>(Kh, [&](int slot) { return row_of(ti * 64, slot); }, t.b); };
+    auto load_sample = [&](TileB& t, int64_t ti) { tile_load<DT, D>(Kh, [&](int slot) { return sample_row(ti * 64 + slot); }, t.b); };
     auto use = [&](TileB& t, int64_t ti) __attribute__((always_inline)) {
         f32x4 c[NT][4];
         mac(t.b, c);
         consume(c, ti * 64);
     };
     if (MODE == MODE_SAMPLE) {
-        walk_tiles<false, false>(tile, tile_end, tile_step, ba, bb, load_rows, use);
+        walk_tiles<false>(tile, tile_end, tile_step, ba, bb, load_sample, use);
     } else if (MODE == MODE_FILTER) {
-        walk_tiles<ScanPipelined<D>::value, true, kAhead>(0, rows_mine, 1, ba, bb, load_seg,
+        walk_tiles<ScanPipelined<D>::value, kAhead>(0, rows_mine, 1, ba, bb, load_seg,
             [&](TileB& t, int64_t i) __attribute__((always_inline)) { use(t, seg_tile(i, sid, n_seg)); });
     } else {
-        walk_tiles<ScanPipelined<D>::value, true>(tile, tile_end, tile_step, ba, bb,
+        walk_tiles<ScanPipelined<D>::value>(tile, tile_end, tile_step, ba, bb,
             [&](TileB& t, int64_t ti) { tile_load_at<DT, D>(Kh, ti, ti < tile_end ? N : 0, lane_off, t.b); }, use);
     }
     if (MODE == MODE_FILTER) {

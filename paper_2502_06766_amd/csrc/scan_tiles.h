@@ -56,7 +56,16 @@ __device__ __forceinline__ void tile_load(const char* Kh, RowFn rowfn, typename 
     }
 }
 
-// The same for `n_rows` consecutive rows (64 for a whole tile), through buffer loads: the tile's address
+// Rows of a tile, 0 .. 64, of the n_rows (wave-uniform) there are from its first one on.
+__device__ __forceinline__ uint32_t bounded_rows(int n_rows) {
+    // (two steps: a clamp to a range is a vector instruction, and a descriptor from there a loop over the lanes)
+    const int have = __builtin_amdgcn_readfirstlane(n_rows);
+    uint32_t rows = (uint32_t)(have < 0 ? 0 : have);
+    asm("" : "+s"(rows));
+    return rows > 64u ? 64u : rows;
+}
+
+// tile_load() for `n_rows` consecutive rows (64 for a whole tile), through buffer loads: the tile's address
 // (wave-uniform) sits in a scalar buffer descriptor and a lane's byte offsets of the four 16-row sub-tiles are
 // loop-invariant, so the loop holds no per-lane address arithmetic at all.  (With per-lane 64-bit addresses the compiler
 // builds them in registers of the buffer it is about to refill and then waits for every
@@ -66,14 +75,6 @@ __device__ __forceinline__ void tile_load(const char* Kh, RowFn rowfn, typename 
 // offset is in the lane's register and the instruction, which are what the range check looks at; a scalar offset need not be.)
 // Whole call, cut-short tile in a round of its own and a tile read again at the end / now: 16k tokens, where a wave has one tile,
 // 23.4 / 21.0 us, 8 layers of 48001 tokens (three tiles a wave) 207.7 / 197.3, 192 sequences of 2k to 4k tokens 308.9 / 300.3.
-// Rows of a tile, 0 .. 64, of the n_rows (wave-uniform) there are from its first one on.
-__device__ __forceinline__ uint32_t bounded_rows(int n_rows) {
-    // (two steps: a clamp to a range is a vector instruction, and a descriptor from there a loop over the lanes)
-    const int have = __builtin_amdgcn_readfirstlane(n_rows);
-    uint32_t rows = (uint32_t)(have < 0 ? 0 : have);
-    asm("" : "+s"(rows));
-    return rows > 64u ? 64u : rows;
-}
 struct LaneOffsets { uint32_t g[4]; };
 template <int D>
 __device__ __forceinline__ LaneOffsets lane_offsets() {
@@ -103,7 +104,8 @@ __device__ __forceinline__ void tile_load_rows(const char* tile_base, int n_rows
         }
     }
 }
-// Tile `tile` of a stream of N rows (positions fit 31 bits; tile * 64 stays within 32).
+// Tile `tile` of a stream of N rows.  (A cache has at most 0x7FFFFF00 of them, and no walk asks for a tile whose first row lies further
+// than that from row N: the difference, and minus the first row of a tile up to three past the end, fit an int.)
 template <int DT, int D>
 __device__ __forceinline__ void tile_load_at(const char* Kh, int64_t tile, int64_t N, const LaneOffsets& off,
                                              typename Mfma<DT>::v8 (&b)[4][D / 32]) {
@@ -112,41 +114,37 @@ __device__ __forceinline__ void tile_load_at(const char* Kh, int64_t tile, int64
 
 // A wave's walk over the tiles tile, tile + step, ... < end with two register buffers: the
 // next tile's loads are in flight while the current one is multiplied and filtered.  The
-// prefetch is unconditional so that the wait before the MFMAs only covers the tile they consume; past the end it re-reads a tile the
-// wave already had, a cache hit (BOUNDED: it asks for the tile past the end, of which `load` reads nothing).  Returns the
-// first tile of the sequence at or past `end`.
+// prefetch is unconditional so that the wait before the MFMAs only covers the tile they consume: the walk asks for one tile past
+// the end too, of which `load` has to read nothing.
 // FIRST_LOADED: the first tile is in `ba` or on its way (double-buffered walks only).
-template <bool PIPELINED, bool BOUNDED, bool FIRST_LOADED = false, class Buf, class Load, class Use>
-__device__ __forceinline__ int64_t walk_tiles(int64_t tile, int64_t end, int64_t step, Buf& ba, Buf& bb, Load load,
-                                              Use use) {
-  if (PIPELINED) {
-    if (tile < end) {
+template <bool PIPELINED, bool FIRST_LOADED = false, class Buf, class Load, class Use>
+__device__ __forceinline__ void walk_tiles(int64_t tile, int64_t end, int64_t step, Buf& ba, Buf& bb, Load load, Use use) {
+    if (PIPELINED) {
+        if (tile >= end) return;
         if (!FIRST_LOADED) load(ba, tile);
         while (true) {
             const int64_t t1 = tile + step;
-            load(bb, BOUNDED || t1 < end ? t1 : tile);
+            load(bb, t1);
             __builtin_amdgcn_sched_barrier(0);
             use(ba, tile);
-            if (t1 >= end) { tile = t1; break; }
+            if (t1 >= end) break;
             const int64_t t2 = t1 + step;
-            load(ba, BOUNDED || t2 < end ? t2 : t1);
+            load(ba, t2);
             __builtin_amdgcn_sched_barrier(0);
             use(bb, t1);
-            if (t2 >= end) { tile = t2; break; }
+            if (t2 >= end) break;
             tile = t2;
         }
+    } else {
+        // One buffer: the other waves of the compute unit cover the latency.  For head_dim 256, and for samples, whose waves have a tile or two: a
+        // second buffer's prefetch read the only tile twice and its registers halved the waves (sample of 16 x 8 streams of 4096 rows,
+        // d = 128, 45.1 -> 35.8 us; of 8 streams of 8192 8.0 -> 6.9, of 2048 for 128k tokens 6.6 -> 5.4 by the whole call's time).
+        for (; tile < end; tile += step) {
+            load(ba, tile);
+            __builtin_amdgcn_sched_barrier(0);
+            use(ba, tile);
+        }
     }
-  } else {
-    // One buffer: the other waves of the compute unit cover the latency.  For head_dim 256, and for samples, whose waves have a tile or two: a
-    // second buffer's prefetch read the only tile twice and its registers halved the waves (sample of 16 x 8 streams of 4096 rows,
-    // d = 128, 45.1 -> 35.8 us; of 8 streams of 8192 8.0 -> 6.9, of 2048 for 128k tokens 6.6 -> 5.4 by the whole call's time).
-    for (; tile < end; tile += step) {
-        load(ba, tile);
-        __builtin_amdgcn_sched_barrier(0);
-        use(ba, tile);
-    }
-  }
-    return tile;
 }
 
 // head_dim 256 makes a 64-key tile 32 KiB: two register buffers of it do not fit, and
