@@ -1,5 +1,7 @@
-"""The tile that the end of a cache cuts short, in every scan over 16-bit keys: rows behind the end (NaN here) are neither read as keys
-nor missed.  Elements of q and K are small integers, so scores are exact in fp32 and the selection has to equal the oracle's."""
+"""The tile that the end of a cache cuts short, in every scan over 16-bit keys and over codes: the last rows are not missed and
+the slots behind the end are no keys.  Those slots hold NaN ("mixed"), which would show in a result, or zeros under keys whose scores are
+all negative ("negative"), so that a slot taken for a key, read from memory or as the zeros of a bounded load, would be selected.  Elements
+of q and K are small integers, so scores are exact in fp32 and the selection has to equal the oracle's."""
 import numpy as np
 import pytest
 import torch
@@ -14,11 +16,12 @@ DEV = torch.device("cuda", 0) if torch.cuda.is_available() else None
 PATHS = {"filter": ta.PATH_FILTER, "full": ta.PATH_FULL, "auto": ta.PATH_AUTO}
 
 
+@pytest.mark.parametrize("scores", ["mixed", "negative"])
 @pytest.mark.parametrize("d", [32, 64, 128, 256])
 @pytest.mark.parametrize("path,Hq,Hkv,seqs", [
     ("filter", 4, 1, 1), ("filter", 6, 2, 3), ("filter", 8, 1, 1), ("filter", 20, 1, 2), ("full", 4, 1, 1), ("full", 16, 2, 2), ("auto", 4, 2, 3),
 ])
-def test_rows_behind_the_end_of_the_cache(d, path, Hq, Hkv, seqs):
+def test_rows_behind_the_end_of_the_cache(d, path, Hq, Hkv, seqs, scores):
     g = np.random.default_rng(d + Hq)
     for n0 in (300, 1983, 5000):                                      # (auto: the one launch over short sequences up to 512)
         lens = [n0 // 64 * 64 + r for r in (1, 63, 16, 17, 0)]
@@ -29,12 +32,16 @@ def test_rows_behind_the_end_of_the_cache(d, path, Hq, Hkv, seqs):
             k = 20
             cache = ta.TopkAttnCache(1, seqs, Hq, Hkv, d, max(ns) + 130, k, wl.F16)
             try:
-                cache.kv.fill_(0xFF)                                  # NaN
+                neg = scores == "negative"
+                cache.kv.fill_(0 if neg else 0xFF)                    # (0xFFFF: NaN)
                 data = []
-                q = wl.quantize(g.integers(-3, 4, (seqs, Hq, d)).astype(np.float32), wl.F16)
+                q = wl.quantize(g.integers(1 if neg else -3, 4, (seqs, Hq, d)).astype(np.float32), wl.F16)
                 for b, nb in enumerate(ns):
-                    K = wl.quantize(g.integers(-8, 9, (Hkv, nb, d)).astype(np.float32), wl.F16)
-                    K[:, -1] = 8 * np.sign(q[b].reshape(Hkv, -1, d)[:, 0])           # the last key is a winner of the group's first head
+                    K = wl.quantize(g.integers(-8, 0 if neg else 9, (Hkv, nb, d)).astype(np.float32), wl.F16)
+                    if neg:
+                        K[:, -1, 1:] = 0                              # the last key is the best there is, and below zero
+                    else:
+                        K[:, -1] = 8 * np.sign(q[b].reshape(Hkv, -1, d)[:, 0])       # the last key is a winner of the group's first head
                     V = wl.quantize(g.standard_normal((Hkv, nb, d)).astype(np.float32), wl.F16)
                     cache.append(0, b, H.to_torch(K, wl.F16, DEV), H.to_torch(V, wl.F16, DEV), head_major=True)
                     data.append((K, V))
@@ -42,6 +49,7 @@ def test_rows_behind_the_end_of_the_cache(d, path, Hq, Hkv, seqs):
                 res = cache.decode(0, H.to_torch(q, wl.F16, DEV), k)
                 torch.cuda.synchronize()
                 for b, (K, V) in enumerate(data):
+                    assert int(res[1][b].max()) < ns[b] and (not neg or (res[1][b] == ns[b] - 1).any(1).all())
                     ref = c_oracle.topk_attention(q[b], K, V, wl.F16, k)
                     H.check_against_oracle(*(r[b].cpu().numpy() for r in res), ref, np.full(Hq, 1e-30), min(k, ns[b]), H.out_tolerance(wl.F16),
                                            float(np.abs(wl.widen(V, wl.F16)).max()), f"d={d} {path} n={ns[b]}")
@@ -49,31 +57,61 @@ def test_rows_behind_the_end_of_the_cache(d, path, Hq, Hkv, seqs):
                 cache.close()
 
 
+@pytest.mark.parametrize("scores", ["mixed", "negative"])
 @pytest.mark.parametrize("d,n", [(64, 20001), (128, 17023), (128, 16448), (256, 17040)])
-def test_codes_behind_the_end_of_the_cache(d, n):
-    """The same through the int8 index (codes of -1 and scales of NaN behind the end): the k keys far above all others, the last
-    one among them, are found."""
+def test_codes_behind_the_end_of_the_cache(d, n, scores):
+    """The same through the int8 index (codes of -1 and scales of NaN behind the end, or zeros under negative scores): the k keys far above
+    all others, the last one among them, are found."""
+    neg = scores == "negative"
     g = np.random.default_rng(d + n)
     Hkv, k = 3, 20
     q = g.integers(1, 4, (Hkv, d)).astype(np.float32) * g.choice([-1.0, 1.0], (Hkv, d)).astype(np.float32)
-    Kf = g.integers(-2, 3, (Hkv, n, d)).astype(np.float32)
+    Kf = g.integers(2, 5, (Hkv, n, d)) * -np.sign(q)[:, None] if neg else g.integers(-2, 3, (Hkv, n, d))
+    Kf = Kf.astype(np.float32)
     for h in range(Hkv):
         pos = np.append(g.permutation(n - 1)[:k - 1], n - 1)
-        for i, p in enumerate(pos):
-            Kf[h, p] = 8 * np.sign(q[h])
-            Kf[h, p, :i] = 0                                          # (scores that differ)
+        for i, p in enumerate(pos):                                   # (scores that differ)
+            Kf[h, p] = -np.sign(q[h]) if neg else 8 * np.sign(q[h])
+            Kf[h, p, slice(i + 1, None) if neg else slice(i)] = 0
     q, K = wl.quantize(q, wl.F16), wl.quantize(Kf, wl.F16)
     V = wl.quantize(g.standard_normal((Hkv, n, d)).astype(np.float32), wl.F16)
     cache = ta.TopkAttnCache(1, 1, Hkv, Hkv, d, n + 130, k, wl.F16, index_kind=ta.INDEX_INT8)
     try:
-        cache.kv.fill_(0xFF)
+        cache.kv.fill_(0 if neg else 0xFF)
         cache.append(0, 0, H.to_torch(K, wl.F16, DEV), H.to_torch(V, wl.F16, DEV), head_major=True)
         cache.set_path(ta.PATH_INDEX)
         res = cache.decode(0, H.to_torch(q[None], wl.F16, DEV), k)
         torch.cuda.synchronize()
+        assert int(res[1].max()) < n
         H.check_against_oracle(*(r[0].cpu().numpy() for r in res), c_oracle.topk_attention(q, K, V, wl.F16, k), np.full(Hkv, 1e-30), k,
                                H.out_tolerance(wl.F16), float(np.abs(wl.widen(V, wl.F16)).max()), f"int8 d={d} n={n}")
         assert cache.last_fallbacks() == 0
+    finally:
+        cache.close()
+
+
+@pytest.mark.parametrize("d,Hq,Hkv,n", [(64, 4, 1, 40001), (128, 8, 2, 34023), (256, 3, 1, 37072), (32, 4, 2, 33000)])
+def test_pages_behind_the_end_of_the_cache(d, Hq, Hkv, n):
+    """The same through the page index: negative scores, a cut-short last page, and pages that are ruled out (the search took that path)."""
+    g = np.random.default_rng(d + n)
+    k = 20
+    q = wl.quantize(g.integers(1, 4, (Hq, d)).astype(np.float32), wl.F16)
+    Kf = g.integers(-2, 0, (Hkv, n, d)).astype(np.float32)
+    Kf[:, :n // 2] -= 100                                             # half the pages lie far below
+    Kf[:, -1, 1:] = 0
+    K, V = wl.quantize(Kf, wl.F16), wl.quantize(g.standard_normal((Hkv, n, d)).astype(np.float32), wl.F16)
+    cache = ta.TopkAttnCache(1, 1, Hq, Hkv, d, n + 130, k, wl.F16, index_kind=ta.INDEX_PAGES)
+    try:
+        cache.kv.zero_()
+        cache.append(0, 0, H.to_torch(K, wl.F16, DEV), H.to_torch(V, wl.F16, DEV), head_major=True)
+        cache.set_path(ta.PATH_PAGES)
+        res = cache.decode(0, H.to_torch(q[None], wl.F16, DEV), k)
+        torch.cuda.synchronize()
+        read, total = ta.topk_attn_last_pages_read(cache.h)
+        assert 0 < read < total
+        assert int(res[1].max()) < n and (res[1][0] == n - 1).any(1).all()
+        H.check_against_oracle(*(r[0].cpu().numpy() for r in res), c_oracle.topk_attention(q, K, V, wl.F16, k), np.full(Hq, 1e-30), k,
+                               H.out_tolerance(wl.F16), float(np.abs(wl.widen(V, wl.F16)).max()), f"pages d={d} n={n}")
     finally:
         cache.close()
 
