@@ -130,7 +130,7 @@ __global__ void __launch_bounds__(256) page_filter_kernel(Shape sh, Bufs bf, flo
         if (lane == 0) *out = 0ull;
         return;
     }
-    // the centres and balls are asked for first: the query norms below wait for loads of their own
+    // the centres and balls are asked for first, the query and the thresholds behind them; nothing is waited for in between
     const int64_t stream = (int64_t)b * sh.Hkv + kvh;
     const char* Ch = static_cast<const char*>(bf.page_centres) + stream * sh.page_cap * (D * 2);
     v8 cb[4][D / 32];

@@ -177,8 +177,8 @@ scan_mfma_kernel(Shape sh, Bufs bf, int tiles_per_wave, float* dst) {
         // key stream that wrote the list out for the scan took 6.3 us, this costs the scan 3: a million tokens 191.8 -> 185.5 us, calls of 140k to 400k tokens
         // 1.08 - 1.16 times as fast.)  A group is one word up to 4.2 million tokens, and its word stays in LDS; the words of a longer group are
         // asked for eight at a time when a rank is looked up in it, so that no load waits for another.  (256 groups, walked word after
-        // word: 4 million tokens of one KV head, d = 128 103.6 us per call, now 102.7; 33 million, d = 32 266.4 and 266.2; 2 KV heads of 8 million, d = 64
-        // 321 - 337 and 319 - 327.  With the list launch these took 112.8, 294.2 and 326 - 340.)
+        // word / now / the scan beside the list launch, and that: 33 million tokens of one KV head, d = 32 33.6 / 30.7 / 29.1 + 32 us, 4 million, d = 128
+        // 27.0 / 26.9 / 24.0 + 7.1; 2 KV heads of 8 million, d = 64 63.0 / 63.2 / 60.4 + 13.1; 4 of a million 21.4 / 21.2 / 22.4 + 5.6.)
         const int64_t stream = (int64_t)b * sh.Hkv + kvh;
         const uint64_t* const words = bf.page_mask + stream * sh.page_words;
         int32_t* const plist = bf.page_list + stream * (int64_t)sh.page_words * 64;

@@ -117,23 +117,26 @@ __device__ __forceinline__ void tile_load_at(const char* Kh, int64_t tile, int64
 // prefetch is unconditional so that the wait before the MFMAs only covers the tile they consume: the walk asks for one tile past
 // the end too, of which `load` has to read nothing.
 // FIRST_LOADED: the first tile is in `ba` or on its way (double-buffered walks only).
+// Returns the first tile of the sequence at or past `end`.  No caller takes it, but without the value the compiler allots the registers of the
+// row-tile scan otherwise (16 queries of 128k tokens 147.4 us per call, 146.7 with it).
 template <bool PIPELINED, bool FIRST_LOADED = false, class Buf, class Load, class Use>
-__device__ __forceinline__ void walk_tiles(int64_t tile, int64_t end, int64_t step, Buf& ba, Buf& bb, Load load, Use use) {
+__device__ __forceinline__ int64_t walk_tiles(int64_t tile, int64_t end, int64_t step, Buf& ba, Buf& bb, Load load, Use use) {
     if (PIPELINED) {
-        if (tile >= end) return;
-        if (!FIRST_LOADED) load(ba, tile);
-        while (true) {
-            const int64_t t1 = tile + step;
-            load(bb, t1);
-            __builtin_amdgcn_sched_barrier(0);
-            use(ba, tile);
-            if (t1 >= end) break;
-            const int64_t t2 = t1 + step;
-            load(ba, t2);
-            __builtin_amdgcn_sched_barrier(0);
-            use(bb, t1);
-            if (t2 >= end) break;
-            tile = t2;
+        if (tile < end) {
+            if (!FIRST_LOADED) load(ba, tile);
+            while (true) {
+                const int64_t t1 = tile + step;
+                load(bb, t1);
+                __builtin_amdgcn_sched_barrier(0);
+                use(ba, tile);
+                if (t1 >= end) { tile = t1; break; }
+                const int64_t t2 = t1 + step;
+                load(ba, t2);
+                __builtin_amdgcn_sched_barrier(0);
+                use(bb, t1);
+                if (t2 >= end) { tile = t2; break; }
+                tile = t2;
+            }
         }
     } else {
         // One buffer: the other waves of the compute unit cover the latency.  For head_dim 256, and for samples, whose waves have a tile or two: a
@@ -145,6 +148,7 @@ __device__ __forceinline__ void walk_tiles(int64_t tile, int64_t end, int64_t st
             use(ba, tile);
         }
     }
+    return tile;
 }
 
 // head_dim 256 makes a 64-key tile 32 KiB: two register buffers of it do not fit, and
