@@ -91,8 +91,8 @@ struct Bufs {
     const void* page_centres;  // this layer's page centres [Bc][Hkv][page_cap][D] (cache dtype), or null
     const float* page_balls;   // this layer's [Bc][Hkv][page_cap][2]: radius of the page's ball, norm of its centre
     uint64_t* page_mask;       // [B][Hkv][page_words] one bit per page: 1 = the scan reads it
-    uint32_t* page_cnt;        // [B][Hkv] pages the scan reads        } left by the scan
-    int32_t* page_list;        // [B][Hkv][64 * page_words] their numbers, ascending } for tests
+    uint32_t* page_cnt;        // [B][Hkv] pages the scan looked up (it leaves both to be held against the mask, no kernel reads them)
+    int32_t* page_list;        // [B][Hkv][64 * page_words] their numbers, ascending
     float* scores;          // [B*Hq][Ncap] full score buffer
     int32_t* sel_idx;       // [B*Hq][k]
     float* sel_val;         // [B*Hq][k]

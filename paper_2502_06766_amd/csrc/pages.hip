@@ -12,7 +12,7 @@
 //   page_filter_kernel  per decode: one bit per page and KV head (1 = scan it), 64 pages per wave
 //                       scored against the group's queries with the MFMA tile routine of the scan
 // The scan deals the pages kept to its waves by rank, so that every wave reads as many pages as any other whatever the
-// pattern of the pages kept (scan.hip), and leaves their numbers, ascending, and their count per key stream.
+// pattern of the pages kept (scan.hip), and leaves their numbers, ascending, and their count per key stream to be held against the mask.
 #include "device_utils.h"
 #include "internal.h"
 #include "scan_tiles.h"

@@ -262,8 +262,8 @@ def test_pages_with_a_window_match_the_plain_scan(dtype, N, d, k, window):
 
 
 def test_page_index_decode_under_graph_capture_replays():
-    """A decode through the page index with a window, captured in a HIP graph (page filter, page list, paged
-    scan, tail: kernels only) and replayed with eager work in between: every replay gives the eager result,
+    """A decode through the page index with a window, captured in a HIP graph (page filter, paged scan,
+    tail: kernels only) and replayed with eager work in between: every replay gives the eager result,
     also after the query has changed (another set of pages is kept)."""
     dtype, Hq, Hkv, d, N, k, W = wl.F16, 8, 2, 128, 120000, 900, 300
     q1, K, V = clustered(N, k, seed=77, sigma=0.03, dtype=dtype, Hq=Hq, Hkv=Hkv, d=d)
